@@ -38,7 +38,7 @@ namespace {
 constexpr uint32_t kStepsPerLaunch = 2048;
 
 struct Layout {
-  size_t arr_thr, len_tab, t_next, iter, remptok, pf_job, n_cls, n_join, fin, job, qring, dring, cstate, tally, hist,
+  size_t arr_thr, len_tab, rec, t_rel, remptok, fin, job, qring, dring, cstate, tally, hist,
       digest, reduced, params, pat_tab, qdl, ddl, cal, dcal, dring_m, ddl_m, dcal_m, total;
 };
 
@@ -60,12 +60,9 @@ Layout make_layout(const sim_config &c, int R, int64_t rows, size_t cal_entries)
   const size_t RN = static_cast<size_t>(R) * c.N;
   L.arr_thr = take(static_cast<size_t>(rows) * 3 * sizeof(uint32_t));
   L.len_tab = take(static_cast<size_t>(c.K) * 2 * kTableSize * sizeof(uint16_t));
-  L.t_next = take(RN * sizeof(int64_t));
-  L.iter = take(RN * sizeof(uint32_t));
+  L.rec = take(RN * sizeof(ServerRec));
+  L.t_rel = take(RN * sizeof(uint32_t));
   L.remptok = take(RN * sizeof(uint32_t));
-  L.pf_job = take(RN * sizeof(uint64_t));
-  L.n_cls = take(RN * sizeof(uint64_t));
-  L.n_join = take(RN * sizeof(uint64_t));
   const size_t BS = (static_cast<size_t>(c.B) + 3) & ~size_t(3);
   L.fin = take(RN * BS * sizeof(uint32_t));
   L.job = take(RN * BS * sizeof(uint64_t));
@@ -173,7 +170,7 @@ int validate(const sim_config *c, int max_reps, Ticks *t)
   if (lam * (static_cast<double>(t->dt) * 1e-9) * (1.0 + std::fabs(c->mod_amp)) > 0.05) return SIM_EINVAL;
   const int lo = host_hbin(t->c0), hi = host_hbin(t->c0 + t->cpre * c->C + t->cdec * c->B);
   if (hi - lo + 1 > kMaxTbtBins) return SIM_EINVAL;
-  // clocks are compared modulo 2^32 ns on the device: the longest iteration must stay far below 2^31 ns
+  // the device computes iteration times in 32 bits: the longest iteration must stay below 2^31 ns
   if (t->c0 + t->cpre * c->C + t->cdec * c->B > 2000000000ll) return SIM_EINVAL;
   // the per-server records of a replication stay on chip for a whole launch
   if (on_chip_bytes(*c, *t, c->M, max_reps) > kOnChipLimit) return SIM_EINVAL;
@@ -374,12 +371,9 @@ int create_in(const sim_config *cfg, int max_replications, void *dev_workspace, 
     unsigned char *w = h->ws;
     p.arr_thr = reinterpret_cast<uint32_t *>(w + L.arr_thr);
     p.len_tab = reinterpret_cast<uint16_t *>(w + L.len_tab);
-    p.t_next = reinterpret_cast<int64_t *>(w + L.t_next);
-    p.iter = reinterpret_cast<uint32_t *>(w + L.iter);
+    p.rec = reinterpret_cast<ServerRec *>(w + L.rec);
+    p.t_rel = reinterpret_cast<uint32_t *>(w + L.t_rel);
     p.remptok = reinterpret_cast<uint32_t *>(w + L.remptok);
-    p.pf_job = reinterpret_cast<uint64_t *>(w + L.pf_job);
-    p.n_cls = reinterpret_cast<uint64_t *>(w + L.n_cls);
-    p.n_join = reinterpret_cast<uint64_t *>(w + L.n_join);
     p.fin = reinterpret_cast<uint32_t *>(w + L.fin);
     p.job = reinterpret_cast<uint64_t *>(w + L.job);
     p.qring = reinterpret_cast<uint32_t *>(w + L.qring);
@@ -636,7 +630,7 @@ int sim_hist(sim_t *h, int r, int which, uint64_t *out, void *hip_stream)
 int sim_digest(sim_t *h, int r, uint64_t *out, void *hip_stream)
 {
   if (!h || !out || !h->started || r < 0 || r >= h->reps || !on_device(h)) return SIM_EINVAL;
-  int rc = launch_digest(h->p, h->reps, hip_stream);
+  int rc = launch_digest(h->p, h->reps, h->steps_done * h->p.dt, hip_stream);
   if (rc != SIM_OK) return rc;
   rc = sync(h, hip_stream);
   if (rc != SIM_OK) return rc;
@@ -661,24 +655,24 @@ int sim_snapshot(sim_t *h, int r, sim_state_t *out, void *hip_stream)
         out->class_state[2 * K + k] = cs[CS_QD + k]; out->class_state[3 * K + k] = cs[CS_YM + k];
         out->class_state[4 * K + k] = cs[CS_YS + k];
       }
-    if (out->t_next && (rc = copy_out(out->t_next, p.t_next + base, N * sizeof(int64_t))) != SIM_OK) return rc;
-    if (out->iter && (rc = copy_out(out->iter, p.iter + base, N * sizeof(uint32_t))) != SIM_OK) return rc;
-    std::vector<uint32_t> pk(N);
-    std::vector<uint64_t> nc(N), nj(N), pj(N);
+    std::vector<uint32_t> pk(N), tr(N);
+    std::vector<ServerRec> sr(N);
     if ((rc = copy_out(pk.data(), p.remptok + base, N * sizeof(uint32_t))) != SIM_OK) return rc;
-    if ((rc = copy_out(nc.data(), p.n_cls + base, N * sizeof(uint64_t))) != SIM_OK) return rc;
-    if ((rc = copy_out(nj.data(), p.n_join + base, N * sizeof(uint64_t))) != SIM_OK) return rc;
-    if ((rc = copy_out(pj.data(), p.pf_job + base, N * sizeof(uint64_t))) != SIM_OK) return rc;
+    if ((rc = copy_out(tr.data(), p.t_rel + base, N * sizeof(uint32_t))) != SIM_OK) return rc;
+    if ((rc = copy_out(sr.data(), p.rec + base, N * sizeof(ServerRec))) != SIM_OK) return rc;
+    const int64_t t_end = h->steps_done * p.dt;   // clocks are stored relative to the boundary the last run ended at
     for (int g = 0; g < N; ++g) {
+      if (out->t_next) out->t_next[g] = tr[g] == kIdleRel ? kIdle : t_end + static_cast<int64_t>(tr[g]);
+      if (out->iter) out->iter[g] = sr[g].iter;
       const int rem = static_cast<int>(pk[g] & 0xFFFFu);
       if (out->rem) out->rem[g] = rem;
       if (out->ptok) out->ptok[g] = static_cast<int>((pk[g] >> 16) & 0x1FFFu);
-      if (out->pfjob) out->pfjob[g] = rem ? pj[g] : 0;
+      if (out->pfjob) out->pfjob[g] = rem ? sr[g].pf_job : 0;
       int nd = 0;
       for (int k = 0; k < kMaxK; ++k) {
-        const uint8_t c = static_cast<uint8_t>(nc[g] >> (8 * k));
+        const uint8_t c = static_cast<uint8_t>(sr[g].n_cls >> (8 * k));
         if (out->n_cls) out->n_cls[g * kMaxK + k] = c;
-        if (out->n_join) out->n_join[g * kMaxK + k] = static_cast<uint8_t>(nj[g] >> (8 * k));
+        if (out->n_join) out->n_join[g * kMaxK + k] = static_cast<uint8_t>(sr[g].n_join >> (8 * k));
         nd += c;
       }
       if (out->n_dec) out->n_dec[g] = nd;
@@ -691,7 +685,7 @@ int sim_snapshot(sim_t *h, int r, sim_state_t *out, void *hip_stream)
       if ((rc = copy_out(j.data(), p.job + base * BS, j.size() * sizeof(uint64_t))) != SIM_OK) return rc;
       for (int g = 0; g < N; ++g) {
         int nd = 0;
-        for (int k = 0; k < kMaxK; ++k) nd += static_cast<uint8_t>(nc[g] >> (8 * k));
+        for (int k = 0; k < kMaxK; ++k) nd += static_cast<uint8_t>(sr[g].n_cls >> (8 * k));
         for (int s = 0; s < B; ++s) {
           const size_t i = static_cast<size_t>(g) * B + s, d = static_cast<size_t>(g) * BS + s;
           if (out->fin) out->fin[i] = s < nd ? f[d] : 0;

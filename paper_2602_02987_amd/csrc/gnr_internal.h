@@ -20,6 +20,7 @@ constexpr int kNTally = SIM_NTALLY;
 constexpr int kNGlobal = SIM_NGLOBAL;
 constexpr int kTallyWords = kMaxK * kNTally + kNGlobal;  // per replication, uint64
 constexpr int64_t kIdle = INT64_MAX;
+constexpr uint32_t kIdleRel = 0xFFFFFFFFu;   // the same in a server's stored clock (see Params::t_rel)
 constexpr int kAdmChunk = 256;    // admissions decided per gate pass
 constexpr int kMaxTbtBins = 256;  // width of the on-chip time-between-tokens histogram window
 
@@ -34,6 +35,14 @@ constexpr uint32_t kNever = 0xFFFFFFFFu;   // deadline of a request that never a
 constexpr int kStreamPatienceP = 2;        // random streams: 0 arrivals, 1 lengths, 2+k prefill-queue patience of class k,
 constexpr int kStreamPatienceD = 10;       // 10 decode-buffer patience (word 0) and group of the randomized routers (word 1)
 constexpr int kStreamSelect = 11;          // 11, 12: class selection of the weighted router in the solo / mixed pool
+
+// A server's record: what an event of the server reads and writes, in one 32-byte piece of memory.
+struct alignas(32) ServerRec {
+  uint64_t n_cls, n_join;     // decodes per class (8 x uint8 packed); of those, not yet part of the running batch
+  uint64_t pf_job;            // request in prefill service
+  uint32_t iter;              // iterations completed and tallied (at the end of a launch: completed)
+  uint32_t next_fin;          // the first iteration in which one of its decodes ends (any value while it has none)
+};
 
 // Everything a kernel needs, passed by value.
 struct Params {
@@ -66,11 +75,9 @@ struct Params {
   const uint16_t *len_tab;    // [K][2][65536]: in, out
   const uint16_t *pat_tab;    // [K][65536] patience in steps (abandonment only)
   // per-server state, [R][N]
-  int64_t *t_next;
-  uint32_t *iter;
+  ServerRec *rec;
+  uint32_t *t_rel;            // end of the running iteration, ns after the boundary the last launch ended at (kIdleRel: idle)
   uint32_t *remptok;          // prompt tokens left | tokens in the running chunk << 16 | class << 29
-  uint64_t *pf_job;
-  uint64_t *n_cls, *n_join;   // 8 x uint8 packed
   // decode slots, [R][N][BS]; slots 0..n_dec-1 of a server are occupied
   uint32_t *fin;
   uint64_t *job;
@@ -108,7 +115,7 @@ int launch_reset(const Params &p, int reps, void *stream);
 int launch_steps(const Params &p, int reps, int threads, size_t lds_bytes, uint32_t step_begin, uint32_t n_steps,
                  void *stream);
 int launch_reduce(const Params &p, int reps, void *stream);
-int launch_digest(const Params &p, int reps, void *stream);
+int launch_digest(const Params &p, int reps, int64_t t_end, void *stream);   // t_end: the boundary the last launch ended at, ns
 // the library's static device workspace on the current device (address resolved once per device)
 int static_workspace(void **dev_ptr, size_t *bytes);
 size_t step_lds_bytes(const Params &p);

@@ -92,7 +92,8 @@ __global__ void gnr_reset_kernel(const Params p, const int reps)
   const size_t stride = static_cast<size_t>(gridDim.x) * blockDim.x;
   const size_t t0 = static_cast<size_t>(blockIdx.x) * blockDim.x + threadIdx.x;
   for (size_t i = t0; i < n_srv; i += stride) {
-    p.t_next[i] = kIdle; p.iter[i] = 0; p.remptok[i] = 0; p.pf_job[i] = 0; p.n_cls[i] = 0; p.n_join[i] = 0;
+    p.rec[i] = ServerRec{0, 0, 0, 0, kNever};
+    p.t_rel[i] = kIdleRel; p.remptok[i] = 0;
   }
   for (size_t i = t0; i < n_srv * p.BS; i += stride) p.fin[i] = 0;   // free slots never match an iteration index
   for (size_t i = t0; i < static_cast<size_t>(reps) * CS_WORDS; i += stride) p.cstate[i] = 0;
@@ -135,7 +136,7 @@ __device__ __forceinline__ uint64_t mix64(uint64_t z)
 }
 __device__ __forceinline__ uint64_t chain(uint64_t h, uint64_t w) { return mix64(h + w + 0x9E3779B97F4A7C15ull); }
 
-__global__ void gnr_digest_kernel(const Params p)
+__global__ void gnr_digest_kernel(const Params p, const int64_t t_end)
 {
   __shared__ unsigned long long total;
   const int r = blockIdx.x, tid = threadIdx.x, NT = blockDim.x;
@@ -195,16 +196,18 @@ __global__ void gnr_digest_kernel(const Params p)
     const uint32_t pk = p.remptok[sg];
     const uint32_t rem = pk & 0xFFFFu;
     const uint32_t ptok = (pk >> 16) & 0x1FFFu;
+    const ServerRec sr = p.rec[sg];
+    const uint32_t tr = p.t_rel[sg];
     uint64_t h = chain(4, static_cast<uint64_t>(g));
-    h = chain(h, static_cast<uint64_t>(p.t_next[sg]));
-    h = chain(h, p.iter[sg]);
+    h = chain(h, static_cast<uint64_t>(tr == kIdleRel ? kIdle : t_end + static_cast<int64_t>(tr)));
+    h = chain(h, sr.iter);
     h = chain(h, rem);
     h = chain(h, ptok);
-    h = chain(h, rem ? p.pf_job[sg] : 0ull);
-    h = chain(h, p.n_cls[sg]);
-    h = chain(h, p.n_join[sg]);
+    h = chain(h, rem ? sr.pf_job : 0ull);
+    h = chain(h, sr.n_cls);
+    h = chain(h, sr.n_join);
     d += h;
-    const int nd = static_cast<int>(byte_sum(p.n_cls[sg]));
+    const int nd = static_cast<int>(byte_sum(sr.n_cls));
     for (int j = 0; j < nd; ++j)
       d += chain(chain(chain(5, static_cast<uint64_t>(g)), p.fin[sg * p.BS + j]), p.job[sg * p.BS + j]);
   }
@@ -279,7 +282,7 @@ int launch_steps(const Params &p, int reps, int threads, size_t lds_bytes, uint3
                                              hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(lds_bytes));
     if (e != hipSuccess) return SIM_EHIP;
   }
-  const StepArrays a = {p.arr_thr, p.len_tab, p.t_next, p.iter, p.remptok, p.pf_job, p.n_cls, p.n_join,
+  const StepArrays a = {p.arr_thr, p.len_tab, p.rec,    p.t_rel, p.remptok,
                         p.fin,     p.job,     p.qring,  p.dring, p.cstate, p.tally,  p.hist,
                         p.pat_tab, p.qdl,     p.ddl,    p.cal,   p.dcal,   p.dring_m, p.ddl_m, p.dcal_m};
   hipLaunchKernelGGL(kernel, dim3(reps), dim3(threads), lds_bytes, static_cast<hipStream_t>(stream), p.self, a, p.key0,
@@ -294,9 +297,9 @@ int launch_reduce(const Params &p, int reps, void *stream)
   return hip_ok(hipGetLastError());
 }
 
-int launch_digest(const Params &p, int reps, void *stream)
+int launch_digest(const Params &p, int reps, int64_t t_end, void *stream)
 {
-  hipLaunchKernelGGL(gnr_digest_kernel, dim3(reps), dim3(256), 0, static_cast<hipStream_t>(stream), p);
+  hipLaunchKernelGGL(gnr_digest_kernel, dim3(reps), dim3(256), 0, static_cast<hipStream_t>(stream), p, t_end);
   return hip_ok(hipGetLastError());
 }
 

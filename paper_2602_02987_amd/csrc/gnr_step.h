@@ -1,9 +1,9 @@
 // HIP kernels of the gate-and-route network simulator (gfx950, wave64).
 //
 // One workgroup owns one replication for a whole launch and loops over the steps itself. The servers are
-// handled in blocks of 64 (one per lane); wave w takes the blocks w, w + nwaves, ... in every sweep, and the
-// servers a wave queues for finishing are finished by that wave, so a server's record and slot row are
-// touched by one wave at a time. Class-level counters (queue lengths, occupancies, tallies) live in LDS and
+// handled in blocks of 64 (one per lane); wave w owns the blocks w, w + nwaves, ..., and a server's clock, record and
+// slot row are changed by the wave that owns it, except for the placements of the router. A server is touched only
+// when its batch changes (an event): the identical iterations in between follow from its event time. Class-level counters (queue lengths, occupancies, tallies) live in LDS and
 // are updated with integer atomics, which commute; the lanes of a wave are combined first, because atomics of
 // several lanes on one LDS address serialise. Everything that the policy defines sequentially (order of
 // simultaneous prefill completions, of gate admissions, of routed requests) is reproduced with 64-server
@@ -17,6 +17,14 @@
 namespace gnr {
 
 // ------------------------------------------------------------------ primitives ----
+// x ^ y ^ z in one instruction: left to itself the compiler makes two of every such pair. The arrival draw is one
+// Philox block per server and step, 2.56e9 of them in 1000 steps of 10000 servers x 256 replications: alone they take
+// 3.0 ms there with this instruction, 3.7 ms without.
+__device__ __forceinline__ uint32_t xor3(uint32_t x, uint32_t y, uint32_t z)
+{
+  return static_cast<uint32_t>(__builtin_amdgcn_bitop3_b32(static_cast<int>(x), static_cast<int>(y), static_cast<int>(z), 0x96));
+}
+
 // Philox4x32-10 (Salmon et al., SC'11).
 __device__ __forceinline__ void philox4x32_10(uint32_t k0, uint32_t k1, uint32_t c0, uint32_t c1, uint32_t c2,
                                               uint32_t c3, uint32_t (&w)[4])
@@ -25,8 +33,8 @@ __device__ __forceinline__ void philox4x32_10(uint32_t k0, uint32_t k1, uint32_t
   for (int round = 0; round < 10; ++round) {
     const uint64_t a = static_cast<uint64_t>(0xD2511F53u) * c0;
     const uint64_t b = static_cast<uint64_t>(0xCD9E8D57u) * c2;
-    const uint32_t n0 = static_cast<uint32_t>(b >> 32) ^ c1 ^ k0;
-    const uint32_t n2 = static_cast<uint32_t>(a >> 32) ^ c3 ^ k1;
+    const uint32_t n0 = xor3(static_cast<uint32_t>(b >> 32), c1, k0);
+    const uint32_t n2 = xor3(static_cast<uint32_t>(a >> 32), c3, k1);
     c1 = static_cast<uint32_t>(b);
     c3 = static_cast<uint32_t>(a);
     c0 = n0;
@@ -89,16 +97,27 @@ __device__ __forceinline__ uint32_t pinned(uint32_t v)
   return v;
 }
 
-// Sixteen bytes of a slot row, read with the non-temporal hint: the rows stream through once per completed
-// iteration and are not needed again before they would have left the caches anyway, so they should not push out
-// the per-server records, ring entries and tables that the rest of the step reads (measured on 10000 servers x
-// 256 replications: 2.9 % faster; the same hint on the few slot and request words that are read again when a
-// decode leaves made it slower).
+// Sixteen bytes of a slot row, read with the non-temporal hint: a row is read when one of its decodes ends and not
+// again before it would have left the caches, so it should not push out the server records, ring entries and tables
+// that the rest of the step reads.
 __device__ __forceinline__ uint4 stream_load(const uint32_t *p)
 {
   typedef uint32_t word4 __attribute__((ext_vector_type(4)));
   const word4 x = __builtin_nontemporal_load(reinterpret_cast<const word4 *>(p));
   return make_uint4(x.x, x.y, x.z, x.w);
+}
+
+// Smallest r with r * d >= x, for 0 < x < 2^40 and a quotient below 2^17 (the iterations a server still has to complete
+// before its event, x ns ahead): estimated in single precision (relative error below 2^-21, so off by less than one),
+// then corrected exactly.
+__device__ __forceinline__ uint32_t iterations_left(uint64_t x, uint32_t d)
+{
+  const float xf = static_cast<float>(static_cast<uint32_t>(x >> 16)) * 65536.0f + static_cast<float>(static_cast<uint32_t>(x) & 0xFFFFu);
+  uint32_t r = static_cast<uint32_t>(xf * __builtin_amdgcn_rcpf(static_cast<float>(d)));
+  if (static_cast<uint64_t>(r) * d < x) ++r;
+  if (static_cast<uint64_t>(r) * d < x) ++r;
+  if (r > 0 && static_cast<uint64_t>(r - 1) * d >= x) --r;
+  return r;
 }
 
 __device__ __forceinline__ uint64_t lanes_below() { return (1ull << (threadIdx.x & 63)) - 1ull; }
@@ -157,7 +176,6 @@ constexpr int kEvPerWave = 128;   // servers a wave can queue for finishing; whe
 constexpr int kEvPerWaveSmall = 96, kJobsLdsSmall = 64, kAdmChunkSmall = 64;
 constexpr int kRouteLevels = 4;
 constexpr int kJobsLds = 256;      // requests of a routing pass staged in LDS; later ones are read from the buffer
-constexpr int kMaxPend = 254;     // untallied iterations a server may accumulate (kept in a byte)
 
 struct Lds {
   int32_t *cs;        // [CS_WORDS]
@@ -169,11 +187,11 @@ struct Lds {
   uint64_t *bm_idle;  // [nwords] servers below Mp with no prefill in service (the gate looks at those below M)
   uint64_t *bm_comp;  // [nwords] servers whose prefill completed this step
   uint64_t *bm_busy;  // [nwords] servers running an iteration
-  uint64_t *bm_join;  // [nwords] servers holding decodes that are not part of their untallied iterations
-  uint64_t *bm_due;   // [nwords] servers that completed an iteration this step
-  uint64_t *bm_touch; // [nwords] idle servers that were given work this step
-  uint64_t *bm_flush; // [nwords] servers whose untallied iterations must be tallied at the restart
-  uint64_t *bm_chunk; // [nwords] mixed-group servers whose running iteration carries a prefill chunk
+  uint64_t *bm_pin;   // [nwords] servers given work in the middle of an iteration: their event is the end of that iteration
+  uint64_t *bm_due;   // [nwords] servers known to be at an iteration boundary in this step: their event time is that boundary
+  uint64_t *bm_touch; // [nwords] servers to settle at the end of the step: at their event, or given work in this step
+  uint64_t *bm_fin;   // [nwords] servers whose event is the end of a decode
+  uint64_t *bm_chunk; // [nwords] servers whose running iteration carries a prefill chunk
   uint64_t *jobs;     // [kJobsLds] the first requests a routing pass places, copied from the decode buffer
   uint32_t *pre_lvl;  // [kRouteLevels][nwords] servers of the routed group with at most (level) decodes: per word, then ranks
   uint32_t *pre_c;    // [nwords] exclusive prefix popcounts of bm_comp
@@ -182,13 +200,13 @@ struct Lds {
   uint16_t *adm_slot; // [kAdmChunk] prefill slot (server) that takes the admission of each rank
   uint32_t *lh;       // [2][kLoadBins] servers per decode count: solo group, mixed group
   uint32_t *ev_g;     // [waves][kEvPerWave] servers queued for finishing, per wave
-  uint32_t *ev_q;     // [waves][kEvPerWave] their slot-quad masks
-  uint16_t *stage;    // [waves][128] row halves to scan of the block a wave has open: lane | half << 6 | decodes << 8
-  uint32_t *t32;      // [N] low 32 bits of the end time of the running iteration
-  uint32_t *iter;     // [N] completed iterations
+  uint32_t *ev_q;     // [waves][kEvPerWave] (spare)
+  uint16_t *stage;    // [waves][128] lanes of the queued servers whose slot rows are scanned
+  uint32_t *ev_t;     // [N] time of the server's event, bits 8..39 of the nanoseconds
+  uint32_t *ev_it;    // [N] iterations the server has completed by then (while idle: has completed)
   uint8_t *loads;     // [N] decodes per server
-  uint8_t *pend;      // [N] completed iterations not yet tallied (all with the server's current batch)
-  uint16_t *rem;      // [Mp] prompt tokens left of the prefill a server has in service (0: none)
+  uint8_t *ev_lo;     // [N] time of the event, bits 0..7
+  uint16_t *rem;      // [Mp] prompt tokens left of the prefill in service (0: none) when the running phase began
   uint32_t *live_off; // [K][kAdmChunk] abandonment only: ring offset from the head of the m-th waiting request of a class
   // weighted router only: the class selections of a routing pass
   uint32_t *sel_u;    // [kJobsLds] random word of each selection
@@ -234,19 +252,19 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(bm_idle, uint64_t, nw)
   GNR_TAKE(bm_comp, uint64_t, nw)
   GNR_TAKE(bm_busy, uint64_t, nw)
-  GNR_TAKE(bm_join, uint64_t, nw)
+  GNR_TAKE(bm_pin, uint64_t, nw)
   GNR_TAKE(bm_due, uint64_t, nw)
   GNR_TAKE(bm_touch, uint64_t, nw)
-  GNR_TAKE(bm_flush, uint64_t, nw)
+  GNR_TAKE(bm_fin, uint64_t, nw)
   GNR_TAKE(bm_chunk, uint64_t, nw)
   GNR_TAKE(pre_lvl, uint32_t, kRouteLevels * nw)
   GNR_TAKE(pre_c, uint32_t, nw + 1)
   GNR_TAKE(pre, uint32_t, nw + 1)
   // from here on the offsets depend on the configuration
-  GNR_TAKE(t32, uint32_t, p.N)
-  GNR_TAKE(iter, uint32_t, p.N)
+  GNR_TAKE(ev_t, uint32_t, p.N)
+  GNR_TAKE(ev_it, uint32_t, p.N)
   GNR_TAKE(loads, uint8_t, p.N)
-  GNR_TAKE(pend, uint8_t, p.N)
+  GNR_TAKE(ev_lo, uint8_t, p.N)
   GNR_TAKE(rem, uint16_t, p.Mp)
   GNR_TAKE(tbth, uint64_t, p.K * p.tbt_w)
   GNR_TAKE(live_off, uint32_t, p.dl_rings ? p.K * kAdmChunk : 0)
@@ -362,7 +380,7 @@ __device__ __forceinline__ uint32_t class_field(uint64_t even, uint64_t odd, int
   return static_cast<uint32_t>(((c & 1) ? odd : even) >> (16 * (c >> 1))) & 0xFFFFu;
 }
 
-// Per-lane sums of this step's iteration tallies; folded into the workgroup's totals once per step.
+// Adds the tallies of executed iterations to the workgroup's totals: per lane
 // m executed iterations of duration d whose batch held the per-class decode counts `comp`; lanes with
 // nothing to tally pass m = 0. Uniform control flow (all 64 lanes). The tallies every lane shares are summed
 // over the wave first (same-address LDS atomics serialise); the time-between-tokens histogram, whose bins
@@ -372,19 +390,19 @@ __device__ __forceinline__ void tally_iterations(uint64_t *tl, uint64_t *tbth, i
 {
   if (__ballot(m != 0) == 0) return;
   const int lane = threadIdx.x & 63;
-  const uint64_t md = static_cast<uint64_t>(m) * static_cast<uint64_t>(d);   // < 2^8 * 2^31
-  const uint32_t its = wave_sum32(chunk ? m << 16 : m);                      // m <= 255: both totals fit 16 bits
+  const uint64_t md = static_cast<uint64_t>(m) * static_cast<uint64_t>(d);   // < 2^16 * 2^31
+  const uint32_t its_solo = wave_sum32(chunk ? 0u : m), its_mix = wave_sum32(chunk ? m : 0u);
   const uint64_t busy_solo = wave_sum64(chunk ? 0ull : md), busy_mix = wave_sum64(chunk ? md : 0ull);
   if (lane == 0) {
-    if (its & 0xFFFFu) { lds_add64(&tl[kMaxK * kNTally + SIM_G_ITERS_SOLO], its & 0xFFFFu); lds_add64(&tl[kMaxK * kNTally + SIM_G_BUSY_SOLO], busy_solo); }
-    if (its >> 16) { lds_add64(&tl[kMaxK * kNTally + SIM_G_ITERS_MIX], its >> 16); lds_add64(&tl[kMaxK * kNTally + SIM_G_BUSY_MIX], busy_mix); }
+    if (its_solo) { lds_add64(&tl[kMaxK * kNTally + SIM_G_ITERS_SOLO], its_solo); lds_add64(&tl[kMaxK * kNTally + SIM_G_BUSY_SOLO], busy_solo); }
+    if (its_mix) { lds_add64(&tl[kMaxK * kNTally + SIM_G_ITERS_MIX], its_mix); lds_add64(&tl[kMaxK * kNTally + SIM_G_BUSY_MIX], busy_mix); }
   }
   const int b = hbin(d) - tbt_lo;
 #pragma unroll
   for (int k = 0; k < kMaxK; ++k) {
     if (k < K) {   // wave-uniform
       const uint32_t c = m ? byte_at(comp, k) : 0u;
-      const uint64_t t = wave_sum64(static_cast<uint64_t>(c) * md);   // < 2^7 * 2^39
+      const uint64_t t = wave_sum64(static_cast<uint64_t>(c) * md);   // < 2^7 * 2^47
       if (lane == 0 && t) lds_add64(&tl[k * kNTally + SIM_T_TBT_SUM], t);
       if (c) lds_add64(&tbth[k * tbt_w + b], static_cast<uint64_t>(m) * c);
     }
@@ -446,19 +464,23 @@ __device__ __forceinline__ bool gate_before(const GateKey &x, int k1, const Gate
 struct PrefillEnd { bool done; int k; uint32_t P; int64_t ttft; uint64_t nc; };
 
 // ------------------------------------------------------------------ step kernel ----
-// Iteration tallies are lazy. A server whose batch does not change runs identical iterations, so the
-// completion pass only counts them (`pend`); they are tallied, with their multiplicity, when the batch is
-// about to change: a decode leaves, a decode that joined mid-iteration becomes part of the batch, a prefill
-// is present, work is placed on a server that is at an iteration boundary, or the launch ends.
+// A server whose batch does not change runs identical iterations, so nothing is done for them one by one. What is kept
+// is the server's next event: the end of the iteration at which its batch may change, because a decode ends there, a
+// phase of its prefill ends there (the run of full chunks, then the last chunk) or work that arrived in the middle of an
+// iteration joins there. Between the last event and the next the batch, and with it the iteration time, is fixed: the
+// iterations completed by any time follow from the event time by one division, and they are tallied with their
+// multiplicity when the event comes, when the batch is changed at an iteration boundary before it, or when the launch
+// ends. A step therefore reads one clock per server, and a record and a slot row only where an event has come. On
+// 10000 servers x 256 replications with full batches this took a step from 86 us (every due server's slot row read,
+// 27 % of the rows a step, 6.2 TB/s while it lasted) to 42 us.
 // The arrays of the simulation state, handed to the step kernel by value: pointers that arrive as kernel
 // arguments are known to point to global memory, so their loads and stores are plain global accesses
 // (counted apart from LDS traffic) instead of generic ones that a wait on LDS would also wait for.
 struct StepArrays {
   const uint32_t *arr_thr;
   const uint16_t *len_tab;
-  int64_t *t_next;
-  uint32_t *iter, *remptok;
-  uint64_t *pf_job, *n_cls, *n_join;
+  ServerRec *rec;
+  uint32_t *t_rel, *remptok;
   uint32_t *fin;
   uint64_t *job;
   uint32_t *qring;
@@ -534,19 +556,16 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   const int gate_mode = static_cast<int>(pinned(static_cast<uint32_t>(p.gate_mode)));
   const uint32_t queue_cap = pinned(p.queue_cap), dbuf_cap = pinned(p.dbuf_cap);
 
-  int64_t *t_next = a.t_next + static_cast<size_t>(r) * N;
-  uint32_t *iter_g = a.iter + static_cast<size_t>(r) * N;
+  ServerRec *rec = a.rec + static_cast<size_t>(r) * N;
+  uint32_t *t_rel = a.t_rel + static_cast<size_t>(r) * N;
   uint32_t *remptok = a.remptok + static_cast<size_t>(r) * N;
-  uint64_t *pf_job = a.pf_job + static_cast<size_t>(r) * N;
-  uint64_t *n_cls = a.n_cls + static_cast<size_t>(r) * N;
-  uint64_t *n_join = a.n_join + static_cast<size_t>(r) * N;
   uint32_t *fin = a.fin + static_cast<size_t>(r) * N * BS;
   uint64_t *job = a.job + static_cast<size_t>(r) * N * BS;
   uint32_t *qring = a.qring + static_cast<size_t>(r) * K * queue_cap;
   uint64_t *dring = a.dring + static_cast<size_t>(r) * dbuf_cap;
   uint64_t *hist = a.hist + static_cast<size_t>(r) * 3 * K * kNBin;
   uint32_t *ev_g = L.ev_g + wave * kEvPerWave;
-  uint32_t *ev_q = L.ev_q + wave * kEvPerWave;
+  uint16_t *stage = L.stage + wave * 128;
   // abandonment only
   const uint32_t cal_n = p.cal_mask + 1u;
   uint32_t *qdl = AB ? a.qdl + static_cast<size_t>(r) * K * queue_cap : nullptr;
@@ -579,33 +598,79 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       if constexpr (RR) L.sc[SC_DLEN_M] = L.cs[CS_DCOUNT_M];
     }
   }
+  // ---- a server's clock: the time of its event, 40 bits of the nanoseconds (an event is never set further ahead than
+  //      2^38 ns: an early one only tallies and is set again)
+  auto iteration_ns = [&](int ptok, uint32_t nd) __attribute__((always_inline)) -> uint32_t {   // below 2^31
+    return c0_ns + cpre_ns * static_cast<uint32_t>(ptok) + cdec_ns * nd;
+  };
+  auto chunk_of = [&](int rem) __attribute__((always_inline)) -> int { return rem < chunk_max ? rem : chunk_max; };
+  auto event_time = [&](int g, int64_t X) __attribute__((always_inline)) -> int64_t {   // relative to X
+    return (static_cast<int64_t>(static_cast<int32_t>(L.ev_t[g] - static_cast<uint32_t>(X >> 8))) << 8) +
+           (static_cast<int>(L.ev_lo[g]) - static_cast<int>(X & 255));
+  };
+  auto set_event = [&](int g, int64_t t, uint32_t it) __attribute__((always_inline)) {
+    L.ev_t[g] = static_cast<uint32_t>(t >> 8);
+    L.ev_lo[g] = static_cast<uint8_t>(t & 255);
+    L.ev_it[g] = it;
+  };
+  // How many iterations like the next one (`nd` decodes, a chunk of `rem` prompt tokens left, d ns long) a server runs
+  // before its batch may change; `to_fin`: iterations up to the first end of one of its decodes.
+  auto phase_length = [&](uint32_t nd, int rem, uint32_t d, uint32_t to_fin) __attribute__((always_inline)) -> uint32_t {
+    uint32_t n = static_cast<uint32_t>(274877906944.0f * __builtin_amdgcn_rcpf(static_cast<float>(d)));   // 2^38 ns
+    n = n < 65535u ? n : 65535u;   // (at least 137: an iteration is at most 2e9 ns long)
+    if (nd && to_fin < n) n = to_fin;
+    if (rem > 0) {   // the full chunks before the last one, or the last one
+      uint32_t full = 1;
+      if (rem > chunk_max) {
+        const uint32_t left = static_cast<uint32_t>(rem - 1), c = static_cast<uint32_t>(chunk_max);
+        full = static_cast<uint32_t>(static_cast<float>(left) * __builtin_amdgcn_rcpf(static_cast<float>(c)));
+        if ((full + 1u) * c <= left) ++full;
+        if (full * c > left) --full;
+      }
+      if (full < n) n = full;
+    }
+    return n;
+  };
+  auto bits64 = [](uint64_t *p) __attribute__((always_inline)) { return reinterpret_cast<unsigned long long *>(p); };
+
   for (int i = 0; i < nper; ++i) {
     const int g = i * NT + tid;
     const bool valid = g < N;
-    bool busy = false, joined = false;
+    bool busy = false, pin = false, fin_ev = false, idle_slot = false, chunk = false;
     if (valid) {
-      const uint32_t nd = byte_sum(n_cls[g]);
+      const ServerRec &sr = rec[g];
+      const uint64_t nc = sr.n_cls, nj = sr.n_join;
+      const uint32_t it = sr.iter, nf = sr.next_fin, tr = t_rel[g];
+      const uint32_t nd = byte_sum(nc);
       L.loads[g] = static_cast<uint8_t>(nd);
-      L.pend[g] = 0;
       atomicAdd(&L.lh[(g < M ? kLoadBins : 0) + nd], 1u);
-      const int64_t tn = t_next[g];
-      busy = tn != kIdle;
-      L.t32[g] = static_cast<uint32_t>(tn);
-      L.iter[g] = iter_g[g];
-      joined = n_join[g] != 0;
+      int rem = 0, ptok = 0;
+      if (g < Mp) {   // the prompt tokens left stay in LDS during the launch
+        const uint32_t pk = remptok[g];
+        rem = pk_rem(pk);
+        ptok = pk_ptok(pk);
+        L.rem[g] = static_cast<uint16_t>(rem);
+        idle_slot = rem == 0 && (!IM || static_cast<int>(nd) < B);
+        chunk = ptok > 0;
+      }
+      busy = tr != kIdleRel;
+      const int64_t start = static_cast<int64_t>(step_begin) * dt_ns;   // the boundary the launch begins at
+      if (busy) {
+        // work that is not part of the running iteration joins at its end: that is the server's event then
+        pin = nj != 0 || (rem > 0 && ptok == 0);
+        const uint32_t d = iteration_ns(ptok, nd);
+        const uint32_t n = pin ? 1u : phase_length(nd, ptok > 0 ? rem : 0, d, nf - it);
+        fin_ev = nd && nf == it + n;
+        set_event(g, start + tr + static_cast<int64_t>(n - 1u) * d, it + n);
+      } else {
+        set_event(g, start, it);
+      }
     }
-    bool idle_slot = false, chunk = false;
-    if (valid && g < Mp) {   // the prefill word stays in LDS during the launch: tokens left, and whether a chunk runs
-      const uint32_t pk = remptok[g];
-      L.rem[g] = static_cast<uint16_t>(pk_rem(pk));
-      idle_slot = pk_rem(pk) == 0 && (!IM || static_cast<int>(byte_sum(n_cls[g])) < B);
-      chunk = pk_ptok(pk) > 0;
-    }
-    const uint64_t bi = __ballot(idle_slot), bb = __ballot(busy), bj = __ballot(joined), bc = __ballot(chunk);
+    const uint64_t bi = __ballot(idle_slot), bb = __ballot(busy), bp = __ballot(pin), bc = __ballot(chunk), bf = __ballot(fin_ev);
     const int wi = (i * NT + wave_base) >> 6;
     if (lane == 0 && wi < nwords) {
-      L.bm_idle[wi] = bi; L.bm_busy[wi] = bb; L.bm_join[wi] = bj; L.bm_flush[wi] = 0; L.bm_chunk[wi] = bc;
-      L.bm_due[wi] = 0; L.bm_touch[wi] = 0;   // nothing waits for a restart when a launch begins
+      L.bm_idle[wi] = bi; L.bm_busy[wi] = bb; L.bm_pin[wi] = bp; L.bm_chunk[wi] = bc; L.bm_fin[wi] = bf;
+      L.bm_due[wi] = 0; L.bm_touch[wi] = 0;   // nothing waits to be settled when a launch begins
     }
   }
   __syncthreads();
@@ -668,21 +733,14 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   };
 
   int64_t T = 0;
-  // A server that completed an iteration, or was given work while idle, is restarted lazily: when its block
-  // is opened in the next step's completion pass (same lane, no extra sweep). After the last step of the launch
-  // one more pass over the blocks does only that, and tallies every iteration still untallied.
-  for (uint32_t s = step_begin; s <= step_begin + n_steps; ++s) {
-    const bool final_pass = s == step_begin + n_steps;
+  for (uint32_t s = step_begin; s < step_begin + n_steps; ++s) {
     T = (static_cast<int64_t>(s) + 1) * dt_ns;
-    const uint32_t T32 = static_cast<uint32_t>(T);
-    const int64_t Tp = T - dt_ns;   // the boundary of the previous step: restarts refer to it
-    const uint32_t Tp32 = static_cast<uint32_t>(Tp);
     if (tid < 8) L.acc[tid] = 0;
     // abandonment only: how many waiting requests of class `tid` leave at the start of this step (asked for
     // here, used after the completion pass)
     uint32_t n_leave_p = 0, n_leave_d = 0, n_leave_dm = 0;
     if constexpr (AB) {
-      if (!final_pass && tid < K) {
+      if (tid < K) {
         n_leave_p = atomicExch(&cal[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
         n_leave_d = atomicExch(&dcal[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
         if constexpr (RR) n_leave_dm = atomicExch(&dcal_m[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
@@ -709,87 +767,131 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       }
     };
 
-    // ---- 2. finishing queued servers, one per lane (uniform control flow; lanes beyond the queue idle).
-    //      Tallies the server's untallied iterations and the one that just ended, removes the decodes
-    //      that emitted their last token (slot quads flagged in the queue entry), advances the prefill.
+    // ---- 2. events: one server per lane (uniform control flow; lanes beyond the queue idle). Tallies the iterations
+    //      since the last event, removes the decodes that emitted their last token, advances the prefill. What the
+    //      lanes need of their servers' records is asked for first, together with the slot rows of the servers whose
+    //      event is the end of a decode: eight lanes read a row, 16 bytes per lane and load, eight rows at a time.
     auto drain_events = [&](int nev) __attribute__((always_inline)) {
       for (int e0 = 0; e0 < nev; e0 += 64) {
-        const int e = e0 + lane;
-        const bool active = e < nev;
+        const bool active = e0 + lane < nev;
+        const int g = active ? static_cast<int>(ev_g[e0 + lane]) : 0;
+        const int wi = g >> 6;
+        const uint64_t bit = active ? 1ull << (g & 63) : 0ull;
+        uint64_t nc = 0, nj = 0;
+        uint32_t it_tal = 0;
+        if (active) { nc = rec[g].n_cls; nj = rec[g].n_join; it_tal = rec[g].iter; }
+        const uint32_t it = L.ev_it[g];
+        int nd = active ? static_cast<int>(L.loads[g]) : 0;
+        const int nd_before = nd;
+        const bool has_chunk = L.bm_chunk[wi] & bit, pinned_ev = L.bm_pin[wi] & bit;
+        int rem = active && g < Mp ? static_cast<int>(L.rem[g]) : 0;
+        const bool mixed_now = rem > 0;
+        const int64_t tn = T + event_time(g, T);   // exact completion time
+        const uint64_t nc_before = nc;
+        uint32_t nf = 0;   // new first end of a decode (set when the row was scanned)
+        bool nf_new = false;
+        // ---- the ends of decodes: one leaves per round, highest slot first (the last slot's request moves into its
+        //      place); a second round follows only where several end together
+        bool leaving = L.bm_fin[wi] & bit;
+        for (uint64_t lm = __ballot(leaving); lm; lm = __ballot(leaving)) {
+          const int nrows = __popcll(lm), my_row = __popcll(lm & lanes_below());
+          if (leaving) stage[my_row] = static_cast<uint16_t>(lane);
+          __builtin_amdgcn_wave_barrier();
+          int slot = -1;
+          bool more = false;
+          uint32_t next = 0xFFFFFFFFu;
+          for (int r0 = 0; r0 < nrows; r0 += 8) {   // wave-uniform
+            const int row = r0 + (lane >> 3), l8 = lane & 7;
+            const int owner = row < nrows ? stage[row] : 0;
+            const int o_g = __shfl(g, owner, 64), nd_owner = __shfl(nd, owner, 64);
+            const int o_nd = row < nrows ? nd_owner : 0;
+            const uint32_t o_it = __shfl(it, owner, 64);
+            const uint32_t *frow = fin + static_cast<size_t>(o_g) * BS;
+            uint4 v[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              v[q] = make_uint4(0u, 0u, 0u, 0u);   // (0: an empty slot, never an iteration a decode ends in)
+              if (4 * (l8 + 8 * q) < o_nd) v[q] = stream_load(frow + 4 * (l8 + 8 * q));
+            }
+            int high = -1, count = 0;
+            uint32_t least = 0xFFFFFFFFu;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const uint32_t wv[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
+#pragma unroll
+              for (int w = 0; w < 4; ++w) {
+                const int j = 4 * (l8 + 8 * q) + w;
+                const uint32_t ahead = wv[w] - o_it - 1u;   // (2^32 - 1 for one that ends now, huge for an empty slot)
+                if (wv[w] == o_it && j < o_nd) { high = j; ++count; }
+                least = ahead < least ? ahead : least;
+              }
+            }
+#pragma unroll
+            for (int sh = 1; sh < 8; sh <<= 1) {   // over the eight lanes of the row
+              const int h2 = __shfl_xor(high, sh, 64);
+              const uint32_t l2 = __shfl_xor(least, sh, 64);
+              high = h2 > high ? h2 : high;
+              least = l2 < least ? l2 : least;
+              count += __shfl_xor(count, sh, 64);
+            }
+            const int src = (my_row - r0) << 3;   // back to the lane that owns the server
+            const int my_high = __shfl(high, src & 63, 64), my_count = __shfl(count, src & 63, 64);
+            const uint32_t my_least = __shfl(least, src & 63, 64);
+            if (leaving && my_row >= r0 && my_row < r0 + 8) { slot = my_high; more = my_count > 1; next = my_least; }
+          }
+          if (leaving) {
+            leaving = more;
+            nf_new = true;
+            nf = next < 0x40000000u ? it + 1u + next : kNever;
+            if (slot >= 0) {
+              uint32_t *frow = fin + static_cast<size_t>(g) * BS;
+              uint64_t *jrow = job + static_cast<size_t>(g) * BS;
+              const uint64_t jw = jrow[slot], jl = jrow[nd - 1];
+              const uint32_t fl = frow[nd - 1];
+              const int k = static_cast<int>(jw >> 29) & 7;
+              const uint32_t stamp = static_cast<uint32_t>(jw) & 0x1FFFFFFFu;
+              const uint32_t Pl = (static_cast<uint32_t>(jw >> 32) & 0xFFFFu) + 1, Dl = static_cast<uint32_t>(jw >> 48) + 1;
+              const int64_t e2e = tn - (static_cast<int64_t>(stamp) + 1) * dt_ns;
+              lds_add64(&L.tl[k * kNTally + (mixed_now ? SIM_T_S_DM : SIM_T_S_DS)], 1);
+              atomicSub(&L.cs[(mixed_now ? CS_YM : CS_YS) + k], 1);
+              lds_add64(&L.tl[k * kNTally + SIM_T_TOKP_DEC], Pl);
+              lds_add64(&L.tl[k * kNTally + SIM_T_TOKD_DEC], Dl);
+              lds_add64(&L.tl[k * kNTally + SIM_T_E2E_SUM], static_cast<uint64_t>(e2e));
+              atomicAdd(reinterpret_cast<unsigned long long *>(&hist[(1 * K + k) * kNBin + hbin(e2e)]), 1ull);
+              nc -= 1ull << (8 * k);
+              --nd;
+              if (slot < nd) { frow[slot] = fl; jrow[slot] = jl; }
+              frow[nd] = 0;   // a vacated slot must never match a later iteration index
+            }
+          }
+          __builtin_amdgcn_wave_barrier();
+        }
         uint32_t m = 0;
         int64_t d = 0;
         bool chunk = false;
         uint64_t comp = 0;
         PrefillEnd pe; pe.done = false; pe.k = 0; pe.P = 0; pe.ttft = 0; pe.nc = 0;
         if (active) {
-          const int g = static_cast<int>(ev_g[e]);
-          uint32_t quads = ev_q[e];
-          uint64_t nc = n_cls[g];
-          const uint64_t bit = 1ull << (g & 63);
-          const bool joined = L.bm_join[g >> 6] & bit;
-          const uint64_t nj = joined ? n_join[g] : 0ull;
-          const bool has_chunk = g < Mp && (L.bm_chunk[g >> 6] & bit);
-          const uint32_t it = L.iter[g];
-          int nd = L.loads[g];
-          int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0;
-          const int ptok = has_chunk ? (rem < chunk_max ? rem : chunk_max) : 0;   // the chunk frozen at the start of the iteration
-          const int64_t tn = T + static_cast<int64_t>(static_cast<int32_t>(L.t32[g] - T32));   // exact completion time
-          comp = nc - nj;   // bytewise: no class joins more decodes than it holds
-          d = static_cast<int64_t>(c0_ns + cpre_ns * static_cast<uint32_t>(ptok) + cdec_ns * byte_sum(comp));
-          chunk = ptok > 0;
-          m = static_cast<uint32_t>(L.pend[g]) + 1u;
-          L.pend[g] = 0;
-          const bool mixed_now = rem > 0;
-          const int nd_before = nd;
-          if (quads) {
-            // Highest slot first, so the slot moved into a hole has already been checked.
-            uint32_t *frow = fin + static_cast<size_t>(g) * BS;
-            uint64_t *jrow = job + static_cast<size_t>(g) * BS;
-            while (quads) {
-              const int q = 31 - __clz(quads);
-              quads &= ~(1u << q);
-              const uint4 v = *reinterpret_cast<const uint4 *>(frow + 4 * q);
-              const uint32_t wv[4] = {v.x, v.y, v.z, v.w};
-#pragma unroll
-              for (int w = 3; w >= 0; --w) {
-                const int j = 4 * q + w;
-                if (j < nd && wv[w] == it) {
-                  const uint64_t jw = jrow[j];
-                  const int k = static_cast<int>(jw >> 29) & 7;
-                  const uint32_t stamp = static_cast<uint32_t>(jw) & 0x1FFFFFFFu;
-                  const uint32_t Pl = (static_cast<uint32_t>(jw >> 32) & 0xFFFFu) + 1, Dl = static_cast<uint32_t>(jw >> 48) + 1;
-                  const int64_t e2e = tn - (static_cast<int64_t>(stamp) + 1) * dt_ns;
-                  lds_add64(&L.tl[k * kNTally + (mixed_now ? SIM_T_S_DM : SIM_T_S_DS)], 1);
-                  atomicSub(&L.cs[(mixed_now ? CS_YM : CS_YS) + k], 1);
-                  lds_add64(&L.tl[k * kNTally + SIM_T_TOKP_DEC], Pl);
-                  lds_add64(&L.tl[k * kNTally + SIM_T_TOKD_DEC], Dl);
-                  lds_add64(&L.tl[k * kNTally + SIM_T_E2E_SUM], static_cast<uint64_t>(e2e));
-                  atomicAdd(reinterpret_cast<unsigned long long *>(&hist[(1 * K + k) * kNBin + hbin(e2e)]), 1ull);
-                  nc -= 1ull << (8 * k);
-                  --nd;
-                  if (j < nd) { frow[j] = frow[nd]; jrow[j] = jrow[nd]; }
-                  frow[nd] = 0;   // a vacated slot must never match a later iteration index
-                }
-              }
-            }
-            if (nd != nd_before) {
-              n_cls[g] = nc;
-              L.loads[g] = static_cast<uint8_t>(nd);
-              const int hb = g < M ? kLoadBins : 0;
-              atomicSub(&L.lh[hb + nd_before], 1u);
-              atomicAdd(&L.lh[hb + nd], 1u);
-              if constexpr (IM) {   // a full server (it holds no prefill then) has a slot again
-                if (nd_before == B && g < Mp) atomicOr(reinterpret_cast<unsigned long long *>(&L.bm_idle[g >> 6]), bit);
-              }
+          comp = nc_before - nj;   // bytewise: no class joins more decodes than it holds
+          const int ptok = has_chunk ? chunk_of(rem) : 0;   // the chunk of every iteration since the last event
+          d = static_cast<int64_t>(iteration_ns(ptok, byte_sum(comp)));
+          chunk = has_chunk;
+          m = it - it_tal;
+          if (nd != nd_before) {
+            L.loads[g] = static_cast<uint8_t>(nd);
+            const int hb = g < M ? kLoadBins : 0;
+            atomicSub(&L.lh[hb + nd_before], 1u);
+            atomicAdd(&L.lh[hb + nd], 1u);
+            if constexpr (IM) {   // a full server (it holds no prefill then) has a slot again
+              if (nd_before == B && g < Mp) atomicOr(bits64(&L.bm_idle[wi]), bit);
             }
           }
-          // the prefill advances by the chunk frozen at the start of the iteration
-          if (ptok > 0) {
-            rem -= ptok;
+          // the prefill advances by the chunks of those iterations
+          if (has_chunk) {
+            rem -= static_cast<int>(m) * ptok;
             L.rem[g] = static_cast<uint16_t>(rem);
-            atomicAnd(reinterpret_cast<unsigned long long *>(&L.bm_chunk[g >> 6]), ~bit);   // set again at the restart
             if (rem == 0) {
-              const uint64_t jw = pf_job[g];
+              const uint64_t jw = rec[g].pf_job;
               const int k = static_cast<int>(jw >> 29) & 7;
               const uint32_t stamp = static_cast<uint32_t>(jw) & 0x1FFFFFFFu;
               pe.done = true; pe.k = k; pe.nc = nc;
@@ -803,29 +905,32 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                   lds_add64(&L.tl[k * kNTally + SIM_T_DROP_D], 1);
                   L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
                 } else {
-                const uint32_t Dl = static_cast<uint32_t>(jw >> 48) + 1;
-                fin[static_cast<size_t>(g) * BS + nd] = it + Dl;
-                job[static_cast<size_t>(g) * BS + nd] = jw;
-                n_cls[g] = nc + (1ull << (8 * k));
-                const int hb = g < M ? kLoadBins : 0;
-                atomicSub(&L.lh[hb + nd], 1u);
-                atomicAdd(&L.lh[hb + nd + 1], 1u);
-                ++nd;
-                L.loads[g] = static_cast<uint8_t>(nd);
-                lds_add64(&L.tl[k * kNTally + SIM_T_U_DS], 1);
-                atomicAdd(&L.cs[CS_YS + k], 1);
-                if (nd < B) atomicOr(reinterpret_cast<unsigned long long *>(&L.bm_idle[g >> 6]), bit);
+                  const uint32_t ends = it + static_cast<uint32_t>(jw >> 48) + 1;
+                  fin[static_cast<size_t>(g) * BS + nd] = ends;
+                  job[static_cast<size_t>(g) * BS + nd] = jw;
+                  if (!nf_new) { nf = rec[g].next_fin; nf_new = true; }
+                  if (nd == 0 || ends < nf) nf = ends;
+                  nc += 1ull << (8 * k);
+                  const int hb = g < M ? kLoadBins : 0;
+                  atomicSub(&L.lh[hb + nd], 1u);
+                  atomicAdd(&L.lh[hb + nd + 1], 1u);
+                  ++nd;
+                  L.loads[g] = static_cast<uint8_t>(nd);
+                  lds_add64(&L.tl[k * kNTally + SIM_T_U_DS], 1);
+                  atomicAdd(&L.cs[CS_YS + k], 1);
+                  if (nd < B) atomicOr(bits64(&L.bm_idle[wi]), bit);
                 }
               } else {
-              atomicOr(reinterpret_cast<unsigned long long *>(&L.bm_comp[g >> 6]), bit);
-              atomicOr(reinterpret_cast<unsigned long long *>(&L.bm_idle[g >> 6]), bit);
+                atomicOr(bits64(&L.bm_comp[wi]), bit);
+                atomicOr(bits64(&L.bm_idle[wi]), bit);
               }
             }
           }
-          if (joined) {
-            n_join[g] = 0;
-            atomicAnd(reinterpret_cast<unsigned long long *>(&L.bm_join[g >> 6]), ~bit);
-          }
+          if (pinned_ev) atomicAnd(bits64(&L.bm_pin[wi]), ~bit);
+          if (nc != nc_before) rec[g].n_cls = nc;
+          if (nj) rec[g].n_join = 0;
+          rec[g].iter = it;
+          if (nf_new) rec[g].next_fin = nf;
         }
         tally_iterations(L.tl, L.tbth, tbt_w, tbt_lo, K, m, d, chunk, comp);
         // a prefill that ended: completion count, recognised prompt tokens, time to first token; the
@@ -848,210 +953,95 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       }
     };
 
-    // ---- completion pass, one round of 64 servers (one per lane) at a time.
-    //      open_round: due test; the slot rows of the due servers are listed in `stage`, 64 slots (half a row)
-    //      per entry. issue_batch: eight lanes read one entry, 16 bytes per lane and load; a group is eight
-    //      entries, a batch Q groups. process_group: the finish words are compared with the server's iteration
-    //      index; the hit masks travel back to the owning lanes. The first batch of a block is issued when the
-    //      block is opened, before the arrivals of the block are drawn. finalize: a server whose batch changes,
-    //      or that carries a prefill, is queued for finishing; for any other the iteration is only counted.
-    //      Slots beyond a server's decode count never hold a future iteration index (they are cleared when
-    //      vacated), so the comparison needs no occupancy mask.
+    // ---- settling, one queued server per lane: the servers at their event and those given work in this step. Work that
+    //      arrived in the middle of an iteration moves the event up to the end of that iteration; if it arrived at
+    //      an iteration boundary the iterations before it are tallied. With `last` (no more work follows in this
+    //      step) a server at a boundary, or idle, starts its next iteration and gets its next event.
+    auto settle = [&](int nset, bool last) __attribute__((always_inline)) {
+      for (int e0 = 0; e0 < nset; e0 += 64) {
+        const bool active = e0 + lane < nset;
+        const int g = active ? static_cast<int>(ev_g[e0 + lane]) : 0;
+        const int wi = g >> 6;
+        const uint64_t bit = active ? 1ull << (g & 63) : 0ull;
+        uint64_t nc = 0, nj = 0;
+        uint32_t it_tal = 0, nf = 0;
+        if (active) { nc = rec[g].n_cls; nj = rec[g].n_join; it_tal = rec[g].iter; nf = rec[g].next_fin; }
+        const bool busy = L.bm_busy[wi] & bit, pin = L.bm_pin[wi] & bit, had_chunk = L.bm_chunk[wi] & bit;
+        bool due = L.bm_due[wi] & bit;
+        const uint32_t nd = L.loads[g];
+        int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0;
+        uint32_t it = L.ev_it[g];
+        int64_t rel = event_time(g, T);
+        uint32_t m = 0;
+        int64_t d = 0;
+        uint64_t comp = 0;
+        if (busy && !due && !pin) {   // (lanes without a server have no bits)
+          comp = nc - nj;
+          const int ptok = had_chunk ? chunk_of(rem) : 0;
+          const uint32_t dur = iteration_ns(ptok, byte_sum(comp));
+          const uint32_t left = iterations_left(static_cast<uint64_t>(rel), dur);
+          const int64_t last_end = rel - static_cast<int64_t>(static_cast<uint64_t>(left) * dur);   // of the latest completed iteration
+          if (last_end > -static_cast<int64_t>(dt_ns)) {   // it ended in this step: a boundary
+            it -= left;
+            m = it - it_tal;
+            d = static_cast<int64_t>(dur);
+            rem -= static_cast<int>(m) * ptok;
+            if (ptok > 0) L.rem[g] = static_cast<uint16_t>(rem);
+            rec[g].iter = it;
+            if (nj) rec[g].n_join = 0;
+            rel = last_end;
+            due = true;
+            if (!last) { set_event(g, T + rel, it); atomicOr(bits64(&L.bm_due[wi]), bit); }
+          } else {
+            it -= left - 1u;
+            set_event(g, T + last_end + dur, it);
+            atomicOr(bits64(&L.bm_pin[wi]), bit);
+            if (nd && nf == it) atomicOr(bits64(&L.bm_fin[wi]), bit); else atomicAnd(bits64(&L.bm_fin[wi]), ~bit);
+          }
+        }
+        if (last && active && (due || !busy)) {
+          const int ptok = rem > 0 ? chunk_of(rem) : 0;
+          bool runs = true, fin_ev = false;
+          if (ptok == 0 && nd == 0) {
+            runs = false;
+            set_event(g, T + rel, it);
+          } else {
+            // back-to-back after a completion, otherwise from the step boundary
+            const uint32_t dur = iteration_ns(ptok, nd);
+            const uint32_t n = phase_length(nd, rem, dur, nf - it);
+            fin_ev = nd && nf == it + n;
+            set_event(g, T + (due ? rel : 0) + static_cast<int64_t>(static_cast<uint64_t>(n) * dur), it + n);
+          }
+          if (runs != busy) { if (runs) atomicOr(bits64(&L.bm_busy[wi]), bit); else atomicAnd(bits64(&L.bm_busy[wi]), ~bit); }
+          if ((ptok > 0) != had_chunk) { if (ptok > 0) atomicOr(bits64(&L.bm_chunk[wi]), bit); else atomicAnd(bits64(&L.bm_chunk[wi]), ~bit); }
+          if (fin_ev) atomicOr(bits64(&L.bm_fin[wi]), bit); else atomicAnd(bits64(&L.bm_fin[wi]), ~bit);
+        }
+        tally_iterations(L.tl, L.tbth, tbt_w, tbt_lo, K, m, d, had_chunk, comp);
+      }
+    };
+
+    // ---- completion pass: which servers have their event in this step (one clock per server and step is all that is
+    //      read), and the arrivals
     {
-      constexpr int Q = 5;   // groups of eight row halves in flight
-      const int l8 = lane & 7, grp = lane >> 3;
       const uint64_t below = lanes_below();
-      uint16_t *stage = L.stage + wave * 128;
-      int nev = 0;          // servers queued by this wave (wave-uniform)
-      int ne = 0;           // row halves listed for the open block (wave-uniform)
-      bool o_due = false, o_must = false, o_scan = false, o_big = false;   // owner-lane state of the open round
-      int o_rank = 0, o_nd = 0, o_pend = 0;
-      uint32_t o_it = 0, o_q = 0;
-      uint4 v[Q][2];
-      uint32_t vit[Q];
-
-      auto open_round = [&](int wi) __attribute__((always_inline)) {
-        const int gw = wi << 6;
-        const int g = gw + lane;
-        const uint64_t lbit = 1ull << lane;
-        const bool valid = g < N;
-        // everything the block needs from LDS is read here in one go: a chain of dependent LDS round trips
-        // costs far more than a few reads that turn out unused
-        const uint64_t busy_word = L.bm_busy[wi], due_prev = L.bm_due[wi], touch_prev = L.bm_touch[wi];
-        const uint64_t flush_prev = L.bm_flush[wi], idle_word = L.bm_idle[wi], chunk_word = L.bm_chunk[wi];
-        uint64_t join_word = L.bm_join[wi];
-        uint32_t t32v = valid ? L.t32[g] : 0u;
-        const uint32_t iter_v = valid ? L.iter[g] : 0u;
-        const int nd = valid ? static_cast<int>(L.loads[g]) : 0;
-        int pend = valid ? static_cast<int>(L.pend[g]) : 0;
-        const int rem_v = g < Mp ? static_cast<int>(L.rem[g]) : 0;
-        bool busy = busy_word & lbit;
-        // ---- (re)start of the servers that completed an iteration or were given work in the previous step.
-        //      Untallied iterations are tallied before the batch changes, and all of them when the launch ends.
-        const bool flush = valid && ((flush_prev & lbit) || (final_pass && pend != 0));
-        if (__ballot(flush)) {
-          uint32_t m = 0;
-          int64_t d = 0;
-          uint64_t comp = 0;
-          bool unjoin = false;
-          if (flush) {
-            const uint64_t nc = n_cls[g];
-            const bool joined = join_word & lbit;
-            const uint64_t nj = joined ? n_join[g] : 0ull;
-            comp = nc - nj;   // bytewise: no class joins more decodes than it holds
-            d = static_cast<int64_t>(c0_ns + cdec_ns * byte_sum(comp));   // untallied iterations never hold a chunk
-            m = static_cast<uint32_t>(pend);
-            pend = 0;
-            L.pend[g] = 0;
-            unjoin = (flush_prev & lbit) && joined;   // the decodes placed at the boundary joined the batch there
-            if (unjoin) n_join[g] = 0;
-          }
-          tally_iterations(L.tl, L.tbth, tbt_w, tbt_lo, K, m, d, false, comp);
-          const uint64_t unjoin_m = __ballot(unjoin);
-          if (unjoin_m) {   // this wave alone works on the block's words
-            join_word &= ~unjoin_m;
-            if (lane == 0) L.bm_join[wi] = join_word;
-          }
-          if (lane == 0 && flush_prev) L.bm_flush[wi] = 0;
+      const uint32_t T_hi = static_cast<uint32_t>(T >> 8), T_lo = static_cast<uint32_t>(T) & 255u;
+      int nev = 0;   // servers queued by this wave (wave-uniform)
+      for (int blk = wave; blk < nwords; blk += nwaves) {
+        const int g = (blk << 6) + lane;
+        const bool busy = (L.bm_busy[blk] >> lane) & 1ull;
+        const int32_t diff = g < N ? static_cast<int32_t>(L.ev_t[g] - T_hi) : 1;
+        bool due = busy && diff < 0;
+        if (__ballot(busy && diff == 0)) due = due || (busy && diff == 0 && L.ev_lo[g] <= T_lo);
+        const uint64_t dm = __ballot(due);
+        if (lane == 0) { L.bm_due[blk] = dm; L.bm_touch[blk] = dm; L.bm_comp[blk] = 0; }
+        if (dm) {
+          if (due) ev_g[nev + __popcll(dm & below)] = static_cast<uint32_t>(g);
+          nev += __popcll(dm);
         }
-        const uint64_t todo = due_prev | touch_prev;
-        if (todo) {
-          bool chunk_now = false;
-          if (todo & lbit) {
-            const int ptok = rem_v > 0 ? (rem_v < chunk_max ? rem_v : chunk_max) : 0;
-            chunk_now = ptok > 0;
-            if (ptok == 0 && nd == 0) {
-              busy = false;
-            } else {
-              // back-to-back after a completion, otherwise from the step boundary; only the low 32 bits of the
-              // clock are kept and an iteration lasts less than 2^31 ns, so 32-bit arithmetic is exact here
-              const uint32_t dur = c0_ns + cpre_ns * static_cast<uint32_t>(ptok) + cdec_ns * static_cast<uint32_t>(nd);
-              t32v = ((due_prev & lbit) ? t32v : Tp32) + dur;
-              L.t32[g] = t32v;
-              busy = true;
-            }
-          }
-          const uint64_t nb = __ballot(busy), nchunk = __ballot(chunk_now);
-          if (lane == 0) {
-            if (nb != busy_word) L.bm_busy[wi] = nb;
-            if (gw < Mp) L.bm_chunk[wi] = (chunk_word & ~todo) | nchunk;
-          }
-        }
-        o_due = false; o_it = 0; o_nd = 0; o_pend = 0; o_q = 0;
-        if (final_pass) {   // only the restarts: the launch ends here
-          if (lane == 0) { L.bm_due[wi] = 0; L.bm_touch[wi] = 0; }
-          o_must = o_scan = o_big = false;
-          ne = 0;
-          return;
-        }
-        // ---- which servers complete an iteration in this step
-        o_due = busy && static_cast<int32_t>(t32v - T32) <= 0;
-        if (o_due) {
-          o_it = iter_v + 1;
-          L.iter[g] = o_it;
-          o_nd = nd;
-          o_pend = pend;
-        }
-        // (with immediate decode the bitmap marks the servers the gate may admit to: a full one is not in it)
-        const bool prefill_here = IM ? rem_v != 0 : (g < Mp && !(idle_word & lbit));
-        o_must = o_due && ((join_word & lbit) || prefill_here || o_pend >= kMaxPend);
-        o_scan = o_due && o_nd > 0;
-        o_big = o_scan && o_nd > 64;   // the row's second half holds decodes too
-        const uint64_t dm = __ballot(o_due), sm = __ballot(o_scan), bg = __ballot(o_big);
-        o_rank = __popcll(sm & below) + __popcll(bg & below);
-        ne = __popcll(sm) + __popcll(bg);
-        if (o_scan) {   // entry: lane | second half << 6 | decode count << 8
-          const uint32_t e = static_cast<uint32_t>(lane) | (static_cast<uint32_t>(o_nd) << 8);
-          stage[o_rank] = static_cast<uint16_t>(e);
-          if (o_big) stage[o_rank + 1] = static_cast<uint16_t>(e | 64u);
-        }
-        if (lane == 0) {
-          L.bm_due[wi] = dm;
-          L.bm_touch[wi] = 0;
-          L.bm_comp[wi] = 0;
-        }
-      };
-      // Groups g0 .. g0+Q-1 of the open block go into the Q register sets. The LDS reads of all of them are
-      // issued together, then the loads, then the shuffles that fetch the iteration indices (needed only when
-      // the words are compared): two LDS round trips per batch instead of two per group.
-      auto issue_batch = [&](int wi, int g0) __attribute__((always_inline)) {
-        const uint32_t gw = static_cast<uint32_t>(wi) << 6;
-        uint32_t e[Q];
-#pragma unroll
-        for (int t = 0; t < Q; ++t) {
-          const int pidx = 8 * (g0 + t) + grp;
-          e[t] = pidx < ne ? stage[pidx] : 0u;   // no entry: decode count 0, nothing is loaded
-        }
-#pragma unroll
-        for (int t = 0; t < Q; ++t) {
-          const uint32_t sid = e[t] & 63u, half = (e[t] >> 6) & 1u;
-          const int nds = static_cast<int>(e[t] >> 8);
-          const int q0 = 16 * static_cast<int>(half) + l8;   // this lane's quads of the row: q0 and q0 + 8
-          const uint32_t off = (gw + sid) * static_cast<uint32_t>(BS) + 4u * q0;
-          // a register that is not loaded holds zeros, which no iteration index equals (the first is 1)
-          v[t][0] = v[t][1] = make_uint4(0u, 0u, 0u, 0u);
-          if (4 * q0 < nds) v[t][0] = stream_load(fin + off);
-          if (4 * q0 + 32 < nds) v[t][1] = stream_load(fin + off + 32u);
-        }
-#pragma unroll
-        for (int t = 0; t < Q; ++t) {
-          const uint32_t it_owner = __shfl(o_it, static_cast<int>(e[t] & 63u), 64);   // every lane takes part
-          vit[t] = 8 * (g0 + t) + grp < ne ? it_owner : 0xFFFFFFFFu;                  // no entry: matches nothing
-        }
-      };
-      auto process_group = [&](int t, int gi) __attribute__((always_inline)) {
-        const uint32_t it = vit[t];
-        const bool m0 = v[t][0].x == it || v[t][0].y == it || v[t][0].z == it || v[t][0].w == it;
-        const bool m1 = v[t][1].x == it || v[t][1].y == it || v[t][1].z == it || v[t][1].w == it;
-        if (__ballot(m0 || m1)) {   // a decode emits its last token: rare
-          const uint64_t bal0 = __ballot(m0), bal1 = __ballot(m1);
-          const int d0 = o_rank - 8 * gi, d1 = d0 + 1;   // this owner's entries, counted within the group
-          if (o_scan && static_cast<unsigned>(d0) < 8u)
-            o_q |= (static_cast<uint32_t>(bal0 >> (8 * d0)) & 0xFFu) | ((static_cast<uint32_t>(bal1 >> (8 * d0)) & 0xFFu) << 8);
-          if (o_big && static_cast<unsigned>(d1) < 8u)
-            o_q |= ((static_cast<uint32_t>(bal0 >> (8 * d1)) & 0xFFu) | ((static_cast<uint32_t>(bal1 >> (8 * d1)) & 0xFFu) << 8)) << 16;
-        }
-      };
-      auto finalize = [&](int wi) __attribute__((always_inline)) {
-        const int g = (wi << 6) + lane;
-        const bool event = o_due && (o_must || o_q != 0);
-        if (o_due && !event) L.pend[g] = static_cast<uint8_t>(o_pend + 1);
-        const uint64_t evm = __ballot(event);
-        if (evm) {
-          if (event) {
-            const int slot = nev + __popcll(evm & below);
-            ev_g[slot] = static_cast<uint32_t>(g);
-            ev_q[slot] = o_q;
-          }
-          nev += __popcll(evm);
-        }
-      };
-
-      // wave w owns the 64-server blocks w, w + nwaves, w + 2 nwaves, ...
-      int blk = wave;
-      if (blk < nwords) { open_round(blk); issue_batch(blk, 0); }
-      while (blk < nwords) {
-        const int nblk = blk + nwaves;
-        if (!final_pass) {
-          const int g = (blk << 6) + lane;
-          if (g < N) arrivals(g);
-        }
-        for (int g0 = 0; 8 * g0 < ne; g0 += Q) {
-          if (g0 > 0) issue_batch(blk, g0);   // the first batch of a block was issued when the block was opened
-#pragma unroll
-          for (int t = 0; t < Q; ++t)
-            if (8 * (g0 + t) < ne) process_group(t, g0 + t);   // wave-uniform
-        }
-        finalize(blk);
-        if (nev > kEvPerWave - 64 || nblk >= nwords) {   // before the next block is opened: fewer live registers
-          drain_events(nev);
-          nev = 0;
-        }
-        if (nblk < nwords) { open_round(nblk); issue_batch(nblk, 0); }   // its loads travel while the arrivals are drawn
-        blk = nblk;
+        if (g < N) arrivals(g);
+        if (nev > kEvPerWave - 64 || blk + nwaves >= nwords) { drain_events(nev); nev = 0; }
       }
     }
-    if (final_pass) break;   // wave-uniform; the barrier after the loop follows
     __syncthreads();
 
     // ================= arrivals into the class queues; ranks of completions and idle slots =================
@@ -1134,7 +1124,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       c_solo = false;
       c_dl = kNever;
       const int g = c_active ? select_bit(L.bm_comp, L.pre_c, nwords_m, j) : 0;
-      c_jw = pf_job[g];   // (slot 0 for the lanes past the end: read, not used)
+      c_jw = rec[g].pf_job;   // (slot 0 for the lanes past the end: read, not used)
       uint32_t w[4];
       philox4x32_10(key0, key1, s, static_cast<uint32_t>(kStreamPatienceD), static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
       c_k = static_cast<int>(c_jw >> 29) & 7;
@@ -1279,7 +1269,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         bool kept = false;
         if (active) {
           const int g = select_bit(L.bm_comp, L.pre_c, nwords_m, j);
-          const uint64_t jw = pf_job[g];
+          const uint64_t jw = rec[g].pf_job;
           k = static_cast<int>(jw >> 29) & 7;
           kept = dcount + j < dbuf_cap;
           if (kept) {
@@ -1676,7 +1666,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           // updated here a word at a time (no atomics).
           // A wave takes a word, a lane a slot; the slot of every admission rank goes into a table.
           for (int w = wave; w < nwords_m; w += nwaves) {   // wave-uniform
-            const uint64_t idle_all = L.bm_idle[w], busy_w = L.bm_busy[w], touch_w = L.bm_touch[w];
+            const uint64_t idle_all = L.bm_idle[w], touch_w = L.bm_touch[w];
             const uint64_t idle = idle_all & bits_below(w, M);   // the gate admits to the mixed group only
             const int before = static_cast<int>(L.pre[w]);   // idle slots in the words before this one
             uint64_t adm = 0;
@@ -1687,7 +1677,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 L.adm_slot[before + __popcll(adm & lanes_below())] = static_cast<uint16_t>((w << 6) + lane);
               if (lane == 0) {
                 L.bm_idle[w] = idle_all & ~adm;
-                L.bm_touch[w] = touch_w | (adm & ~busy_w);   // an idle server is given work
+                L.bm_touch[w] = touch_w | adm;
               }
             }
           }
@@ -1932,7 +1922,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 const uint32_t dl = qdl[static_cast<size_t>(a_k) * queue_cap + pos];
                 if (dl != kNever) atomicSub(&cal[static_cast<size_t>(a_k) * cal_n + (dl & p.cal_mask)], 1u);
               }
-              if (L.loads[a_g]) a_nc = n_cls[a_g];   // (before this pass's placements on the server)
+              if (L.loads[a_g]) a_nc = rec[a_g].n_cls;   // (before this pass's placements on the server)
             }
           }
           if (nadm == kAdmChunk && nidle > kAdmChunk) {   // rare: more idle slots than one pass serves
@@ -1988,14 +1978,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             philox4x32_10(key0, key1, s, 1u, static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
             const uint32_t Pl = a.len_tab[(static_cast<size_t>(k) * 2 + 0) * kTableSize + (w[0] >> 16)];
             const uint32_t Dl = a.len_tab[(static_cast<size_t>(k) * 2 + 1) * kTableSize + (w[1] >> 16)];
-            pf_job[g] = static_cast<uint64_t>(a_stamp) | (static_cast<uint64_t>(k) << 29) |
-                        (static_cast<uint64_t>(Pl - 1) << 32) | (static_cast<uint64_t>(Dl - 1) << 48);
+            rec[g].pf_job = static_cast<uint64_t>(a_stamp) | (static_cast<uint64_t>(k) << 29) |
+                            (static_cast<uint64_t>(Pl - 1) << 32) | (static_cast<uint64_t>(Dl - 1) << 48);
             // an idle prefill slot implies that the running iteration holds no chunk
             L.rem[g] = static_cast<uint16_t>(Pl);
-            const uint64_t bit = 1ull << (g & 63);
-            // at an iteration boundary the next iteration carries a chunk: tally the untallied ones first
-            if ((L.bm_busy[g >> 6] & bit) && (L.bm_due[g >> 6] & bit) && L.pend[g])
-              atomicOr(reinterpret_cast<unsigned long long *>(&L.bm_flush[g >> 6]), bit);
           }
           wave_sum_by_class(a_active, a_k, K, wait, &L.tl[SIM_T_WAIT_STEPS], kNTally);
           uint64_t even, odd;   // co-resident decodes switch solo -> mixed
@@ -2063,8 +2049,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             const uint64_t bit = 1ull << lane;
             // what the block needs from LDS is read in one go
             const int n_own = g < N ? static_cast<int>(L.loads[g]) : 0;   // decodes of this lane's server
-            const int pend_own = g < N ? static_cast<int>(L.pend[g]) : 0;
             const uint64_t busy_word = L.bm_busy[wi], due_word = L.bm_due[wi], idle_word = L.bm_idle[wi];
+            const uint64_t pin_word = L.bm_pin[wi], chunk_word = L.bm_chunk[wi];
             int pre_r[kRouteLevels];
 #pragma unroll
             for (int t = 0; t < kRouteLevels; ++t)
@@ -2075,54 +2061,67 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             const int tend = g < N ? first + my_n : 0;
             const int tmin = first + (n_own > my_lmin ? n_own - my_lmin : 0);
             if (__ballot(tmin < tend) == 0) continue;   // wave-uniform
-            const bool busy0 = busy_word & bit, at_boundary = due_word & bit;
-            const bool mid = busy0 && !at_boundary;   // a job placed now joins at the next restart
-            const bool has_prefill = g < Mp && !(idle_word & bit);
-            // the new decode is not part of the iterations still to be tallied for this server
-            const bool joins = mid || (at_boundary && pend_own != 0);
+            int q_r[kRouteLevels];
             bool got = false, got_last = false;
 #pragma unroll
             for (int t = 0; t < kRouteLevels; ++t) {
-              if (t < nl) {   // wave-uniform
-                const bool in = t >= tmin && t < tend;
-                const uint64_t bal = __ballot(in);
-                if (bal) {
-                  const int q = pre_r[t] + __popcll(bal & lanes_below());
-                  if (in && q < take_r[t]) {
-                    got = true;
-                    got_last = t == tend - 1;
-                    const int j = w_r[t] + q;   // position in this pass
-                    uint64_t jw;
-                    if (j < kJobsLds) {
-                      jw = L.jobs[j];
-                    } else {
-                      uint32_t pos = dhead0 + static_cast<uint32_t>(next + j);
-                      if (pos >= dbuf_cap) pos -= dbuf_cap;
-                      if (pos >= dbuf_cap) pos -= dbuf_cap;
-                      jw = dring[pos];
-                    }
-                    const int k = static_cast<int>(jw >> 29) & 7;
-                    const uint32_t Dl = static_cast<uint32_t>(jw >> 48) + 1;
-                    const int nd = my_lmin + (t - first);   // the server holds exactly this many decodes by now
-                    fin[static_cast<size_t>(g) * BS + nd] = L.iter[g] + Dl + (mid ? 1u : 0u);
-                    job[static_cast<size_t>(g) * BS + nd] = jw;
-                    atomicAdd(reinterpret_cast<unsigned long long *>(&n_cls[g]), 1ull << (8 * k));
-                    if (joins) atomicAdd(reinterpret_cast<unsigned long long *>(&n_join[g]), 1ull << (8 * k));
-                    lds_add64(&L.tl[k * kNTally + (has_prefill ? SIM_T_U_DM : SIM_T_U_DS)], 1);
-                    atomicAdd(&L.cs[(has_prefill ? CS_YM : CS_YS) + k], 1);
-                    atomicSub(&L.cs[CS_QD + k], 1);
-                  }
-                }
-              }
+              const bool in = t < nl && t >= tmin && t < tend;
+              q_r[t] = pre_r[t] + __popcll(__ballot(in) & lanes_below());
+              if (!in || q_r[t] >= take_r[t]) q_r[t] = -1;
+              got = got || q_r[t] >= 0;
+              if (t == tend - 1) got_last = q_r[t] >= 0;
             }
-            // marks for the next completion pass: decodes that are not part of the untallied iterations;
-            // untallied iterations to tally before the restart; idle servers that now hold work
-            const uint64_t join_m = __ballot(got && joins), flush_m = __ballot(got && joins && !mid);
-            const uint64_t touch_m = __ballot(got && !busy0);
-            if (lane == 0) {   // fire and forget: nothing here waits for the old words
-              if (join_m) atomicOr(reinterpret_cast<unsigned long long *>(&L.bm_join[wi]), join_m);
-              if (flush_m) atomicOr(reinterpret_cast<unsigned long long *>(&L.bm_flush[wi]), flush_m);
-              if (touch_m) atomicOr(reinterpret_cast<unsigned long long *>(&L.bm_touch[wi]), touch_m);
+            if (__ballot(got)) {   // wave-uniform
+              const bool busy0 = busy_word & bit;
+              const bool runs = busy0 && !(due_word & bit);   // not known to be at a boundary: the settling works it out
+              const bool has_prefill = g < Mp && !(idle_word & bit);
+              if (got) {
+                // iterations the server has completed, and whether it is in the middle of one: a job placed now then
+                // joins at the next restart
+                uint32_t it = L.ev_it[g];
+                bool mid = runs;
+                if (runs && (pin_word & bit)) {
+                  it -= 1u;
+                } else if (runs) {
+                  const int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0;
+                  const uint32_t dur = iteration_ns((chunk_word & bit) ? chunk_of(rem) : 0, static_cast<uint32_t>(n_own));
+                  const int64_t rel = event_time(g, T);
+                  const uint32_t left = iterations_left(static_cast<uint64_t>(rel), dur);
+                  it -= left;
+                  mid = rel - static_cast<int64_t>(static_cast<uint64_t>(left) * dur) <= -static_cast<int64_t>(dt_ns);
+                }
+                uint32_t first_end = kNever;
+#pragma unroll
+                for (int t = 0; t < kRouteLevels; ++t) {
+                  if (q_r[t] < 0) continue;
+                  const int j = w_r[t] + q_r[t];   // position in this pass
+                  uint64_t jw;
+                  if (j < kJobsLds) {
+                    jw = L.jobs[j];
+                  } else {
+                    uint32_t pos = dhead0 + static_cast<uint32_t>(next + j);
+                    if (pos >= dbuf_cap) pos -= dbuf_cap;
+                    if (pos >= dbuf_cap) pos -= dbuf_cap;
+                    jw = dring[pos];
+                  }
+                  const int k = static_cast<int>(jw >> 29) & 7;
+                  const uint32_t Dl = static_cast<uint32_t>(jw >> 48) + 1;
+                  const int nd = my_lmin + (t - first);   // the server holds exactly this many decodes by now
+                  const uint32_t ends = it + Dl + (mid ? 1u : 0u);
+                  first_end = ends < first_end ? ends : first_end;
+                  fin[static_cast<size_t>(g) * BS + nd] = ends;
+                  job[static_cast<size_t>(g) * BS + nd] = jw;
+                  atomicAdd(reinterpret_cast<unsigned long long *>(&rec[g].n_cls), 1ull << (8 * k));
+                  // not part of the iterations still to be tallied for this server
+                  if (runs) atomicAdd(reinterpret_cast<unsigned long long *>(&rec[g].n_join), 1ull << (8 * k));
+                  lds_add64(&L.tl[k * kNTally + (has_prefill ? SIM_T_U_DM : SIM_T_U_DS)], 1);
+                  atomicAdd(&L.cs[(has_prefill ? CS_YM : CS_YS) + k], 1);
+                  atomicSub(&L.cs[CS_QD + k], 1);
+                }
+                if (n_own == 0) rec[g].next_fin = first_end; else atomicMin(&rec[g].next_fin, first_end);
+              }
+              const uint64_t touch_m = __ballot(got);
+              if (lane == 0) atomicOr(bits64(&L.bm_touch[wi]), touch_m);
             }
             // every server below the last level of its group now holds that level, plus one if that level reached it
             if (tmin < tend) L.loads[g] = static_cast<uint8_t>(my_lmin + my_n - 1 + (got_last ? 1 : 0));
@@ -2151,6 +2150,19 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         }
         gate_on = gate_more;
         __syncthreads();
+        // every wave settles the touched servers among its own
+        {
+          const bool last = !gate_on && !route_on;
+          int nset = 0;
+          for (int blk = wave; blk < nwords; blk += nwaves) {
+            const uint64_t tm = L.bm_touch[blk];
+            if (tm) {
+              if ((tm >> lane) & 1ull) ev_g[nset + __popcll(tm & lanes_below())] = static_cast<uint32_t>((blk << 6) + lane);
+              nset += __popcll(tm);
+            }
+            if (nset > kEvPerWave - 64 || blk + nwaves >= nwords) { settle(nset, last); nset = 0; }
+          }
+        }
       }
       if constexpr (AB) {
         if (tid == 0) {   // the head moves past everything the routing passes walked over
@@ -2213,6 +2225,34 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     __syncthreads();
   }
 
+  // ---- tally what each server has completed since its last event; its clock and prefill as of now
+  for (int blk = wave; blk < nwords; blk += nwaves) {
+    const int g = (blk << 6) + lane;
+    const uint64_t bit = 1ull << lane;
+    const bool busy = L.bm_busy[blk] & bit;
+    uint32_t m = 0, tr = kIdleRel;
+    int64_t d = 0;
+    bool chunk = false;
+    uint64_t comp = 0;
+    if (busy) {
+      comp = rec[g].n_cls - rec[g].n_join;
+      chunk = L.bm_chunk[blk] & bit;
+      const int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0, ptok = chunk ? chunk_of(rem) : 0;
+      const uint32_t dur = iteration_ns(ptok, byte_sum(comp));
+      const int64_t rel = event_time(g, T);
+      const uint32_t left = (L.bm_pin[blk] & bit) ? 1u : iterations_left(static_cast<uint64_t>(rel), dur);
+      const uint32_t it = L.ev_it[g] - left;
+      m = it - rec[g].iter;
+      d = static_cast<int64_t>(dur);
+      tr = static_cast<uint32_t>(rel - static_cast<int64_t>(static_cast<uint64_t>(left - 1u) * dur));
+      if (m) rec[g].iter = it;
+      if (ptok > 0) L.rem[g] = static_cast<uint16_t>(rem - static_cast<int>(m) * ptok);
+    }
+    if (g < N) t_rel[g] = tr;
+    tally_iterations(L.tl, L.tbth, tbt_w, tbt_lo, K, m, d, chunk, comp);
+  }
+  __syncthreads();
+
   // ---- the emitted-token tally is the total of the time-between-tokens counts of this launch
   if (tid < K) {
     uint64_t tot = 0;
@@ -2222,18 +2262,15 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   if (tid < 8) L.acc[tid] = 0;
   __syncthreads();
 
-  // ---- write the server clocks and the class state back; add this launch's tallies to the totals
+  // ---- write the prefill words and the class state back; add this launch's tallies to the totals
   for (int i = 0; i < nper; ++i) {
     const int g = i * NT + tid;
     if (g >= N) break;
-    const bool busy = (L.bm_busy[g >> 6] >> (g & 63)) & 1ull;
-    t_next[g] = busy ? T + static_cast<int64_t>(static_cast<int32_t>(L.t32[g] - static_cast<uint32_t>(T))) : kIdle;
-    iter_g[g] = L.iter[g];
     if (g < Mp) {   // prompt tokens already processed of the prefill in service
       const uint32_t rem = L.rem[g];
       uint32_t pk = 0;
       if (rem) {
-        const uint64_t jw = pf_job[g];
+        const uint64_t jw = rec[g].pf_job;
         const uint32_t Pl = (static_cast<uint32_t>(jw >> 32) & 0xFFFFu) + 1, k = static_cast<uint32_t>(jw >> 29) & 7u;
         atomicAdd(&L.acc[k], Pl - rem);
         const bool chunk = (L.bm_chunk[g >> 6] >> (g & 63)) & 1ull;
