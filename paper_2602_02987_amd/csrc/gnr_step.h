@@ -77,7 +77,7 @@ __device__ __forceinline__ int nth_set_bit(uint64_t word, int n)
 }
 
 // Index of the j-th set bit of a bitmap given the exclusive prefix popcounts of its words.
-__device__ __forceinline__ int select_bit(const uint64_t *bm, const uint32_t *pre, int nwords, uint32_t j)
+__device__ __forceinline__ int select_bit(const uint64_t *bm, const uint16_t *pre, int nwords, uint32_t j)
 {
   int lo = 0, hi = nwords - 1;   // largest w with pre[w] <= j
   while (lo < hi) {
@@ -193,14 +193,14 @@ struct Lds {
   uint64_t *bm_fin;   // [nwords] servers whose event is the end of a decode
   uint64_t *bm_chunk; // [nwords] servers whose running iteration carries a prefill chunk
   uint64_t *jobs;     // [kJobsLds] the first requests a routing pass places, copied from the decode buffer
-  uint32_t *pre_lvl;  // [kRouteLevels][nwords] servers of the routed group with at most (level) decodes: per word, then ranks
-  uint32_t *pre_c;    // [nwords] exclusive prefix popcounts of bm_comp
-  uint32_t *pre;      // [nwords] exclusive prefix popcounts of bm_idle
+  uint64_t *bm_lvl;   // [kRouteLevels][nwords] routing pass: servers of the routed group with at most (level) decodes
+  uint16_t *pre_lvl;  // [kRouteLevels][nwords] exclusive prefix popcounts of bm_lvl, per level
+  uint16_t *pre_c;    // [nwords] exclusive prefix popcounts of bm_comp
+  uint16_t *pre;      // [nwords] exclusive prefix popcounts of bm_idle
   uint32_t *adm;      // [kAdmChunk] class | sequence-in-class << 3 of each admission
   uint16_t *adm_slot; // [kAdmChunk] prefill slot (server) that takes the admission of each rank
   uint32_t *lh;       // [2][kLoadBins] servers per decode count: solo group, mixed group
-  uint32_t *ev_g;     // [waves][kEvPerWave] servers queued for finishing, per wave
-  uint32_t *ev_q;     // [waves][kEvPerWave] (spare)
+  uint32_t *ev_g;     // [waves][kEvPerWave] servers queued by a wave: at their event, given jobs, or to settle
   uint16_t *stage;    // [waves][128] lanes of the queued servers whose slot rows are scanned
   uint32_t *ev_t;     // [N] time of the server's event, bits 8..39 of the nanoseconds
   uint32_t *ev_it;    // [N] iterations the server has completed by then (while idle: has completed)
@@ -247,7 +247,6 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(adm_slot, uint16_t, kAdmChunk)
   GNR_TAKE(lh, uint32_t, 2 * kLoadBins)
   GNR_TAKE(ev_g, uint32_t, waves * kEvPerWave)
-  GNR_TAKE(ev_q, uint32_t, waves * kEvPerWave)
   GNR_TAKE(stage, uint16_t, waves * 128)
   GNR_TAKE(bm_idle, uint64_t, nw)
   GNR_TAKE(bm_comp, uint64_t, nw)
@@ -257,9 +256,14 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(bm_touch, uint64_t, nw)
   GNR_TAKE(bm_fin, uint64_t, nw)
   GNR_TAKE(bm_chunk, uint64_t, nw)
-  GNR_TAKE(pre_lvl, uint32_t, kRouteLevels * nw)
-  GNR_TAKE(pre_c, uint32_t, nw + 1)
-  GNR_TAKE(pre, uint32_t, nw + 1)
+  const size_t lvl_off = off, lvl_least = waves * kEvPerWave * 4 + 16 * nw + 2 * ((4 * (nw + 1) + 7) & ~size_t(7));
+  GNR_TAKE(bm_lvl, uint64_t, kRouteLevels * nw)
+  GNR_TAKE(pre_lvl, uint16_t, kRouteLevels * nw)
+  GNR_TAKE(pre_c, uint16_t, nw + 1)
+  GNR_TAKE(pre, uint16_t, nw + 1)
+  // (no smaller than the tables that stood here before them, so that the same numbers of servers fit and the launch
+  // shapes stay: four bytes per queue entry, 16 per word, two tables of four bytes a word and one more)
+  off = off - lvl_off < lvl_least ? lvl_off + lvl_least : off;
   // from here on the offsets depend on the configuration
   GNR_TAKE(ev_t, uint32_t, p.N)
   GNR_TAKE(ev_it, uint32_t, p.N)
@@ -307,7 +311,7 @@ __device__ __forceinline__ uint64_t bits_below(int w, int nbits)
 
 // Exclusive prefix popcounts of the first `nbits` bits of a bitmap, computed by one whole wave; returns the
 // total in every lane.
-__device__ __forceinline__ uint32_t rank_bitmap(const uint64_t *bm, uint32_t *pre, int nwords, int nbits)
+__device__ __forceinline__ uint32_t rank_bitmap(const uint64_t *bm, uint16_t *pre, int nwords, int nbits)
 {
   const int lane = threadIdx.x & 63;
   uint32_t running = 0;
@@ -315,7 +319,7 @@ __device__ __forceinline__ uint32_t rank_bitmap(const uint64_t *bm, uint32_t *pr
     const int w = base + lane;
     const uint32_t v = w < nwords ? static_cast<uint32_t>(__popcll(bm[w] & bits_below(w, nbits))) : 0u;
     const uint32_t inc = wave_incl_scan(v);
-    if (w < nwords) pre[w] = running + inc - v;
+    if (w < nwords) pre[w] = static_cast<uint16_t>(running + inc - v);
     running += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), 63));
   }
   return running;
@@ -1601,7 +1605,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         };
 
         // ---------------- segment A ----------------
-        int nadm = 0, nidle = 0, ncand_pass = 0;
+        int nadm = 0, nidle = 0;
         if (gate_on) {
           nidle = __builtin_amdgcn_readfirstlane(L.sc[SC_NIDLE]);
           const int limit = nidle < kAdmChunk ? nidle : kAdmChunk;
@@ -1619,7 +1623,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             ncand += cnt[k];
           }
           nadm = ncand < limit ? ncand : limit;
-          ncand_pass = ncand;
           if constexpr (AB) {
             // where the candidates sit in their rings: a wave per class walks from the head past the dead entries
             // (the last waves take this: the first ones rank the candidates below)
@@ -1840,55 +1843,31 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 if (wave >= ring_wave && wave < ring_wave + n_ring) cw = nwords;   // nothing to count
               }
             }
-            // In a sixteen-wave workgroup the first waves also rank the gate's candidates, the first four most of
-            // them: when there are candidates for four waves or more, the words are dealt out in runs of unequal
-            // length (2 : 7 : 11 : 19 per wave of each quarter).
-            int w_lo = cw, w_hi = nwords, w_next = cn;
-            if (nwaves == 16 && ncand_pass >= 256) {
-              // (halves of a word: with the weighted router waves 4 and 5 run the selection and the others take runs of
-              // 6, 6, 6, 6, 0, 0, then 11 a wave and 16.5 for the last four)
-              const int q = wave >> 2, o = wave & 3;   // quarter of the workgroup, place in it
-              int lo2, len2;   // start and length of the run, in halves of a word (312 in all)
-              if (kStageEarly) {
-                lo2 = q == 0 ? 12 * o : q == 1 ? (o < 2 ? 48 : 48 + 22 * (o - 2)) : q == 2 ? 92 + 22 * o : 180 + 33 * o;
-                len2 = q == 0 ? 12 : q == 1 ? (o < 2 ? 0 : 22) : q == 2 ? 22 : 33;
-              } else {
-                lo2 = q == 0 ? 4 * o : q == 1 ? 16 + 14 * o : q == 2 ? 72 + 22 * o : 160 + 38 * o;
-                len2 = q == 0 ? 4 : q == 1 ? 14 : q == 2 ? 22 : 38;
-              }
-              w_lo = nwords * lo2 / 312;
-              w_hi = nwords * (lo2 + len2) / 312;
-              w_next = 1;
-            }
-            // four blocks per round: their decode counts are read together, then compared level by level
-            for (int w0 = w_lo; w0 < w_hi; w0 += 4 * w_next) {
-              int tmin4[4], tend4[4];
+            // Four words per round: their decode counts are read together, and a level's members in a word are one
+            // comparison over the wave; lane 4 u + t stores those of level t in the round's word u.
+            for (int w0 = cw; w0 < nwords; w0 += 4 * cn) {   // wave-uniform
+              int ld[4];
 #pragma unroll
               for (int u = 0; u < 4; ++u) {
-                const int wi = w0 + u * w_next;
-                const int g = (wi << 6) + lane;
-                tmin4[u] = 0; tend4[u] = 0;
-                if (wi < w_hi && g < N) {
-                  const int gi = g >= M ? 0 : 1;
-                  const int first = gi == 0 ? 0 : nG[0];
-                  const int d = static_cast<int>(L.loads[g]) - (gi == 0 ? lminG[0] : lminG[1]);
-                  tmin4[u] = first + (d > 0 ? d : 0);
-                  tend4[u] = first + (gi == 0 ? nG[0] : nG[1]);
-                }
+                const int wi = w0 + u * cn, g = (wi << 6) + lane;
+                ld[u] = wi < nwords && g < N ? static_cast<int>(L.loads[g]) : 255;   // (255: in no level)
               }
+              uint64_t members = 0;
 #pragma unroll
-              for (int u = 0; u < 4; ++u) {
-                const int wi = w0 + u * w_next;
-                if (wi < w_hi) {   // wave-uniform
+              for (int t = 0; t < kRouteLevels; ++t) {
+                if (t < nl) {   // wave-uniform
+                  const bool solo = t < nG[0];
+                  const int most = solo ? lminG[0] + t : lminG[1] + (t - nG[0]);
 #pragma unroll
-                  for (int t = 0; t < kRouteLevels; ++t) {
-                    if (t < nl) {
-                      const uint64_t bal = __ballot(t >= tmin4[u] && t < tend4[u]);
-                      if (lane == 0) L.pre_lvl[t * nwords + wi] = static_cast<uint32_t>(__popcll(bal));
-                    }
+                  for (int u = 0; u < 4; ++u) {
+                    const uint64_t mixed = bits_below(w0 + u * cn, M);
+                    const uint64_t in = __ballot(ld[u] <= most) & (solo ? ~mixed : mixed);
+                    if (lane == 4 * u + t) members = in;
                   }
                 }
               }
+              const int t = lane & 3, wi = w0 + (lane >> 2) * cn;
+              if (lane < 16 && t < nl && wi < nwords) L.bm_lvl[t * nwords + wi] = members;
             }
           }
         }
@@ -1953,18 +1932,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             L.jobs[j] = dring[pos];
           }
           }
-          // counts -> exclusive prefix over the words; the last waves take this
-          for (int t = nwaves - 1 - wave; t < nl; t += nwaves) {
-            uint32_t *pre = L.pre_lvl + t * nwords;
-            uint32_t running = 0;
-            for (int base = 0; base < nwords; base += 64) {
-              const int w = base + lane;
-              const uint32_t v = w < nwords ? pre[w] : 0u;
-              const uint32_t inc = wave_incl_scan(v);
-              if (w < nwords) pre[w] = running + inc - v;
-              running += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(inc), 63));
-            }
-          }
+          // ranks of each level's members; the last waves take this
+          for (int t = nwaves - 1 - wave; t < nl; t += nwaves) rank_bitmap(L.bm_lvl + t * nwords, L.pre_lvl + t * nwords, nwords, N);
         }
         __syncthreads();
 
@@ -2029,53 +1998,64 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             take_r[t] = __builtin_amdgcn_readfirstlane(L.sc[SC_TAKE_T + t]);
             w_r[t] = __builtin_amdgcn_readfirstlane(L.sc[SC_W_T + t]);
           }
-          // (sixteen waves, a pass with admissions: the first waves have just finished those, so they take shorter runs of
-          // words, and the later waves of a SIMD, which are served first, longer ones: 4, 4, 7, 9, then 9, 11 and 13 a wave)
-          int c_lo = wave, c_hi = nwords, c_next = nwaves;
-          if (nwaves == 16 && gate_on && nadm > 32) {
-            // (with two buffers a word costs more, and the last waves gain less from being served first: 5, 5, 8, 10,
-            // then 10, 11, 11)
-            auto run_start = [](int i) {
-              if (RR) return i < 2 ? 5 * i : i == 2 ? 10 : i == 3 ? 18 : i < 8 ? 28 + 10 * (i - 4) : 68 + 11 * (i - 8);
-              return i < 2 ? 4 * i : i == 2 ? 8 : i == 3 ? 15 : i < 8 ? 24 + 9 * (i - 4) : i < 12 ? 60 + 11 * (i - 8) : 104 + 13 * (i - 12);
-            };
-            c_lo = nwords * run_start(wave) / 156;
-            c_hi = nwords * run_start(wave + 1) / 156;
-            c_next = 1;
-          }
-          for (int wi = c_lo; wi < c_hi; wi += c_next) {
-            const int gw = wi << 6;
-            const int g = gw + lane;
-            const uint64_t bit = 1ull << lane;
-            // what the block needs from LDS is read in one go
-            const int n_own = g < N ? static_cast<int>(L.loads[g]) : 0;   // decodes of this lane's server
-            const uint64_t busy_word = L.bm_busy[wi], due_word = L.bm_due[wi], idle_word = L.bm_idle[wi];
-            const uint64_t pin_word = L.bm_pin[wi], chunk_word = L.bm_chunk[wi];
-            int pre_r[kRouteLevels];
+          // The servers that get jobs: in every level the first take_r of its members. A lane looks at one word (the
+          // wave's words are wave, wave + nwaves, ...), and the servers found are queued, so that the placements
+          // themselves are made one server per lane: taken word by word, with a lane per server of the word, they
+          // cost a pass through the code below for the one job that a word gets.
+          int nplace = 0, w_next = wave, w_from = 0;
+          uint64_t got_w = 0, todo = 0;   // servers of this lane's word that get jobs; lanes whose word has any left to queue
+          for (bool more = true; more;) {   // wave-uniform
+            while (nplace <= kEvPerWave - 64) {
+              if (todo == 0) {
+                if (w_next >= nwords) { more = false; break; }
+                const int wl = w_next + lane * nwaves;
+                got_w = 0;
+                if (wl < nwords) {
 #pragma unroll
-            for (int t = 0; t < kRouteLevels; ++t)
-              pre_r[t] = __builtin_amdgcn_readfirstlane(static_cast<int>(L.pre_lvl[(t < nl ? t : 0) * nwords + wi]));
-            // levels tmin..tend-1 of the pass hold this lane's server
-            const int gi = g >= M ? 0 : 1;
-            const int first = gi == 0 ? 0 : nG[0], my_n = gi == 0 ? nG[0] : nG[1], my_lmin = gi == 0 ? lminG[0] : lminG[1];
-            const int tend = g < N ? first + my_n : 0;
-            const int tmin = first + (n_own > my_lmin ? n_own - my_lmin : 0);
-            if (__ballot(tmin < tend) == 0) continue;   // wave-uniform
-            int q_r[kRouteLevels];
-            bool got = false, got_last = false;
-#pragma unroll
-            for (int t = 0; t < kRouteLevels; ++t) {
-              const bool in = t < nl && t >= tmin && t < tend;
-              q_r[t] = pre_r[t] + __popcll(__ballot(in) & lanes_below());
-              if (!in || q_r[t] >= take_r[t]) q_r[t] = -1;
-              got = got || q_r[t] >= 0;
-              if (t == tend - 1) got_last = q_r[t] >= 0;
+                  for (int t = 0; t < kRouteLevels; ++t) {
+                    if (t < nl) {   // wave-uniform
+                      const uint64_t in = L.bm_lvl[t * nwords + wl];
+                      const int left = take_r[t] - static_cast<int>(L.pre_lvl[t * nwords + wl]);
+                      if (left > 0) got_w |= __popcll(in) <= left ? in : in & ((1ull << nth_set_bit(in, left)) - 1ull);
+                    }
+                  }
+                  if (got_w) L.bm_touch[wl] |= got_w;   // (no other wave looks at the word in this segment)
+                }
+                todo = __ballot(got_w != 0);
+                w_from = w_next;
+                w_next += 64 * nwaves;
+              } else {
+                const int src = __ffsll(static_cast<long long>(todo)) - 1;
+                todo &= todo - 1ull;
+                const uint64_t got = static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(got_w), src))) |
+                                     (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(got_w >> 32), src))) << 32);
+                if ((got >> lane) & 1ull) ev_g[nplace + __popcll(got & lanes_below())] = static_cast<uint32_t>(((w_from + src * nwaves) << 6) + lane);
+                nplace += __popcll(got);
+              }
             }
-            if (__ballot(got)) {   // wave-uniform
-              const bool busy0 = busy_word & bit;
-              const bool runs = busy0 && !(due_word & bit);   // not known to be at a boundary: the settling works it out
-              const bool has_prefill = g < Mp && !(idle_word & bit);
-              if (got) {
+            for (int e0 = 0; e0 < nplace; e0 += 64) {   // wave-uniform
+              if (e0 + lane < nplace) {
+                const int g = static_cast<int>(ev_g[e0 + lane]), wi = g >> 6;
+                const uint64_t bit = 1ull << (g & 63);
+                const int n_own = static_cast<int>(L.loads[g]);   // decodes of the server
+                const uint64_t pin_word = L.bm_pin[wi], chunk_word = L.bm_chunk[wi];
+                const bool runs = (L.bm_busy[wi] & bit) && !(L.bm_due[wi] & bit);   // not known to be at a boundary: the settling works it out
+                const bool has_prefill = g < Mp && !(L.bm_idle[wi] & bit);
+                // which job of each level the server takes, by its rank among the level's members
+                const int gi = g >= M ? 0 : 1;
+                const int first = gi == 0 ? 0 : nG[0], my_n = gi == 0 ? nG[0] : nG[1], my_lmin = gi == 0 ? lminG[0] : lminG[1];
+                int q_r[kRouteLevels];
+                bool got_last = false;
+#pragma unroll
+                for (int t = 0; t < kRouteLevels; ++t) {
+                  q_r[t] = -1;
+                  if (t < nl) {   // wave-uniform
+                    const uint64_t in = L.bm_lvl[t * nwords + wi];
+                    const int q = static_cast<int>(L.pre_lvl[t * nwords + wi]) + __popcll(in & (bit - 1ull));
+                    if ((in & bit) && q < take_r[t]) q_r[t] = q;
+                  }
+                  if (t == first + my_n - 1) got_last = q_r[t] >= 0;
+                }
                 // iterations the server has completed, and whether it is in the middle of one: a job placed now then
                 // joins at the next restart
                 uint32_t it = L.ev_it[g];
@@ -2119,12 +2099,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                   atomicSub(&L.cs[CS_QD + k], 1);
                 }
                 if (n_own == 0) rec[g].next_fin = first_end; else atomicMin(&rec[g].next_fin, first_end);
+                // a server below the last level of its group now holds that level, plus one if that level reached it
+                L.loads[g] = static_cast<uint8_t>(my_lmin + my_n - 1 + (got_last ? 1 : 0));
               }
-              const uint64_t touch_m = __ballot(got);
-              if (lane == 0) atomicOr(bits64(&L.bm_touch[wi]), touch_m);
             }
-            // every server below the last level of its group now holds that level, plus one if that level reached it
-            if (tmin < tend) L.loads[g] = static_cast<uint8_t>(my_lmin + my_n - 1 + (got_last ? 1 : 0));
+            nplace = 0;
           }
           if constexpr (WS) {   // what the pass took from the solo group's buffer, per class
             if (tid >= NT - 64 && lane < K) L.cs[CS_QDS + lane] -= L.sel_n[lane];
