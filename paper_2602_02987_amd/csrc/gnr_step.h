@@ -1693,53 +1693,57 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             }
           }
           const bool ranks = !(kStageEarly && nwaves >= 8 && (wave == ring_wave || wave == ring_wave_m));   // wave-uniform
-          for (int c0 = rank_first; ranks && c0 < ncand; c0 += rank_step) {   // wave-uniform trip count
-            const int c = c0 + lane;
-            bool admitted = false;
-            int k = 0, m = c;
-            if (c < ncand) {
+          // A lane takes one candidate and one class: how many candidates of that class sort before it. The lanes of a
+          // candidate (2, 4 or 8 of them, as many as there are classes) are neighbours and add up what they find, so
+          // that the searches of a candidate in the other classes run side by side on all waves.
+          const int lg = K <= 2 ? 1 : K <= 4 ? 2 : 3;
+          for (int c0 = rank_first; ranks && c0 < (ncand << lg); c0 += rank_step) {   // wave-uniform trip count
+            const int c = (c0 + lane) >> lg, k2 = lane & ((1 << lg) - 1);
+            int k = 0, m = c, lo = 0;
 #pragma unroll
             for (int kk = 0; kk < kMaxK - 1; ++kk)
               if (k == kk && m >= cnt[kk]) { m -= cnt[kk]; k = kk + 1; }
-            // this candidate's own key: its class's targets and counters, fetched by class (one trip to LDS)
-            const ClassTargets own = load_targets(L.gtab, k);
-            const int xs_own = L.cs[CS_X + k], qp_own = L.cs[CS_QP + k];
-            const uint32_t head_own = static_cast<uint32_t>(L.cs[CS_QHEAD + k]);
-            const GateKey key = gate_key(gate_mode, queue_cap, own, qring, lo_tab, xs_own, qp_own, head_own, k, m, kAdmChunk);
-            int rank = m;
-#pragma unroll
-            for (int k2 = 0; k2 < kMaxK; ++k2) {
-              if (k2 == k || cnt[k2] == 0 || rank >= nadm) continue;
-              // number of candidates of class k2 that sort before this one: they form a prefix of the class
-              const ClassTargets t2 = load_targets(L.gtab, k2);
-              int lo = 0, hi = cnt[k2];
-              if (gate_mode == SIM_GATE_OCCUPANCY) {
-                // the key is linear in the sequence number: bracket the crossing next to its estimate with two
-                // exact comparisons, so the search below runs over a few candidates only (or, if the
-                // estimate is off, over the side the comparisons point to)
-                const double est = key.a * t2.xstar - (static_cast<double>(xs[k2]) - t2.nx);
-                const int g0 = est > 0.0 ? (est < static_cast<double>(hi) ? static_cast<int>(est) : hi) : 0;
-                const int l2 = g0 > 1 ? g0 - 1 : 0, h2 = g0 + 2 < hi ? g0 + 2 : hi;
-                if (l2 > 0) {
-                  if (gate_before(gate_key(gate_mode, queue_cap, t2, qring, lo_tab, xs[k2], qp[k2], head[k2], k2, l2 - 1, kAdmChunk), k2, key, k)) lo = l2; else hi = l2 - 1;
+            if (c < ncand && k2 < K) {
+              // this candidate's own key, and the other class's targets and counters: one trip to LDS
+              const ClassTargets own = load_targets(L.gtab, k), t2 = load_targets(L.gtab, k2);
+              const int xs_own = L.cs[CS_X + k], qp_own = L.cs[CS_QP + k], xs2 = L.cs[CS_X + k2], qp2 = L.cs[CS_QP + k2];
+              const uint32_t head_own = static_cast<uint32_t>(L.cs[CS_QHEAD + k]), head2 = static_cast<uint32_t>(L.cs[CS_QHEAD + k2]);
+              const GateKey key = gate_key(gate_mode, queue_cap, own, qring, lo_tab, xs_own, qp_own, head_own, k, m, kAdmChunk);
+              auto before = [&](int j) __attribute__((always_inline)) -> bool {   // is the j-th of class k2 admitted before it
+                return gate_before(gate_key(gate_mode, queue_cap, t2, qring, lo_tab, xs2, qp2, head2, k2, j, kAdmChunk), k2, key, k);
+              };
+              const bool eligible2 = qp2 > 0 && (gate_mode != SIM_GATE_OCCUPANCY || t2.invx > 0.0);
+              const int cnt2 = eligible2 ? (qp2 < limit ? qp2 : limit) : 0;
+              if (k2 == k) {
+                lo = m;
+              } else if (cnt2 > 0) {   // those before it form a prefix of the class
+                int hi = cnt2;
+                if (gate_mode == SIM_GATE_OCCUPANCY) {
+                  // the key is linear in the sequence number: the prefix ends next to its estimate; if the exact
+                  // comparisons on both sides say otherwise, the search below runs over the side they point to
+                  const double est = key.a * t2.xstar - (static_cast<double>(xs2) - t2.nx);
+                  const int g0 = est > 0.0 ? (est < static_cast<double>(hi) ? static_cast<int>(est) : hi) : 0;
+                  const int l2 = g0 > 1 ? g0 - 1 : 0, h2 = g0 + 2 < hi ? g0 + 2 : hi;
+                  const bool b0 = l2 == 0 || before(l2 - 1), b1 = h2 < hi && before(h2);
+                  if (b0) lo = b1 ? h2 + 1 : l2; else hi = l2 - 1;
+                  if (b0 && !b1) hi = h2;
+                } else if (gate_mode == SIM_GATE_PRIORITY) {   // one key for the whole class
+                  lo = before(0) ? hi : 0;
+                  hi = lo;
                 }
-                if (h2 < hi) {
-                  if (gate_before(gate_key(gate_mode, queue_cap, t2, qring, lo_tab, xs[k2], qp[k2], head[k2], k2, h2, kAdmChunk), k2, key, k)) lo = h2 + 1; else hi = h2;
+                while (lo < hi) {
+                  const int mid = (lo + hi) >> 1;
+                  if (before(mid)) lo = mid + 1; else hi = mid;
                 }
               }
-              while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (gate_before(gate_key(gate_mode, queue_cap, t2, qring, lo_tab, xs[k2], qp[k2], head[k2], k2, mid, kAdmChunk), k2, key, k)) lo = mid + 1; else hi = mid;
-              }
-              rank += lo;
             }
-            admitted = rank < nadm;
-            if (admitted) L.adm[rank] = static_cast<uint32_t>(k) | (static_cast<uint32_t>(m) << 3);
-            }
-            // admissions per class: counted over the wave first (candidates of a class sit in neighbouring lanes)
-            for (int c = 0; c < K; ++c) {
-              const uint64_t mk = __ballot(admitted && k == c);
-              if (mk && lane == 0) atomicAdd(&L.sc[SC_ADMK + c], __popcll(mk));
+            uint32_t rank_sum = dpp_add<0xB1, 0xF>(static_cast<uint32_t>(lo));    // quad_perm [1,0,3,2]
+            if (lg > 1) rank_sum = dpp_add<0x4E, 0xF>(rank_sum);                  // quad_perm [2,3,0,1]
+            if (lg > 2) rank_sum = dpp_add<0x141, 0xF>(rank_sum);                 // row_half_mirror
+            const int rank = static_cast<int>(rank_sum);
+            if (c < ncand && k2 == 0 && rank < nadm) {
+              L.adm[rank] = static_cast<uint32_t>(k) | (static_cast<uint32_t>(m) << 3);
+              atomicAdd(&L.sc[SC_ADMK + k], 1);
             }
           }
         }
@@ -1854,15 +1858,17 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               }
               uint64_t members = 0;
 #pragma unroll
-              for (int t = 0; t < kRouteLevels; ++t) {
-                if (t < nl) {   // wave-uniform
-                  const bool solo = t < nG[0];
-                  const int most = solo ? lminG[0] + t : lminG[1] + (t - nG[0]);
+              for (int u = 0; u < 4; ++u) {
+                if (w0 + u * cn < nwords) {   // wave-uniform
+                  const uint64_t mixed = bits_below(w0 + u * cn, M);
 #pragma unroll
-                  for (int u = 0; u < 4; ++u) {
-                    const uint64_t mixed = bits_below(w0 + u * cn, M);
-                    const uint64_t in = __ballot(ld[u] <= most) & (solo ? ~mixed : mixed);
-                    if (lane == 4 * u + t) members = in;
+                  for (int t = 0; t < kRouteLevels; ++t) {
+                    if (t < nl) {   // wave-uniform
+                      const bool solo = t < nG[0];
+                      const int most = solo ? lminG[0] + t : lminG[1] + (t - nG[0]);
+                      const uint64_t in = __ballot(ld[u] <= most) & (solo ? ~mixed : mixed);
+                      if (lane == 4 * u + t) members = in;
+                    }
                   }
                 }
               }
