@@ -192,6 +192,7 @@ constexpr int kJobsLds = 256;      // requests of a routing pass staged in LDS; 
 struct Lds {
   int32_t *cs;        // [CS_WORDS]
   uint32_t *acc;      // [8]
+  uint32_t *cthr;     // [8] class thresholds of the arrival draw
   double *gtab;       // [5][kMaxK] gate targets of the launch: n x*, 1/x*, x*, n q*, priority index
   int32_t *sc;        // [SC_WORDS]
   uint64_t *tl;       // [kTallyWords]
@@ -212,8 +213,8 @@ struct Lds {
   uint32_t *adm;      // [kAdmChunk] class | sequence-in-class << 3 of each admission
   uint16_t *adm_slot; // [kAdmChunk] prefill slot (server) that takes the admission of each rank
   uint32_t *lh;       // [2][kLoadBins] servers per decode count: solo group, mixed group
-  uint32_t *ev_g;     // [waves][kEvPerWave] servers queued by a wave: at their event, given jobs, or to settle
-  uint16_t *stage;    // [waves][128] lanes of the queued servers whose slot rows are scanned
+  uint16_t *ev_g;     // [waves][kEvPerWave] servers queued by a wave: at their event, given jobs, or to settle
+  uint16_t *stage;    // [waves][64] lanes of the queued servers whose slot rows are scanned
   uint32_t *ev_t;     // [N] time of the server's event, bits 8..39 of the nanoseconds
   uint32_t *ev_it;    // [N] iterations the server has completed by then (while idle: has completed)
   uint8_t *loads;     // [N] decodes per server
@@ -254,13 +255,14 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(jobs, uint64_t, kJobsLds)
   GNR_TAKE(cs, int32_t, CS_WORDS)
   GNR_TAKE(acc, uint32_t, 8)
+  GNR_TAKE(cthr, uint32_t, 8)
   GNR_TAKE(gtab, double, 5 * kMaxK)
   GNR_TAKE(sc, int32_t, SC_WORDS)
   GNR_TAKE(adm, uint32_t, kAdmChunk)
   GNR_TAKE(adm_slot, uint16_t, kAdmChunk)
   GNR_TAKE(lh, uint32_t, 2 * kLoadBins)
-  GNR_TAKE(ev_g, uint32_t, waves * kEvPerWave)
-  GNR_TAKE(stage, uint16_t, waves * 128)
+  GNR_TAKE(ev_g, uint16_t, waves * kEvPerWave)
+  GNR_TAKE(stage, uint16_t, waves * 64)
   GNR_TAKE(bm_idle, uint64_t, nw)
   GNR_TAKE(bm_comp, uint64_t, nw)
   GNR_TAKE(bm_busy, uint64_t, nw)
@@ -567,11 +569,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   const uint32_t cdec_ns = pinned(static_cast<uint32_t>(p.cdec)), dt_ns = pinned(static_cast<uint32_t>(p.dt));
   const int chunk_max = static_cast<int>(pinned(static_cast<uint32_t>(p.C)));
   const int tbt_w = static_cast<int>(pinned(static_cast<uint32_t>(p.tbt_w))), tbt_lo = static_cast<int>(pinned(static_cast<uint32_t>(p.tbt_lo)));
-  // an arrival's class is the number of thresholds its random word has reached; classes beyond K-1 do not exist:
-  // their thresholds are the largest word, and the count is capped
-  uint32_t cthr[kMaxK - 1];
-#pragma unroll
-  for (int c = 0; c + 1 < kMaxK; ++c) cthr[c] = pinned(c + 1 < K ? p.cls_thr[c] : 0xFFFFFFFFu);
   const int gate_mode = static_cast<int>(pinned(static_cast<uint32_t>(p.gate_mode)));
   const uint32_t queue_cap = pinned(p.queue_cap), dbuf_cap = pinned(p.dbuf_cap);
 
@@ -583,8 +580,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   uint32_t *qring = a.qring + static_cast<size_t>(r) * K * queue_cap;
   uint64_t *dring = a.dring + static_cast<size_t>(r) * dbuf_cap;
   uint64_t *hist = a.hist + static_cast<size_t>(r) * 3 * K * kNBin;
-  uint32_t *ev_g = L.ev_g + wave * kEvPerWave;
-  uint16_t *stage = L.stage + wave * 128;
+  uint16_t *ev_g = L.ev_g + wave * kEvPerWave;
+  uint16_t *stage = L.stage + wave * 64;
   // abandonment only
   const uint32_t cal_n = p.cal_mask + 1u;
   uint32_t *qdl = AB ? a.qdl + static_cast<size_t>(r) * K * queue_cap : nullptr;
@@ -602,6 +599,9 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   for (int i = tid; i < K * p.tbt_w; i += NT) L.tbth[i] = 0;
   for (int i = tid; i < (TA_TBT + K) * kTallyRowsHere; i += NT) L.ta[i] = 0;
   for (int i = tid; i < SC_WORDS; i += NT) L.sc[i] = 0;
+  // an arrival's class is the number of thresholds its random word has reached; classes beyond K-1 do not exist:
+  // their thresholds are the largest word, and the count is capped
+  if (tid < kMaxK) L.cthr[tid] = tid + 1 < K ? p.cls_thr[tid] : 0xFFFFFFFFu;
   if (tid < kMaxK) {
     L.gtab[GT_NX * kMaxK + tid] = tid < K ? p.nx[tid] : 0.0;
     L.gtab[GT_INVX * kMaxK + tid] = tid < K ? p.invx[tid] : 0.0;
@@ -770,21 +770,23 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     const uint32_t thr0 = pinned(thr[0]), thr1 = pinned(thr[1]), thr2 = pinned(thr[2]);
     __syncthreads();
 
-    // ---- 1. arrivals of one server: one random block, word 0 -> count, words 1.. -> classes
-    auto arrivals = [&](int g) __attribute__((always_inline)) {
-      uint32_t w[4];
-      philox4x32_10(key0, key1, s, 0u, static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
-      if (w[0] >= thr0) {
-        const int a = 1 + (w[0] >= thr1) + (w[0] >= thr2);
+    // ---- 1. arrivals: one random block per server, word 0 -> count, words 1.. -> classes. The pass over the servers
+    //      looks at word 0; the few servers that get requests leave the other words in registers of their lane, and the
+    //      classes are worked out when a lane gets a second server or the pass ends (worked out where they are found,
+    //      62 % of the blocks of 64 went through the class thresholds for the one lane that had any).
+    uint32_t arr_n = 0, arr_w[3] = {0, 0, 0};   // requests of this lane's last server with arrivals, their words
+    auto classify_arrivals = [&]() __attribute__((always_inline)) {
+      if (arr_n) {
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
-          if (j >= a) break;
+          if (static_cast<uint32_t>(j) >= arr_n) break;
           int k = 0;
 #pragma unroll
-          for (int c = 0; c + 1 < kMaxK; ++c) k += w[1 + j] >= cthr[c];
+          for (int c = 0; c + 1 < kMaxK; ++c) k += arr_w[j] >= L.cthr[c];
           atomicAdd(&L.acc[k < K ? k : K - 1], 1u);
         }
       }
+      arr_n = 0;
     };
 
     // ---- 2. events: one server per lane (uniform control flow; lanes beyond the queue idle). Tallies the iterations
@@ -1046,19 +1048,35 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       int nev = 0;   // servers queued by this wave (wave-uniform)
       for (int blk = wave; blk < nwords; blk += nwaves) {
         const int g = (blk << 6) + lane;
-        const bool busy = (L.bm_busy[blk] >> lane) & 1ull;
-        const int32_t diff = g < N ? static_cast<int32_t>(L.ev_t[g] - T_hi) : 1;
+        const uint64_t busy_w = L.bm_busy[blk];
+        const uint32_t ev = L.ev_t[g < N ? g : N - 1];   // (the lanes past the last server are not busy)
+        uint32_t w[4];
+        // the round keys are formed anew with scalar additions: as loop invariants there are twenty of them, and they are
+        // kept in lanes of vector registers, from which each costs two vector instructions a round
+        uint32_t k0 = key0, k1 = key1;
+        asm volatile("" : "+s"(k0), "+s"(k1));
+        philox4x32_10(k0, k1, s, 0u, static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
+        const bool hit = g < N && w[0] >= thr0;
+        if (__ballot(hit)) {
+          if (__ballot(hit && arr_n != 0)) classify_arrivals();
+          if (hit) {
+            arr_n = 1u + (w[0] >= thr1) + (w[0] >= thr2);
+            arr_w[0] = w[1]; arr_w[1] = w[2]; arr_w[2] = w[3];
+          }
+        }
+        const bool busy = (busy_w >> lane) & 1ull;
+        const int32_t diff = static_cast<int32_t>(ev - T_hi);
         bool due = busy && diff < 0;
         if (__ballot(busy && diff == 0)) due = due || (busy && diff == 0 && L.ev_lo[g] <= T_lo);
         const uint64_t dm = __ballot(due);
         if (lane == 0) { L.bm_due[blk] = dm; L.bm_touch[blk] = dm; L.bm_comp[blk] = 0; }
         if (dm) {
-          if (due) ev_g[nev + __popcll(dm & below)] = static_cast<uint32_t>(g);
+          if (due) ev_g[nev + __popcll(dm & below)] = static_cast<uint16_t>(g);
           nev += __popcll(dm);
         }
-        if (g < N) arrivals(g);
         if (nev > kEvPerWave - 64 || blk + nwaves >= nwords) { drain_events(nev); nev = 0; }
       }
+      if (__ballot(arr_n != 0)) classify_arrivals();
     }
     __syncthreads();
 
@@ -2049,7 +2067,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 todo &= todo - 1ull;
                 const uint64_t got = static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(got_w), src))) |
                                      (static_cast<uint64_t>(static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(got_w >> 32), src))) << 32);
-                if ((got >> lane) & 1ull) ev_g[nplace + __popcll(got & lanes_below())] = static_cast<uint32_t>(((w_from + src * nwaves) << 6) + lane);
+                if ((got >> lane) & 1ull) ev_g[nplace + __popcll(got & lanes_below())] = static_cast<uint16_t>(((w_from + src * nwaves) << 6) + lane);
                 nplace += __popcll(got);
               }
             }
@@ -2156,7 +2174,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           for (int blk = wave; blk < nwords; blk += nwaves) {
             const uint64_t tm = L.bm_touch[blk];
             if (tm) {
-              if ((tm >> lane) & 1ull) ev_g[nset + __popcll(tm & lanes_below())] = static_cast<uint32_t>((blk << 6) + lane);
+              if ((tm >> lane) & 1ull) ev_g[nset + __popcll(tm & lanes_below())] = static_cast<uint16_t>((blk << 6) + lane);
               nset += __popcll(tm);
             }
             if (nset > kEvPerWave - 64 || blk + nwaves >= nwords) { settle(nset, last); nset = 0; }
