@@ -175,6 +175,9 @@ enum Scalar {
   SC_W_T = 56,    // [kRouteLevels] jobs of the pass that come before each level
   SC_WORDS = 64
 };
+// Per class: arrivals of the step; changes of the prefills in service and of the mixed and solo decodes. The class state
+// itself stays as the last step left it until the pass is over.
+enum PassSum { AC_ARRIVALS = 0, AC_X = 8, AC_YM = 16, AC_YS = 24, AC_WORDS = 32 };
 constexpr int kLoadBins = kMaxB + 1;
 // Running sums of the executed iterations, each spread over a row of words (see tally_iterations): iterations and busy time
 // of the solo and, one row further, the mixed ones; time between tokens per class.
@@ -191,7 +194,7 @@ constexpr int kJobsLds = 256;      // requests of a routing pass staged in LDS; 
 
 struct Lds {
   int32_t *cs;        // [CS_WORDS]
-  uint32_t *acc;      // [8]
+  uint32_t *acc;      // [AC_WORDS] what the completion pass of a step adds up: arrivals and changes of the class counters
   uint32_t *cthr;     // [8] class thresholds of the arrival draw
   double *gtab;       // [5][kMaxK] gate targets of the launch: n x*, 1/x*, x*, n q*, priority index
   int32_t *sc;        // [SC_WORDS]
@@ -254,7 +257,7 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(tl, uint64_t, kTallyWords)
   GNR_TAKE(jobs, uint64_t, kJobsLds)
   GNR_TAKE(cs, int32_t, CS_WORDS)
-  GNR_TAKE(acc, uint32_t, 8)
+  GNR_TAKE(acc, uint32_t, AC_WORDS)
   GNR_TAKE(cthr, uint32_t, 8)
   GNR_TAKE(gtab, double, 5 * kMaxK)
   GNR_TAKE(sc, int32_t, SC_WORDS)
@@ -599,6 +602,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   for (int i = tid; i < K * p.tbt_w; i += NT) L.tbth[i] = 0;
   for (int i = tid; i < (TA_TBT + K) * kTallyRowsHere; i += NT) L.ta[i] = 0;
   for (int i = tid; i < SC_WORDS; i += NT) L.sc[i] = 0;
+  for (int i = tid; i < AC_WORDS; i += NT) L.acc[i] = 0;
   // an arrival's class is the number of thresholds its random word has reached; classes beyond K-1 do not exist:
   // their thresholds are the largest word, and the count is capped
   if (tid < kMaxK) L.cthr[tid] = tid + 1 < K ? p.cls_thr[tid] : 0xFFFFFFFFu;
@@ -651,6 +655,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     }
     return n;
   };
+  // classes that the gate may admit: under the occupancy gate those with a positive target
+  const uint64_t admissible = __ballot(lane < K && (gate_mode != SIM_GATE_OCCUPANCY || L.gtab[GT_INVX * kMaxK + (lane & (kMaxK - 1))] > 0.0));
   auto bits64 = [](uint64_t *p) __attribute__((always_inline)) { return reinterpret_cast<unsigned long long *>(p); };
 
   for (int i = 0; i < nper; ++i) {
@@ -752,10 +758,24 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     if (lane == 0) L.sc[mixed ? SC_DLEN_M : SC_DLEN] = static_cast<int32_t>(w);
   };
 
+  // arrival thresholds of the step to come: asked for a step ahead, the first three lanes hold them
+  const uint32_t mod_rows = p.mod_period > 0xFFFFFFFFll ? 0xFFFFFFFFu : (p.mod_period > 0 ? static_cast<uint32_t>(p.mod_period) : 1u);
+  uint32_t mod_row = step_begin % mod_rows;
+  uint32_t thr_ahead = a.arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
+  // what a step's end leaves in the class counters enters the sums over steps
+  auto add_step_sums = [&](int k, int qp, int qd, int x, int ym, int ys) __attribute__((always_inline)) {
+    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_QP], static_cast<uint64_t>(qp));
+    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_QD], static_cast<uint64_t>(qd));
+    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_X], static_cast<uint64_t>(x));
+    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_YM], static_cast<uint64_t>(ym));
+    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_YS], static_cast<uint64_t>(ys));
+  };
+
   int64_t T = 0;
   for (uint32_t s = step_begin; s < step_begin + n_steps; ++s) {
     T = (static_cast<int64_t>(s) + 1) * dt_ns;
-    if (tid < 8) L.acc[tid] = 0;
+    // (No barrier here: a wave goes from its last settling straight into the next step's completion pass. Until the
+    // barrier that ends it a wave touches its own servers and bitmap words only, and adds to sums that nobody reads before.)
     // abandonment only: how many waiting requests of class `tid` leave at the start of this step (asked for
     // here, used after the completion pass)
     uint32_t n_leave_p = 0, n_leave_d = 0, n_leave_dm = 0;
@@ -766,9 +786,13 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         if constexpr (RR) n_leave_dm = atomicExch(&dcal_m[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
       }
     }
-    const uint32_t *thr = a.arr_thr + 3 * (p.mod_period > 0 ? static_cast<int64_t>(s % static_cast<uint64_t>(p.mod_period)) : 0);
-    const uint32_t thr0 = pinned(thr[0]), thr1 = pinned(thr[1]), thr2 = pinned(thr[2]);
-    __syncthreads();
+    const uint32_t thr0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 0));
+    const uint32_t thr1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 1));
+    const uint32_t thr2 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 2));
+    if (mod_rows > 1u) {
+      mod_row = mod_row + 1u == mod_rows ? 0u : mod_row + 1u;
+      thr_ahead = a.arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
+    }
 
     // ---- 1. arrivals: one random block per server, word 0 -> count, words 1.. -> classes. The pass over the servers
     //      looks at word 0; the few servers that get requests leave the other words in registers of their lane, and the
@@ -875,7 +899,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               const uint32_t Pl = (static_cast<uint32_t>(jw >> 32) & 0xFFFFu) + 1, Dl = static_cast<uint32_t>(jw >> 48) + 1;
               const int64_t e2e = tn - (static_cast<int64_t>(stamp) + 1) * dt_ns;
               lds_add64(&L.tl[k * kNTally + (mixed_now ? SIM_T_S_DM : SIM_T_S_DS)], 1);
-              atomicSub(&L.cs[(mixed_now ? CS_YM : CS_YS) + k], 1);
+              atomicSub(&L.acc[(mixed_now ? AC_YM : AC_YS) + k], 1u);
               lds_add64(&L.tl[k * kNTally + SIM_T_TOKP_DEC], Pl);
               lds_add64(&L.tl[k * kNTally + SIM_T_TOKD_DEC], Dl);
               lds_add64(&L.tl[k * kNTally + SIM_T_E2E_SUM], static_cast<uint64_t>(e2e));
@@ -938,7 +962,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                   ++nd;
                   L.loads[g] = static_cast<uint8_t>(nd);
                   lds_add64(&L.tl[k * kNTally + SIM_T_U_DS], 1);
-                  atomicAdd(&L.cs[CS_YS + k], 1);
+                  atomicAdd(&L.acc[AC_YS + k], 1u);
                   if (nd < B) atomicOr(bits64(&L.bm_idle[wi]), bit);
                 }
               } else {
@@ -958,16 +982,16 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         // co-resident decodes switch mixed -> solo
         if (pe.done) {
           lds_add64(&L.tl[pe.k * kNTally + SIM_T_S_P], 1);
-          atomicSub(&L.cs[CS_X + pe.k], 1);
+          atomicSub(&L.acc[AC_X + pe.k], 1u);
           lds_add64(&L.tl[pe.k * kNTally + SIM_T_TOKP_PRE], pe.P);
           lds_add64(&L.tl[pe.k * kNTally + SIM_T_TTFT_SUM], static_cast<uint64_t>(pe.ttft));
 #pragma unroll
           for (int c = 0; c < kMaxK; ++c) {
-            const int v = static_cast<int>(byte_at(pe.nc, c));
+            const uint32_t v = byte_at(pe.nc, c);
             if (v) {
-              lds_add64(&L.tl[c * kNTally + SIM_T_M_MS], static_cast<uint64_t>(v));
-              atomicSub(&L.cs[CS_YM + c], v);
-              atomicAdd(&L.cs[CS_YS + c], v);
+              lds_add64(&L.tl[c * kNTally + SIM_T_M_MS], v);
+              atomicSub(&L.acc[AC_YM + c], v);
+              atomicAdd(&L.acc[AC_YS + c], v);
             }
           }
         }
@@ -1083,31 +1107,41 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     // ================= arrivals into the class queues; ranks of completions and idle slots =================
     if (tid < K) {
       const int k = tid;
+      // (everything that is needed is read first: one trip to LDS)
+      const uint32_t arrived = L.acc[AC_ARRIVALS + k];
+      const int dx = static_cast<int>(L.acc[AC_X + k]), dym = static_cast<int>(L.acc[AC_YM + k]), dys = static_cast<int>(L.acc[AC_YS + k]);
+      int qp = L.cs[CS_QP + k], qd = L.cs[CS_QD + k];
+      const int x = L.cs[CS_X + k], ym = L.cs[CS_YM + k], ys = L.cs[CS_YS + k];
+      uint32_t tail = static_cast<uint32_t>(L.cs[CS_QHEAD + k]);
+      const uint32_t ring_len = AB ? static_cast<uint32_t>(L.sc[SC_QLEN + k]) : 0u;
+      if (s != step_begin) add_step_sums(k, qp, qd, x, ym, ys);   // of the step before
+      L.acc[AC_ARRIVALS + k] = 0; L.acc[AC_X + k] = 0; L.acc[AC_YM + k] = 0; L.acc[AC_YS + k] = 0;
+      L.cs[CS_X + k] = x + dx; L.cs[CS_YM + k] = ym + dym; L.cs[CS_YS + k] = ys + dys;
       if constexpr (AB) {   // abandonments come first: they free room in the queue
         if (n_leave_p) {
-          L.cs[CS_QP + k] -= static_cast<int32_t>(n_leave_p);
-          L.tl[k * kNTally + SIM_T_AB_P] += n_leave_p;
+          qp -= static_cast<int32_t>(n_leave_p);
+          lds_add64(&L.tl[k * kNTally + SIM_T_AB_P], n_leave_p);
         }
         if (n_leave_d) {
-          L.cs[CS_QD + k] -= static_cast<int32_t>(n_leave_d);
-          L.tl[k * kNTally + SIM_T_AB_D] += n_leave_d;
+          qd -= static_cast<int32_t>(n_leave_d);
+          lds_add64(&L.tl[k * kNTally + SIM_T_AB_D], n_leave_d);
           atomicSub(&L.cs[CS_DCOUNT], static_cast<int32_t>(n_leave_d));
           if constexpr (WS) L.cs[CS_QDS + k] -= static_cast<int32_t>(n_leave_d);
         }
         if constexpr (RR) {
           if (n_leave_dm) {
-            L.cs[CS_QD + k] -= static_cast<int32_t>(n_leave_dm);
-            L.tl[k * kNTally + SIM_T_AB_D] += n_leave_dm;
+            qd -= static_cast<int32_t>(n_leave_dm);
+            lds_add64(&L.tl[k * kNTally + SIM_T_AB_D], n_leave_dm);
             atomicSub(&L.cs[CS_DCOUNT_M], static_cast<int32_t>(n_leave_dm));
           }
         }
+        L.cs[CS_QD + k] = qd;
       }
-      const uint32_t a = L.acc[k];
-      const uint32_t room = queue_cap - static_cast<uint32_t>(L.cs[CS_QP + k]);
-      const uint32_t take = a < room ? a : room;
+      const uint32_t room = queue_cap - static_cast<uint32_t>(qp);
+      const uint32_t take = arrived < room ? arrived : room;
       // entries between head and tail: the waiting requests, with abandonment also the dead entries
-      const uint32_t in_ring = static_cast<uint32_t>(AB ? L.sc[SC_QLEN + k] : L.cs[CS_QP + k]);
-      uint32_t tail = static_cast<uint32_t>(L.cs[CS_QHEAD + k]) + in_ring;
+      const uint32_t in_ring = AB ? ring_len : static_cast<uint32_t>(qp);
+      tail += in_ring;
       if (tail >= queue_cap) tail -= queue_cap;
       if constexpr (AB) {
         if (in_ring + take > queue_cap) atomicOr(&L.sc[SC_COMPACT], 1 << k);
@@ -1115,10 +1149,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       }
       L.sc[SC_TAKE + k] = static_cast<int32_t>(take);
       L.sc[SC_TAIL + k] = static_cast<int32_t>(tail);
-      L.cs[CS_QP + k] += static_cast<int32_t>(take);
-      L.tl[k * kNTally + SIM_T_A] += take;
-      L.tl[k * kNTally + SIM_T_DROP_P] += a - take;
-      if (a > take) L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
+      L.cs[CS_QP + k] = qp + static_cast<int32_t>(take);
+      if (arrived) lds_add64(&L.tl[k * kNTally + SIM_T_A], take);
+      if (arrived > take) {
+        lds_add64(&L.tl[k * kNTally + SIM_T_DROP_P], arrived - take);
+        L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
+      }
     }
     uint32_t ncomp_own = 0;   // (the first wave's count of completed prefills)
     if (tid < 64) {
@@ -1225,8 +1261,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         qdl[static_cast<size_t>(k) * queue_cap + pos] = dl;
       }
     } else {
+      const int sc_lane = L.sc[lane];   // one word per lane: one trip to LDS
       for (int k = 0; k < K; ++k) {
-        const uint32_t take = static_cast<uint32_t>(L.sc[SC_TAKE + k]), tail = static_cast<uint32_t>(L.sc[SC_TAIL + k]);
+        const uint32_t take = static_cast<uint32_t>(__builtin_amdgcn_readlane(sc_lane, SC_TAKE + k));
+        const uint32_t tail = static_cast<uint32_t>(__builtin_amdgcn_readlane(sc_lane, SC_TAIL + k));
         for (uint32_t j = tid; j < take; j += NT) {
           uint32_t pos = tail + j;
           if (pos >= queue_cap) pos -= queue_cap;
@@ -1650,7 +1688,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             qp[k] = k < K ? __builtin_amdgcn_readlane(cs_lane, CS_QP + k) : 0;
             xs[k] = k < K ? __builtin_amdgcn_readlane(cs_lane, CS_X + k) : 0;
             head[k] = k < K ? static_cast<uint32_t>(__builtin_amdgcn_readlane(cs_lane, CS_QHEAD + k)) : 0u;
-            const bool eligible = k < K && qp[k] > 0 && (gate_mode != SIM_GATE_OCCUPANCY || L.gtab[GT_INVX * kMaxK + k] > 0.0);
+            const bool eligible = qp[k] > 0 && ((admissible >> k) & 1ull);
             cnt[k] = eligible ? (qp[k] < limit ? qp[k] : limit) : 0;
             ncand += cnt[k];
           }
@@ -1744,7 +1782,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               auto before = [&](int j) __attribute__((always_inline)) -> bool {   // is the j-th of class k2 admitted before it
                 return gate_before(gate_key(gate_mode, queue_cap, t2, qring, lo_tab, xs2, qp2, head2, k2, j, kAdmChunk), k2, key, k);
               };
-              const bool eligible2 = qp2 > 0 && (gate_mode != SIM_GATE_OCCUPANCY || t2.invx > 0.0);
+              const bool eligible2 = qp2 > 0 && ((admissible >> k2) & 1ull);
               const int cnt2 = eligible2 ? (qp2 < limit ? qp2 : limit) : 0;
               if (k2 == k) {
                 lo = m;
@@ -1944,8 +1982,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           }
           if (nadm == kAdmChunk && nidle > kAdmChunk) {   // rare: more idle slots than one pass serves
             for (int k = 0; k < K; ++k) {
-              const bool eligible = gate_mode != SIM_GATE_OCCUPANCY || L.gtab[GT_INVX * kMaxK + k] > 0.0;
-              if (eligible && L.cs[CS_QP + k] - L.sc[SC_ADMK + k] > 0) gate_more = true;
+              if (((admissible >> k) & 1ull) && L.cs[CS_QP + k] - L.sc[SC_ADMK + k] > 0) gate_more = true;
             }
           }
         }
@@ -2219,19 +2256,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       }
       }
     }
-
-    // ================= 6. end-of-step sums =================
-    if (tid < K) {
-      const int k = tid;
-      L.tl[k * kNTally + SIM_T_SUM_QP] += static_cast<uint64_t>(L.cs[CS_QP + k]);
-      L.tl[k * kNTally + SIM_T_SUM_QD] += static_cast<uint64_t>(L.cs[CS_QD + k]);
-      L.tl[k * kNTally + SIM_T_SUM_X] += static_cast<uint64_t>(L.cs[CS_X + k]);
-      L.tl[k * kNTally + SIM_T_SUM_YM] += static_cast<uint64_t>(L.cs[CS_YM + k]);
-      L.tl[k * kNTally + SIM_T_SUM_YS] += static_cast<uint64_t>(L.cs[CS_YS + k]);
-    }
-    if (tid == 0) L.tl[kMaxK * kNTally + SIM_G_STEPS] += 1;
   }
   __syncthreads();
+  // the sums over steps get the last step's counters (those of the others are added a step later)
+  if (n_steps > 0 && tid < K) add_step_sums(tid, L.cs[CS_QP + tid], L.cs[CS_QD + tid], L.cs[CS_X + tid], L.cs[CS_YM + tid], L.cs[CS_YS + tid]);
+  if (tid == 0) L.tl[kMaxK * kNTally + SIM_G_STEPS] += n_steps;
   if constexpr (AB) {   // the rings leave the launch without dead entries
     const uint32_t s_last = step_begin + n_steps - 1u;
     for (int k = wave; k < K; k += nwaves) compact_queue(k, s_last, 0u);
