@@ -762,18 +762,69 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   const uint32_t mod_rows = p.mod_period > 0xFFFFFFFFll ? 0xFFFFFFFFu : (p.mod_period > 0 ? static_cast<uint32_t>(p.mod_period) : 1u);
   uint32_t mod_row = step_begin % mod_rows;
   uint32_t thr_ahead = a.arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
-  // what a step's end leaves in the class counters enters the sums over steps
-  auto add_step_sums = [&](int k, int qp, int qd, int x, int ym, int ys) __attribute__((always_inline)) {
-    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_QP], static_cast<uint64_t>(qp));
-    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_QD], static_cast<uint64_t>(qd));
-    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_X], static_cast<uint64_t>(x));
-    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_YM], static_cast<uint64_t>(ym));
-    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_YS], static_cast<uint64_t>(ys));
+  // what `n` steps leave in the class counters at their end enters the sums over steps
+  auto add_step_sums = [&](int k, uint32_t n, int qp, int qd, int x, int ym, int ys) __attribute__((always_inline)) {
+    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_QP], static_cast<uint64_t>(n) * static_cast<uint32_t>(qp));
+    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_QD], static_cast<uint64_t>(n) * static_cast<uint32_t>(qd));
+    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_X], static_cast<uint64_t>(n) * static_cast<uint32_t>(x));
+    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_YM], static_cast<uint64_t>(n) * static_cast<uint32_t>(ym));
+    lds_add64(&L.tl[k * kNTally + SIM_T_SUM_YS], static_cast<uint64_t>(n) * static_cast<uint32_t>(ys));
   };
+  uint32_t ended = 0;   // steps that have ended with the class counters as they are, not yet in those sums
+
+  // Quiet steps. A step without an arrival and without an event leaves everything as it is but for the clock: the gate and
+  // the router went on in the step before until no slot or no request was left for them, and nothing has changed since
+  // (in the first step of a launch it may have: the targets or the split). With a few servers most steps are like that
+  // (8 servers of two classes: seven of ten), and going through all of a step costs a wave 9 thousand cycles. So the
+  // only wave of a small workgroup looks for the next step in which anything happens: one random block per lane tells the
+  // arrivals of 64 / servers steps. Above 32 servers a quiet step hardly occurs.
+  constexpr int kQuietServers = 32;
+  const bool quiet_search = SMALL && NT == 64 && N <= kQuietServers;
+  const int lg_n = N <= 1 ? 0 : 32 - __clz(N - 1);   // a step's servers take 2^lg_n lanes
+  uint64_t ahead = 0;    // servers with arrivals in the steps drawn ahead, the step to come in the lowest 2^lg_n bits
+  int steps_ahead = 0;   // how many
+  const uint32_t step_end = step_begin + n_steps;
 
   int64_t T = 0;
-  for (uint32_t s = step_begin; s < step_begin + n_steps; ++s) {
+  for (uint32_t s = step_begin; s < step_end; ++s, ++ended) {
     T = (static_cast<int64_t>(s) + 1) * dt_ns;
+    if constexpr (SMALL) {
+      if (quiet_search) {
+        bool search = s != step_begin;
+        if constexpr (AB)   // (while nobody waits nobody leaves)
+          search = search && __ballot(lane < K && (L.cs[CS_QP + (lane & (kMaxK - 1))] | L.cs[CS_QD + (lane & (kMaxK - 1))]) != 0) == 0;
+        if (search) {
+          const uint32_t s_first = s;
+          const int64_t never = static_cast<int64_t>(1) << 62;
+          int64_t rel = (L.bm_busy[0] >> lane) & 1ull ? event_time(lane < N ? lane : 0, T) : never;   // (events lie after the step before)
+          for (; s < step_end; ++s) {
+            if (steps_ahead == 0) {
+              const uint32_t s_lane = s + (static_cast<uint32_t>(lane) >> lg_n);
+              const int g = lane & ((1 << lg_n) - 1);
+              const uint32_t thr = a.arr_thr[mod_rows > 1u ? 3 * static_cast<size_t>(s_lane % mod_rows) : 0];
+              uint32_t w[4];
+              philox4x32_10(key0, key1, s_lane, 0u, static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
+              ahead = __ballot(g < N && w[0] >= thr);
+              steps_ahead = 64 >> lg_n;
+            }
+            if ((ahead & ((1ull << (1 << lg_n)) - 1ull)) || __ballot(rel <= 0)) break;
+            rel -= dt_ns;
+            ahead >>= 1 << lg_n;
+            --steps_ahead;
+          }
+          if (s != s_first) {
+            ended += s - s_first;
+            T = (static_cast<int64_t>(s) + 1) * dt_ns;
+            if (s == step_end) { T = static_cast<int64_t>(s) * dt_ns; break; }
+            if (mod_rows > 1u) {
+              mod_row = s % mod_rows;
+              thr_ahead = a.arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
+            }
+          }
+        }
+        if (steps_ahead > 0) { ahead >>= 1 << lg_n; --steps_ahead; }   // this step is gone through now
+      }
+    }
     // (No barrier here: a wave goes from its last settling straight into the next step's completion pass. Until the
     // barrier that ends it a wave touches its own servers and bitmap words only, and adds to sums that nobody reads before.)
     // abandonment only: how many waiting requests of class `tid` leave at the start of this step (asked for
@@ -1114,7 +1165,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       const int x = L.cs[CS_X + k], ym = L.cs[CS_YM + k], ys = L.cs[CS_YS + k];
       uint32_t tail = static_cast<uint32_t>(L.cs[CS_QHEAD + k]);
       const uint32_t ring_len = AB ? static_cast<uint32_t>(L.sc[SC_QLEN + k]) : 0u;
-      if (s != step_begin) add_step_sums(k, qp, qd, x, ym, ys);   // of the step before
+      add_step_sums(k, ended, qp, qd, x, ym, ys);   // of the steps before
       L.acc[AC_ARRIVALS + k] = 0; L.acc[AC_X + k] = 0; L.acc[AC_YM + k] = 0; L.acc[AC_YS + k] = 0;
       L.cs[CS_X + k] = x + dx; L.cs[CS_YM + k] = ym + dym; L.cs[CS_YS + k] = ys + dys;
       if constexpr (AB) {   // abandonments come first: they free room in the queue
@@ -1156,6 +1207,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
       }
     }
+    ended = 0;
     uint32_t ncomp_own = 0;   // (the first wave's count of completed prefills)
     if (tid < 64) {
       const uint32_t ncomp = rank_bitmap(L.bm_comp, L.pre_c, nwords_m, Mp);
@@ -2258,8 +2310,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     }
   }
   __syncthreads();
-  // the sums over steps get the last step's counters (those of the others are added a step later)
-  if (n_steps > 0 && tid < K) add_step_sums(tid, L.cs[CS_QP + tid], L.cs[CS_QD + tid], L.cs[CS_X + tid], L.cs[CS_YM + tid], L.cs[CS_YS + tid]);
+  // the sums over steps get the last step's counters (those of the others are in them)
+  if (tid < K) add_step_sums(tid, ended, L.cs[CS_QP + tid], L.cs[CS_QD + tid], L.cs[CS_X + tid], L.cs[CS_YM + tid], L.cs[CS_YS + tid]);
   if (tid == 0) L.tl[kMaxK * kNTally + SIM_G_STEPS] += n_steps;
   if constexpr (AB) {   // the rings leave the launch without dead entries
     const uint32_t s_last = step_begin + n_steps - 1u;
