@@ -366,6 +366,38 @@ __device__ __forceinline__ uint64_t wave_sum64(uint64_t v)
   return s0 + (s1 << 16) + (s2 << 32);
 }
 
+// The same value of the lane that a data-parallel-primitive control pairs this one with.
+template <int CTRL>
+__device__ __forceinline__ double dpp_of(double v)
+{
+  const int64_t b = __double_as_longlong(v);
+  const int lo = static_cast<int>(b), hi = static_cast<int>(b >> 32);
+  const int l2 = __builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xF, 0xF, false), h2 = __builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xF, 0xF, false);
+  return __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(static_cast<uint32_t>(h2)) << 32) | static_cast<uint32_t>(l2)));
+}
+// Sum, least and largest over groups of 2, 4 or 8 neighbouring lanes (lg = 1, 2, 3, wave-uniform); every lane gets it.
+__device__ __forceinline__ uint32_t group_sum(uint32_t v, int lg)
+{
+  v = dpp_add<0xB1, 0xF>(v);               // quad_perm [1,0,3,2]
+  if (lg > 1) v = dpp_add<0x4E, 0xF>(v);   // quad_perm [2,3,0,1]
+  if (lg > 2) v = dpp_add<0x141, 0xF>(v);  // row_half_mirror
+  return v;
+}
+__device__ __forceinline__ double group_min(double v, int lg)
+{
+  v = fmin(v, dpp_of<0xB1>(v));
+  if (lg > 1) v = fmin(v, dpp_of<0x4E>(v));
+  if (lg > 2) v = fmin(v, dpp_of<0x141>(v));
+  return v;
+}
+__device__ __forceinline__ double readlane_f64(double v, int l)
+{
+  const int64_t b = __double_as_longlong(v);
+  const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(b), l));
+  const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(b >> 32), l));
+  return __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo));
+}
+
 // ---- wave-level folding of per-event class updates: lanes of one class are combined first, so that a
 // counter sees one LDS atomic per wave and class instead of one per event. All take uniform control flow.
 __device__ __forceinline__ void wave_count_by_class(bool active, int k, int K, uint64_t *base, int stride)
@@ -1731,28 +1763,51 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         if (gate_on) {
           nidle = __builtin_amdgcn_readfirstlane(L.sc[SC_NIDLE]);
           const int limit = nidle < kAdmChunk ? nidle : kAdmChunk;
-          int cnt[kMaxK], qp[kMaxK], xs[kMaxK], ncand = 0;
-          uint32_t head[kMaxK];
-          const int cs_lane = L.cs[lane];   // the class state, one word per lane: one trip to LDS
-#pragma unroll
-          for (int k = 0; k < kMaxK; ++k) {
-            // wave-uniform values, kept in scalar registers
-            qp[k] = k < K ? __builtin_amdgcn_readlane(cs_lane, CS_QP + k) : 0;
-            xs[k] = k < K ? __builtin_amdgcn_readlane(cs_lane, CS_X + k) : 0;
-            head[k] = k < K ? static_cast<uint32_t>(__builtin_amdgcn_readlane(cs_lane, CS_QHEAD + k)) : 0u;
-            const bool eligible = qp[k] > 0 && ((admissible >> k) & 1ull);
-            cnt[k] = eligible ? (qp[k] < limit ? qp[k] : limit) : 0;
-            ncand += cnt[k];
-          }
+          // A candidate is ranked by 2, 4 or 8 neighbouring lanes (as many as there are classes), each of which counts
+          // the candidates of one class that sort before it. A lane keeps its class for the pass: targets, counters and
+          // how many candidates the class has.
+          const int lg = K <= 2 ? 1 : K <= 4 ? 2 : 3;
+          const int k2 = lane & ((1 << lg) - 1);
+          const ClassTargets t2 = load_targets(L.gtab, k2);
+          const int xs2 = L.cs[CS_X + k2], qp2 = L.cs[CS_QP + k2];
+          const uint32_t head2 = static_cast<uint32_t>(L.cs[CS_QHEAD + k2]);
+          int cnt2 = ((admissible >> k2) & 1ull) && qp2 > 0 ? (qp2 < limit ? qp2 : limit) : 0;
+          int ncand = __builtin_amdgcn_readfirstlane(static_cast<int>(group_sum(static_cast<uint32_t>(cnt2), lg)));
           nadm = ncand < limit ? ncand : limit;
+          if (gate_mode == SIM_GATE_OCCUPANCY && (ncand << lg) > NT && ncand > nadm) {
+            // Long queues offer up to `limit` candidates of every class, `limit` of which are admitted in all, and the others
+            // need no rank. The keys of a class rise linearly, so a bound on the key tells how many of its candidates lie
+            // below: the lanes try 64 bounds between the least key and one that is certainly high enough, and the classes
+            // are cut behind the least bound with nadm candidates below it. Counted with a margin of one candidate a
+            // class on the one side and cut with two on the other, so rounding cannot lose one that is admitted (what
+            // is not a number cuts nothing). With six classes and 150 admissions a step the ranking went over 900 candidates,
+            // seven rounds of sixteen waves.
+            const double inf = __longlong_as_double(0x7FF0000000000000ll);
+            const double base2 = static_cast<double>(xs2) - t2.nx;
+            const double least = group_min(cnt2 > 0 ? base2 * t2.invx : inf, lg);
+            const double most = -group_min(cnt2 > 0 ? -((base2 + static_cast<double>(cnt2 - 1)) * t2.invx) : inf, lg);
+            const double full = group_min(cnt2 >= nadm ? (base2 + static_cast<double>(nadm - 1)) * t2.invx : inf, lg);
+            const double high = full < inf ? full : most;
+            const double bound = least + (high - least) * (static_cast<double>(lane + 1) * 0.015625);
+            int below = 0;
+            for (int k = 0; k < K; ++k) {   // wave-uniform
+              const double n = bound * readlane_f64(t2.xstar, k) - readlane_f64(base2, k);
+              const int c = __builtin_amdgcn_readlane(cnt2, k);
+              below += n > 0.0 ? (n < static_cast<double>(c) ? static_cast<int>(n) : c) : 0;
+            }
+            const uint64_t enough = __ballot(below >= nadm);
+            if (enough) {
+              const double cut = readlane_f64(bound, __ffsll(static_cast<long long>(enough)) - 1);
+              const double n = cut * t2.xstar - base2 + 3.0;
+              if (n < static_cast<double>(cnt2)) cnt2 = n > 0.0 ? static_cast<int>(n) : 0;
+              ncand = __builtin_amdgcn_readfirstlane(static_cast<int>(group_sum(static_cast<uint32_t>(cnt2), lg)));
+            }
+          }
           if constexpr (AB) {
             // where the candidates sit in their rings: a wave per class walks from the head past the dead entries
             // (the last waves take this: the first ones rank the candidates below)
             for (int k = nwaves - 1 - wave; k < K; k += nwaves) {   // wave-uniform
-              uint32_t need = 0;
-#pragma unroll
-              for (int kk = 0; kk < kMaxK; ++kk)
-                if (kk == k) need = static_cast<uint32_t>(cnt[kk]);
+              const uint32_t need = static_cast<uint32_t>(__builtin_amdgcn_readlane(cnt2, k));
               uint32_t qlen = static_cast<uint32_t>(L.sc[SC_QLEN + k]);
               if (qlen > queue_cap) qlen = queue_cap;
               const uint32_t hd = static_cast<uint32_t>(L.cs[CS_QHEAD + k]);
@@ -1815,30 +1870,34 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             }
           }
           const bool ranks = !(kStageEarly && nwaves >= 8 && (wave == ring_wave || wave == ring_wave_m));   // wave-uniform
-          // A lane takes one candidate and one class: how many candidates of that class sort before it. The lanes of a
-          // candidate (2, 4 or 8 of them, as many as there are classes) are neighbours and add up what they find, so
-          // that the searches of a candidate in the other classes run side by side on all waves.
-          const int lg = K <= 2 ? 1 : K <= 4 ? 2 : 3;
+          // The searches of a candidate in the other classes run side by side on neighbouring lanes, which add up what they
+          // find; the candidates of a class follow those of the class before it.
+          int first_of[kMaxK];   // first candidate of each class
+          {
+            int run = 0;
+#pragma unroll
+            for (int kk = 0; kk < kMaxK; ++kk) {
+              first_of[kk] = run;
+              if (kk < K) run += __builtin_amdgcn_readlane(cnt2, kk);
+            }
+          }
           for (int c0 = rank_first; ranks && c0 < (ncand << lg); c0 += rank_step) {   // wave-uniform trip count
-            const int c = (c0 + lane) >> lg, k2 = lane & ((1 << lg) - 1);
+            const int c = (c0 + lane) >> lg;
             int k = 0, m = c, lo = 0;
 #pragma unroll
-            for (int kk = 0; kk < kMaxK - 1; ++kk)
-              if (k == kk && m >= cnt[kk]) { m -= cnt[kk]; k = kk + 1; }
-            if (c < ncand && k2 < K) {
-              // this candidate's own key, and the other class's targets and counters: one trip to LDS
-              const ClassTargets own = load_targets(L.gtab, k), t2 = load_targets(L.gtab, k2);
-              const int xs_own = L.cs[CS_X + k], qp_own = L.cs[CS_QP + k], xs2 = L.cs[CS_X + k2], qp2 = L.cs[CS_QP + k2];
-              const uint32_t head_own = static_cast<uint32_t>(L.cs[CS_QHEAD + k]), head2 = static_cast<uint32_t>(L.cs[CS_QHEAD + k2]);
-              const GateKey key = gate_key(gate_mode, queue_cap, own, qring, lo_tab, xs_own, qp_own, head_own, k, m, kAdmChunk);
-              auto before = [&](int j) __attribute__((always_inline)) -> bool {   // is the j-th of class k2 admitted before it
-                return gate_before(gate_key(gate_mode, queue_cap, t2, qring, lo_tab, xs2, qp2, head2, k2, j, kAdmChunk), k2, key, k);
-              };
-              const bool eligible2 = qp2 > 0 && ((admissible >> k2) & 1ull);
-              const int cnt2 = eligible2 ? (qp2 < limit ? qp2 : limit) : 0;
+            for (int kk = 1; kk < kMaxK; ++kk)
+              if (kk < K && c >= first_of[kk]) { k = kk; m = c - first_of[kk]; }
+            if (c < ncand) {
               if (k2 == k) {
                 lo = m;
               } else if (cnt2 > 0) {   // those before it form a prefix of the class
+                // this candidate's own key: one trip to LDS
+                const ClassTargets own = load_targets(L.gtab, k);
+                const GateKey key = gate_key(gate_mode, queue_cap, own, qring, lo_tab, L.cs[CS_X + k], L.cs[CS_QP + k],
+                                             static_cast<uint32_t>(L.cs[CS_QHEAD + k]), k, m, kAdmChunk);
+                auto before = [&](int j) __attribute__((always_inline)) -> bool {   // is the j-th of class k2 admitted before it
+                  return gate_before(gate_key(gate_mode, queue_cap, t2, qring, lo_tab, xs2, qp2, head2, k2, j, kAdmChunk), k2, key, k);
+                };
                 int hi = cnt2;
                 if (gate_mode == SIM_GATE_OCCUPANCY) {
                   // the key is linear in the sequence number: the prefix ends next to its estimate; if the exact
@@ -1859,10 +1918,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 }
               }
             }
-            uint32_t rank_sum = dpp_add<0xB1, 0xF>(static_cast<uint32_t>(lo));    // quad_perm [1,0,3,2]
-            if (lg > 1) rank_sum = dpp_add<0x4E, 0xF>(rank_sum);                  // quad_perm [2,3,0,1]
-            if (lg > 2) rank_sum = dpp_add<0x141, 0xF>(rank_sum);                 // row_half_mirror
-            const int rank = static_cast<int>(rank_sum);
+            const int rank = static_cast<int>(group_sum(static_cast<uint32_t>(lo), lg));
             if (c < ncand && k2 == 0 && rank < nadm) {
               L.adm[rank] = static_cast<uint32_t>(k) | (static_cast<uint32_t>(m) << 3);
               atomicAdd(&L.sc[SC_ADMK + k], 1);
