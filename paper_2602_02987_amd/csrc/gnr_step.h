@@ -1900,14 +1900,21 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 };
                 int hi = cnt2;
                 if (gate_mode == SIM_GATE_OCCUPANCY) {
-                  // the key is linear in the sequence number: the prefix ends next to its estimate; if the exact
-                  // comparisons on both sides say otherwise, the search below runs over the side they point to
-                  const double est = key.a * t2.xstar - (static_cast<double>(xs2) - t2.nx);
+                  // The key is linear in the sequence number, so the prefix ends at an estimate whose rounding errors are
+                  // below 1e-8 while the terms are below 1e6: no comparison is needed unless it lies next to a whole
+                  // number (equal keys among them). There, or with larger terms, the exact comparisons on both sides of
+                  // it are made, and if they say otherwise the search below runs over the side they point to.
+                  const double reach = key.a * t2.xstar, est = reach - (static_cast<double>(xs2) - t2.nx);
                   const int g0 = est > 0.0 ? (est < static_cast<double>(hi) ? static_cast<int>(est) : hi) : 0;
-                  const int l2 = g0 > 1 ? g0 - 1 : 0, h2 = g0 + 2 < hi ? g0 + 2 : hi;
-                  const bool b0 = l2 == 0 || before(l2 - 1), b1 = h2 < hi && before(h2);
-                  if (b0) lo = b1 ? h2 + 1 : l2; else hi = l2 - 1;
-                  if (b0 && !b1) hi = h2;
+                  if (fabs(est - rint(est)) > 1e-6 && fabs(reach) < 1e6 && fabs(t2.nx) < 1e6) {
+                    lo = est > 0.0 ? (g0 + 1 < hi ? g0 + 1 : hi) : 0;
+                    hi = lo;
+                  } else {
+                    const int l2 = g0 > 1 ? g0 - 1 : 0, h2 = g0 + 2 < hi ? g0 + 2 : hi;
+                    const bool b0 = l2 == 0 || before(l2 - 1), b1 = h2 < hi && before(h2);
+                    if (b0) lo = b1 ? h2 + 1 : l2; else hi = l2 - 1;
+                    if (b0 && !b1) hi = h2;
+                  }
                 } else if (gate_mode == SIM_GATE_PRIORITY) {   // one key for the whole class
                   lo = before(0) ? hi : 0;
                   hi = lo;
