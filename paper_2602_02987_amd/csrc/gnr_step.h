@@ -4,8 +4,8 @@
 // handled in blocks of 64 (one per lane); wave w owns the blocks w, w + nwaves, ..., and a server's clock, record and
 // slot row are changed by the wave that owns it, except for the placements of the router. A server is touched only
 // when its batch changes (an event): the identical iterations in between follow from its event time. Class-level counters (queue lengths, occupancies, tallies) live in LDS and
-// are updated with integer atomics, which commute; the lanes of a wave are combined first, because atomics of
-// several lanes on one LDS address serialise. Everything that the policy defines sequentially (order of
+// are updated with integer atomics, which commute, by the lanes that have something to add (a few of a wave as a rule;
+// sums that all lanes add to are spread over several words). Everything that the policy defines sequentially (order of
 // simultaneous prefill completions, of gate admissions, of routed requests) is reproduced with 64-server
 // ballot words in LDS and prefix popcounts over them.
 #ifndef GNR_STEP_H
@@ -398,32 +398,6 @@ __device__ __forceinline__ double readlane_f64(double v, int l)
   return __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo));
 }
 
-// ---- wave-level folding of per-event class updates: lanes of one class are combined first, so that a
-// counter sees one LDS atomic per wave and class instead of one per event. All take uniform control flow.
-__device__ __forceinline__ void wave_count_by_class(bool active, int k, int K, uint64_t *base, int stride)
-{
-  for (int c = 0; c < K; ++c) {
-    const uint64_t m = __ballot(active && k == c);
-    if (m && (threadIdx.x & 63) == 0) lds_add64(&base[c * stride], static_cast<uint64_t>(__popcll(m)));
-  }
-}
-__device__ __forceinline__ void wave_count_by_class_i32(bool active, int k, int K, int32_t *base, int sign)
-{
-  for (int c = 0; c < K; ++c) {
-    const uint64_t m = __ballot(active && k == c);
-    if (m && (threadIdx.x & 63) == 0) atomicAdd(&base[c], sign * __popcll(m));
-  }
-}
-__device__ __forceinline__ void wave_sum_by_class(bool active, int k, int K, uint64_t v, uint64_t *base, int stride)
-{
-  for (int c = 0; c < K; ++c) {
-    const bool in = active && k == c;
-    if (__ballot(in)) {
-      const uint64_t t = wave_sum64(in ? v : 0ull);
-      if ((threadIdx.x & 63) == 0) lds_add64(&base[c * stride], t);
-    }
-  }
-}
 // Sum over the wave of per-class byte vectors (8 x uint8, each <= 128): 16-bit fields, even and odd classes.
 __device__ __forceinline__ void wave_sum_bytes(uint64_t v, uint64_t &even, uint64_t &odd)
 {
@@ -906,9 +880,9 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         const int g = active ? static_cast<int>(ev_g[e0 + lane]) : 0;
         const int wi = g >> 6;
         const uint64_t bit = active ? 1ull << (g & 63) : 0ull;
-        uint64_t nc = 0, nj = 0;
+        uint64_t nc = 0, nj = 0, pf = 0;
         uint32_t it_tal = 0;
-        if (active) { nc = rec[g].n_cls; nj = rec[g].n_join; it_tal = rec[g].iter; }
+        if (active) { nc = rec[g].n_cls; nj = rec[g].n_join; pf = rec[g].pf_job; it_tal = rec[g].iter; }
         const uint32_t it = L.ev_it[g];
         int nd = active ? static_cast<int>(L.loads[g]) : 0;
         const int nd_before = nd;
@@ -1019,7 +993,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             rem -= static_cast<int>(m) * ptok;
             L.rem[g] = static_cast<uint16_t>(rem);
             if (rem == 0) {
-              const uint64_t jw = rec[g].pf_job;
+              const uint64_t jw = pf;
               const int k = static_cast<int>(jw >> 29) & 7;
               const uint32_t stamp = static_cast<uint32_t>(jw) & 0x1FFFFFFFu;
               pe.done = true; pe.k = k; pe.nc = nc;
@@ -1395,13 +1369,13 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               if (c_dl != kNever) atomicAdd(&(solo ? dcal : dcal_m)[static_cast<size_t>(k) * cal_n + (c_dl & p.cal_mask)], 1u);
             }
           }
-          wave_count_by_class_i32(kept, k, K, &L.cs[CS_QD], 1);
-          if constexpr (AB) {   // the weighted router also counts what waits in the solo group's buffer per class
-            if constexpr (WS) wave_count_by_class_i32(kept && solo, k, K, &L.cs[CS_QDS], 1);
-          }
-          if (__ballot(active && !kept)) {
-            wave_count_by_class(active && !kept, k, K, &L.tl[SIM_T_DROP_D], kNTally);
-            if (lane == 0) L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
+          if (kept) {
+            atomicAdd(&L.cs[CS_QD + k], 1);
+            // the weighted router also counts what waits in the solo group's buffer per class
+            if constexpr (WS) { if (solo) atomicAdd(&L.cs[CS_QDS + k], 1); }
+          } else if (active) {
+            lds_add64(&L.tl[k * kNTally + SIM_T_DROP_D], 1);
+            L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
           }
         }
         seen0 += solo_round;
@@ -1417,9 +1391,9 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       const uint32_t ncomp = static_cast<uint32_t>(L.sc[SC_NCOMP]);
       const uint32_t dcount = static_cast<uint32_t>(L.cs[CS_DCOUNT]), dhead = static_cast<uint32_t>(L.cs[CS_DHEAD]);
       const uint32_t dfill = AB ? static_cast<uint32_t>(L.sc[SC_DLEN]) : dcount;   // ring entries before the tail
-      // (64 to a wave; in a large workgroup not the first waves, which have ranked the bitmaps and go on to rank the
-      // gate's candidates: the last waves, or with abandonment, whose arrivals the last two waves take, the ones before them)
-      const int comp_turn = nwaves < 8 ? wave : (AB ? (2 * nwaves - 3 - wave) % nwaves : nwaves - 1 - wave);
+      // (64 to a wave; not the first waves, which have ranked the bitmaps and go on to rank the gate's candidates: the last
+      // ones, or with abandonment, whose arrivals the last two waves take, in a large workgroup the ones before them)
+      const int comp_turn = AB && nwaves >= 8 ? (2 * nwaves - 3 - wave) % nwaves : nwaves - 1 - wave;
       for (uint32_t j0 = static_cast<uint32_t>(comp_turn) * 64u; j0 < ncomp; j0 += NT) {   // wave-uniform trip count
         const uint32_t j = j0 + lane;
         const bool active = j < ncomp;
@@ -1447,10 +1421,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             }
           }
         }
-        wave_count_by_class_i32(active && kept, k, K, &L.cs[CS_QD], 1);
-        if (__ballot(active && !kept)) {
-          wave_count_by_class(active && !kept, k, K, &L.tl[SIM_T_DROP_D], kNTally);
-          if (lane == 0) L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
+        if (kept) {
+          atomicAdd(&L.cs[CS_QD + k], 1);
+        } else if (active) {
+          lds_add64(&L.tl[k * kNTally + SIM_T_DROP_D], 1);
+          L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
         }
       }
     }
@@ -2068,7 +2043,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         bool gate_more = false;
         bool a_active = false;   // this lane's admission of the pass: slot, class, arrival stamp, decodes beside it
         int a_g = 0, a_k = 0;
-        uint32_t a_stamp = 0;
+        uint32_t a_stamp = 0, a_in = 0, a_out = 0;
         uint64_t a_nc = 0;
         if (gate_on) {
           if (pass == 0 && tid == 0) {   // the completions of this step are in the buffer
@@ -2077,7 +2052,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           }
           // Admission j goes to the idle prefill slot of rank j; one thread per admission (a pass admits no more than
           // the workgroup has threads). Here the wave only reads what segment C changes (queue heads, decode
-          // counts of the servers) and asks memory for the request's stamp; the rest follows in segment C.
+          // counts of the servers) and asks memory for the request's stamp and lengths; the rest follows in segment C.
           if (wave_base < nadm) {   // wave-uniform
             const int j = wave_base + lane;
             a_active = j < nadm;
@@ -2093,6 +2068,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 if (dl != kNever) atomicSub(&cal[static_cast<size_t>(a_k) * cal_n + (dl & p.cal_mask)], 1u);
               }
               if (L.loads[a_g]) a_nc = rec[a_g].n_cls;   // (before this pass's placements on the server)
+              uint32_t w[4];
+              philox4x32_10(key0, key1, s, 1u, static_cast<uint32_t>(a_g), static_cast<uint32_t>(r), w);
+              a_in = a.len_tab[(static_cast<size_t>(a_k) * 2 + 0) * kTableSize + (w[0] >> 16)];
+              a_out = a.len_tab[(static_cast<size_t>(a_k) * 2 + 1) * kTableSize + (w[1] >> 16)];
             }
           }
           if (nadm == kAdmChunk && nidle > kAdmChunk) {   // rare: more idle slots than one pass serves
@@ -2129,22 +2108,16 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
 
         // ---------------- segment C ----------------
         if (gate_on && wave_base < nadm) {   // wave-uniform: the admissions this wave began in segment B
-          uint64_t wait = 0;
           if (a_active) {
             const int g = a_g, k = a_k;
-            wait = static_cast<uint64_t>(s - a_stamp);
-            uint32_t w[4];
-            philox4x32_10(key0, key1, s, 1u, static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
-            const uint32_t Pl = a.len_tab[(static_cast<size_t>(k) * 2 + 0) * kTableSize + (w[0] >> 16)];
-            const uint32_t Dl = a.len_tab[(static_cast<size_t>(k) * 2 + 1) * kTableSize + (w[1] >> 16)];
             rec[g].pf_job = static_cast<uint64_t>(a_stamp) | (static_cast<uint64_t>(k) << 29) |
-                            (static_cast<uint64_t>(Pl - 1) << 32) | (static_cast<uint64_t>(Dl - 1) << 48);
+                            (static_cast<uint64_t>(a_in - 1) << 32) | (static_cast<uint64_t>(a_out - 1) << 48);
             // an idle prefill slot implies that the running iteration holds no chunk
-            L.rem[g] = static_cast<uint16_t>(Pl);
+            L.rem[g] = static_cast<uint16_t>(a_in);
+            lds_add64(&L.tl[k * kNTally + SIM_T_WAIT_STEPS], static_cast<uint64_t>(s - a_stamp));
           }
-          wave_sum_by_class(a_active, a_k, K, wait, &L.tl[SIM_T_WAIT_STEPS], kNTally);
-          uint64_t even, odd;   // co-resident decodes switch solo -> mixed
-          wave_sum_bytes(a_nc, even, odd);
+          uint64_t even = 0, odd = 0;   // co-resident decodes switch solo -> mixed
+          if (__ballot(a_nc != 0)) wave_sum_bytes(a_nc, even, odd);
           if (lane == 0 && (even | odd))
             for (int c = 0; c < K; ++c) {
               const int v = static_cast<int>(class_field(even, odd, c));
