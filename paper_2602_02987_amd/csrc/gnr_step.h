@@ -293,14 +293,15 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(bm_touch, uint64_t, nw)
   GNR_TAKE(bm_fin, uint64_t, nw)
   GNR_TAKE(bm_chunk, uint64_t, nw)
-  const size_t lvl_off = off, lvl_least = waves * kEvPerWave * 4 + 16 * nw + 2 * ((4 * (nw + 1) + 7) & ~size_t(7));
+  const size_t lvl_off = off, lvl_least = waves * (kEvPerWave * 6 + 128) - 128 + 16 * nw + 2 * ((4 * (nw + 1) + 7) & ~size_t(7));
   GNR_TAKE(bm_lvl, uint64_t, kRouteLevels * nw)
   GNR_TAKE(pre_lvl, uint16_t, kRouteLevels * nw)
   GNR_TAKE(pre_c, uint16_t, nw + 1)
   GNR_TAKE(pre, uint16_t, nw + 1)
   GNR_TAKE(ta, uint64_t, (TA_TBT + (NWS ? kMaxK : p.K)) * (SMALL ? kTallyRowsSmall : kTallyRows))
   // (no smaller than the tables that stood here before them, so that the same numbers of servers fit and the launch
-  // shapes stay: four bytes per queue entry, 16 per word, two tables of four bytes a word and one more)
+  // shapes stay: six bytes per queue entry and 128 a wave, 16 per word, two tables of four bytes a word and one more, less
+  // what the class sums and thresholds above have grown by)
   off = off - lvl_off < lvl_least ? lvl_off + lvl_least : off;
   // from here on the offsets depend on the configuration
   GNR_TAKE(ev_t, uint32_t, p.N)
