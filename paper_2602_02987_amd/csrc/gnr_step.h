@@ -1788,14 +1788,16 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           int cnt2 = ((admissible >> k2) & 1ull) && qp2 > 0 ? (qp2 < limit ? qp2 : limit) : 0;
           int ncand = __builtin_amdgcn_readfirstlane(static_cast<int>(group_sum(static_cast<uint32_t>(cnt2), lg)));
           nadm = ncand < limit ? ncand : limit;
-          if (gate_mode == SIM_GATE_OCCUPANCY && (ncand << lg) > NT && ncand > nadm) {
+          if (gate_mode == SIM_GATE_OCCUPANCY && (ncand << lg) > NT && ncand > nadm &&
+              __ballot(cnt2 > 0 && !(fabs(t2.nx) < 1e9)) == 0) {
             // Long queues offer up to `limit` candidates of every class, `limit` of which are admitted in all, and the others
             // need no rank. The keys of a class rise linearly, so a bound on the key tells how many of its candidates lie
             // below: the lanes try 64 bounds between the least key and one that is certainly high enough, and the classes
             // are cut behind the least bound with nadm candidates below it. Counted with a margin of one candidate a
-            // class on the one side and cut with two on the other, so rounding cannot lose one that is admitted (what
-            // is not a number cuts nothing). With six classes and 150 admissions a step the ranking went over 900 candidates,
-            // seven rounds of sixteen waves.
+            // class on the one side and cut with two on the other, so rounding cannot lose one that is admitted: no class
+            // has a term of a milliard or more (below that a product's error, a part in 2^52 of it, is under 1e-6; with
+            // larger targets nothing is cut). With six classes and 150 admissions a step the ranking went over 900
+            // candidates, seven rounds of sixteen waves.
             const double inf = __longlong_as_double(0x7FF0000000000000ll);
             const double base2 = static_cast<double>(xs2) - t2.nx;
             const double least = group_min(cnt2 > 0 ? base2 * t2.invx : inf, lg);

@@ -1,6 +1,7 @@
 """GPU parity of the occupancy gate where its short cuts decide: queues much longer than a step's admissions (the classes are cut
 before the ranking), targets whose estimate is exact, lies next to a whole number (equal targets, ties down to the class
-index), or is not used (terms of a million and more), and a burst of idle slots after a move of the split."""
+index), is not used (terms of a million and more), or nothing may be cut (a milliard and more), and a burst of idle slots after
+a move of the split."""
 from dataclasses import replace
 
 import pytest
@@ -18,6 +19,9 @@ _TARGETS = {
     "one_zero": lambda k: 0.0 if k == 1 else 0.03 + 0.011 * k,
     "huge": lambda k: 1e6 * (1 + k),
     "huge_and_tiny": lambda k: 1e9 if k % 2 else 1e-9,
+    # a request more or less is lost in the rounding of these
+    "beyond_rounding": lambda k: (0.03, 1e16, 1e300)[k % 3] * (1 + 0.1 * k),
+    "all_beyond": lambda k: 1e200 * (1 + k),
     "tiny": lambda k: 1e-12 * (1 + 0.37 * k),
 }
 
