@@ -269,3 +269,26 @@ def test_launch_shape_follows_the_replications():
         assert lds <= 160 * 1024 and t in (64, 128, 256, 512, 1024) and w in (2, 4)
     # what a handle is created with is what the plan says (no device: compared through the on-chip need)
     assert B.sim_onchip_bytes(W.config(3))[0] == B.sim_launch_plan(W.config(3), 1)[1]
+
+
+@pytest.mark.parametrize("bits", [62, 63, 64])
+def test_statistics_are_the_structure_value_by_value(B, bits):
+    """The arrays handed out by Sim.stats against the structure's fields read one value at a time: whole numbers on both
+    sides of the signed range, not-a-number patterns among the reals."""
+    rng = np.random.default_rng(bits)
+    st = B.SimStatsC.from_buffer_copy(rng.integers(0, 256, ctypes.sizeof(B.SimStatsC), dtype=np.uint8).tobytes())
+    for i in range(len(st.glob)):
+        st.glob[i] = int(rng.integers(0, 1 << 62)) >> 1 if i else (1 << bits) - 1
+    got = B._stats_dict(st)
+    assert list(got) == [name for name, _ in st._fields_]
+    for name, _ in st._fields_:
+        v = getattr(st, name)
+        if name == "tally":
+            want = np.array([[v[k][t] for t in range(len(B.TALLY))] for k in range(B.MAXK)], dtype=np.uint64)
+        elif hasattr(v, "__len__"):
+            want = np.array(list(v))
+        else:
+            assert repr(got[name]) == repr(v)
+            continue
+        assert got[name].dtype == want.dtype and got[name].shape == want.shape and got[name].tobytes() == want.tobytes()
+        got[name][...] = 0   # writable, and no other field's
