@@ -70,7 +70,11 @@ int step_threads(Params q, int reps)
   // that keeps the number of rounds lowest was the fastest or within 3 % of it in every case; sixteen waves
   // measured 4 to 26 % faster than eight on 2048 to 5000 servers with up to 256 replications.
   // With fewer than two blocks to a wave the larger workgroup only pays where it can still run in the roomy form
-  // (256 servers, 1024 replications: 128 threads roomy 19.0 ms per 1000 steps, 256 threads dense 19.6).
+  // (256 servers, 1024 replications: 128 threads roomy 19.0 ms per 1000 steps, 256 threads dense 19.6). With deadline rings
+  // eight waves pay in the dense form too, from a block a wave on: the walks of the rings and the class selection take waves of their own, which
+  // in four waves rank and count beside it (500 steps of 512 replications, 256 threads roomy -> 512 dense: abandonment,
+  // 700 servers 8.9 -> 8.3 ms; weighted router 12.7 -> 10.8; convergence instance of 500 servers 8.4 -> 7.8. Without such
+  // rings -4 to +3 %: 600 servers of two classes 6.4 -> 6.6; four waves instead of two -4 to +1 % with them).
   const int blocks = (q.N + 63) / 64;
   int best = 64, best_rounds = 0;
   for (int t = 64; t <= 1024 && t / 64 < 2 * blocks; t *= 2) {   // (a wave more than there are blocks only waits)
@@ -79,7 +83,7 @@ int step_threads(Params q, int reps)
     if (lds > kLdsPerComputeUnit) break;
     const int rounds = launch_rounds(reps, t, lds, 4);
     // few blocks a wave, and dense (sixteen waves have no roomy form)
-    const bool thin = blocks < 2 * (t / 64) && (t > 512 || launch_rounds(reps, t, lds, 2) > rounds);
+    const bool thin = blocks < 2 * (t / 64) && !(q.dl_rings && t == 512 && blocks >= 8) && (t > 512 || launch_rounds(reps, t, lds, 2) > rounds);
     if (best_rounds == 0 || rounds < best_rounds || (rounds == best_rounds && !thin)) { best = t; best_rounds = rounds; }
   }
   return best;
