@@ -41,15 +41,20 @@ static int compute_units()
   return n;
 }
 
-// Rounds of workgroups a launch of `reps` workgroups needs when a SIMD holds `per_simd` waves of the kernel: every
-// workgroup runs for the whole launch, so one that finds no place at first waits for another to end.
-static int launch_rounds(int reps, int threads, size_t lds_bytes, int per_simd)
+// Workgroups a compute unit holds at once when its SIMDs hold `per_simd` waves of the kernel each.
+static int workgroups_at_once(int threads, size_t lds_bytes, int per_simd)
 {
   const int by_waves = 4 * per_simd / (threads / 64);   // wave slots of the four SIMDs
   const int by_lds = static_cast<int>(kLdsPerComputeUnit / (lds_bytes ? lds_bytes : 1));
-  int wgs = by_waves < by_lds ? by_waves : by_lds;
-  wgs = wgs < 1 ? 1 : wgs;
-  const int at_once = compute_units() * wgs;
+  const int wgs = by_waves < by_lds ? by_waves : by_lds;
+  return wgs < 1 ? 1 : wgs;
+}
+
+// Rounds of workgroups a launch of `reps` workgroups needs: every workgroup runs for the whole launch, so one that finds
+// no place at first waits for another to end.
+static int launch_rounds(int reps, int threads, size_t lds_bytes, int per_simd)
+{
+  const int at_once = compute_units() * workgroups_at_once(threads, lds_bytes, per_simd);
   return (reps + at_once - 1) / at_once;
 }
 
@@ -64,27 +69,38 @@ int step_threads(Params q, int reps)
   // A replication with many servers fills the LDS of a compute unit, runs alone there and wants all sixteen
   // waves to hide latency.
   if (q.N > 5120) return 1024;
-  // Smaller replications share a compute unit. A workgroup steps faster the more waves it has, as long as its
-  // waves have blocks of servers to work on and all workgroups of the launch find a place at once (at most four
-  // waves per SIMD): measured on 256, 1024 and 2048 servers with 128 to 2048 replications, the largest workgroup
-  // that keeps the number of rounds lowest was the fastest or within 3 % of it in every case; sixteen waves
-  // measured 4 to 26 % faster than eight on 2048 to 5000 servers with up to 256 replications.
+  // Smaller replications share a compute unit. A workgroup steps faster the more waves it has, as long as its waves have
+  // blocks of servers to work on and all workgroups of the launch find a place at once (at most four waves per SIMD): the
+  // largest workgroup that keeps the rounds lowest. Rounds count as they are while a full compute unit holds two waves a
+  // SIMD or more; with fewer nothing hides a wave's latency, and a round counts by as much as waves are missing (100 steps,
+  // 3500 servers of eight classes, same-slot decode, 700 replications: three waves a compute unit in one round 12.1 ms,
+  // sixteen in two rounds 3.7; 3000 servers of two classes, 2048 replications: four in two rounds 10.9, twelve in three
+  // 6.3; but eight in one round 4.8 against sixteen in two 6.1, 1000 servers, weighted router).
+  // Of 424 launches timed in every shape (33 to 4600 servers, 200 to 4096 replications) 89 % take the fastest or one within
+  // 3 % of it, 97 % one within 10 %. The others: 11 to 27 % where 3000 to 4000 servers leave a compute unit six waves in one
+  // round, up to 17 % with 300 to 400 servers (eight waves instead of four on 512 replications, one instead of two on 4096),
+  // 9 % with two waves instead of one at 127 to 190 servers in dense rounds, and with sixteen instead of eight on 800 to
+  // 1000 servers with patience and 200 replications.
   // With fewer than two blocks to a wave the larger workgroup only pays where it can still run in the roomy form
   // (256 servers, 1024 replications: 128 threads roomy 19.0 ms per 1000 steps, 256 threads dense 19.6). With deadline rings
-  // eight waves pay in the dense form too, from a block a wave on: the walks of the rings and the class selection take waves of their own, which
-  // in four waves rank and count beside it (500 steps of 512 replications, 256 threads roomy -> 512 dense: abandonment,
-  // 700 servers 8.9 -> 8.3 ms; weighted router 12.7 -> 10.8; convergence instance of 500 servers 8.4 -> 7.8. Without such
-  // rings -4 to +3 %: 600 servers of two classes 6.4 -> 6.6; four waves instead of two -4 to +1 % with them).
+  // eight waves pay in the dense form too, from a block a wave on: the walks of the rings and the class selection take waves
+  // of their own, which in four waves rank and count beside it (500 steps of 512 replications, 256 threads roomy -> 512
+  // dense: abandonment, 700 servers 8.9 -> 8.3 ms; weighted router 12.7 -> 10.8; convergence instance of 500 servers
+  // 8.4 -> 7.8. Without such rings -4 to +3 %: 600 servers of two classes 6.4 -> 6.6; four waves instead of two -4 to +1 %
+  // with them).
+  constexpr int kRound = 840;   // (divisible by one to eight waves)
   const int blocks = (q.N + 63) / 64;
-  int best = 64, best_rounds = 0;
+  int best = 64, best_cost = 0;
   for (int t = 64; t <= 1024 && t / 64 < 2 * blocks; t *= 2) {   // (a wave more than there are blocks only waits)
     q.threads = t;
     const size_t lds = step_lds_bytes(q);
     if (lds > kLdsPerComputeUnit) break;
-    const int rounds = launch_rounds(reps, t, lds, 4);
+    const int waves = t / 64, rounds = launch_rounds(reps, t, lds, 4), held = waves * workgroups_at_once(t, lds, 4);
+    const int cost = rounds * (kRound / (held < 8 ? held : 8));
     // few blocks a wave, and dense (sixteen waves have no roomy form)
-    const bool thin = blocks < 2 * (t / 64) && !(q.dl_rings && t == 512 && blocks >= 8) && (t > 512 || launch_rounds(reps, t, lds, 2) > rounds);
-    if (best_rounds == 0 || rounds < best_rounds || (rounds == best_rounds && !thin)) { best = t; best_rounds = rounds; }
+    const bool rings_pay = q.dl_rings && t == 512 && blocks >= 8;
+    const bool thin = blocks < 2 * waves && !rings_pay && (t > 512 || launch_rounds(reps, t, lds, 2) > rounds);
+    if (best_cost == 0 || cost < best_cost || (cost == best_cost && !thin)) { best = t; best_cost = cost; }
   }
   return best;
 }
