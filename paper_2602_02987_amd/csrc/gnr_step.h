@@ -220,19 +220,18 @@ struct Lds {
   uint64_t *tl;       // [kTallyWords]
   uint64_t *tbth;     // [K][tbt_w]
   uint64_t *bm_idle;  // [nwords] servers below Mp with no prefill in service (the gate looks at those below M)
-  uint64_t *bm_comp;  // [nwords] servers whose prefill completed this step
+  uint64_t *bm_comp;  // [nwords] servers whose prefill completed this step (read until the pass's first segment ends)
   uint64_t *bm_busy;  // [nwords] servers running an iteration
   uint64_t *bm_pin;   // [nwords] servers given work in the middle of an iteration: their event is the end of that iteration
-  uint64_t *bm_due;   // [nwords] servers known to be at an iteration boundary in this step: their event time is that boundary
   uint64_t *bm_touch; // [nwords] servers to settle at the end of the step: at their event, or given work in this step
   uint64_t *bm_fin;   // [nwords] servers whose event is the end of a decode
   uint64_t *bm_chunk; // [nwords] servers whose running iteration carries a prefill chunk
   uint64_t *jobs;     // [kJobsLds] the first requests a routing pass places, copied from the decode buffer
   uint64_t *bm_lvl;   // [kRouteLevels][nwords] routing pass: servers of the routed group with at most (level) decodes
   uint16_t *pre_lvl;  // [kRouteLevels][nwords] exclusive prefix popcounts of bm_lvl, per level
-  uint16_t *pre_c;    // [nwords] exclusive prefix popcounts of bm_comp
-  uint16_t *pre;      // [nwords] exclusive prefix popcounts of bm_idle
-  uint32_t *adm;      // [kAdmChunk] class | sequence-in-class << 3 of each admission
+  uint16_t *pre_c;    // [nwords] exclusive prefix popcounts of bm_comp; in the space of pre_lvl
+  uint16_t *pre;      // [nwords] exclusive prefix popcounts of bm_idle; in the space of pre_lvl
+  uint16_t *adm;      // [kAdmChunk] class | sequence-in-class << 3 of each admission
   uint16_t *adm_slot; // [kAdmChunk] prefill slot (server) that takes the admission of each rank
   uint32_t *lh;       // [2][kLoadBins] servers per decode count: solo group, mixed group
   uint16_t *ev_g;     // [waves][kEvPerWave] servers queued by a wave: at their event, given jobs, or to settle
@@ -280,29 +279,47 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(cthr, uint32_t, 8)
   GNR_TAKE(gtab, double, 5 * kMaxK)
   GNR_TAKE(sc, int32_t, SC_WORDS)
-  GNR_TAKE(adm, uint32_t, kAdmChunk)
+  GNR_TAKE(adm, uint16_t, kAdmChunk)
   GNR_TAKE(adm_slot, uint16_t, kAdmChunk)
   GNR_TAKE(lh, uint32_t, 2 * kLoadBins)
   GNR_TAKE(ev_g, uint16_t, waves * kEvPerWave)
-  GNR_TAKE(stage, uint16_t, waves * 64)
+  if (SMALL) {
+    // the events of a step are over when its admissions are ranked, and those have taken their slots when the next ones begin
+    static_assert(2 * kAdmChunkSmall >= 2 * 64, "two waves' lanes in the two tables of the admissions");
+    L.stage = L.adm;
+  } else {
+    GNR_TAKE(stage, uint16_t, waves * 64)
+  }
   GNR_TAKE(bm_idle, uint64_t, nw)
-  GNR_TAKE(bm_comp, uint64_t, nw)
   GNR_TAKE(bm_busy, uint64_t, nw)
   GNR_TAKE(bm_pin, uint64_t, nw)
-  GNR_TAKE(bm_due, uint64_t, nw)
   GNR_TAKE(bm_touch, uint64_t, nw)
   GNR_TAKE(bm_fin, uint64_t, nw)
   GNR_TAKE(bm_chunk, uint64_t, nw)
-  const size_t lvl_off = off, lvl_least = waves * (kEvPerWave * 6 + 128) - 128 + 16 * nw + 2 * ((4 * (nw + 1) + 7) & ~size_t(7));
   GNR_TAKE(bm_lvl, uint64_t, kRouteLevels * nw)
+  if (SMALL && waves == 1) {
+    // a wave alone has put the completed prefills into the buffer before it counts the levels of the first pass (with more
+    // waves one may still read them while another counts)
+    L.bm_comp = L.bm_lvl + (kRouteLevels - 1) * nw;
+  } else {
+    GNR_TAKE(bm_comp, uint64_t, nw)
+  }
+  // the ranks of a pass's levels are formed when those of the completions and of the idle slots are no longer read (a
+  // barrier lies between; a further gate pass ranks the idle slots anew)
   GNR_TAKE(pre_lvl, uint16_t, kRouteLevels * nw)
-  GNR_TAKE(pre_c, uint16_t, nw + 1)
-  GNR_TAKE(pre, uint16_t, nw + 1)
+  L.pre_c = L.pre_lvl;
+  L.pre = L.pre_lvl + nw;
   GNR_TAKE(ta, uint64_t, (TA_TBT + (NWS ? kMaxK : p.K)) * (SMALL ? kTallyRowsSmall : kTallyRows))
-  // (no smaller than the tables that stood here before them, so that the same numbers of servers fit and the launch
-  // shapes stay: six bytes per queue entry and 128 a wave, 16 per word, two tables of four bytes a word and one more, less
-  // what the class sums and thresholds above have grown by)
-  off = off - lvl_off < lvl_least ? lvl_off + lvl_least : off;
+  // What is refused for want of room, and how many workgroups share a compute unit, follows from the total. Both were set
+  // and measured with the tables of a kernel that executed every iteration (two words and a row list per queued server,
+  // four-byte ranks, ...), and the total is theirs in every configuration: the tables above never need more (one and two
+  // waves go up to 5120 servers), and where they need less (12 KB of 145 with 10000 servers) the rest is held free. A few
+  // bytes more cost a round or half the waves (200 steps: 33 servers of eight classes with patience, 4096 replications,
+  // 10248 bytes in two rounds 4.9 ms, 10032 in one 3.2; 100 steps: 900 servers, 2048 replications 4.8, 4.2).
+  constexpr size_t held_fixed = sizeof(uint64_t) * (kTallyWords + kJobsLds) + sizeof(int32_t) * (CS_WORDS + SC_WORDS + kMaxK) +
+                                sizeof(double) * 5 * kMaxK + 6 * kAdmChunk + sizeof(uint32_t) * 2 * kLoadBins;
+  const size_t held = held_fixed + waves * (8 * kEvPerWave + 256) + 80 * nw + 2 * ((4 * (nw + 1) + 7) & ~size_t(7));
+  off = off < held ? held : off;
   // from here on the offsets depend on the configuration
   GNR_TAKE(ev_t, uint32_t, p.N)
   GNR_TAKE(ev_it, uint32_t, p.N)
@@ -722,7 +739,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     const int wi = (i * NT + wave_base) >> 6;
     if (lane == 0 && wi < nwords) {
       L.bm_idle[wi] = bi; L.bm_busy[wi] = bb; L.bm_pin[wi] = bp; L.bm_chunk[wi] = bc; L.bm_fin[wi] = bf;
-      L.bm_due[wi] = 0; L.bm_touch[wi] = 0;   // nothing waits to be settled when a launch begins
+      L.bm_touch[wi] = 0;   // nothing waits to be settled when a launch begins
     }
   }
   __syncthreads();
@@ -1089,11 +1106,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         uint32_t it_tal = 0, nf = 0;
         if (active) { nc = rec[g].n_cls; nj = rec[g].n_join; it_tal = rec[g].iter; nf = rec[g].next_fin; }
         const bool busy = L.bm_busy[wi] & bit, pin = L.bm_pin[wi] & bit, had_chunk = L.bm_chunk[wi] & bit;
-        bool due = L.bm_due[wi] & bit;
         const uint32_t nd = L.loads[g];
         int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0;
         uint32_t it = L.ev_it[g];
         int64_t rel = event_time(g, T);
+        bool due = busy && rel <= 0;   // known to be at an iteration boundary in this step: its event time is that boundary
         uint32_t m = 0, d = 0;
         uint64_t comp = 0;
         if (busy && !due && !pin) {   // (lanes without a server have no bits)
@@ -1112,7 +1129,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             if (nj) rec[g].n_join = 0;
             rel = last_end;
             due = true;
-            if (!last) { set_event(g, T + rel, it); atomicOr(bits64(&L.bm_due[wi]), bit); }
+            if (!last) set_event(g, T + rel, it);
           } else {
             it -= left - 1u;
             set_event(g, T + last_end + dur, it);
@@ -1192,7 +1209,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           if (lane == j) due_lane = dm;
         }
         if (++j == 64 || last) {   // the round's last word
-          if (w_lane < nwords) { L.bm_due[w_lane] = due_lane; L.bm_touch[w_lane] = due_lane; }
+          if (w_lane < nwords) L.bm_touch[w_lane] = due_lane;
           j = 0;
         }
         if (nev > kEvPerWave - 64 || last) { drain_events(nev); nev = 0; }
@@ -1943,7 +1960,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             }
             const int rank = static_cast<int>(group_sum(static_cast<uint32_t>(lo), lg));
             if (c < ncand && k2 == 0 && rank < nadm) {
-              L.adm[rank] = static_cast<uint32_t>(k) | (static_cast<uint32_t>(m) << 3);
+              L.adm[rank] = static_cast<uint16_t>(k | (m << 3));
               atomicAdd(&L.sc[SC_ADMK + k], 1);
             }
           }
@@ -2242,7 +2259,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 const uint64_t bit = 1ull << (g & 63);
                 const int n_own = static_cast<int>(L.loads[g]);   // decodes of the server
                 const uint64_t pin_word = L.bm_pin[wi], chunk_word = L.bm_chunk[wi];
-                const bool runs = (L.bm_busy[wi] & bit) && !(L.bm_due[wi] & bit);   // not known to be at a boundary: the settling works it out
+                const int64_t rel = event_time(g, T);
+                const bool runs = (L.bm_busy[wi] & bit) && rel > 0;   // not known to be at a boundary: the settling works it out
                 const bool has_prefill = g < Mp && !(L.bm_idle[wi] & bit);
                 // which job of each level the server takes, by its rank among the level's members
                 const int gi = g >= M ? 0 : 1;
@@ -2268,7 +2286,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 } else if (runs) {
                   const int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0;
                   const uint32_t dur = iteration_ns((chunk_word & bit) ? chunk_of(rem) : 0, static_cast<uint32_t>(n_own));
-                  const int64_t rel = event_time(g, T);
                   const uint32_t left = iterations_left(static_cast<uint64_t>(rel), dur);
                   it -= left;
                   mid = rel - static_cast<int64_t>(static_cast<uint64_t>(left) * dur) <= -static_cast<int64_t>(dt_ns);
