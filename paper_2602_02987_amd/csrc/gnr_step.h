@@ -3,11 +3,11 @@
 // One workgroup owns one replication for a whole launch and loops over the steps itself. The servers are
 // handled in blocks of 64 (one per lane); wave w owns the blocks w, w + nwaves, ..., and a server's clock, record and
 // slot row are changed by the wave that owns it, except for the placements of the router. A server is touched only
-// when its batch changes (an event): the identical iterations in between follow from its event time. Class-level counters (queue lengths, occupancies, tallies) live in LDS and
-// are updated with integer atomics, which commute, by the lanes that have something to add (a few of a wave as a rule;
-// sums that all lanes add to are spread over several words). Everything that the policy defines sequentially (order of
-// simultaneous prefill completions, of gate admissions, of routed requests) is reproduced with 64-server
-// ballot words in LDS and prefix popcounts over them.
+// when its batch changes (an event): the identical iterations in between follow from its event time. Class-level
+// counters (queue lengths, occupancies, tallies) live in LDS and are updated with integer atomics, which commute, by the
+// lanes that have something to add (a few of a wave as a rule; sums that all lanes add to are spread over several words).
+// Everything that the policy defines sequentially (order of simultaneous prefill completions, of gate admissions, of
+// routed requests) is reproduced with 64-server ballot words in LDS and prefix popcounts over them.
 #ifndef GNR_STEP_H
 #define GNR_STEP_H
 #include <hip/hip_runtime.h>
@@ -202,7 +202,7 @@ constexpr int kLoadBins = kMaxB + 1;
 // of the solo and, one row further, the mixed ones; time between tokens per class.
 enum TallySum { TA_ITERS = 0, TA_BUSY = 2, TA_TBT = 4 };
 constexpr int kTallyRows = 16, kTallyRowsSmall = 8;
-// Table sizes. Workgroups of one or two waves (N up to 2560) share a compute unit with others of their kind and are
+// Table sizes. Workgroups of one or two waves (N up to 5120) share a compute unit with others of their kind and are
 // given smaller tables, so that eight of them fit its LDS: gate and routing passes then decide 64 admissions and stage
 // 64 requests at a time (more passes when a step brings more), and a wave finishes its queued servers when more than
 // 32 wait.
@@ -346,9 +346,11 @@ __host__ __device__ constexpr int size_class(int threads, int nwords)
 }
 // Waves of an instantiation that are guaranteed to fit a SIMD together (the compiler keeps its registers within
 // 512 / this many). A workgroup of 1024 threads needs four; the smaller classes are compiled twice: roomy, with up
-// to 256 registers and two waves per SIMD, which is fastest while every workgroup of the launch finds a place at
-// that density, and dense, with 128 registers and four waves per SIMD, for launches that would otherwise run their
-// workgroups in more rounds.
+// to 256 registers and two waves per SIMD, taken while every workgroup of the launch finds a place at that density, and
+// dense, with 128 registers and four waves per SIMD, for launches that would otherwise run their workgroups in more
+// rounds. Registers roomy / dense (spilled when dense): base and same-slot decode 120 / 120 in eight waves, the same code,
+// 128 / 128 in one or two; randomized router 121 / 121, 129 / 128 (1); with deadline rings 131 to 138 / 128 (2 to 6) and 140
+// to 148 / 128 (8 to 16). So only the deadline rings' forms differ by more than a register.
 __host__ __device__ constexpr int waves_per_simd(int max_threads, bool dense)
 {
   return max_threads > 512 || dense ? 4 : 2;
@@ -818,9 +820,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   // Quiet steps. A step without an arrival and without an event leaves everything as it is but for the clock: the gate and
   // the router went on in the step before until no slot or no request was left for them, and nothing has changed since
   // (in the first step of a launch it may have: the targets or the split). With a few servers most steps are like that
-  // (8 servers of two classes: seven of ten), and going through all of a step costs a wave 9 thousand cycles. So the
+  // (8 servers of two classes: three of four), and going through all of a step costs a wave 9 thousand cycles. So the
   // only wave of a small workgroup looks for the next step in which anything happens: one random block per lane tells the
-  // arrivals of 64 / servers steps. Above 32 servers a quiet step hardly occurs.
+  // arrivals of 64 / servers steps. With more than 32 servers a block would tell those of one step only (2^lg_n lanes a step,
+  // and `ahead` would be shifted by its whole width), and the search is left out: of the steps of two classes 33 % are quiet
+  // with 33 servers and 13 % with 64 (58 % with 16, 36 % with 32), of four classes at 0.95 of the capacity 11 and 1.5 %.
   constexpr int kQuietServers = 32;
   const bool quiet_search = SMALL && NT == 64 && N <= kQuietServers;
   const int lg_n = N <= 1 ? 0 : 32 - __clz(N - 1);   // a step's servers take 2^lg_n lanes
