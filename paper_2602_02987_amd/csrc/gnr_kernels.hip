@@ -81,8 +81,8 @@ int step_threads(Params q, int reps)
   // round, up to 17 % with 300 to 400 servers (eight waves instead of four on 512 replications, one instead of two on 4096),
   // 9 % with two waves instead of one at 127 to 190 servers in dense rounds, and with sixteen instead of eight on 800 to
   // 1000 servers with patience and 200 replications.
-  // With fewer than two blocks to a wave the larger workgroup only pays where it can still run in the roomy form
-  // (256 servers, 1024 replications: 128 threads roomy 19.0 ms per 1000 steps, 256 threads dense 19.6). With deadline rings
+  // With fewer than two blocks to a wave the larger workgroup gains nothing where the launch needs more than two waves a SIMD
+  // for it (256 servers, 1024 replications: 128 threads 11.3 ms per 1000 steps, 256 threads 11.4). With deadline rings
   // eight waves pay in the dense form too, from a block a wave on: the walks of the rings and the class selection take waves
   // of their own, which in four waves rank and count beside it (500 steps of 512 replications, 256 threads roomy -> 512
   // dense: abandonment, 700 servers 8.9 -> 8.3 ms; weighted router 12.7 -> 10.8; convergence instance of 500 servers
