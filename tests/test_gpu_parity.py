@@ -244,8 +244,8 @@ def test_jobs_spread_over_many_load_levels(B, oracle_mod):
 
 
 def test_long_runs_of_identical_iterations(B, oracle_mod):
-    """A lone decode of thousands of tokens: its server repeats the same iteration far more often than the
-    untallied-iteration counter holds (254), and launches end in the middle of such runs."""
+    """A lone decode of thousands of tokens: its server repeats the same iteration hundreds of times between two
+    events, and launches end in the middle of such runs."""
     cls = [_limits_class(lam=0.25, in_p0=100.0, out_law=W.LAW_CONST, out_p0=2000.0)]
     cfg = _limits_cfg("runs", cls, N=8, M=2, B=4, steps=7000, x_star=[0.1])
     sim, orc = run_both(B, oracle_mod, cfg, 7000, checkpoints=3)

@@ -19,6 +19,8 @@ pytestmark = pytest.mark.gpu
     (1, 0.01, W.GATE_FCFS, W.ROUTE_IMMEDIATE, 0.2, 7),
     (2, 0.03, W.GATE_FCFS, W.ROUTE_SOLO_FIRST, 0.4, 0),
     (3, 0.02, W.GATE_PRIORITY, W.ROUTE_RANDOM_SPLIT, 0.0, 5),
+    (4, 0.03, W.GATE_OCCUPANCY, W.ROUTE_WEIGHTED_SPLIT, 0.2, 13),
+    (5, 0.04, W.GATE_OCCUPANCY, W.ROUTE_SOLO_FIRST, 0.0, 9),
     (8, 0.07, W.GATE_OCCUPANCY, W.ROUTE_SOLO_FIRST, 0.0, 400),
     (8, 0.10, W.GATE_OCCUPANCY, W.ROUTE_RANDOM_SPLIT, 0.3, 0),
     (9, 0.10, W.GATE_OCCUPANCY, W.ROUTE_WEIGHTED_SPLIT, 0.0, 3),
