@@ -18,11 +18,14 @@ HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=off",
          # no packed fp32 instructions in device code (the host pass does not know the feature and says so)
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function",
-         # the kernels combine the lanes of a wave themselves before they touch a shared counter; the
-         # compiler's own rewrite of atomics into wave-wide scans only adds code around them
+         # atomics stay one per lane: a few lanes of a wave have something to add as a rule, and where all have the sum is
+         # spread over several words. The compiler's rewrite into wave-wide scans costs 5 % with 1024 servers x 2048
+         # replications (28.1 -> 29.4 ms per 1000 steps), 9 % with the weighted router (11.3 -> 12.2 per 300), 7 % with
+         # immediate decode (22.8 -> 24.4 per 2000), nothing with 10000 servers x 256, and gives 1 % with 256 x 1024
          "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
-         # loops are unrolled where the source asks for it (#pragma unroll); unrolling the others by heuristic only
-         # lengthened the step kernel and measured slightly slower
+         # loops are unrolled where the source asks for it (#pragma unroll); measured faster than unrolling the others by
+         # heuristic too with the kernel that executed every iteration, with this one 0 to 1.5 % slower on the timed cases
+         # (10000 servers x 256 replications 25.6 -> 26.0 ms per 1000 steps) and 2 % smaller
          "-fno-unroll-loops",
          # the step kernel lives at its register limit: loop strength reduction and the hoisting of loop invariants
          # in machine code both trade registers for instructions, which here ends in spills (sixteen waves: base form 22
