@@ -101,7 +101,7 @@ def test_random_configurations(B, oracle_mod, batch):
 @pytest.mark.skipif(os.environ.get("GNR_LONG_TESTS") != "1", reason="set GNR_LONG_TESTS=1 to run (about 20 s)")
 def test_long_random_runs(B, oracle_mod):
     """Random configurations of up to 400 servers followed over 30000 steps (rings wrap, clocks wrap, launches end
-    and resume), the split moved twice on the way. 580 such runs passed on the kernel as committed."""
+    and resume), the split moved twice on the way."""
     rng = np.random.default_rng(777)
     ran = idx = 0
     while ran < 40:
