@@ -48,6 +48,7 @@ __device__ __forceinline__ void philox_rounds(uint32_t k0, uint32_t k1, uint32_t
 __device__ __forceinline__ void philox4x32_10(uint32_t k0, uint32_t k1, uint32_t c0, uint32_t c1, uint32_t c2,
                                               uint32_t c3, uint32_t (&w)[4])
 {
+  asm volatile("" : "+s"(k0), "+s"(k1));   // (the round keys are formed anew: see draw_arrivals)
   philox_rounds<1>(k0, k1, c0, c1, c2, c3, w);
 }
 
@@ -77,6 +78,9 @@ __device__ __forceinline__ uint32_t byte_at(uint64_t packed, int k) { return sta
 // Prefill word of a server: prompt tokens left | tokens in the running chunk << 16 | class << 29.
 __device__ __forceinline__ int pk_rem(uint32_t pk) { return static_cast<int>(pk & 0xFFFFu); }
 __device__ __forceinline__ int pk_ptok(uint32_t pk) { return static_cast<int>((pk >> 16) & 0x1FFFu); }
+
+// A value that is the same in every lane, as a scalar.
+__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
 // Position of the n-th set bit (n counted from 0) of a word that has more than n bits set.
 __device__ __forceinline__ int nth_set_bit(uint64_t word, int n)
@@ -141,6 +145,14 @@ __device__ __forceinline__ int rank_in(uint64_t mask)
 }
 // Whether a wave-uniform mask has this lane.
 __device__ __forceinline__ bool lane_in(uint64_t mask) { return __builtin_amdgcn_inverse_ballot_w64(mask); }
+// v with lane l's value replaced by a wave-uniform x (the compiler has no builtin for the instruction).
+__device__ int writelane32(int x, int l, int v) __asm("llvm.amdgcn.writelane.i32");
+__device__ __forceinline__ uint64_t writelane64(uint64_t v, uint64_t x, int l)
+{
+  const uint32_t lo = static_cast<uint32_t>(writelane32(static_cast<int>(x), l, static_cast<int>(v)));
+  const uint32_t hi = static_cast<uint32_t>(writelane32(static_cast<int>(x >> 32), l, static_cast<int>(v >> 32)));
+  return (static_cast<uint64_t>(hi) << 32) | lo;
+}
 // A lane's 64-bit word as a wave-uniform value.
 __device__ __forceinline__ uint64_t readlane64(uint64_t v, int l)
 {
@@ -176,8 +188,8 @@ __device__ __forceinline__ void lds_add64(uint64_t *p, uint64_t v)
 // ------------------------------------------------------------------ LDS layout ----
 enum Scalar {
   SC_NIDLE = 0, SC_NCOMP,
+  SC_HEAD = 2,    // [8] head of each class queue as the pass's admissions find it
   // abandonment only:
-  SC_LEAD = 2,    // [8] 1 if the gate's scan of the class queue found a waiting request in this pass
   SC_DLEN = 10,   // entries of the decode buffer ring between head and tail, abandoned ones included
   SC_DSCAN = 11,  // entries of that ring the routing passes of this step have gone past
   SC_COMPACT = 12,// bit k: class queue ring k (bit 8: the decode buffer ring) must be compacted before the appends
@@ -185,12 +197,16 @@ enum Scalar {
   SC_NCS = 13,    // completed prefills of this step that joined the solo group's buffer
   SC_NCM = 14,    // ... the mixed group's buffer
   SC_DLEN_M = 15, // randomized router with abandonment: SC_DLEN / SC_DSCAN of the mixed group's buffer ring
-  SC_DSCAN_M = 52,
+  SC_DSCAN_M = 60,
+  SC_NADM = 61,   // admissions of the pass (bit 16: another gate pass follows)
+  SC_LEVELS = 62, // the pass's routing levels: how many, of them the solo group's (8 bits each), bit 16: the mixed group has to wait
+  SC_LMIN = 63,   // lowest level of the solo and (16 bits up) of the mixed group
   SC_QLEN = 32,   // [8] entries of each class queue ring between head and tail, abandoned ones included
   SC_TAKE = 16,   // [8] accepted arrivals this step
   SC_TAIL = 24,   // [8] ring position of the first accepted arrival
   SC_ADMK = 40,   // [8] admissions per class in this gate pass
   SC_TAKE_T = 48, // [kRouteLevels] jobs each level of the routing pass takes
+  SC_CNT_T = 52,  // [kRouteLevels] servers with exactly the level's decodes
   SC_W_T = 56,    // [kRouteLevels] jobs of the pass that come before each level
   SC_WORDS = 64
 };
@@ -198,6 +214,8 @@ enum Scalar {
 // itself stays as the last step left it until the pass is over.
 enum PassSum { AC_ARRIVALS = 0, AC_X = 8, AC_YM = 16, AC_YS = 24, AC_WORDS = 32 };
 constexpr int kLoadBins = kMaxB + 1;
+// (a run has fewer than 2^29 steps, an iteration is no shorter than a step, and an event lies at most 65535 iterations ahead)
+constexpr uint32_t kEvChunk = 1u << 30, kEvFin = 1u << 31, kEvIter = kEvChunk - 1u;
 // Running sums of the executed iterations, each spread over a row of words (see tally_iterations): iterations and busy time
 // of the solo and, one row further, the mixed ones; time between tokens per class.
 enum TallySum { TA_ITERS = 0, TA_BUSY = 2, TA_TBT = 4 };
@@ -222,22 +240,18 @@ struct Lds {
   uint64_t *bm_idle;  // [nwords] servers below Mp with no prefill in service (the gate looks at those below M)
   uint64_t *bm_comp;  // [nwords] servers whose prefill completed this step (read until the pass's first segment ends)
   uint64_t *bm_busy;  // [nwords] servers running an iteration
-  uint64_t *bm_pin;   // [nwords] servers given work in the middle of an iteration: their event is the end of that iteration
-  uint64_t *bm_touch; // [nwords] servers to settle at the end of the step: at their event, or given work in this step
-  uint64_t *bm_fin;   // [nwords] servers whose event is the end of a decode
-  uint64_t *bm_chunk; // [nwords] servers whose running iteration carries a prefill chunk
+  uint64_t *bm_due;   // [nwords] servers that had their event in this step (and busy ones whose event is next)
   uint64_t *jobs;     // [kJobsLds] the first requests a routing pass places, copied from the decode buffer
   uint64_t *bm_lvl;   // [kRouteLevels][nwords] routing pass: servers of the routed group with at most (level) decodes
   uint16_t *pre_lvl;  // [kRouteLevels][nwords] exclusive prefix popcounts of bm_lvl, per level
   uint16_t *pre_c;    // [nwords] exclusive prefix popcounts of bm_comp; in the space of pre_lvl
-  uint16_t *pre;      // [nwords] exclusive prefix popcounts of bm_idle; in the space of pre_lvl
+  uint16_t *pre;      // [nwords] exclusive prefix popcounts of bm_idle (read until the pass's last segment ends)
   uint16_t *adm;      // [kAdmChunk] class | sequence-in-class << 3 of each admission
-  uint16_t *adm_slot; // [kAdmChunk] prefill slot (server) that takes the admission of each rank
   uint32_t *lh;       // [2][kLoadBins] servers per decode count: solo group, mixed group
-  uint16_t *ev_g;     // [waves][kEvPerWave] servers queued by a wave: at their event, given jobs, or to settle
-  uint16_t *stage;    // [waves][64] lanes of the queued servers whose slot rows are scanned
+  uint16_t *ev_g;     // [waves][kEvPerWave] servers queued by a wave: at their event, or given work
   uint32_t *ev_t;     // [N] time of the server's event, bits 8..39 of the nanoseconds
-  uint32_t *ev_it;    // [N] iterations the server has completed by then (while idle: has completed)
+  uint32_t *ev_it;    // [N] iterations the server has completed by then (while idle: has completed), bits 0..29;
+                      //     kEvChunk: the iterations up to then carry a prefill chunk, kEvFin: a decode ends then
   uint8_t *loads;     // [N] decodes per server
   uint8_t *ev_lo;     // [N] time of the event, bits 0..7
   uint16_t *rem;      // [Mp] prompt tokens left of the prefill in service (0: none) when the running phase began
@@ -280,22 +294,11 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(gtab, double, 5 * kMaxK)
   GNR_TAKE(sc, int32_t, SC_WORDS)
   GNR_TAKE(adm, uint16_t, kAdmChunk)
-  GNR_TAKE(adm_slot, uint16_t, kAdmChunk)
   GNR_TAKE(lh, uint32_t, 2 * kLoadBins)
   GNR_TAKE(ev_g, uint16_t, waves * kEvPerWave)
-  if (SMALL) {
-    // the events of a step are over when its admissions are ranked, and those have taken their slots when the next ones begin
-    static_assert(2 * kAdmChunkSmall >= 2 * 64, "two waves' lanes in the two tables of the admissions");
-    L.stage = L.adm;
-  } else {
-    GNR_TAKE(stage, uint16_t, waves * 64)
-  }
   GNR_TAKE(bm_idle, uint64_t, nw)
   GNR_TAKE(bm_busy, uint64_t, nw)
-  GNR_TAKE(bm_pin, uint64_t, nw)
-  GNR_TAKE(bm_touch, uint64_t, nw)
-  GNR_TAKE(bm_fin, uint64_t, nw)
-  GNR_TAKE(bm_chunk, uint64_t, nw)
+  GNR_TAKE(bm_due, uint64_t, nw)
   GNR_TAKE(bm_lvl, uint64_t, kRouteLevels * nw)
   if (SMALL && waves == 1) {
     // a wave alone has put the completed prefills into the buffer before it counts the levels of the first pass (with more
@@ -304,11 +307,10 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   } else {
     GNR_TAKE(bm_comp, uint64_t, nw)
   }
-  // the ranks of a pass's levels are formed when those of the completions and of the idle slots are no longer read (a
-  // barrier lies between; a further gate pass ranks the idle slots anew)
+  // the ranks of a pass's levels are formed when those of the completions are no longer read (a barrier lies between)
   GNR_TAKE(pre_lvl, uint16_t, kRouteLevels * nw)
   L.pre_c = L.pre_lvl;
-  L.pre = L.pre_lvl + nw;
+  GNR_TAKE(pre, uint16_t, nw)
   GNR_TAKE(ta, uint64_t, (TA_TBT + (NWS ? kMaxK : p.K)) * (SMALL ? kTallyRowsSmall : kTallyRows))
   // What is refused for want of room, and how many workgroups share a compute unit, follows from the total. Both were set
   // and measured with the tables of a kernel that executed every iteration (two words and a row list per queued server,
@@ -468,10 +470,10 @@ __device__ __forceinline__ void tally_iterations(uint64_t *ta, uint64_t *tbth, i
 #pragma unroll
   for (int k = 0; k < kMaxK; ++k) {
     if (k < K) {   // wave-uniform
-      const uint32_t c = byte_at(comp, k);
-      if (c) {
-        lds_add64(&mine[(TA_TBT + k) * ROWS], c * md);   // < 2^7 * 2^47
-        lds_add64(&bin[k * tbt_w], static_cast<uint64_t>(m) * c);
+      const uint32_t mc = m * byte_at(comp, k);   // < 2^24
+      if (mc) {
+        lds_add64(&mine[(TA_TBT + k) * ROWS], static_cast<uint64_t>(mc) * d);
+        lds_add64(&bin[k * tbt_w], mc);
       }
     }
   }
@@ -629,7 +631,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   uint64_t *dring = a.dring + static_cast<size_t>(r) * dbuf_cap;
   uint64_t *hist = a.hist + static_cast<size_t>(r) * 3 * K * kNBin;
   uint16_t *ev_g = L.ev_g + wave * kEvPerWave;
-  uint16_t *stage = L.stage + wave * 64;
   // abandonment only
   const uint32_t cal_n = p.cal_mask + 1u;
   uint32_t *qdl = AB ? a.qdl + static_cast<size_t>(r) * K * queue_cap : nullptr;
@@ -677,11 +678,14 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     return (static_cast<int64_t>(static_cast<int32_t>(L.ev_t[g] - static_cast<uint32_t>(X >> 8))) << 8) +
            (static_cast<int>(L.ev_lo[g]) - static_cast<int>(X & 255));
   };
-  auto set_event = [&](int g, int64_t t, uint32_t it) __attribute__((always_inline)) {
+  auto set_event = [&](int g, int64_t t, uint32_t it, bool chunk, bool fin_ev) __attribute__((always_inline)) {
     L.ev_t[g] = static_cast<uint32_t>(t >> 8);
     L.ev_lo[g] = static_cast<uint8_t>(t & 255);
-    L.ev_it[g] = it;
+    L.ev_it[g] = it | (chunk ? kEvChunk : 0u) | (fin_ev ? kEvFin : 0u);
   };
+  // Work that a server was given in the middle of an iteration joins at its end, and that is the server's event then. Such a
+  // server has decodes that are not yet in the batch, or a prefill that the running iteration does not carry.
+  auto joins_next = [](uint64_t nj, int rem, bool chunk) __attribute__((always_inline)) { return nj != 0 || (rem > 0 && !chunk); };
   // How many iterations like the next one (`nd` decodes, a chunk of `rem` prompt tokens left, d ns long) a server runs
   // before its batch may change; `to_fin`: iterations up to the first end of one of its decodes.
   auto phase_length = [&](uint32_t nd, int rem, uint32_t d, uint32_t to_fin) __attribute__((always_inline)) -> uint32_t {
@@ -707,7 +711,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   for (int i = 0; i < nper; ++i) {
     const int g = i * NT + tid;
     const bool valid = g < N;
-    bool busy = false, pin = false, fin_ev = false, idle_slot = false, chunk = false;
+    bool busy = false, idle_slot = false;
     if (valid) {
       const ServerRec &sr = rec[g];
       const uint64_t nc = sr.n_cls, nj = sr.n_join;
@@ -722,26 +726,22 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         ptok = pk_ptok(pk);
         L.rem[g] = static_cast<uint16_t>(rem);
         idle_slot = rem == 0 && (!IM || static_cast<int>(nd) < B);
-        chunk = ptok > 0;
       }
       busy = tr != kIdleRel;
       const int64_t start = static_cast<int64_t>(step_begin) * dt_ns;   // the boundary the launch begins at
       if (busy) {
-        // work that is not part of the running iteration joins at its end: that is the server's event then
-        pin = nj != 0 || (rem > 0 && ptok == 0);
         const uint32_t d = iteration_ns(ptok, nd);
-        const uint32_t n = pin ? 1u : phase_length(nd, ptok > 0 ? rem : 0, d, nf - it);
-        fin_ev = nd && nf == it + n;
-        set_event(g, start + tr + static_cast<int64_t>(n - 1u) * d, it + n);
+        const uint32_t n = joins_next(nj, rem, ptok > 0) ? 1u : phase_length(nd, ptok > 0 ? rem : 0, d, nf - it);
+        set_event(g, start + tr + static_cast<int64_t>(n - 1u) * d, it + n, ptok > 0, nd && nf == it + n);
       } else {
-        set_event(g, start, it);
+        set_event(g, start, it, false, false);
       }
     }
-    const uint64_t bi = __ballot(idle_slot), bb = __ballot(busy), bp = __ballot(pin), bc = __ballot(chunk), bf = __ballot(fin_ev);
+    const uint64_t bi = __ballot(idle_slot), bb = __ballot(busy);
     const int wi = (i * NT + wave_base) >> 6;
     if (lane == 0 && wi < nwords) {
-      L.bm_idle[wi] = bi; L.bm_busy[wi] = bb; L.bm_pin[wi] = bp; L.bm_chunk[wi] = bc; L.bm_fin[wi] = bf;
-      L.bm_touch[wi] = 0;   // nothing waits to be settled when a launch begins
+      L.bm_idle[wi] = bi; L.bm_busy[wi] = bb;
+      L.bm_due[wi] = 0;
     }
   }
   __syncthreads();
@@ -830,6 +830,69 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   const int lg_n = N <= 1 ? 0 : 32 - __clz(N - 1);   // a step's servers take 2^lg_n lanes
   uint64_t ahead = 0;    // servers with arrivals in the steps drawn ahead, the step to come in the lowest 2^lg_n bits
   int steps_ahead = 0;   // how many
+  // ---- arrivals: one random block per server and step, word 0 -> count, words 1.. -> classes. Word 0 alone is worked out
+  //      for every server (its last rounds take half the products); the few servers that get requests are queued and
+  //      their blocks drawn in full, one a lane. Draws those of step `sd` for the words first, first + stride, ... (wave-uniform).
+  auto draw_arrivals = [&](uint32_t sd, int first, int stride) __attribute__((always_inline)) {
+    const uint32_t thr0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 0));
+    const uint32_t thr1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 1));
+    const uint32_t thr2 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 2));
+    // the random block's first round has the server in one product only; the other one is the same for all
+    const uint64_t ps = static_cast<uint64_t>(0xD2511F53u) * sd;
+    const uint32_t c2_1 = pinned(static_cast<uint32_t>(ps >> 32) ^ static_cast<uint32_t>(r) ^ key1), c3_1 = static_cast<uint32_t>(ps);
+    for (int b0 = first; b0 < nwords; b0 += 64 * stride) {   // wave-uniform; 64 words a round, one a lane
+      uint64_t hits = 0;
+      int j = 0;
+      for (int blk = b0; j < 64 && blk < nwords; blk += stride, ++j) {   // wave-uniform
+        // the round keys are formed anew with scalar additions: as loop invariants there are twenty of them, and they are
+        // kept in lanes of vector registers, from which each costs two vector instructions a round
+        uint32_t k0 = key0, k1 = key1;
+        asm volatile("" : "+s"(k0), "+s"(k1));
+        const uint64_t pg = static_cast<uint64_t>(0xCD9E8D57u) * static_cast<uint32_t>((blk << 6) + lane);
+        uint32_t w[4];
+        philox_rounds<2>(k0 + 0x9E3779B9u, k1 + 0xBB67AE85u, static_cast<uint32_t>(pg >> 32) ^ k0, static_cast<uint32_t>(pg), c2_1, c3_1, w);
+        hits = writelane64(hits, __ballot(w[0] >= thr0), j);
+      }
+      const int word = b0 + lane * stride;
+      hits &= bits_below(word, N);   // (of a lane without a word it is empty)
+      int n = 0;
+      for (uint64_t todo = __ballot(hits != 0); todo;) {   // a lane queues one server of its word at a time
+        if (hits) {
+          ev_g[n + rank_in(todo)] = static_cast<uint16_t>((word << 6) + __ffsll(static_cast<long long>(hits)) - 1);
+          hits &= hits - 1ull;
+        }
+        n += __popcll(todo);
+        todo = __ballot(hits != 0);
+        if (n > kEvPerWave - 64 || !todo) {
+          for (int e0 = 0; e0 < n; e0 += 64) {   // wave-uniform
+            if (e0 + lane < n) {
+              uint32_t w[4];
+              philox4x32_10(key0, key1, sd, 0u, static_cast<uint32_t>(ev_g[e0 + lane]), static_cast<uint32_t>(r), w);
+              const int count = 1 + (w[0] >= thr1) + (w[0] >= thr2);
+#pragma unroll
+              for (int i = 0; i < 3; ++i) {
+                if (i >= count) break;
+                int k = 0;
+#pragma unroll
+                for (int c = 0; c + 1 < kMaxK; ++c) k += w[i + 1] >= L.cthr[c];
+                atomicAdd(&L.acc[k < K ? k : K - 1], 1u);
+              }
+            }
+          }
+          n = 0;
+        }
+      }
+    }
+  };
+  auto next_thresholds = [&]() __attribute__((always_inline)) {   // of the step after the one drawn (in every wave, whether it draws or not)
+    if (mod_rows > 1u) {
+      mod_row = mod_row + 1u == mod_rows ? 0u : mod_row + 1u;
+      thr_ahead = a.arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
+    }
+  };
+  bool drawn = false;        // the arrivals of the step to come have been drawn
+  bool slots_taken = false;  // bm_comp holds the prefill slots the last gate pass has given away, and they are still in bm_idle
+
   const uint32_t step_end = step_begin + n_steps;
 
   int64_t T = 0;
@@ -884,83 +947,57 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         if constexpr (RR) n_leave_dm = atomicExch(&dcal_m[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
       }
     }
-    const uint32_t thr0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 0));
-    const uint32_t thr1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 1));
-    const uint32_t thr2 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 2));
-    if (mod_rows > 1u) {
-      mod_row = mod_row + 1u == mod_rows ? 0u : mod_row + 1u;
-      thr_ahead = a.arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
-    }
-
-    // ---- 1. arrivals: one random block per server, word 0 -> count, words 1.. -> classes. The pass over the servers
-    //      looks at word 0; the few servers that get requests leave the other words in registers of their lane, and the
-    //      classes are worked out when a lane gets a second server or the pass ends (worked out where they are found,
-    //      62 % of the blocks of 64 went through the class thresholds for the one lane that had any).
-    uint32_t arr_n = 0, arr_w[3] = {0, 0, 0};   // requests of this lane's last server with arrivals, their words
-    auto classify_arrivals = [&]() __attribute__((always_inline)) {
-      if (arr_n) {
-#pragma unroll
-        for (int j = 0; j < 3; ++j) {
-          if (static_cast<uint32_t>(j) >= arr_n) break;
-          int k = 0;
-#pragma unroll
-          for (int c = 0; c + 1 < kMaxK; ++c) k += arr_w[j] >= L.cthr[c];
-          atomicAdd(&L.acc[k < K ? k : K - 1], 1u);
-        }
-      }
-      arr_n = 0;
-    };
-
     // ---- 2. events: one server per lane (uniform control flow; lanes beyond the queue idle). Tallies the iterations
     //      since the last event, removes the decodes that emitted their last token, advances the prefill. What the
     //      lanes need of their servers' records is asked for first, together with the slot rows of the servers whose
     //      event is the end of a decode: eight lanes read a row, 16 bytes per lane and load, eight rows at a time.
     auto drain_events = [&](int nev) __attribute__((always_inline)) {
       for (int e0 = 0; e0 < nev; e0 += 64) {
-        const bool active = e0 + lane < nev;
-        const int g = active ? static_cast<int>(ev_g[e0 + lane]) : 0;
+        const bool queued = e0 + lane < nev;
+        const int g = queued ? static_cast<int>(ev_g[e0 + lane]) : 0;
         const int wi = g >> 6;
+        const int64_t tn = T + event_time(g, T);   // exact completion time
+        const bool active = queued && tn <= T;
         const uint64_t bit = active ? 1ull << (g & 63) : 0ull;
         uint64_t nc = 0, nj = 0, pf = 0;
-        uint32_t it_tal = 0;
-        if (active) { nc = rec[g].n_cls; nj = rec[g].n_join; pf = rec[g].pf_job; it_tal = rec[g].iter; }
-        const uint32_t it = L.ev_it[g];
+        uint32_t it_tal = 0, nf = 0;
+        if (active) { nc = rec[g].n_cls; nj = rec[g].n_join; pf = rec[g].pf_job; it_tal = rec[g].iter; nf = rec[g].next_fin; }
+        const uint32_t ev = active ? L.ev_it[g] : 0u, it = ev & kEvIter;
         int nd = active ? static_cast<int>(L.loads[g]) : 0;
         const int nd_before = nd;
-        const bool has_chunk = L.bm_chunk[wi] & bit, pinned_ev = L.bm_pin[wi] & bit;
+        const bool has_chunk = ev & kEvChunk;
         int rem = active && g < Mp ? static_cast<int>(L.rem[g]) : 0;
         const bool mixed_now = rem > 0;
-        const int64_t tn = T + event_time(g, T);   // exact completion time
         const uint64_t nc_before = nc;
-        uint32_t nf = 0;   // new first end of a decode (set when the row was scanned)
-        bool nf_new = false;
         // ---- the ends of decodes: one leaves per round, highest slot first (the last slot's request moves into its
         //      place); a second round follows only where several end together
-        bool leaving = L.bm_fin[wi] & bit;
+        bool leaving = ev & kEvFin;
         for (uint64_t lm = __ballot(leaving); lm; lm = __ballot(leaving)) {
+          // lane q gets the server, the decodes and the iteration of the q-th row (the other lanes' follow behind them)
           const int nrows = __popcll(lm), my_row = rank_in(lm);
-          if (leaving) stage[my_row] = static_cast<uint16_t>(lane);
-          __builtin_amdgcn_wave_barrier();
+          const int to = (leaving ? my_row : nrows + rank_in(~lm)) << 2;
+          const int row_gn = __builtin_amdgcn_ds_permute(to, g | (nd << 16));
+          const int row_it = __builtin_amdgcn_ds_permute(to, static_cast<int>(it));
           int slot = -1;
           bool more = false;
           uint32_t next = 0xFFFFFFFFu;
           for (int r0 = 0; r0 < nrows; r0 += 8) {   // wave-uniform
             const int row = r0 + (lane >> 3), l8 = lane & 7;
-            const int owner = row < nrows ? stage[row] : 0;
-            const int o_g = __shfl(g, owner, 64), nd_owner = __shfl(nd, owner, 64);
-            const int o_nd = row < nrows ? nd_owner : 0;
-            const uint32_t o_it = __shfl(it, owner, 64);
+            const int o_gn = __shfl(row_gn, row & 63, 64);
+            const int o_g = o_gn & 0xFFFF, o_nd = row < nrows ? o_gn >> 16 : 0;
+            const uint32_t o_it = static_cast<uint32_t>(__shfl(row_it, row & 63, 64));
             const uint32_t *frow = fin + static_cast<size_t>(o_g) * BS;
             uint4 v[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               v[q] = make_uint4(0u, 0u, 0u, 0u);   // (0: an empty slot, never an iteration a decode ends in)
-              if (4 * (l8 + 8 * q) < o_nd) v[q] = stream_load(frow + 4 * (l8 + 8 * q));
+              if (32 * q < BS && 4 * (l8 + 8 * q) < o_nd) v[q] = stream_load(frow + 4 * (l8 + 8 * q));
             }
             int high = -1, count = 0;
             uint32_t least = 0xFFFFFFFFu;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
+              if (q > 0 && 32 * q >= BS) break;   // wave-uniform: no such slots
               const uint32_t wv[4] = {v[q].x, v[q].y, v[q].z, v[q].w};
 #pragma unroll
               for (int w = 0; w < 4; ++w) {
@@ -985,7 +1022,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           }
           if (leaving) {
             leaving = more;
-            nf_new = true;
             nf = next < 0x40000000u ? it + 1u + next : kNever;
             if (slot >= 0) {
               uint32_t *frow = fin + static_cast<size_t>(g) * BS;
@@ -1008,7 +1044,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               frow[nd] = 0;   // a vacated slot must never match a later iteration index
             }
           }
-          __builtin_amdgcn_wave_barrier();
         }
         uint32_t m = 0, d = 0;
         bool chunk = false;
@@ -1051,7 +1086,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                   const uint32_t ends = it + static_cast<uint32_t>(jw >> 48) + 1;
                   fin[static_cast<size_t>(g) * BS + nd] = ends;
                   job[static_cast<size_t>(g) * BS + nd] = jw;
-                  if (!nf_new) { nf = rec[g].next_fin; nf_new = true; }
                   if (nd == 0 || ends < nf) nf = ends;
                   nc += 1ull << (8 * k);
                   const int hb = g < M ? kLoadBins : 0;
@@ -1069,11 +1103,21 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               }
             }
           }
-          if (pinned_ev) atomicAnd(bits64(&L.bm_pin[wi]), ~bit);
-          if (nc != nc_before) rec[g].n_cls = nc;
-          if (nj) rec[g].n_join = 0;
+          // The next iteration starts where this one has ended, with what the server holds now. Work that this step still
+          // brings is then found to come at an iteration boundary (see `serve`) and starts the iteration anew.
+          const int ptok_next = rem > 0 ? chunk_of(rem) : 0;
+          if (ptok_next == 0 && nd == 0) {
+            set_event(g, tn, it, false, false);
+            atomicAnd(bits64(&L.bm_busy[wi]), ~bit);
+          } else {
+            const uint32_t dur = iteration_ns(ptok_next, static_cast<uint32_t>(nd));
+            const uint32_t n = phase_length(static_cast<uint32_t>(nd), rem, dur, nf - it);
+            set_event(g, tn + static_cast<int64_t>(static_cast<uint64_t>(n) * dur), it + n, ptok_next > 0, nd && nf == it + n);
+          }
+          rec[g].n_cls = nc;
+          rec[g].n_join = 0;
           rec[g].iter = it;
-          if (nf_new) rec[g].next_fin = nf;
+          rec[g].next_fin = nf;
         }
         tally_iterations<kTallyRowsHere>(L.ta, L.tbth, tbt_w, tbt_lo, K, m, d, chunk, comp);
         // a prefill that ended: completion count, recognised prompt tokens, time to first token; the
@@ -1096,128 +1140,44 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       }
     };
 
-    // ---- settling, one queued server per lane: the servers at their event and those given work in this step. Work that
-    //      arrived in the middle of an iteration moves the event up to the end of that iteration; if it arrived at
-    //      an iteration boundary the iterations before it are tallied. With `last` (no more work follows in this
-    //      step) a server at a boundary, or idle, starts its next iteration and gets its next event.
-    auto settle = [&](int nset, bool last) __attribute__((always_inline)) {
-      for (int e0 = 0; e0 < nset; e0 += 64) {
-        const bool active = e0 + lane < nset;
-        const int g = active ? static_cast<int>(ev_g[e0 + lane]) : 0;
-        const int wi = g >> 6;
-        const uint64_t bit = active ? 1ull << (g & 63) : 0ull;
-        uint64_t nc = 0, nj = 0;
-        uint32_t it_tal = 0, nf = 0;
-        if (active) { nc = rec[g].n_cls; nj = rec[g].n_join; it_tal = rec[g].iter; nf = rec[g].next_fin; }
-        const bool busy = L.bm_busy[wi] & bit, pin = L.bm_pin[wi] & bit, had_chunk = L.bm_chunk[wi] & bit;
-        const uint32_t nd = L.loads[g];
-        int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0;
-        uint32_t it = L.ev_it[g];
-        int64_t rel = event_time(g, T);
-        bool due = busy && rel <= 0;   // known to be at an iteration boundary in this step: its event time is that boundary
-        uint32_t m = 0, d = 0;
-        uint64_t comp = 0;
-        if (busy && !due && !pin) {   // (lanes without a server have no bits)
-          comp = nc - nj;
-          const int ptok = had_chunk ? chunk_of(rem) : 0;
-          const uint32_t dur = iteration_ns(ptok, byte_sum(comp));
-          const uint32_t left = iterations_left(static_cast<uint64_t>(rel), dur);
-          const int64_t last_end = rel - static_cast<int64_t>(static_cast<uint64_t>(left) * dur);   // of the latest completed iteration
-          if (last_end > -static_cast<int64_t>(dt_ns)) {   // it ended in this step: a boundary
-            it -= left;
-            m = it - it_tal;
-            d = dur;
-            rem -= static_cast<int>(m) * ptok;
-            if (ptok > 0) L.rem[g] = static_cast<uint16_t>(rem);
-            rec[g].iter = it;
-            if (nj) rec[g].n_join = 0;
-            rel = last_end;
-            due = true;
-            if (!last) set_event(g, T + rel, it);
-          } else {
-            it -= left - 1u;
-            set_event(g, T + last_end + dur, it);
-            atomicOr(bits64(&L.bm_pin[wi]), bit);
-            if (nd && nf == it) atomicOr(bits64(&L.bm_fin[wi]), bit); else atomicAnd(bits64(&L.bm_fin[wi]), ~bit);
-          }
-        }
-        if (last && active && (due || !busy)) {
-          const int ptok = rem > 0 ? chunk_of(rem) : 0;
-          bool runs = true, fin_ev = false;
-          if (ptok == 0 && nd == 0) {
-            runs = false;
-            set_event(g, T + rel, it);
-          } else {
-            // back-to-back after a completion, otherwise from the step boundary
-            const uint32_t dur = iteration_ns(ptok, nd);
-            const uint32_t n = phase_length(nd, rem, dur, nf - it);
-            fin_ev = nd && nf == it + n;
-            set_event(g, T + (due ? rel : 0) + static_cast<int64_t>(static_cast<uint64_t>(n) * dur), it + n);
-          }
-          if (runs != busy) { if (runs) atomicOr(bits64(&L.bm_busy[wi]), bit); else atomicAnd(bits64(&L.bm_busy[wi]), ~bit); }
-          if ((ptok > 0) != had_chunk) { if (ptok > 0) atomicOr(bits64(&L.bm_chunk[wi]), bit); else atomicAnd(bits64(&L.bm_chunk[wi]), ~bit); }
-          if (fin_ev) atomicOr(bits64(&L.bm_fin[wi]), bit); else atomicAnd(bits64(&L.bm_fin[wi]), ~bit);
-        }
-        tally_iterations<kTallyRowsHere>(L.ta, L.tbth, tbt_w, tbt_lo, K, m, d, had_chunk, comp);
-      }
-    };
-
-    // ---- completion pass: which servers have their event in this step (one clock per server and step is all that is
-    //      read), and the arrivals. The vector units are what this pass waits for (16 waves of ten words each), so whatever
-    //      a word has but one of is kept one word a lane or in scalar registers: a word costs 36 vector instructions for the
-    //      random block and a dozen or so for the rest (forty before; 10000 servers: 27.0 -> 26.0 ms per 1000 steps).
+    // ---- completion pass: the arrivals, where they have not been drawn yet, and which servers have their event in this
+    //      step (one clock per server and step is all that is read). What a word has but one of is kept one word a lane.
+    if (!drawn) {
+      draw_arrivals(s, wave, nwaves);
+      next_thresholds();
+    }
+    drawn = false;
     {
-      const uint32_t T_hi = static_cast<uint32_t>(T >> 8), T_lo = static_cast<uint32_t>(T) & 255u;
-      // the random block's first round has the server in one product only; the other one is the same for all
-      const uint64_t ps = static_cast<uint64_t>(0xD2511F53u) * s;
-      const uint32_t c2_1 = pinned(static_cast<uint32_t>(ps >> 32) ^ static_cast<uint32_t>(r) ^ key1), c3_1 = static_cast<uint32_t>(ps);
+      const uint32_t T_hi = static_cast<uint32_t>(T >> 8);
       int nev = 0;   // servers queued by this wave (wave-uniform)
       int w_lane = 0, j = 0;   // the wave's words are wave, wave + nwaves, ...: 64 of them a round, one a lane
       uint64_t busy_lane = 0, due_lane = 0;
       for (int blk = wave; blk < nwords; blk += nwaves) {   // wave-uniform
-        const int g = (blk << 6) + lane, g_in = g < N ? g : N - 1;   // (lanes past the last server are not busy)
+        const int g = (blk << 6) + lane;
         const bool last = blk + nwaves >= nwords;
         if (j == 0) {
           w_lane = blk + lane * nwaves;
           busy_lane = due_lane = 0;
-          if (w_lane < nwords) { busy_lane = L.bm_busy[w_lane]; L.bm_comp[w_lane] = 0; }
-        }
-        const uint32_t ev = L.ev_t[g_in];
-        // the round keys are formed anew with scalar additions: as loop invariants there are twenty of them, and they are
-        // kept in lanes of vector registers, from which each costs two vector instructions a round
-        uint32_t k0 = key0, k1 = key1;
-        asm volatile("" : "+s"(k0), "+s"(k1));
-        const uint64_t pg = static_cast<uint64_t>(0xCD9E8D57u) * static_cast<uint32_t>(g);
-        uint32_t w[4];
-        philox_rounds<2>(k0 + 0x9E3779B9u, k1 + 0xBB67AE85u, static_cast<uint32_t>(pg >> 32) ^ k0, static_cast<uint32_t>(pg), c2_1, c3_1, w);
-        uint64_t hit = __ballot(w[0] >= thr0);
-        if (last) hit &= bits_below(blk, N);
-        // the words that wait in a lane are worked off before it gets others and after the last
-        for (uint64_t full = hit & __ballot(arr_n != 0);;) {
-          if (full) classify_arrivals();
-          if (lane_in(hit)) {
-            arr_n = 1u + (w[0] >= thr1) + (w[0] >= thr2);
-            arr_w[0] = w[1]; arr_w[1] = w[2]; arr_w[2] = w[3];
+          if (w_lane < nwords) {
+            busy_lane = L.bm_busy[w_lane];
+            if (slots_taken) L.bm_idle[w_lane] &= ~L.bm_comp[w_lane];
+            L.bm_comp[w_lane] = 0;
           }
-          hit = 0;
-          full = last ? __ballot(arr_n != 0) : 0ull;
-          if (!full) break;
         }
-        const int32_t diff = static_cast<int32_t>(ev - T_hi);
-        const uint64_t busy = readlane64(busy_lane, j), level = busy & __ballot(diff == 0);
-        uint64_t dm = busy & __ballot(diff < 0);
-        if (level) dm |= level & __ballot(L.ev_lo[g_in] <= T_lo);
+        // (a clock a few ns ahead may pass here for its upper bits: the servers queued are looked at exactly)
+        const uint64_t dm = readlane64(busy_lane, j) & __ballot(static_cast<int32_t>(L.ev_t[g < N ? g : N - 1] - T_hi) <= 0);
         if (dm) {
           if (lane_in(dm)) ev_g[nev + rank_in(dm)] = static_cast<uint16_t>(g);
           nev += __popcll(dm);
-          if (lane == j) due_lane = dm;
+          due_lane = writelane64(due_lane, dm, j);
         }
         if (++j == 64 || last) {   // the round's last word
-          if (w_lane < nwords) L.bm_touch[w_lane] = due_lane;
+          if (w_lane < nwords) L.bm_due[w_lane] = due_lane;
           j = 0;
         }
         if (nev > kEvPerWave - 64 || last) { drain_events(nev); nev = 0; }
       }
+      slots_taken = false;
     }
     __syncthreads();
 
@@ -1234,6 +1194,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       add_step_sums(k, ended, qp, qd, x, ym, ys);   // of the steps before
       L.acc[AC_ARRIVALS + k] = 0; L.acc[AC_X + k] = 0; L.acc[AC_YM + k] = 0; L.acc[AC_YS + k] = 0;
       L.cs[CS_X + k] = x + dx; L.cs[CS_YM + k] = ym + dym; L.cs[CS_YS + k] = ys + dys;
+      L.sc[SC_HEAD + k] = L.cs[CS_QHEAD + k];
       if constexpr (AB) {   // abandonments come first: they free room in the queue
         if (n_leave_p) {
           qp -= static_cast<int32_t>(n_leave_p);
@@ -1333,6 +1294,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       }
     }
     __syncthreads();
+    // what follows is shared out: the first waves rank the gate's candidates, the others look for the router's servers
+    const int n_gate = nwaves > 1 ? nwaves >> 1 : 1, route_first = nwaves > 1 ? n_gate : 0, n_route = nwaves - route_first;
     if constexpr (AB) {
       // a ring that cannot hold this step's appends behind its dead entries is compacted first
       const int flags = L.sc[SC_COMPACT];   // cleared at the end of the step
@@ -1424,6 +1387,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             uint32_t pos = (solo ? dh0 + fill0 : dh1 + fill1) + idx;
             if (pos >= dbuf_cap) pos -= dbuf_cap;
             (solo ? dring : dring_m)[pos] = c_jw;
+            if (!AB && idx < kJobsLds / 2) L.jobs[(solo ? 0u : kJobsLds / 2) + idx] = c_jw;
             if constexpr (AB) {
               (solo ? ddl : ddl_m)[pos] = c_dl;
               if (c_dl != kNever) atomicAdd(&(solo ? dcal : dcal_m)[static_cast<size_t>(k) * cal_n + (c_dl & p.cal_mask)], 1u);
@@ -1451,9 +1415,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       const uint32_t ncomp = static_cast<uint32_t>(L.sc[SC_NCOMP]);
       const uint32_t dcount = static_cast<uint32_t>(L.cs[CS_DCOUNT]), dhead = static_cast<uint32_t>(L.cs[CS_DHEAD]);
       const uint32_t dfill = AB ? static_cast<uint32_t>(L.sc[SC_DLEN]) : dcount;   // ring entries before the tail
-      // (64 to a wave; not the first waves, which have ranked the bitmaps and go on to rank the gate's candidates: the last
-      // ones, or with abandonment, whose arrivals the last two waves take, in a large workgroup the ones before them)
-      const int comp_turn = AB && nwaves >= 8 ? (2 * nwaves - 3 - wave) % nwaves : nwaves - 1 - wave;
+      // (64 to a wave, the last wave that ranks the gate's candidates first: it has the least to do next)
+      const int comp_turn = wave < n_gate ? n_gate - 1 - wave : wave;
       for (uint32_t j0 = static_cast<uint32_t>(comp_turn) * 64u; j0 < ncomp; j0 += NT) {   // wave-uniform trip count
         const uint32_t j = j0 + lane;
         const bool active = j < ncomp;
@@ -1468,6 +1431,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             uint32_t pos = dhead + dfill + j;
             if (pos >= dbuf_cap) pos -= dbuf_cap;
             dring[pos] = jw;
+            if (!AB && j < kJobsLds) L.jobs[j] = jw;
             if constexpr (AB) {   // patience for the wait in the decode buffer
               uint32_t dl = kNever;
               if ((p.ab_classes >> k) & 1u) {
@@ -1508,7 +1472,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     // One pass is the rule; more follow only when more than kAdmChunk slots are idle or the jobs reach past
     // kRouteLevels levels or into the mixed group.
     {
-      const int dcount0 = L.cs[CS_DCOUNT];
+      const int dcount0 = L.cs[CS_DCOUNT], dcount0_m = RR ? L.cs[CS_DCOUNT_M] : 0;
       int jrem, next = 0;
       {
         const int ncp = L.sc[SC_NCOMP], room = static_cast<int>(dbuf_cap) - dcount0;
@@ -1520,7 +1484,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       const uint32_t dheadL[2] = {dhead0, RR ? static_cast<uint32_t>(L.cs[CS_DHEAD_M]) : 0u};
       if constexpr (RR) {
         jremL[0] = dcount0 + L.sc[SC_NCS];
-        jremL[1] = L.cs[CS_DCOUNT_M] + L.sc[SC_NCM];
+        jremL[1] = dcount0_m + L.sc[SC_NCM];
         jrem = jremL[0] + jremL[1];
       }
       // abandonment only: ring entries of the decode buffer, this step's completions included
@@ -1536,21 +1500,26 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       }
       bool gate_on = true, route_on = jrem > 0;
       for (int pass = 0; gate_on || route_on; ++pass) {
+        if (slots_taken) {   // (in a pass after the first)
+          for (int w = tid; w < nwords; w += NT) L.bm_idle[w] &= ~L.bm_comp[w];
+          slots_taken = false;
+          __syncthreads();
+        }
         if (gate_on && pass > 0) {
           if (tid < 64) {
             const uint32_t nidle = rank_bitmap(L.bm_idle, L.pre, nwords_m, M);
             if (tid == 0) L.sc[SC_NIDLE] = static_cast<int32_t>(nidle);
+            if (tid < K) L.sc[SC_HEAD + tid] = L.cs[CS_QHEAD + tid];
           }
           __syncthreads();
         }
         if ((AB || gate_mode == SIM_GATE_FCFS) && pass == 0) __syncthreads();   // ring entries written above are read below
         // With abandonment the requests a routing pass places are first staged in LDS, by the waves that own the decode
         // buffers (each buffer has a wave of its own, on different SIMDs).
-        const int ring_wave = nwaves >= 8 ? (WS ? 4 : nwaves / 2) : nwaves - 1;
-        const int ring_wave_m = nwaves >= 8 ? ring_wave + 1 : nwaves - 1;
+        const int ring_wave = nwaves >= 8 ? route_first : nwaves - 1;
+        const int ring_wave_m = nwaves >= 8 ? route_first + 1 : nwaves - 1;
         // the weighted router's selection is long: it runs in segment A beside the gate's ranking, on waves that are
         // given nothing else to do there; the plain walk of a ring runs in segment B
-        constexpr bool kStageEarly = AB && WS;
         // one wave walks a ring from where the last pass stopped and stages the next `need` waiting jobs
         auto stage_ring = [&](const uint64_t *ring, const uint32_t *dlr, uint32_t *calr, uint32_t hd, uint32_t len,
                               int scan_word, uint32_t need, int first_job) __attribute__((always_inline)) {
@@ -1794,9 +1763,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         };
 
         // ---------------- segment A ----------------
-        int nadm = 0, nidle = 0;
-        if (gate_on) {
-          nidle = __builtin_amdgcn_readfirstlane(L.sc[SC_NIDLE]);
+        const int nidle = gate_on ? uniform(L.sc[SC_NIDLE]) : 0;
+        if (gate_on && wave < n_gate) {
           const int limit = nidle < kAdmChunk ? nidle : kAdmChunk;
           // A candidate is ranked by 2, 4 or 8 neighbouring lanes (as many as there are classes), each of which counts
           // the candidates of one class that sort before it. A lane keeps its class for the pass: targets, counters and
@@ -1808,8 +1776,15 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           const uint32_t head2 = static_cast<uint32_t>(L.cs[CS_QHEAD + k2]);
           int cnt2 = ((admissible >> k2) & 1ull) && qp2 > 0 ? (qp2 < limit ? qp2 : limit) : 0;
           int ncand = __builtin_amdgcn_readfirstlane(static_cast<int>(group_sum(static_cast<uint32_t>(cnt2), lg)));
-          nadm = ncand < limit ? ncand : limit;
-          if (gate_mode == SIM_GATE_OCCUPANCY && (ncand << lg) > NT && ncand > nadm &&
+          const int nadm = ncand < limit ? ncand : limit;
+          bool gate_more = false;
+          // rare: more idle slots than one pass serves, and requests left to take them
+          if (nadm == kAdmChunk && nidle > kAdmChunk) {
+            const uint32_t left = ((admissible >> k2) & 1ull) ? static_cast<uint32_t>(qp2) : 0u;
+            gate_more = uniform(static_cast<int>(group_sum(left, lg))) > nadm;
+          }
+          if (tid == 0) L.sc[SC_NADM] = nadm | (gate_more ? 0x10000 : 0);
+          if (gate_mode == SIM_GATE_OCCUPANCY && (ncand << lg) > (n_gate << 6) && ncand > nadm &&
               __ballot(cnt2 > 0 && !(fabs(t2.nx) < 1e9)) == 0) {
             // Long queues offer up to `limit` candidates of every class, `limit` of which are admitted in all, and the others
             // need no rank. The keys of a class rise linearly, so a bound on the key tells how many of its candidates lie
@@ -1843,7 +1818,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           if constexpr (AB) {
             // where the candidates sit in their rings: a wave per class walks from the head past the dead entries
             // (the last waves take this: the first ones rank the candidates below)
-            for (int k = nwaves - 1 - wave; k < K; k += nwaves) {   // wave-uniform
+            for (int k = n_gate - 1 - wave; k < K; k += n_gate) {   // wave-uniform
               const uint32_t need = static_cast<uint32_t>(__builtin_amdgcn_readlane(cnt2, k));
               uint32_t qlen = static_cast<uint32_t>(L.sc[SC_QLEN + k]);
               if (qlen > queue_cap) qlen = queue_cap;
@@ -1873,40 +1848,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               // (the ring holds as many live entries as the class counter says; if it ever did not, the
               // candidates beyond them would point at the head entry)
               for (uint32_t rk = found + lane; rk < need; rk += 64) L.live_off[k * kAdmChunk + rk] = 0;
-              if (lane == 0) L.sc[SC_LEAD + k] = (need > 0 && found > 0) ? 1 : 0;
+              if (lane == 0 && need == 0) L.live_off[k * kAdmChunk] = 0;   // (no candidate: the head stays)
             }
             // only the FCFS gate reads the offsets while it ranks the candidates; the other gates first use them
             // after the barrier that ends this segment
             if (gate_mode == SIM_GATE_FCFS) __syncthreads();
           }
-          // The admissions take the first nadm idle prefill slots, whatever their order: the slot bitmaps are
-          // updated here a word at a time (no atomics).
-          // A wave takes a word, a lane a slot; the slot of every admission rank goes into a table.
-          for (int w = wave; w < nwords_m; w += nwaves) {   // wave-uniform
-            const uint64_t idle_all = L.bm_idle[w], touch_w = L.bm_touch[w];
-            const uint64_t idle = idle_all & bits_below(w, M);   // the gate admits to the mixed group only
-            const int before = static_cast<int>(L.pre[w]);   // idle slots in the words before this one
-            uint64_t adm = 0;
-            if (before < nadm)
-              adm = before + __popcll(idle) <= nadm ? idle : idle & ((1ull << nth_set_bit(idle, nadm - before)) - 1ull);
-            if (adm) {
-              if ((adm >> lane) & 1ull)
-                L.adm_slot[before + rank_in(adm)] = static_cast<uint16_t>((w << 6) + lane);
-              if (lane == 0) {
-                L.bm_idle[w] = idle_all & ~adm;
-                L.bm_touch[w] = touch_w | adm;
-              }
-            }
-          }
-          // (the waves that run the weighted router's selection in this segment rank no candidates)
-          int rank_first = wave_base, rank_step = NT;
-          if constexpr (kStageEarly) {
-            if (nwaves >= 8) {
-              rank_step = NT - 128;
-              rank_first = wave < ring_wave ? wave_base : wave_base - 128;
-            }
-          }
-          const bool ranks = !(kStageEarly && nwaves >= 8 && (wave == ring_wave || wave == ring_wave_m));   // wave-uniform
           // The searches of a candidate in the other classes run side by side on neighbouring lanes, which add up what they
           // find; the candidates of a class follow those of the class before it.
           int first_of[kMaxK];   // first candidate of each class
@@ -1918,7 +1865,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               if (kk < K) run += __builtin_amdgcn_readlane(cnt2, kk);
             }
           }
-          for (int c0 = rank_first; ranks && c0 < (ncand << lg); c0 += rank_step) {   // wave-uniform trip count
+          for (int c0 = wave << 6; c0 < (ncand << lg); c0 += n_gate << 6) {   // wave-uniform trip count
             const int c = (c0 + lane) >> lg;
             int k = 0, m = c, lo = 0;
 #pragma unroll
@@ -1969,17 +1916,27 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             }
           }
         }
+        if constexpr (AB) {   // (the barrier between the walk and the ranking, for the other waves)
+          if (gate_on && wave >= n_gate && gate_mode == SIM_GATE_FCFS) __syncthreads();
+        }
         // routing pass: up to kRouteLevels levels, first of the solo group (servers M..N-1), then, if that group
         // is full by then, of the mixed group (servers 0..M-1, one slot less). Level t of group G holds the
         // servers of G with at most lminG + (t - firstG) decodes.
         int nl = 0, total = 0;
         int lminG[2] = {0, 0}, nG[2] = {0, 0}, csumG[2] = {0, 0}, tlastG[2] = {0, 0};
-        // Placements on a mixed-group server must see every admission of the step (it decides whether the job
-        // counts as mixed or solo decode): while the gate may need another pass, only the solo group is routed.
-        const bool gate_unfinished = gate_on && nadm == kAdmChunk && nidle > kAdmChunk;
-        bool route_wait = false;   // nothing to route in this pass, but the mixed group is still to come
-        if (route_on) {
-          // (every wave computes the same values and stores them: no broadcast, no barrier)
+        if (route_on && wave >= route_first) {
+          // Placements on a mixed-group server must see every admission of the step (it decides whether the job
+          // counts as mixed or solo decode): while the gate may need another pass, only the solo group is routed.
+          bool gate_unfinished = false;
+          if (nidle > kAdmChunk) {   // rare (wave-uniform): does the pass admit all it can
+            int n = 0;
+            for (int k = 0; k < K; ++k) {
+              const int qp = uniform(L.cs[CS_QP + k]);
+              if ((admissible >> k) & 1ull) n += qp < kAdmChunk ? qp : kAdmChunk;
+            }
+            gate_unfinished = n >= kAdmChunk;
+          }
+          // (every one of these waves computes the same values and stores them: no broadcast, no barrier)
           // (with abandonment a pass places no more jobs than are staged in LDS)
           const int jpass = AB && jrem > kJobsLds ? kJobsLds : jrem;
           int rem_jobs = jpass;
@@ -2019,9 +1976,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               if (lm < 0) continue;   // no free slot in this group
               lminG[gi] = lm;
               for (int u = 0; nl < kRouteLevels && rem_g > 0 && lm + u < capg; ++u) {
-                csumG[gi] += static_cast<int>(level_count(gi, lm + u));
+                const int cnt = static_cast<int>(level_count(gi, lm + u));
+              csumG[gi] += cnt;
                 const int tk = csumG[gi] < rem_g ? csumG[gi] : rem_g;
-                if (lane == 0) { L.sc[SC_TAKE_T + nl] = tk; L.sc[SC_W_T + nl] = listed + (start_g - rem_g); }
+                if (lane == 0) { L.sc[SC_TAKE_T + nl] = tk; L.sc[SC_CNT_T + nl] = cnt; L.sc[SC_W_T + nl] = listed + (start_g - rem_g); }
                 rem_g -= tk;
                 tlastG[gi] = tk;
                 ++nG[gi];
@@ -2041,9 +1999,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             if (lm < 0) continue;   // no free slot in this group
             lminG[gi] = lm;
             for (int u = 0; nl < kRouteLevels && rem_jobs > 0 && lm + u < capg; ++u) {
-              csumG[gi] += static_cast<int>(level_count(gi, lm + u));
+              const int cnt = static_cast<int>(level_count(gi, lm + u));
+              csumG[gi] += cnt;
               const int tk = csumG[gi] < rem_jobs ? csumG[gi] : rem_jobs;
-              if (lane == 0) { L.sc[SC_TAKE_T + nl] = tk; L.sc[SC_W_T + nl] = jpass - rem_jobs; }
+              if (lane == 0) { L.sc[SC_TAKE_T + nl] = tk; L.sc[SC_CNT_T + nl] = cnt; L.sc[SC_W_T + nl] = jpass - rem_jobs; }
               rem_jobs -= tk;
               tlastG[gi] = tk;
               ++nG[gi];
@@ -2052,21 +2011,22 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           }
           }
           total = jpass - rem_jobs;
-          if (nl == 0) {
-            if (gate_unfinished) route_wait = true;
-            else route_on = false;   // every slot is taken: the jobs stay in the buffer
-          } else {
+          // (no level: every slot is taken, and the jobs stay in the buffer, or the mixed group is still to come)
+          if (lane == 0) {
+            L.sc[SC_LEVELS] = nl | (nG[0] << 8) | (gate_unfinished ? 0x10000 : 0);
+            L.sc[SC_LMIN] = lminG[0] | (lminG[1] << 16);
+          }
+          if (nl > 0) {
             // Waves that count the servers of each level, and this wave's place among them. With abandonment the
             // requests the pass places are first staged in LDS by the waves that own the decode buffers: a large
             // workgroup gives them no counting to do, so that the staging runs beside the gate's ranking.
-            int cw = wave, cn = nwaves;
-            if constexpr (kStageEarly) {
+            int cw = wave - route_first, cn = n_route;
+            if constexpr (AB) {
               stage_pass(total);
-              if (nwaves >= 8) {
+              if (nwaves >= 8) {   // the first of these waves are the buffers'
                 constexpr int n_ring = RR ? 2 : 1;
-                cn = nwaves - n_ring;
-                cw = wave < ring_wave ? wave : wave - n_ring;   // (negative for the buffers' waves)
-                if (wave >= ring_wave && wave < ring_wave + n_ring) cw = nwords;   // nothing to count
+                cn = n_route - n_ring;
+                cw = cw < n_ring ? nwords : cw - n_ring;   // (nothing to count)
               }
             }
             // Four words per round: their decode counts are read together, and a level's members in a word are one
@@ -2089,7 +2049,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                       const bool solo = t < nG[0];
                       const int most = solo ? lminG[0] + t : lminG[1] + (t - nG[0]);
                       const uint64_t in = __ballot(ld[u] <= most) & (solo ? ~mixed : mixed);
-                      if (lane == 4 * u + t) members = in;
+                      members = writelane64(members, in, 4 * u + t);
                     }
                   }
                 }
@@ -2101,94 +2061,25 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         }
         __syncthreads();
 
-        // ---------------- segment B ----------------
-        bool gate_more = false;
-        bool a_active = false;   // this lane's admission of the pass: slot, class, arrival stamp, decodes beside it
-        int a_g = 0, a_k = 0;
-        uint32_t a_stamp = 0, a_in = 0, a_out = 0;
-        uint64_t a_nc = 0;
-        if (gate_on) {
-          if (pass == 0 && tid == 0) {   // the completions of this step are in the buffer
-            if constexpr (RR) { L.cs[CS_DCOUNT] = jremL[0]; L.cs[CS_DCOUNT_M] = jremL[1]; }
-            else L.cs[CS_DCOUNT] = jrem;
-          }
-          // Admission j goes to the idle prefill slot of rank j; one thread per admission (a pass admits no more than
-          // the workgroup has threads). Here the wave only reads what segment C changes (queue heads, decode
-          // counts of the servers) and asks memory for the request's stamp and lengths; the rest follows in segment C.
-          if (wave_base < nadm) {   // wave-uniform
-            const int j = wave_base + lane;
-            a_active = j < nadm;
-            if (a_active) {
-              a_g = L.adm_slot[j];
-              const uint32_t e = L.adm[j];
-              a_k = static_cast<int>(e & 7u);
-              uint32_t pos = static_cast<uint32_t>(L.cs[CS_QHEAD + a_k]) + (AB ? L.live_off[a_k * kAdmChunk + (e >> 3)] : (e >> 3));
-              if (pos >= queue_cap) pos -= queue_cap;
-              a_stamp = qring[static_cast<size_t>(a_k) * queue_cap + pos];
-              if constexpr (AB) {   // the request no longer waits: it leaves the calendar of its deadline
-                const uint32_t dl = qdl[static_cast<size_t>(a_k) * queue_cap + pos];
-                if (dl != kNever) atomicSub(&cal[static_cast<size_t>(a_k) * cal_n + (dl & p.cal_mask)], 1u);
-              }
-              if (L.loads[a_g]) a_nc = rec[a_g].n_cls;   // (before this pass's placements on the server)
-              uint32_t w[4];
-              philox4x32_10(key0, key1, s, 1u, static_cast<uint32_t>(a_g), static_cast<uint32_t>(r), w);
-              a_in = a.len_tab[(static_cast<size_t>(a_k) * 2 + 0) * kTableSize + (w[0] >> 16)];
-              a_out = a.len_tab[(static_cast<size_t>(a_k) * 2 + 1) * kTableSize + (w[1] >> 16)];
-            }
-          }
-          if (nadm == kAdmChunk && nidle > kAdmChunk) {   // rare: more idle slots than one pass serves
-            for (int k = 0; k < K; ++k) {
-              if (((admissible >> k) & 1ull) && L.cs[CS_QP + k] - L.sc[SC_ADMK + k] > 0) gate_more = true;
-            }
-          }
-        }
-        if (route_on && !route_wait) {
-          // the requests this pass places are staged in LDS
-          const int nstage = total < kJobsLds ? total : kJobsLds;
-          if constexpr (AB) {
-            if constexpr (!kStageEarly) stage_pass(total);
-          } else if constexpr (RR) {
-            for (int j = tid; j < nstage; j += NT) {
-              const int li = j < takenL[0] ? 0 : 1;
-              uint32_t pos = dheadL[li] + static_cast<uint32_t>(nextL[li] + (li ? j - takenL[0] : j));
-              if (pos >= dbuf_cap) pos -= dbuf_cap;
-              if (pos >= dbuf_cap) pos -= dbuf_cap;
-              L.jobs[j] = (li ? dring_m : dring)[pos];
-            }
-          } else {
-          for (int j = tid; j < nstage; j += NT) {
-            uint32_t pos = dhead0 + static_cast<uint32_t>(next + j);
-            if (pos >= dbuf_cap) pos -= dbuf_cap;
-            if (pos >= dbuf_cap) pos -= dbuf_cap;
-            L.jobs[j] = dring[pos];
-          }
-          }
-          // ranks of each level's members; the last waves take this
-          for (int t = nwaves - 1 - wave; t < nl; t += nwaves) rank_bitmap(L.bm_lvl + t * nwords, L.pre_lvl + t * nwords, nwords, N);
-        }
-        __syncthreads();
-
         // ---------------- segment C ----------------
-        if (gate_on && wave_base < nadm) {   // wave-uniform: the admissions this wave began in segment B
-          if (a_active) {
-            const int g = a_g, k = a_k;
-            rec[g].pf_job = static_cast<uint64_t>(a_stamp) | (static_cast<uint64_t>(k) << 29) |
-                            (static_cast<uint64_t>(a_in - 1) << 32) | (static_cast<uint64_t>(a_out - 1) << 48);
-            // an idle prefill slot implies that the running iteration holds no chunk
-            L.rem[g] = static_cast<uint16_t>(a_in);
-            lds_add64(&L.tl[k * kNTally + SIM_T_WAIT_STEPS], static_cast<uint64_t>(s - a_stamp));
-          }
-          uint64_t even = 0, odd = 0;   // co-resident decodes switch solo -> mixed
-          if (__ballot(a_nc != 0)) wave_sum_bytes(a_nc, even, odd);
-          if (lane == 0 && (even | odd))
-            for (int c = 0; c < K; ++c) {
-              const int v = static_cast<int>(class_field(even, odd, c));
-              if (v) {
-                lds_add64(&L.tl[c * kNTally + SIM_T_M_SM], static_cast<uint64_t>(v));
-                atomicSub(&L.cs[CS_YS + c], v);
-                atomicAdd(&L.cs[CS_YM + c], v);
-              }
-            }
+        const int sc_pass = L.sc[lane];   // one word a lane: one trip to LDS
+        auto word_of = [&](int i) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(sc_pass, i); };
+        const int nadm = gate_on ? word_of(SC_NADM) & 0xFFFF : 0;
+        const bool gate_more = gate_on && (word_of(SC_NADM) & 0x10000);
+        const int levels = route_on ? word_of(SC_LEVELS) : 0;
+        const int nl_here = levels & 0xFF, nl_solo = (levels >> 8) & 0xFF;
+        int take_r[kRouteLevels], w_r[kRouteLevels];
+#pragma unroll
+        for (int t = 0; t < kRouteLevels; ++t) { take_r[t] = word_of(SC_TAKE_T + t); w_r[t] = word_of(SC_W_T + t); }
+        int placed = 0, placed_solo = 0;   // jobs the pass places, of them (two buffers) from the solo group's
+#pragma unroll
+        for (int t = 0; t < kRouteLevels; ++t) {
+          if (t < nl_here) placed = w_r[t] + take_r[t];
+          if (t < nl_solo) placed_solo = w_r[t] + take_r[t];
+        }
+        if (pass == 0 && tid == 0) {   // the completions of this step are in the buffer
+          if constexpr (RR) { L.cs[CS_DCOUNT] = jremL[0]; L.cs[CS_DCOUNT_M] = jremL[1]; }
+          else L.cs[CS_DCOUNT] = jrem;
         }
         if (gate_on && tid < K) {   // class counters follow the admissions of this pass
           const int k = tid, adm_k = L.sc[SC_ADMK + k];
@@ -2196,7 +2087,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           // before the last of them (before the first waiting request when none was admitted)
           uint32_t past = static_cast<uint32_t>(adm_k);
           if constexpr (AB) {
-            past = adm_k ? L.live_off[k * kAdmChunk + adm_k - 1] + 1u : (L.sc[SC_LEAD + k] ? L.live_off[k * kAdmChunk] : 0u);
+            past = adm_k ? L.live_off[k * kAdmChunk + adm_k - 1] + 1u : L.live_off[k * kAdmChunk];
             if (past) {
               L.sc[SC_QLEN + k] -= static_cast<int32_t>(past);
               if (!adm_k) {
@@ -2216,167 +2107,305 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             L.sc[SC_ADMK + k] = 0;
           }
         }
-        if (route_on && !route_wait) {
-          int take_r[kRouteLevels], w_r[kRouteLevels];
-#pragma unroll
-          for (int t = 0; t < kRouteLevels; ++t) {
-            take_r[t] = __builtin_amdgcn_readfirstlane(L.sc[SC_TAKE_T + t]);
-            w_r[t] = __builtin_amdgcn_readfirstlane(L.sc[SC_W_T + t]);
-          }
-          // The servers that get jobs: in every level the first take_r of its members. A lane looks at one word (the
-          // wave's words are wave, wave + nwaves, ...), and the servers found are queued, so that the placements
-          // themselves are made one server per lane: taken word by word, with a lane per server of the word, they
-          // cost a pass through the code below for the one job that a word gets.
-          int nplace = 0, w_next = wave, w_from = 0;
-          uint64_t got_w = 0, todo = 0;   // servers of this lane's word that get jobs; lanes whose word has any left to queue
-          for (bool more = true; more;) {   // wave-uniform
-            while (nplace <= kEvPerWave - 64) {
-              if (todo == 0) {
-                if (w_next >= nwords) { more = false; break; }
-                const int wl = w_next + lane * nwaves;
-                got_w = 0;
-                if (wl < nwords) {
-#pragma unroll
-                  for (int t = 0; t < kRouteLevels; ++t) {
-                    if (t < nl) {   // wave-uniform
-                      const uint64_t in = L.bm_lvl[t * nwords + wl];
-                      const int left = take_r[t] - static_cast<int>(L.pre_lvl[t * nwords + wl]);
-                      if (left > 0) got_w |= __popcll(in) <= left ? in : in & ((1ull << nth_set_bit(in, left)) - 1ull);
+        // The servers that are given work: the admissions take the first nadm idle prefill slots, in every routing level the
+        // first take_r of its members get a job. The last waves, as many as it takes, each find all of these servers (a lane
+        // looks at one to three neighbouring words), queue 64 of them and serve those, one a lane. The other waves draw the
+        // next step's arrivals meanwhile.
+        const int work = nadm + placed;   // (servers, or more: one may get an admission and jobs)
+        const int n_serve = work <= 64 ? 1 : (work + 63) >> 6 < nwaves ? (work + 63) >> 6 : nwaves;
+        if (work > 0 && wave < nwaves - n_serve) {
+          // (left to the next completion pass, where all waves take part, if these would get more than sixteen words each)
+          if (!drawn && s + 1u < step_end && 16 * (nwaves - n_serve) >= nwords) draw_arrivals(s + 1u, wave, nwaves - n_serve);
+        } else if (work > 0) {
+          // Everything a step gives a server, and what follows from it, in one go: its admission, its jobs, and either the next
+          // event (the server is idle or at an iteration boundary) or the end of the running iteration as its event.
+          auto serve = [&](int nsrv) __attribute__((always_inline)) {   // (up to 64)
+              const bool active = lane < nsrv;
+              uint32_t m = 0, d = 0;   // iterations to tally
+              bool chunk = false;
+              uint64_t comp = 0;
+              if (active) {
+                const int entry = ev_g[lane], g = entry & 0x7FFF, wi = g >> 6;
+                const bool admitted = entry & 0x8000;   // the idle slot of rank j takes the candidate of rank j
+                const uint64_t bit = 1ull << (g & 63);
+                uint64_t nc = rec[g].n_cls, nj = rec[g].n_join;
+                uint32_t it_tal = rec[g].iter, nf = rec[g].next_fin;
+                const uint64_t idle = L.bm_idle[wi];
+                const bool busy = L.bm_busy[wi] & bit, due = L.bm_due[wi] & bit;
+                const int n_own = static_cast<int>(L.loads[g]);   // decodes of the server
+                int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0;
+                const uint32_t ev = L.ev_it[g];
+                uint32_t it = ev & kEvIter;
+                const bool had_chunk = ev & kEvChunk, pin = joins_next(nj, rem, had_chunk);
+                const int64_t rel = event_time(g, T);
+                // ---- the admission
+                int a_k = 0;
+                uint32_t a_stamp = 0, a_in = 0, a_out = 0;
+                if (admitted) {
+                  const int j = static_cast<int>(L.pre[wi]) + __popcll(idle & (bit - 1ull));
+                  const uint32_t e = L.adm[j];
+                  a_k = static_cast<int>(e & 7u);
+                  uint32_t pos = static_cast<uint32_t>(L.sc[SC_HEAD + a_k]) + (AB ? L.live_off[a_k * kAdmChunk + (e >> 3)] : (e >> 3));
+                  if (pos >= queue_cap) pos -= queue_cap;
+                  a_stamp = qring[static_cast<size_t>(a_k) * queue_cap + pos];
+                  if constexpr (AB) {   // the request no longer waits: it leaves the calendar of its deadline
+                    const uint32_t dl = qdl[static_cast<size_t>(a_k) * queue_cap + pos];
+                    if (dl != kNever) atomicSub(&cal[static_cast<size_t>(a_k) * cal_n + (dl & p.cal_mask)], 1u);
+                  }
+                  uint32_t w[4];
+                  philox4x32_10(key0, key1, s, 1u, static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
+                  a_in = a.len_tab[(static_cast<size_t>(a_k) * 2 + 0) * kTableSize + (w[0] >> 16)];
+                  a_out = a.len_tab[(static_cast<size_t>(a_k) * 2 + 1) * kTableSize + (w[1] >> 16)];
+                }
+                // ---- where the server stands: `it` iterations are completed; in the middle of one (`mid`: what it is given
+                //      now joins when that one ends), at a boundary, the iterations before it then being tallied, or idle.
+                //      A server that has had its event in this step is at the boundary it was started anew from.
+                int64_t start = due ? rel : 0;   // (idle: back to back after a completion in this step, else from the step boundary)
+                bool mid = false;
+                uint32_t dur = 0;
+                if (busy) {
+                  uint32_t left = 1;   // iterations up to the event
+                  mid = pin;
+                  if (!pin) {
+                    const int ptok = had_chunk ? chunk_of(rem) : 0;
+                    dur = iteration_ns(ptok, static_cast<uint32_t>(n_own));
+                    left = iterations_left(static_cast<uint64_t>(rel), dur);
+                    start = rel - static_cast<int64_t>(static_cast<uint64_t>(left) * dur);   // end of the latest completed iteration
+                    mid = start <= -static_cast<int64_t>(dt_ns);
+                    if (!mid) {
+                      m = it - left - it_tal;
+                      d = dur;
+                      chunk = had_chunk;
+                      comp = nc;
+                      rem -= static_cast<int>(m) * ptok;
                     }
                   }
-                  if (got_w) L.bm_touch[wl] |= got_w;   // (no other wave looks at the word in this segment)
+                  it -= left;
                 }
-                todo = __ballot(got_w != 0);
-                w_from = w_next;
-                w_next += 64 * nwaves;
-              } else {
-                const int src = __ffsll(static_cast<long long>(todo)) - 1;
-                todo &= todo - 1ull;
-                const uint64_t got = readlane64(got_w, src);
-                if (lane_in(got)) ev_g[nplace + rank_in(got)] = static_cast<uint16_t>(((w_from + src * nwaves) << 6) + lane);
-                nplace += __popcll(got);
-              }
-            }
-            for (int e0 = 0; e0 < nplace; e0 += 64) {   // wave-uniform
-              if (e0 + lane < nplace) {
-                const int g = static_cast<int>(ev_g[e0 + lane]), wi = g >> 6;
-                const uint64_t bit = 1ull << (g & 63);
-                const int n_own = static_cast<int>(L.loads[g]);   // decodes of the server
-                const uint64_t pin_word = L.bm_pin[wi], chunk_word = L.bm_chunk[wi];
-                const int64_t rel = event_time(g, T);
-                const bool runs = (L.bm_busy[wi] & bit) && rel > 0;   // not known to be at a boundary: the settling works it out
-                const bool has_prefill = g < Mp && !(L.bm_idle[wi] & bit);
-                // which job of each level the server takes, by its rank among the level's members
+                if (!mid) { it_tal = it; nj = 0; }
+                // ---- the request admitted; decodes beside it switch solo -> mixed
+                if (admitted) {
+                  rec[g].pf_job = static_cast<uint64_t>(a_stamp) | (static_cast<uint64_t>(a_k) << 29) |
+                                  (static_cast<uint64_t>(a_in - 1) << 32) | (static_cast<uint64_t>(a_out - 1) << 48);
+                  rem = static_cast<int>(a_in);   // an idle prefill slot implies that the running iteration holds no chunk
+                  lds_add64(&L.tl[a_k * kNTally + SIM_T_WAIT_STEPS], static_cast<uint64_t>(s - a_stamp));
+                  if (n_own) {
+#pragma unroll
+                    for (int c = 0; c < kMaxK; ++c) {
+                      const uint32_t v = byte_at(nc, c);
+                      if (v) {
+                        lds_add64(&L.tl[c * kNTally + SIM_T_M_SM], v);
+                        atomicSub(&L.cs[CS_YS + c], static_cast<int>(v));
+                        atomicAdd(&L.cs[CS_YM + c], static_cast<int>(v));
+                      }
+                    }
+                  }
+                }
+                // ---- the jobs: which one of each level the server takes follows from its rank among the level's members
+                int nd = n_own;
+                const bool has_prefill = g < Mp && (admitted || !(idle & bit));
                 const int gi = g >= M ? 0 : 1;
-                const int first = gi == 0 ? 0 : nG[0], my_n = gi == 0 ? nG[0] : nG[1], my_lmin = gi == 0 ? lminG[0] : lminG[1];
-                int q_r[kRouteLevels];
-                bool got_last = false;
+                const int lmins = word_of(SC_LMIN);
+                const int first = gi == 0 ? 0 : nl_solo, my_lmin = gi == 0 ? lmins & 0xFFFF : lmins >> 16;
 #pragma unroll
                 for (int t = 0; t < kRouteLevels; ++t) {
-                  q_r[t] = -1;
-                  if (t < nl) {   // wave-uniform
+                  if (t < nl_here) {   // wave-uniform
                     const uint64_t in = L.bm_lvl[t * nwords + wi];
                     const int q = static_cast<int>(L.pre_lvl[t * nwords + wi]) + __popcll(in & (bit - 1ull));
-                    if ((in & bit) && q < take_r[t]) q_r[t] = q;
+                    if ((in & bit) && q < take_r[t]) {
+                      const int j = w_r[t] + q;   // position in this pass
+                      uint64_t jw;
+                      if constexpr (AB) {
+                        jw = L.jobs[j];
+                      } else {   // this step's completions are in LDS too, behind them what has waited in the ring
+                        const int i = RR ? (gi == 0 ? nextL[0] + j : nextL[1] + j - placed_solo) : next + j;
+                        const int ci = i - (RR && gi ? dcount0_m : dcount0);
+                        constexpr int kHere = RR ? kJobsLds / 2 : kJobsLds;
+                        const bool here = ci >= 0 && ci < kHere;
+                        jw = L.jobs[here ? (RR && gi ? kHere : 0) + ci : 0];
+                        asm("" : "+v"(jw));   // (else the two loads become one through a pointer to either memory)
+                        if (!here) {
+                          uint32_t pos = (RR ? dheadL[gi] : dhead0) + static_cast<uint32_t>(i);
+                          if (pos >= dbuf_cap) pos -= dbuf_cap;
+                          if (pos >= dbuf_cap) pos -= dbuf_cap;
+                          if (!RR || gi == 0) jw = dring[pos]; else jw = dring_m[pos];
+                        }
+                      }
+                      const int k = static_cast<int>(jw >> 29) & 7;
+                      const int slot = my_lmin + (t - first);   // the server holds exactly this many decodes by now
+                      const uint32_t ends = it + static_cast<uint32_t>(jw >> 48) + 1u + (mid ? 1u : 0u);
+                      nf = nd == 0 || ends < nf ? ends : nf;
+                      fin[static_cast<size_t>(g) * BS + slot] = ends;
+                      job[static_cast<size_t>(g) * BS + slot] = jw;
+                      nc += 1ull << (8 * k);
+                      if (mid) nj += 1ull << (8 * k);   // not part of the iterations still to be tallied for this server
+                      nd = slot + 1;
+                      lds_add64(&L.tl[k * kNTally + (has_prefill ? SIM_T_U_DM : SIM_T_U_DS)], 1);
+                      atomicAdd(&L.cs[(has_prefill ? CS_YM : CS_YS) + k], 1);
+                      atomicSub(&L.cs[CS_QD + k], 1);
+                    }
                   }
-                  if (t == first + my_n - 1) got_last = q_r[t] >= 0;
                 }
-                // iterations the server has completed, and whether it is in the middle of one: a job placed now then
-                // joins at the next restart
-                uint32_t it = L.ev_it[g];
-                bool mid = runs;
-                if (runs && (pin_word & bit)) {
-                  it -= 1u;
-                } else if (runs) {
-                  const int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0;
-                  const uint32_t dur = iteration_ns((chunk_word & bit) ? chunk_of(rem) : 0, static_cast<uint32_t>(n_own));
-                  const uint32_t left = iterations_left(static_cast<uint64_t>(rel), dur);
-                  it -= left;
-                  mid = rel - static_cast<int64_t>(static_cast<uint64_t>(left) * dur) <= -static_cast<int64_t>(dt_ns);
+                // ---- the next event
+                if (!mid) {   // starts the next iteration with what it holds now
+                  const int ptok = rem > 0 ? chunk_of(rem) : 0;
+                  dur = iteration_ns(ptok, static_cast<uint32_t>(nd));
+                  const uint32_t n = phase_length(static_cast<uint32_t>(nd), rem, dur, nf - it);
+                  set_event(g, T + start + static_cast<int64_t>(static_cast<uint64_t>(n) * dur), it + n, ptok > 0, nd && nf == it + n);
+                  if (!busy) atomicOr(bits64(&L.bm_busy[wi]), bit);
+                } else if (!pin) {   // the end of the running iteration
+                  set_event(g, T + start + dur, it + 1u, had_chunk, nd && nf == it + 1u);
                 }
-                uint32_t first_end = kNever;
+                if (admitted || (chunk && m)) L.rem[g] = static_cast<uint16_t>(rem);
+                L.loads[g] = static_cast<uint8_t>(nd);
+                rec[g].n_cls = nc;
+                rec[g].n_join = nj;
+                rec[g].iter = it_tal;
+                rec[g].next_fin = nf;
+              }
+              tally_iterations<kTallyRowsHere>(L.ta, L.tbth, tbt_w, tbt_lo, K, m, d, chunk, comp);
+          };
+          // Which servers: the members of every level before a lane's words are counted, two levels in one sum. The first
+          // `left` members of a word: all of them, or (one word a level) some.
+          constexpr int kWords = MAXT > 512 ? (NWS + 63) / 64 : 2;   // words a lane may have to look at
+          const int n_words = (nwords + 63) >> 6;
+          auto first_members = [&](uint64_t in, int left) __attribute__((always_inline)) -> uint64_t {
+            const int c = __popcll(in);
+            uint64_t out = left >= c ? in : 0ull;
+            for (uint64_t part = __ballot(left > 0 && left < c); part; part &= part - 1ull) {   // wave-uniform
+              const int src = __ffsll(static_cast<long long>(part)) - 1;
+              const uint64_t w = readlane64(in, src);
+              out = writelane64(out, __ballot(lane_in(w) && rank_in(w) < __builtin_amdgcn_readlane(left, src)), src);
+            }
+            return out;
+          };
+          uint64_t got[kWords], adm[kWords];
 #pragma unroll
-                for (int t = 0; t < kRouteLevels; ++t) {
-                  if (q_r[t] < 0) continue;
-                  const int j = w_r[t] + q_r[t];   // position in this pass
-                  uint64_t jw;
-                  if (j < kJobsLds) {
-                    jw = L.jobs[j];
-                  } else {
-                    uint32_t pos = dhead0 + static_cast<uint32_t>(next + j);
-                    if (pos >= dbuf_cap) pos -= dbuf_cap;
-                    if (pos >= dbuf_cap) pos -= dbuf_cap;
-                    jw = dring[pos];
-                  }
-                  const int k = static_cast<int>(jw >> 29) & 7;
-                  const uint32_t Dl = static_cast<uint32_t>(jw >> 48) + 1;
-                  const int nd = my_lmin + (t - first);   // the server holds exactly this many decodes by now
-                  const uint32_t ends = it + Dl + (mid ? 1u : 0u);
-                  first_end = ends < first_end ? ends : first_end;
-                  fin[static_cast<size_t>(g) * BS + nd] = ends;
-                  job[static_cast<size_t>(g) * BS + nd] = jw;
-                  atomicAdd(reinterpret_cast<unsigned long long *>(&rec[g].n_cls), 1ull << (8 * k));
-                  // not part of the iterations still to be tallied for this server
-                  if (runs) atomicAdd(reinterpret_cast<unsigned long long *>(&rec[g].n_join), 1ull << (8 * k));
-                  lds_add64(&L.tl[k * kNTally + (has_prefill ? SIM_T_U_DM : SIM_T_U_DS)], 1);
-                  atomicAdd(&L.cs[(has_prefill ? CS_YM : CS_YS) + k], 1);
-                  atomicSub(&L.cs[CS_QD + k], 1);
+          for (int i = 0; i < kWords; ++i) {
+            got[i] = adm[i] = 0;
+            if (i < n_words && nadm > 0) {   // wave-uniform
+              const int w = lane * n_words + i;
+              uint64_t slots = 0;
+              int left = 0;
+              if (w < nwords_m) {
+                slots = L.bm_idle[w] & bits_below(w, M);   // the gate admits to the mixed group only
+                left = nadm - static_cast<int>(L.pre[w]);
+              }
+              got[i] = adm[i] = first_members(slots, left);
+            }
+          }
+#pragma unroll
+          for (int t0 = 0; t0 < kRouteLevels; t0 += 2) {
+            if (t0 < nl_here) {   // wave-uniform
+              uint64_t in[2][kWords];
+              uint32_t n = 0;
+#pragma unroll
+              for (int i = 0; i < kWords; ++i) {
+                const int w = lane * n_words + i;
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                  in[u][i] = i < n_words && t0 + u < nl_here && w < nwords ? L.bm_lvl[(t0 + u) * nwords + w] : 0ull;
+                  n += static_cast<uint32_t>(__popcll(in[u][i])) << (16 * u);
                 }
-                if (n_own == 0) rec[g].next_fin = first_end; else atomicMin(&rec[g].next_fin, first_end);
-                // a server below the last level of its group now holds that level, plus one if that level reached it
-                L.loads[g] = static_cast<uint8_t>(my_lmin + my_n - 1 + (got_last ? 1 : 0));
+              }
+              uint32_t rank = wave_incl_scan(n) - n;
+#pragma unroll
+              for (int i = 0; i < kWords; ++i) {
+                const int w = lane * n_words + i;
+                if (i < n_words) {   // wave-uniform
+#pragma unroll
+                  for (int u = 0; u < 2; ++u) {
+                    if (t0 + u < nl_here) {   // wave-uniform
+                      const uint32_t r_u = u ? rank >> 16 : rank & 0xFFFFu;
+                      if (w < nwords) L.pre_lvl[(t0 + u) * nwords + w] = static_cast<uint16_t>(r_u);   // (the same from every wave that serves)
+                      got[i] |= first_members(in[u][i], take_r[t0 + u] - static_cast<int>(r_u));
+                      rank += static_cast<uint32_t>(__popcll(in[u][i])) << (16 * u);
+                    }
+                  }
+                }
               }
             }
-            nplace = 0;
           }
+          uint32_t n_lane = 0;   // servers of this lane's words, and of the lanes before
+#pragma unroll
+          for (int i = 0; i < kWords; ++i) n_lane += static_cast<uint32_t>(__popcll(got[i]));
+          const uint32_t n_upto = wave_incl_scan(n_lane);
+          const int n_all = __builtin_amdgcn_readlane(static_cast<int>(n_upto), 63);
+          // This wave's 64 of them are queued and served (a second time round only where even all waves were too few): a word with
+          // many by a lane per server, of the others every lane queues one server at a time.
+          for (int lo = (nwaves - 1 - wave) << 6; lo < n_all; lo += n_serve << 6) {   // wave-uniform
+            int at = static_cast<int>(n_upto - n_lane) - lo;   // place of this lane's next server
+#pragma unroll
+            for (int i = 0; i < kWords; ++i) {
+              if (i >= n_words) break;   // wave-uniform
+              const int w = lane * n_words + i, c = __popcll(got[i]);
+              const bool here = c > 0 && at < 64 && at + c > 0;
+              uint64_t left = here && c <= 6 ? got[i] : 0ull;
+              for (uint64_t many = __ballot(here && c > 6); many; many &= many - 1ull) {
+                const int src = __ffsll(static_cast<long long>(many)) - 1;
+                const uint64_t g_w = readlane64(got[i], src), a_w = readlane64(adm[i], src);
+                const int to = __builtin_amdgcn_readlane(at, src) + rank_in(g_w);
+                if (lane_in(g_w) && to >= 0 && to < 64)
+                  ev_g[to] = static_cast<uint16_t>(((src * n_words + i) << 6) + lane + (lane_in(a_w) ? 0x8000 : 0));
+              }
+              for (int to = at; __ballot(left != 0); ++to) {
+                if (left) {
+                  const int b = __ffsll(static_cast<long long>(left)) - 1;
+                  if (to >= 0 && to < 64) ev_g[to] = static_cast<uint16_t>((w << 6) + b + ((adm[i] >> b) & 1ull ? 0x8000 : 0));
+                  left &= left - 1ull;
+                }
+              }
+              at += c;
+            }
+            serve(n_all - lo < 64 ? n_all - lo : 64);
+          }
+          // the slots that were given away: other waves that serve may still look at bm_idle, so the owners take them out later
+          if (wave == nwaves - 1) {
+#pragma unroll
+            for (int i = 0; i < kWords; ++i) {
+              const int w = lane * n_words + i;
+              if (i < n_words && w < nwords) {
+                if (nwaves > 1) L.bm_comp[w] = adm[i];
+                else if (adm[i]) L.bm_idle[w] &= ~adm[i];
+              }
+            }
+          }
+        }
+        if (work > 0) {
+          if (!drawn && s + 1u < step_end && n_serve < nwaves && 16 * (nwaves - n_serve) >= nwords) {
+            next_thresholds();
+            drawn = true;
+          }
+          if (nadm > 0 && nwaves > 1) slots_taken = true;
+        }
+        if (placed > 0) {
           if constexpr (WS) {   // what the pass took from the solo group's buffer, per class
             if (tid >= NT - 64 && lane < K) L.cs[CS_QDS + lane] -= L.sel_n[lane];
           }
-          if (tid == 0) {
+          if (wave == route_first && lane == 0) {   // (by differences: another wave may already be at the next step's events)
 #pragma unroll
             for (int gi = 0; gi < 2; ++gi) {
               if (nG[gi] > 0) {
-                const int lmaxg = lminG[gi] + nG[gi] - 1;
-                for (int t = 0; t + 1 < nG[gi]; ++t) L.lh[gi * kLoadBins + lminG[gi] + t] = 0;
-                L.lh[gi * kLoadBins + lmaxg] = static_cast<uint32_t>(csumG[gi] - tlastG[gi]);
-                L.lh[gi * kLoadBins + lmaxg + 1] += static_cast<uint32_t>(tlastG[gi]);
+                uint32_t *h = &L.lh[gi * kLoadBins + lminG[gi]];
+                const int32_t *cnt = &L.sc[SC_CNT_T + (gi == 0 ? 0 : nG[0])];
+                for (int t = 0; t < nG[gi]; ++t)   // the last level keeps the servers that got no job in it
+                  atomicAdd(&h[t], static_cast<uint32_t>((t + 1 < nG[gi] ? 0 : csumG[gi] - tlastG[gi]) - cnt[t]));
+                atomicAdd(&h[nG[gi]], static_cast<uint32_t>(tlastG[gi]));
               }
             }
           }
-          jrem -= total;
-          next += total;
+          jrem -= placed;
+          next += placed;
           if constexpr (RR) {
-            jremL[0] -= takenL[0]; nextL[0] += takenL[0];
-            jremL[1] -= takenL[1]; nextL[1] += takenL[1];
+            jremL[0] -= placed_solo; nextL[0] += placed_solo;
+            jremL[1] -= placed - placed_solo; nextL[1] += placed - placed_solo;
           }
           route_on = jrem > 0;
+        } else if (!(levels & 0x10000)) {
+          route_on = false;   // every slot is taken
         }
         gate_on = gate_more;
-        __syncthreads();
-        // every wave settles the touched servers among its own
-        {
-          const bool last = !gate_on && !route_on;
-          int nset = 0, w_from = wave, w_next = wave;   // (64 of the wave's words a round, one a lane)
-          uint64_t touch_lane = 0, todo = 0;
-          for (bool more = wave < nwords; more;) {   // wave-uniform
-            if (todo == 0) {
-              const int w_lane = w_next + lane * nwaves;
-              touch_lane = w_lane < nwords ? L.bm_touch[w_lane] : 0ull;
-              todo = __ballot(touch_lane != 0);
-              w_from = w_next;
-              w_next += 64 * nwaves;
-            }
-            if (todo) {
-              const int src = __ffsll(static_cast<long long>(todo)) - 1;
-              const uint64_t tm = readlane64(touch_lane, src);
-              todo &= todo - 1ull;
-              if (lane_in(tm)) ev_g[nset + rank_in(tm)] = static_cast<uint16_t>(((w_from + src * nwaves) << 6) + lane);
-              nset += __popcll(tm);
-            }
-            more = todo != 0 || w_next < nwords;
-            if (nset > kEvPerWave - 64 || !more) { settle(nset, last); nset = 0; }
-          }
-        }
+        if (work > 0 || gate_on || route_on) __syncthreads();   // (the same for every thread)
       }
       if constexpr (AB) {
         if (tid == 0) {   // the head moves past everything the routing passes walked over
@@ -2441,12 +2470,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     uint64_t comp = 0;
     if (busy) {
       comp = rec[g].n_cls - rec[g].n_join;
-      chunk = L.bm_chunk[blk] & bit;
+      chunk = L.ev_it[g] & kEvChunk;
       const int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0, ptok = chunk ? chunk_of(rem) : 0;
       const uint32_t dur = iteration_ns(ptok, byte_sum(comp));
       const int64_t rel = event_time(g, T);
-      const uint32_t left = (L.bm_pin[blk] & bit) ? 1u : iterations_left(static_cast<uint64_t>(rel), dur);
-      const uint32_t it = L.ev_it[g] - left;
+      const uint32_t left = joins_next(rec[g].n_join, rem, chunk) ? 1u : iterations_left(static_cast<uint64_t>(rel), dur);
+      const uint32_t it = (L.ev_it[g] & kEvIter) - left;
       m = it - rec[g].iter;
       d = dur;
       tr = static_cast<uint32_t>(rel - static_cast<int64_t>(static_cast<uint64_t>(left - 1u) * dur));
@@ -2487,7 +2516,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         const uint64_t jw = rec[g].pf_job;
         const uint32_t Pl = (static_cast<uint32_t>(jw >> 32) & 0xFFFFu) + 1, k = static_cast<uint32_t>(jw >> 29) & 7u;
         atomicAdd(&L.acc[k], Pl - rem);
-        const bool chunk = (L.bm_chunk[g >> 6] >> (g & 63)) & 1ull;
+        const bool chunk = L.ev_it[g] & kEvChunk;
         const uint32_t cmax = static_cast<uint32_t>(p.C);
         pk = rem | ((chunk ? (rem < cmax ? rem : cmax) : 0u) << 16) | (k << 29);
       }
