@@ -194,8 +194,6 @@ enum Scalar {
   SC_DSCAN = 11,  // entries of that ring the routing passes of this step have gone past
   SC_COMPACT = 12,// bit k: class queue ring k (bit 8: the decode buffer ring) must be compacted before the appends
   // randomized router only:
-  SC_NCS = 13,    // completed prefills of this step that joined the solo group's buffer
-  SC_NCM = 14,    // ... the mixed group's buffer
   SC_DLEN_M = 15, // randomized router with abandonment: SC_DLEN / SC_DSCAN of the mixed group's buffer ring
   SC_DSCAN_M = 60,
   SC_NADM = 61,   // admissions of the pass (bit 16: another gate pass follows)
@@ -242,6 +240,7 @@ struct Lds {
   uint64_t *bm_busy;  // [nwords] servers running an iteration
   uint64_t *bm_due;   // [nwords] servers that had their event in this step (and busy ones whose event is next)
   uint64_t *jobs;     // [kJobsLds] the first requests a routing pass places, copied from the decode buffer
+  uint64_t *fresh;    // [kJobsLds] abandonment, more than one wave: this step's first completed prefills (two buffers: half each)
   uint64_t *bm_lvl;   // [kRouteLevels][nwords] routing pass: servers of the routed group with at most (level) decodes
   uint16_t *pre_lvl;  // [kRouteLevels][nwords] exclusive prefix popcounts of bm_lvl, per level
   uint16_t *pre_c;    // [nwords] exclusive prefix popcounts of bm_comp; in the space of pre_lvl
@@ -311,6 +310,7 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(pre_lvl, uint16_t, kRouteLevels * nw)
   L.pre_c = L.pre_lvl;
   GNR_TAKE(pre, uint16_t, nw)
+  GNR_TAKE(fresh, uint64_t, p.dl_rings && waves > 1 ? kJobsLds : 0)
   GNR_TAKE(ta, uint64_t, (TA_TBT + (NWS ? kMaxK : p.K)) * (SMALL ? kTallyRowsSmall : kTallyRows))
   // What is refused for want of room, and how many workgroups share a compute unit, follows from the total. Both were set
   // and measured with the tables of a kernel that executed every iteration (two words and a row list per queued server,
@@ -501,10 +501,11 @@ __device__ __forceinline__ ClassTargets load_targets(const double *tab, int k)
   return t;
 }
 // Key of the m-th waiting request of class k, of which X_k = xs_k are in prefill and Q_p,k = qp_k wait; head_k: ring
-// position of the class queue's head.
+// position of the class queue's head, fresh_k: entries from there on that are of steps before `now` (the others are this
+// step's arrivals, which another wave may be writing).
 __device__ __forceinline__ GateKey gate_key(const int gate_mode, const uint32_t queue_cap, const ClassTargets &t,
                                             const uint32_t *qring, const uint32_t *live_off, int xs_k, int qp_k,
-                                            uint32_t head_k, int k, int m, int adm_chunk)
+                                            uint32_t head_k, uint32_t fresh_k, uint32_t now, int k, int m, int adm_chunk)
 {
   GateKey key;
   if (gate_mode == SIM_GATE_OCCUPANCY) {
@@ -514,9 +515,10 @@ __device__ __forceinline__ GateKey gate_key(const int gate_mode, const uint32_t 
     key.a = -t.prio;
     key.b = 0.0;
   } else {
-    uint32_t pos = head_k + (live_off ? live_off[k * adm_chunk + m] : static_cast<uint32_t>(m));
+    const uint32_t off = live_off ? live_off[k * adm_chunk + m] : static_cast<uint32_t>(m);
+    uint32_t pos = head_k + off;
     if (pos >= queue_cap) pos -= queue_cap;
-    key.a = static_cast<double>(qring[static_cast<size_t>(k) * queue_cap + pos]);
+    key.a = static_cast<double>(off < fresh_k ? qring[static_cast<size_t>(k) * queue_cap + pos] : now);
     key.b = 0.0;
   }
   return key;
@@ -600,12 +602,14 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   const int wave_base = wave << 6;
   // The instruction arbiter of a SIMD prefers its oldest wave: left alone, the first four waves of the workgroup
   // finish every sweep early and the last four late, and the barrier waits for those. Raising the priority of the
-  // younger waves evens this out.
-  if (nwaves > 4) {
+  // younger waves evens this out. (In workgroups of up to four waves, which share a SIMD with others, only the draw of
+  // the next step's arrivals has a lower priority than the rest: nobody waits for it as long as another wave serves.)
+  auto own_priority = [&]() __attribute__((always_inline)) {
     if (wave >= 12) __builtin_amdgcn_s_setprio(3);
     else if (wave >= 8) __builtin_amdgcn_s_setprio(2);
-    else if (wave >= 4) __builtin_amdgcn_s_setprio(1);
-  }
+    else if (wave >= 4 || nwaves <= 4) __builtin_amdgcn_s_setprio(1);
+  };
+  own_priority();
   const int K = p.K, N = p.N, B = p.B, M = p.M, BS = p.BS;
   const int nper = (N + NT - 1) / NT;
   const int nwords = p.nwords;
@@ -842,16 +846,25 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     const uint32_t c2_1 = pinned(static_cast<uint32_t>(ps >> 32) ^ static_cast<uint32_t>(r) ^ key1), c3_1 = static_cast<uint32_t>(ps);
     for (int b0 = first; b0 < nwords; b0 += 64 * stride) {   // wave-uniform; 64 words a round, one a lane
       uint64_t hits = 0;
-      int j = 0;
-      for (int blk = b0; j < 64 && blk < nwords; blk += stride, ++j) {   // wave-uniform
+      auto first_word = [&](int blk, uint32_t k0, uint32_t k1) __attribute__((always_inline)) -> uint64_t {   // servers with requests
+        const uint64_t pg = static_cast<uint64_t>(0xCD9E8D57u) * static_cast<uint32_t>((blk << 6) + lane);
+        uint32_t w[4];
+        philox_rounds<2>(k0 + 0x9E3779B9u, k1 + 0xBB67AE85u, static_cast<uint32_t>(pg >> 32) ^ k0, static_cast<uint32_t>(pg), c2_1, c3_1, w);
+        return __ballot(w[0] >= thr0);
+      };
+      int j = 0, blk = b0;
+      for (; j < 64 && blk + stride < nwords; j += 2, blk += 2 * stride) {   // wave-uniform; two words with the same round keys
         // the round keys are formed anew with scalar additions: as loop invariants there are twenty of them, and they are
         // kept in lanes of vector registers, from which each costs two vector instructions a round
         uint32_t k0 = key0, k1 = key1;
         asm volatile("" : "+s"(k0), "+s"(k1));
-        const uint64_t pg = static_cast<uint64_t>(0xCD9E8D57u) * static_cast<uint32_t>((blk << 6) + lane);
-        uint32_t w[4];
-        philox_rounds<2>(k0 + 0x9E3779B9u, k1 + 0xBB67AE85u, static_cast<uint32_t>(pg >> 32) ^ k0, static_cast<uint32_t>(pg), c2_1, c3_1, w);
-        hits = writelane64(hits, __ballot(w[0] >= thr0), j);
+        const uint64_t hit0 = first_word(blk, k0, k1), hit1 = first_word(blk + stride, k0, k1);
+        hits = writelane64(writelane64(hits, hit0, j), hit1, j + 1);
+      }
+      if (j < 64 && blk < nwords) {
+        uint32_t k0 = key0, k1 = key1;
+        asm volatile("" : "+s"(k0), "+s"(k1));
+        hits = writelane64(hits, first_word(blk, k0, k1), j);
       }
       const int word = b0 + lane * stride;
       hits &= bits_below(word, N);   // (of a lane without a word it is empty)
@@ -1149,33 +1162,41 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     drawn = false;
     {
       const uint32_t T_hi = static_cast<uint32_t>(T >> 8);
-      int nev = 0;   // servers queued by this wave (wave-uniform)
-      int w_lane = 0, j = 0;   // the wave's words are wave, wave + nwaves, ...: 64 of them a round, one a lane
-      uint64_t busy_lane = 0, due_lane = 0;
-      for (int blk = wave; blk < nwords; blk += nwaves) {   // wave-uniform
-        const int g = (blk << 6) + lane;
-        const bool last = blk + nwaves >= nwords;
-        if (j == 0) {
-          w_lane = blk + lane * nwaves;
-          busy_lane = due_lane = 0;
-          if (w_lane < nwords) {
-            busy_lane = L.bm_busy[w_lane];
-            if (slots_taken) L.bm_idle[w_lane] &= ~L.bm_comp[w_lane];
-            L.bm_comp[w_lane] = 0;
-          }
+      for (int b0 = wave; b0 < nwords; b0 += 64 * nwaves) {   // wave-uniform; the wave's words, 64 a round, one a lane
+        const int w_lane = b0 + lane * nwaves;
+        uint64_t due = 0;
+        // (lanes past the last server are not busy; a clock a few ns ahead may pass here for its upper bits: the servers
+        // queued are looked at exactly)
+        auto clock_of = [&](int j) __attribute__((always_inline)) {
+          const int g = ((b0 + j * nwaves) << 6) + lane;
+          return L.ev_t[g < N ? g : N - 1];
+        };
+        int j = 0;
+        for (; j < 64 && b0 + (j + 3) * nwaves < nwords; j += 4) {   // wave-uniform
+          uint32_t ev[4];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) ev[u] = clock_of(j + u);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) due = writelane64(due, __ballot(static_cast<int32_t>(ev[u] - T_hi) <= 0), j + u);
         }
-        // (a clock a few ns ahead may pass here for its upper bits: the servers queued are looked at exactly)
-        const uint64_t dm = readlane64(busy_lane, j) & __ballot(static_cast<int32_t>(L.ev_t[g < N ? g : N - 1] - T_hi) <= 0);
-        if (dm) {
-          if (lane_in(dm)) ev_g[nev + rank_in(dm)] = static_cast<uint16_t>(g);
+        for (; j < 64 && b0 + j * nwaves < nwords; ++j) due = writelane64(due, __ballot(static_cast<int32_t>(clock_of(j) - T_hi) <= 0), j);
+        if (w_lane < nwords) {
+          due &= L.bm_busy[w_lane];
+          L.bm_due[w_lane] = due;
+          if (slots_taken) L.bm_idle[w_lane] &= ~L.bm_comp[w_lane];
+          L.bm_comp[w_lane] = 0;
+        } else {
+          due = 0;
+        }
+        int nev = 0;   // servers queued by this wave (wave-uniform)
+        for (uint64_t todo = __ballot(due != 0); todo;) {
+          const int src = __ffsll(static_cast<long long>(todo)) - 1;
+          const uint64_t dm = readlane64(due, src);
+          todo &= todo - 1ull;
+          if (lane_in(dm)) ev_g[nev + rank_in(dm)] = static_cast<uint16_t>(((b0 + src * nwaves) << 6) + lane);
           nev += __popcll(dm);
-          due_lane = writelane64(due_lane, dm, j);
+          if (nev > kEvPerWave - 64 || !todo) { drain_events(nev); nev = 0; }
         }
-        if (++j == 64 || last) {   // the round's last word
-          if (w_lane < nwords) L.bm_due[w_lane] = due_lane;
-          j = 0;
-        }
-        if (nev > kEvPerWave - 64 || last) { drain_events(nev); nev = 0; }
       }
       slots_taken = false;
     }
@@ -1354,6 +1375,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       }
     }
     // completed prefills join the decode buffer in ascending server order
+    int ncs = 0, ncm = 0;   // two buffers: how many joined the solo and the mixed group's
     if constexpr (RR) {
       const uint32_t ncomp = static_cast<uint32_t>(L.sc[SC_NCOMP]);
       const uint32_t dc0 = static_cast<uint32_t>(L.cs[CS_DCOUNT]), dc1 = static_cast<uint32_t>(L.cs[CS_DCOUNT_M]);
@@ -1387,7 +1409,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             uint32_t pos = (solo ? dh0 + fill0 : dh1 + fill1) + idx;
             if (pos >= dbuf_cap) pos -= dbuf_cap;
             (solo ? dring : dring_m)[pos] = c_jw;
-            if (!AB && idx < kJobsLds / 2) L.jobs[(solo ? 0u : kJobsLds / 2) + idx] = c_jw;
+            if (idx < kJobsLds / 2) {
+              if constexpr (!AB) L.jobs[(solo ? 0u : kJobsLds / 2) + idx] = c_jw;
+              else if (!WS && nwaves > 1) L.fresh[(solo ? 0u : kJobsLds / 2) + idx] = c_jw;
+            }
             if constexpr (AB) {
               (solo ? ddl : ddl_m)[pos] = c_dl;
               if (c_dl != kNever) atomicAdd(&(solo ? dcal : dcal_m)[static_cast<size_t>(k) * cal_n + (c_dl & p.cal_mask)], 1u);
@@ -1405,12 +1430,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         seen0 += solo_round;
         seen1 += in_round - solo_round;
       }
-      if (tid == 0) {   // what each ring accepted (a prefix of what it was sent)
-        const uint32_t room0 = dbuf_cap - dc0, room1 = dbuf_cap - dc1;
-        L.sc[SC_NCS] = static_cast<int32_t>(seen0 < room0 ? seen0 : room0);
-        L.sc[SC_NCM] = static_cast<int32_t>(seen1 < room1 ? seen1 : room1);
-      }
-      __syncthreads();
+      // what each ring accepted (a prefix of what it was sent)
+      const uint32_t room0 = dbuf_cap - dc0, room1 = dbuf_cap - dc1;
+      ncs = uniform(static_cast<int>(seen0 < room0 ? seen0 : room0));
+      ncm = uniform(static_cast<int>(seen1 < room1 ? seen1 : room1));
     } else {
       const uint32_t ncomp = static_cast<uint32_t>(L.sc[SC_NCOMP]);
       const uint32_t dcount = static_cast<uint32_t>(L.cs[CS_DCOUNT]), dhead = static_cast<uint32_t>(L.cs[CS_DHEAD]);
@@ -1431,7 +1454,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             uint32_t pos = dhead + dfill + j;
             if (pos >= dbuf_cap) pos -= dbuf_cap;
             dring[pos] = jw;
-            if (!AB && j < kJobsLds) L.jobs[j] = jw;
+            if (j < kJobsLds) {
+              if constexpr (!AB) L.jobs[j] = jw;
+              else if (nwaves > 1) L.fresh[j] = jw;
+            }
             if constexpr (AB) {   // patience for the wait in the decode buffer
               uint32_t dl = kNever;
               if ((p.ab_classes >> k) & 1u) {
@@ -1483,21 +1509,15 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       int jremL[2] = {0, 0}, nextL[2] = {0, 0}, takenL[2] = {0, 0};
       const uint32_t dheadL[2] = {dhead0, RR ? static_cast<uint32_t>(L.cs[CS_DHEAD_M]) : 0u};
       if constexpr (RR) {
-        jremL[0] = dcount0 + L.sc[SC_NCS];
-        jremL[1] = dcount0_m + L.sc[SC_NCM];
+        jremL[0] = dcount0 + ncs;
+        jremL[1] = dcount0_m + ncm;
         jrem = jremL[0] + jremL[1];
       }
       // abandonment only: ring entries of the decode buffer, this step's completions included
-      uint32_t dlen_all = AB ? static_cast<uint32_t>(L.sc[SC_DLEN]) + static_cast<uint32_t>(RR ? L.sc[SC_NCS] : jrem - dcount0) : 0u;
+      uint32_t dlen_all = AB ? static_cast<uint32_t>(L.sc[SC_DLEN]) + static_cast<uint32_t>(RR ? ncs : jrem - dcount0) : 0u;
       if (dlen_all > dbuf_cap) dlen_all = dbuf_cap;   // (never more: the ring was compacted if it had to be)
-      uint32_t dlen_all_m = AB && RR ? static_cast<uint32_t>(L.sc[SC_DLEN_M]) + static_cast<uint32_t>(L.sc[SC_NCM]) : 0u;
+      uint32_t dlen_all_m = AB && RR ? static_cast<uint32_t>(L.sc[SC_DLEN_M]) + static_cast<uint32_t>(ncm) : 0u;
       if (dlen_all_m > dbuf_cap) dlen_all_m = dbuf_cap;
-      if constexpr (AB) {
-        if (tid == 0) {
-          L.sc[SC_DSCAN] = 0;
-          if constexpr (RR) L.sc[SC_DSCAN_M] = 0;
-        }
-      }
       bool gate_on = true, route_on = jrem > 0;
       for (int pass = 0; gate_on || route_on; ++pass) {
         if (slots_taken) {   // (in a pass after the first)
@@ -1513,7 +1533,9 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           }
           __syncthreads();
         }
-        if ((AB || gate_mode == SIM_GATE_FCFS) && pass == 0) __syncthreads();   // ring entries written above are read below
+        if constexpr (WS) {
+          if (pass == 0) __syncthreads();   // the class selection reads buffer entries and counts written above
+        }
         // With abandonment the requests a routing pass places are first staged in LDS, by the waves that own the decode
         // buffers (each buffer has a wave of its own, on different SIMDs).
         const int ring_wave = nwaves >= 8 ? route_first : nwaves - 1;
@@ -1521,9 +1543,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         // the weighted router's selection is long: it runs in segment A beside the gate's ranking, on waves that are
         // given nothing else to do there; the plain walk of a ring runs in segment B
         // one wave walks a ring from where the last pass stopped and stages the next `need` waiting jobs
+        // (in the first pass this step's completions may not have reached the ring: they are taken from `fresh`)
+        const bool fresh_kept = AB && !WS && nwaves > 1 && pass == 0;
         auto stage_ring = [&](const uint64_t *ring, const uint32_t *dlr, uint32_t *calr, uint32_t hd, uint32_t len,
                               int scan_word, uint32_t need, int first_job) __attribute__((always_inline)) {
-          uint32_t off = static_cast<uint32_t>(L.sc[scan_word]), found = 0, stop = off;
+          uint32_t off = static_cast<uint32_t>(L.sc[scan_word]), found = 0, stop = off;   // (0 when a step begins)
           // four chunks of 64 entries per round: deadlines and requests are loaded together
           for (; off < len && found < need; off += 256) {   // wave-uniform
             uint32_t dl4[4];
@@ -1553,7 +1577,9 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               found += static_cast<uint32_t>(__popcll(bal));
             }
           }
-          if (lane == 0) L.sc[scan_word] = static_cast<int32_t>(found >= need ? stop : len);   // (found < need: see the gate's scan)
+          // (what was not found among the entries of the steps before is the first of this step's completions, which follow
+          // them; else see the gate's scan)
+          if (lane == 0) L.sc[scan_word] = static_cast<int32_t>(found >= need ? stop : fresh_kept ? len + (need - found) : len);
         };
         // Weighted router: the pass's `need` placements in a pool each draw a class among those that still
         // wait in the pool's buffer (one after the other: a class that runs out drops from the later draws) and
@@ -1746,7 +1772,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 }
               } else {
                 if (takenL[0] > 0)
-                  stage_ring(dring, ddl, dcal, dheadL[0], dlen_all, SC_DSCAN, static_cast<uint32_t>(takenL[0]), 0);
+                  stage_ring(dring, ddl, dcal, dheadL[0], fresh_kept ? dlen_all - static_cast<uint32_t>(ncs) : dlen_all, SC_DSCAN, static_cast<uint32_t>(takenL[0]), 0);
               }
             }
             if (wave == ring_wave_m && takenL[1] > 0) {
@@ -1754,11 +1780,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 int nsel_m[kMaxK];
                 select_and_stage(1, dring_m, ddl_m, dcal_m, dheadL[1], dlen_all_m, SC_DSCAN_M, takenL[1], takenL[0], nextL[1], nsel_m);
               } else {
-                stage_ring(dring_m, ddl_m, dcal_m, dheadL[1], dlen_all_m, SC_DSCAN_M, static_cast<uint32_t>(takenL[1]), takenL[0]);
+                stage_ring(dring_m, ddl_m, dcal_m, dheadL[1], fresh_kept ? dlen_all_m - static_cast<uint32_t>(ncm) : dlen_all_m, SC_DSCAN_M, static_cast<uint32_t>(takenL[1]), takenL[0]);
               }
             }
           } else {
-            if (wave == ring_wave) stage_ring(dring, ddl, dcal, dhead0, dlen_all, SC_DSCAN, static_cast<uint32_t>(total_pass), 0);
+            if (wave == ring_wave)
+              stage_ring(dring, ddl, dcal, dhead0, fresh_kept ? dlen_all - static_cast<uint32_t>(jrem - dcount0) : dlen_all, SC_DSCAN, static_cast<uint32_t>(total_pass), 0);
           }
         };
 
@@ -1774,6 +1801,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           const ClassTargets t2 = load_targets(L.gtab, k2);
           const int xs2 = L.cs[CS_X + k2], qp2 = L.cs[CS_QP + k2];
           const uint32_t head2 = static_cast<uint32_t>(L.cs[CS_QHEAD + k2]);
+          auto fresh_of = [&](int k) __attribute__((always_inline)) -> uint32_t {   // (a later pass comes after a barrier)
+            return pass > 0 ? 0xFFFFFFFFu : static_cast<uint32_t>((AB ? L.sc[SC_QLEN + k] : L.cs[CS_QP + k]) - L.sc[SC_TAKE + k]);
+          };
+          const uint32_t fresh2 = gate_mode == SIM_GATE_FCFS ? fresh_of(k2) : 0u;
           int cnt2 = ((admissible >> k2) & 1ull) && qp2 > 0 ? (qp2 < limit ? qp2 : limit) : 0;
           int ncand = __builtin_amdgcn_readfirstlane(static_cast<int>(group_sum(static_cast<uint32_t>(cnt2), lg)));
           const int nadm = ncand < limit ? ncand : limit;
@@ -1822,6 +1853,9 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               const uint32_t need = static_cast<uint32_t>(__builtin_amdgcn_readlane(cnt2, k));
               uint32_t qlen = static_cast<uint32_t>(L.sc[SC_QLEN + k]);
               if (qlen > queue_cap) qlen = queue_cap;
+              // (in the first pass this step's arrivals may not have reached the ring: they wait behind the others, all of them)
+              const uint32_t arrived = pass > 0 ? 0u : static_cast<uint32_t>(L.sc[SC_TAKE + k]);
+              qlen -= arrived < qlen ? arrived : qlen;
               const uint32_t hd = static_cast<uint32_t>(L.cs[CS_QHEAD + k]);
               const uint32_t *dlr = qdl + static_cast<size_t>(k) * queue_cap;
               uint32_t found = 0;
@@ -1845,9 +1879,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                   found += static_cast<uint32_t>(__popcll(bal));
                 }
               }
-              // (the ring holds as many live entries as the class counter says; if it ever did not, the
+              // (ring and arrivals hold as many live entries as the class counter says; if they ever did not, the
               // candidates beyond them would point at the head entry)
-              for (uint32_t rk = found + lane; rk < need; rk += 64) L.live_off[k * kAdmChunk + rk] = 0;
+              for (uint32_t rk = found + lane; rk < need; rk += 64)
+                L.live_off[k * kAdmChunk + rk] = rk - found < arrived ? qlen + (rk - found) : 0u;
               if (lane == 0 && need == 0) L.live_off[k * kAdmChunk] = 0;   // (no candidate: the head stays)
             }
             // only the FCFS gate reads the offsets while it ranks the candidates; the other gates first use them
@@ -1878,9 +1913,9 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 // this candidate's own key: one trip to LDS
                 const ClassTargets own = load_targets(L.gtab, k);
                 const GateKey key = gate_key(gate_mode, queue_cap, own, qring, lo_tab, L.cs[CS_X + k], L.cs[CS_QP + k],
-                                             static_cast<uint32_t>(L.cs[CS_QHEAD + k]), k, m, kAdmChunk);
+                                             static_cast<uint32_t>(L.cs[CS_QHEAD + k]), fresh_of(k), s, k, m, kAdmChunk);
                 auto before = [&](int j) __attribute__((always_inline)) -> bool {   // is the j-th of class k2 admitted before it
-                  return gate_before(gate_key(gate_mode, queue_cap, t2, qring, lo_tab, xs2, qp2, head2, k2, j, kAdmChunk), k2, key, k);
+                  return gate_before(gate_key(gate_mode, queue_cap, t2, qring, lo_tab, xs2, qp2, head2, fresh2, s, k2, j, kAdmChunk), k2, key, k);
                 };
                 int hi = cnt2;
                 if (gate_mode == SIM_GATE_OCCUPANCY) {
@@ -2030,32 +2065,34 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               }
             }
             // Four words per round: their decode counts are read together, and a level's members in a word are one
-            // comparison over the wave; lane 4 u + t stores those of level t in the round's word u.
-            for (int w0 = cw; w0 < nwords; w0 += 4 * cn) {   // wave-uniform
+            // comparison over the wave; lane 4 u + t stores those of level t in the round's word u. The words of a group that
+            // no level is of are left out.
+            const int w_end = nG[0] > 0 ? nwords : ((M + 63) >> 6);
+            for (int w0 = (nG[1] > 0 ? 0 : M >> 6) + cw; w0 < w_end; w0 += 4 * cn) {   // wave-uniform
               int ld[4];
 #pragma unroll
               for (int u = 0; u < 4; ++u) {
-                const int wi = w0 + u * cn, g = (wi << 6) + lane;
-                ld[u] = wi < nwords && g < N ? static_cast<int>(L.loads[g]) : 255;   // (255: in no level)
+                const int g = ((w0 + u * cn) << 6) + lane;
+                ld[u] = static_cast<int>(L.loads[g < N ? g : N - 1]);
               }
               uint64_t members = 0;
 #pragma unroll
               for (int u = 0; u < 4; ++u) {
-                if (w0 + u * cn < nwords) {   // wave-uniform
-                  const uint64_t mixed = bits_below(w0 + u * cn, M);
+                if (w0 + u * cn < w_end) {   // wave-uniform
+                  const int g = ((w0 + u * cn) << 6) + lane;
+                  const uint64_t mixed = __ballot(g < M), solo = ~mixed & __ballot(g < N);
 #pragma unroll
                   for (int t = 0; t < kRouteLevels; ++t) {
                     if (t < nl) {   // wave-uniform
-                      const bool solo = t < nG[0];
-                      const int most = solo ? lminG[0] + t : lminG[1] + (t - nG[0]);
-                      const uint64_t in = __ballot(ld[u] <= most) & (solo ? ~mixed : mixed);
-                      members = writelane64(members, in, 4 * u + t);
+                      const bool of_solo = t < nG[0];
+                      const int most = of_solo ? lminG[0] + t : lminG[1] + (t - nG[0]);
+                      members = writelane64(members, __ballot(ld[u] <= most) & (of_solo ? solo : mixed), 4 * u + t);
                     }
                   }
                 }
               }
               const int t = lane & 3, wi = w0 + (lane >> 2) * cn;
-              if (lane < 16 && t < nl && wi < nwords) L.bm_lvl[t * nwords + wi] = members;
+              if (lane < 16 && t < nl && wi < w_end) L.bm_lvl[t * nwords + wi] = members;
             }
           }
         }
@@ -2115,8 +2152,13 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         const int n_serve = work <= 64 ? 1 : (work + 63) >> 6 < nwaves ? (work + 63) >> 6 : nwaves;
         if (work > 0 && wave < nwaves - n_serve) {
           // (left to the next completion pass, where all waves take part, if these would get more than sixteen words each)
-          if (!drawn && s + 1u < step_end && 16 * (nwaves - n_serve) >= nwords) draw_arrivals(s + 1u, wave, nwaves - n_serve);
+          if (!drawn && s + 1u < step_end && 16 * (nwaves - n_serve) >= nwords) {
+            __builtin_amdgcn_s_setprio(0);
+            draw_arrivals(s + 1u, wave, nwaves - n_serve);
+            own_priority();
+          }
         } else if (work > 0) {
+          const int lvl_first = nl_here > nl_solo ? 0 : M >> 6, lvl_end = nl_solo > 0 ? nwords : (M + 63) >> 6;   // words with levels
           // Everything a step gives a server, and what follows from it, in one go: its admission, its jobs, and either the next
           // event (the server is idle or at an iteration boundary) or the end of the running iteration as its event.
           auto serve = [&](int nsrv) __attribute__((always_inline)) {   // (up to 64)
@@ -2210,13 +2252,34 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
 #pragma unroll
                 for (int t = 0; t < kRouteLevels; ++t) {
                   if (t < nl_here) {   // wave-uniform
-                    const uint64_t in = L.bm_lvl[t * nwords + wi];
+                    const uint64_t in = wi >= lvl_first && wi < lvl_end ? L.bm_lvl[t * nwords + wi] : 0ull;
                     const int q = static_cast<int>(L.pre_lvl[t * nwords + wi]) + __popcll(in & (bit - 1ull));
                     if ((in & bit) && q < take_r[t]) {
                       const int j = w_r[t] + q;   // position in this pass
                       uint64_t jw;
                       if constexpr (AB) {
                         jw = L.jobs[j];
+                        if (fresh_kept) {
+                          const int i = RR && gi ? j - placed_solo : j;   // place in the group's buffer, live requests only
+                          const int ci = i - (RR && gi ? dcount0_m : dcount0);
+                          if (ci >= 0) {   // one of this step's completions: it leaves the calendar of its deadline
+                            const uint32_t fill = RR && gi ? dlen_all_m - static_cast<uint32_t>(ncm) : dlen_all - static_cast<uint32_t>(RR ? ncs : jrem - dcount0);
+                            uint32_t pos = (RR ? dheadL[gi] : dhead0) + fill + static_cast<uint32_t>(ci);
+                            if (pos >= dbuf_cap) pos -= dbuf_cap;
+                            if (pos >= dbuf_cap) pos -= dbuf_cap;
+                            constexpr int kHere = RR ? kJobsLds / 2 : kJobsLds;
+                            jw = L.fresh[(RR && gi ? kHere : 0) + (ci < kHere ? ci : 0)];
+                            asm("" : "+v"(jw));   // (see below)
+                            if (ci >= kHere) { if (!RR || gi == 0) jw = dring[pos]; else jw = dring_m[pos]; }
+                            uint32_t dl;
+                            if (!RR || gi == 0) dl = ddl[pos]; else dl = ddl_m[pos];
+                            if (dl != kNever) {
+                              uint32_t *at = &dcal[((jw >> 29) & 7u) * static_cast<size_t>(cal_n) + (dl & p.cal_mask)];
+                              if constexpr (RR) { if (gi) at = &dcal_m[((jw >> 29) & 7u) * static_cast<size_t>(cal_n) + (dl & p.cal_mask)]; }
+                              atomicSub(at, 1u);
+                            }
+                          }
+                        }
                       } else {   // this step's completions are in LDS too, behind them what has waited in the ring
                         const int i = RR ? (gi == 0 ? nextL[0] + j : nextL[1] + j - placed_solo) : next + j;
                         const int ci = i - (RR && gi ? dcount0_m : dcount0);
@@ -2304,7 +2367,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 const int w = lane * n_words + i;
 #pragma unroll
                 for (int u = 0; u < 2; ++u) {
-                  in[u][i] = i < n_words && t0 + u < nl_here && w < nwords ? L.bm_lvl[(t0 + u) * nwords + w] : 0ull;
+                  in[u][i] = i < n_words && t0 + u < nl_here && w >= lvl_first && w < lvl_end ? L.bm_lvl[(t0 + u) * nwords + w] : 0ull;
                   n += static_cast<uint32_t>(__popcll(in[u][i])) << (16 * u);
                 }
               }
@@ -2410,6 +2473,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       if constexpr (AB) {
         if (tid == 0) {   // the head moves past everything the routing passes walked over
           const uint32_t past = static_cast<uint32_t>(L.sc[SC_DSCAN]);
+          L.sc[SC_DSCAN] = 0;
           uint32_t h = dhead0 + past;
           if (h >= dbuf_cap) h -= dbuf_cap;
           L.cs[CS_DHEAD] = static_cast<int32_t>(h);
@@ -2417,6 +2481,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           L.sc[SC_DLEN] = static_cast<int32_t>(dlen_all - past);
           if constexpr (RR) {
             const uint32_t past_m = static_cast<uint32_t>(L.sc[SC_DSCAN_M]);
+            L.sc[SC_DSCAN_M] = 0;
             h = dheadL[1] + past_m;
             if (h >= dbuf_cap) h -= dbuf_cap;
             L.cs[CS_DHEAD_M] = static_cast<int32_t>(h);
