@@ -197,7 +197,7 @@ enum Scalar {
   SC_DLEN_M = 15, // randomized router with abandonment: SC_DLEN / SC_DSCAN of the mixed group's buffer ring
   SC_DSCAN_M = 60,
   SC_NADM = 61,   // admissions of the pass (bit 16: another gate pass follows)
-  SC_LEVELS = 62, // the pass's routing levels: how many, of them the solo group's (8 bits each), bit 16: the mixed group has to wait
+  SC_LEVELS = 62, // the pass's routing levels: how many, of them the solo group's (8 bits each), bit 16: another pass follows
   SC_LMIN = 63,   // lowest level of the solo and (16 bits up) of the mixed group
   SC_QLEN = 32,   // [8] entries of each class queue ring between head and tail, abandoned ones included
   SC_TAKE = 16,   // [8] accepted arrivals this step
@@ -1995,6 +1995,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             const int hi = __builtin_amdgcn_readlane(static_cast<int>(hv[gi][1]), level & 63);
             return static_cast<uint32_t>(level < 64 ? lo : hi);
           };
+          bool full[2] = {M >= N, M == 0};   // no slot of the group is left behind the pass (as far as it has looked)
           if constexpr (RR) {
             // each group takes jobs from its own ring; the pass's list holds the solo ring's jobs first and is
             // never longer than what is staged in LDS
@@ -2008,11 +2009,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               const int start_g = rem_g;
               if (glo >= ghi || nl >= kRouteLevels || rem_g <= 0 || (gi == 1 && gate_unfinished)) continue;   // wave-uniform
               const int lm = lowest_level(gi, capg);
-              if (lm < 0) continue;   // no free slot in this group
+              if (lm < 0) { full[gi] = true; continue; }
               lminG[gi] = lm;
               for (int u = 0; nl < kRouteLevels && rem_g > 0 && lm + u < capg; ++u) {
                 const int cnt = static_cast<int>(level_count(gi, lm + u));
-              csumG[gi] += cnt;
+                csumG[gi] += cnt;
                 const int tk = csumG[gi] < rem_g ? csumG[gi] : rem_g;
                 if (lane == 0) { L.sc[SC_TAKE_T + nl] = tk; L.sc[SC_CNT_T + nl] = cnt; L.sc[SC_W_T + nl] = listed + (start_g - rem_g); }
                 rem_g -= tk;
@@ -2020,6 +2021,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 ++nG[gi];
                 ++nl;
               }
+              full[gi] = rem_g > 0 && lm + nG[gi] >= capg;
               takenL[gi] = start_g - rem_g;
               listed += takenL[gi];
             }
@@ -2031,7 +2033,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             const int capg = gi == 0 ? B : B - 1;
             if (glo >= ghi || nl >= kRouteLevels || rem_jobs <= 0 || (gi == 1 && gate_unfinished)) continue;   // wave-uniform
             const int lm = lowest_level(gi, capg);
-            if (lm < 0) continue;   // no free slot in this group
+            if (lm < 0) { full[gi] = true; continue; }
             lminG[gi] = lm;
             for (int u = 0; nl < kRouteLevels && rem_jobs > 0 && lm + u < capg; ++u) {
               const int cnt = static_cast<int>(level_count(gi, lm + u));
@@ -2043,12 +2045,16 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               ++nG[gi];
               ++nl;
             }
+            full[gi] = rem_jobs > 0 && lm + nG[gi] >= capg;
           }
           }
           total = jpass - rem_jobs;
-          // (no level: every slot is taken, and the jobs stay in the buffer, or the mixed group is still to come)
+          // another pass follows if jobs and slots for them may be left (the levels of a pass, what it stages, or a mixed group
+          // that waits for the gate set its bounds)
+          const bool more = RR ? (jremL[0] > takenL[0] && !full[0]) || (jremL[1] > takenL[1] && !full[1])
+                               : jrem > total && !(full[0] && full[1]);
           if (lane == 0) {
-            L.sc[SC_LEVELS] = nl | (nG[0] << 8) | (gate_unfinished ? 0x10000 : 0);
+            L.sc[SC_LEVELS] = nl | (nG[0] << 8) | (more ? 0x10000 : 0);
             L.sc[SC_LMIN] = lminG[0] | (lminG[1] << 16);
           }
           if (nl > 0) {
@@ -2463,10 +2469,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             jremL[0] -= placed_solo; nextL[0] += placed_solo;
             jremL[1] -= placed - placed_solo; nextL[1] += placed - placed_solo;
           }
-          route_on = jrem > 0;
-        } else if (!(levels & 0x10000)) {
-          route_on = false;   // every slot is taken
         }
+        route_on = levels & 0x10000;
         gate_on = gate_more;
         if (work > 0 || gate_on || route_on) __syncthreads();   // (the same for every thread)
       }
