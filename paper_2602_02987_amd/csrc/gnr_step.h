@@ -299,13 +299,7 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(bm_busy, uint64_t, nw)
   GNR_TAKE(bm_due, uint64_t, nw)
   GNR_TAKE(bm_lvl, uint64_t, kRouteLevels * nw)
-  if (SMALL && waves == 1) {
-    // a wave alone has put the completed prefills into the buffer before it counts the levels of the first pass (with more
-    // waves one may still read them while another counts)
-    L.bm_comp = L.bm_lvl + (kRouteLevels - 1) * nw;
-  } else {
-    GNR_TAKE(bm_comp, uint64_t, nw)
-  }
+  GNR_TAKE(bm_comp, uint64_t, nw)
   // the ranks of a pass's levels are formed when those of the completions are no longer read (a barrier lies between)
   GNR_TAKE(pre_lvl, uint16_t, kRouteLevels * nw)
   L.pre_c = L.pre_lvl;
@@ -2151,19 +2145,27 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           }
         }
         // The servers that are given work: the admissions take the first nadm idle prefill slots, in every routing level the
-        // first take_r of its members get a job. The last waves, as many as it takes, each find all of these servers (a lane
-        // looks at one to three neighbouring words), queue 64 of them and serve those, one a lane. The other waves draw the
-        // next step's arrivals meanwhile.
+        // first take_r of its members get a job. The last waves find these servers (a lane looks at a word), queue 64 of them
+        // and serve those, one a lane; as long as no level is of the mixed group no server gets both, and admissions
+        // and jobs are served by waves of their own. The other waves draw the next step's arrivals meanwhile.
         const int work = nadm + placed;   // (servers, or more: one may get an admission and jobs)
-        const int n_serve = work <= 64 ? 1 : (work + 63) >> 6 < nwaves ? (work + 63) >> 6 : nwaves;
+        const int n_adm = (nadm + 63) >> 6, n_job = (placed + 63) >> 6, n_both = (work + 63) >> 6;
+        const bool apart = nadm > 0 && placed > 0 && nl_here == nl_solo && nwaves >= 4 && n_adm + n_job <= (nwaves >> 1);
+        const int n_serve = apart ? n_adm + n_job : n_both < nwaves ? n_both : nwaves;
+        const bool draws_here = work > 0 && !drawn && s + 1u < step_end && n_serve < nwaves && 16 * (nwaves - n_serve) >= nwords;
         if (work > 0 && wave < nwaves - n_serve) {
           // (left to the next completion pass, where all waves take part, if these would get more than sixteen words each)
-          if (!drawn && s + 1u < step_end && 16 * (nwaves - n_serve) >= nwords) {
+          if (draws_here) {
             __builtin_amdgcn_s_setprio(0);
             draw_arrivals(s + 1u, wave, nwaves - n_serve);
             own_priority();
           }
         } else if (work > 0) {
+          // this wave is the my_serve-th of n_serve_kind that serve its kind
+          const bool for_jobs = !apart || wave >= nwaves - n_job, for_adm = !apart || !for_jobs;
+          const int n_serve_kind = !apart ? n_serve : for_jobs ? n_job : n_adm;
+          const int my_serve = (apart && !for_jobs ? nwaves - n_job : nwaves) - 1 - wave;
+          const int nadm_here = for_adm ? nadm : 0, nl_mine = for_jobs ? nl_here : 0;
           const int lvl_first = nl_here > nl_solo ? 0 : M >> 6, lvl_end = nl_solo > 0 ? nwords : (M + 63) >> 6;   // words with levels
           // Everything a step gives a server, and what follows from it, in one go: its admission, its jobs, and either the next
           // event (the server is idle or at an iteration boundary) or the end of the running iteration as its event.
@@ -2257,7 +2259,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                 const int first = gi == 0 ? 0 : nl_solo, my_lmin = gi == 0 ? lmins & 0xFFFF : lmins >> 16;
 #pragma unroll
                 for (int t = 0; t < kRouteLevels; ++t) {
-                  if (t < nl_here) {   // wave-uniform
+                  if (t < nl_mine) {   // wave-uniform
                     const uint64_t in = wi >= lvl_first && wi < lvl_end ? L.bm_lvl[t * nwords + wi] : 0ull;
                     const int q = static_cast<int>(L.pre_lvl[t * nwords + wi]) + __popcll(in & (bit - 1ull));
                     if ((in & bit) && q < take_r[t]) {
@@ -2334,119 +2336,92 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               }
               tally_iterations<kTallyRowsHere>(L.ta, L.tbth, tbt_w, tbt_lo, K, m, d, chunk, comp);
           };
-          // Which servers: the members of every level before a lane's words are counted, two levels in one sum. The first
+          // Which servers: the members of every level before a lane's word are counted, two levels in one sum. The first
           // `left` members of a word: all of them, or (one word a level) some.
-          constexpr int kWords = MAXT > 512 ? (NWS + 63) / 64 : 2;   // words a lane may have to look at
-          const int n_words = (nwords + 63) >> 6;
           auto first_members = [&](uint64_t in, int left) __attribute__((always_inline)) -> uint64_t {
             const int c = __popcll(in);
             uint64_t out = left >= c ? in : 0ull;
-            for (uint64_t part = __ballot(left > 0 && left < c); part; part &= part - 1ull) {   // wave-uniform
+            const uint64_t part = __ballot(left > 0 && left < c);
+            if (part) {   // wave-uniform
               const int src = __ffsll(static_cast<long long>(part)) - 1;
               const uint64_t w = readlane64(in, src);
               out = writelane64(out, __ballot(lane_in(w) && rank_in(w) < __builtin_amdgcn_readlane(left, src)), src);
             }
             return out;
           };
-          uint64_t got[kWords], adm[kWords];
-#pragma unroll
-          for (int i = 0; i < kWords; ++i) {
-            got[i] = adm[i] = 0;
-            if (i < n_words && nadm > 0) {   // wave-uniform
-              const int w = lane * n_words + i;
-              uint64_t slots = 0;
-              int left = 0;
-              if (w < nwords_m) {
-                slots = L.bm_idle[w] & bits_below(w, M);   // the gate admits to the mixed group only
-                left = nadm - static_cast<int>(L.pre[w]);
-              }
-              got[i] = adm[i] = first_members(slots, left);
-            }
-          }
-#pragma unroll
-          for (int t0 = 0; t0 < kRouteLevels; t0 += 2) {
-            if (t0 < nl_here) {   // wave-uniform
-              uint64_t in[2][kWords];
-              uint32_t n = 0;
-#pragma unroll
-              for (int i = 0; i < kWords; ++i) {
-                const int w = lane * n_words + i;
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                  in[u][i] = i < n_words && t0 + u < nl_here && w >= lvl_first && w < lvl_end ? L.bm_lvl[(t0 + u) * nwords + w] : 0ull;
-                  n += static_cast<uint32_t>(__popcll(in[u][i])) << (16 * u);
+          int lo = my_serve << 6, n_all = 0;   // this wave's are lo, lo + 1, ... of n_all
+          do {   // (a second time round only where even all waves are too few)
+            uint32_t before[2] = {0, 0};   // members of the levels in the words before
+            n_all = 0;
+            for (int w0 = 0; w0 < nwords; w0 += 64) {   // wave-uniform
+              const int w = w0 + lane;
+              uint64_t adm = 0, got = 0;
+              if (nadm_here > 0 && w0 < nwords_m) {   // wave-uniform
+                uint64_t slots = 0;
+                int left = 0;
+                if (w < nwords_m) {
+                  slots = L.bm_idle[w] & bits_below(w, M);   // the gate admits to the mixed group only
+                  left = nadm_here - static_cast<int>(L.pre[w]);
                 }
+                adm = first_members(slots, left);
+                got = adm;
+                // (other waves may still look at bm_idle: the slots given away are taken out of it later)
+                if (my_serve == 0 && w < nwords_m) L.bm_comp[w] = adm;
               }
-              uint32_t rank = wave_incl_scan(n) - n;
 #pragma unroll
-              for (int i = 0; i < kWords; ++i) {
-                const int w = lane * n_words + i;
-                if (i < n_words) {   // wave-uniform
+              for (int t0 = 0; t0 < kRouteLevels; t0 += 2) {
+                if (t0 < nl_mine && w0 < lvl_end && w0 + 64 > lvl_first) {   // wave-uniform
+                  uint64_t in[2];
+                  uint32_t n = 0;
 #pragma unroll
                   for (int u = 0; u < 2; ++u) {
-                    if (t0 + u < nl_here) {   // wave-uniform
+                    in[u] = t0 + u < nl_mine && w >= lvl_first && w < lvl_end ? L.bm_lvl[(t0 + u) * nwords + w] : 0ull;
+                    n += static_cast<uint32_t>(__popcll(in[u])) << (16 * u);
+                  }
+                  const uint32_t upto = wave_incl_scan(n), rank = before[t0 / 2] + upto - n;
+                  before[t0 / 2] += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(upto), 63));
+#pragma unroll
+                  for (int u = 0; u < 2; ++u) {
+                    if (t0 + u < nl_mine) {   // wave-uniform
                       const uint32_t r_u = u ? rank >> 16 : rank & 0xFFFFu;
                       if (w < nwords) L.pre_lvl[(t0 + u) * nwords + w] = static_cast<uint16_t>(r_u);   // (the same from every wave that serves)
-                      got[i] |= first_members(in[u][i], take_r[t0 + u] - static_cast<int>(r_u));
-                      rank += static_cast<uint32_t>(__popcll(in[u][i])) << (16 * u);
+                      got |= first_members(in[u], take_r[t0 + u] - static_cast<int>(r_u));
                     }
                   }
                 }
               }
-            }
-          }
-          uint32_t n_lane = 0;   // servers of this lane's words, and of the lanes before
-#pragma unroll
-          for (int i = 0; i < kWords; ++i) n_lane += static_cast<uint32_t>(__popcll(got[i]));
-          const uint32_t n_upto = wave_incl_scan(n_lane);
-          const int n_all = __builtin_amdgcn_readlane(static_cast<int>(n_upto), 63);
-          // This wave's 64 of them are queued and served (a second time round only where even all waves were too few): a word with
-          // many by a lane per server, of the others every lane queues one server at a time.
-          for (int lo = (nwaves - 1 - wave) << 6; lo < n_all; lo += n_serve << 6) {   // wave-uniform
-            int at = static_cast<int>(n_upto - n_lane) - lo;   // place of this lane's next server
-#pragma unroll
-            for (int i = 0; i < kWords; ++i) {
-              if (i >= n_words) break;   // wave-uniform
-              const int w = lane * n_words + i, c = __popcll(got[i]);
+              // the servers' places among all; those of this wave are queued: a word with many by a lane per server, of the others
+              // every lane queues one server at a time
+              const int c = __popcll(got);
+              const uint32_t upto = wave_incl_scan(static_cast<uint32_t>(c));
+              const int at = n_all + static_cast<int>(upto) - c - lo;
+              n_all += __builtin_amdgcn_readlane(static_cast<int>(upto), 63);
               const bool here = c > 0 && at < 64 && at + c > 0;
-              uint64_t left = here && c <= 6 ? got[i] : 0ull;
+              uint64_t left = here && c <= 6 ? got : 0ull;
               for (uint64_t many = __ballot(here && c > 6); many; many &= many - 1ull) {
                 const int src = __ffsll(static_cast<long long>(many)) - 1;
-                const uint64_t g_w = readlane64(got[i], src), a_w = readlane64(adm[i], src);
+                const uint64_t g_w = readlane64(got, src), a_w = readlane64(adm, src);
                 const int to = __builtin_amdgcn_readlane(at, src) + rank_in(g_w);
                 if (lane_in(g_w) && to >= 0 && to < 64)
-                  ev_g[to] = static_cast<uint16_t>(((src * n_words + i) << 6) + lane + (lane_in(a_w) ? 0x8000 : 0));
+                  ev_g[to] = static_cast<uint16_t>(((w0 + src) << 6) + lane + (lane_in(a_w) ? 0x8000 : 0));
               }
               for (int to = at; __ballot(left != 0); ++to) {
                 if (left) {
                   const int b = __ffsll(static_cast<long long>(left)) - 1;
-                  if (to >= 0 && to < 64) ev_g[to] = static_cast<uint16_t>((w << 6) + b + ((adm[i] >> b) & 1ull ? 0x8000 : 0));
+                  if (to >= 0 && to < 64) ev_g[to] = static_cast<uint16_t>((w << 6) + b + ((adm >> b) & 1ull ? 0x8000 : 0));
                   left &= left - 1ull;
                 }
               }
-              at += c;
             }
-            serve(n_all - lo < 64 ? n_all - lo : 64);
-          }
-          // the slots that were given away: other waves that serve may still look at bm_idle, so the owners take them out later
-          if (wave == nwaves - 1) {
-#pragma unroll
-            for (int i = 0; i < kWords; ++i) {
-              const int w = lane * n_words + i;
-              if (i < n_words && w < nwords) {
-                if (nwaves > 1) L.bm_comp[w] = adm[i];
-                else if (adm[i]) L.bm_idle[w] &= ~adm[i];
-              }
-            }
-          }
+            if (n_all > lo) serve(n_all - lo < 64 ? n_all - lo : 64);
+            lo += n_serve_kind << 6;
+          } while (lo < n_all);
         }
-        if (work > 0) {
-          if (!drawn && s + 1u < step_end && n_serve < nwaves && 16 * (nwaves - n_serve) >= nwords) {
-            next_thresholds();
-            drawn = true;
-          }
-          if (nadm > 0 && nwaves > 1) slots_taken = true;
+        if (draws_here) {
+          next_thresholds();
+          drawn = true;
         }
+        if (nadm > 0) slots_taken = true;
         if (placed > 0) {
           if constexpr (WS) {   // what the pass took from the solo group's buffer, per class
             if (tid >= NT - 64 && lane < K) L.cs[CS_QDS + lane] -= L.sel_n[lane];
