@@ -461,6 +461,8 @@ __device__ __forceinline__ void tally_iterations(uint64_t *ta, uint64_t *tbth, i
   lds_add64(&kind[TA_ITERS * ROWS], m);
   lds_add64(&kind[TA_BUSY * ROWS], md);
   uint64_t *bin = tbth + (hbin32(d) - tbt_lo);
+  // (taken anew, else the comparisons below are kept in lanes of vector registers from one step to the next)
+  asm volatile("" : "+s"(K));
 #pragma unroll
   for (int k = 0; k < kMaxK; ++k) {
     if (k < K) {   // wave-uniform
@@ -963,8 +965,9 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         const bool queued = e0 + lane < nev;
         const int g = queued ? static_cast<int>(ev_g[e0 + lane]) : 0;
         const int wi = g >> 6;
-        const int64_t tn = T + event_time(g, T);   // exact completion time
-        const bool active = queued && tn <= T;
+        // exact completion time, relative to T: within a step of it
+        const int32_t rel = static_cast<int32_t>(((L.ev_t[g] - static_cast<uint32_t>(T >> 8)) << 8) + L.ev_lo[g] - (static_cast<uint32_t>(T) & 255u));
+        const bool active = queued && rel <= 0;
         const uint64_t bit = active ? 1ull << (g & 63) : 0ull;
         uint64_t nc = 0, nj = 0, pf = 0;
         uint32_t it_tal = 0, nf = 0;
@@ -993,12 +996,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             const int o_gn = __shfl(row_gn, row & 63, 64);
             const int o_g = o_gn & 0xFFFF, o_nd = row < nrows ? o_gn >> 16 : 0;
             const uint32_t o_it = static_cast<uint32_t>(__shfl(row_it, row & 63, 64));
-            const uint32_t *frow = fin + static_cast<size_t>(o_g) * BS;
+            const uint32_t *frow = fin + (static_cast<uint32_t>(o_g) * static_cast<uint32_t>(BS) + 4u * static_cast<uint32_t>(l8));
             uint4 v[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
               v[q] = make_uint4(0u, 0u, 0u, 0u);   // (0: an empty slot, never an iteration a decode ends in)
-              if (32 * q < BS && 4 * (l8 + 8 * q) < o_nd) v[q] = stream_load(frow + 4 * (l8 + 8 * q));
+              if (32 * q < BS && 4 * (l8 + 8 * q) < o_nd) v[q] = stream_load(frow + 32 * q);
             }
             int high = -1, count = 0;
             uint32_t least = 0xFFFFFFFFu;
@@ -1010,26 +1013,28 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               for (int w = 0; w < 4; ++w) {
                 const int j = 4 * (l8 + 8 * q) + w;
                 const uint32_t ahead = wv[w] - o_it - 1u;   // (2^32 - 1 for one that ends now, huge for an empty slot)
-                if (wv[w] == o_it && j < o_nd) { high = j; ++count; }
+                if (wv[w] == o_it) { high = j; ++count; }   // (a slot without a decode holds 0, and `it` is at least 1)
                 least = ahead < least ? ahead : least;
               }
             }
-#pragma unroll
-            for (int sh = 1; sh < 8; sh <<= 1) {   // over the eight lanes of the row
-              const int h2 = __shfl_xor(high, sh, 64);
-              const uint32_t l2 = __shfl_xor(least, sh, 64);
-              high = h2 > high ? h2 : high;
-              least = l2 < least ? l2 : least;
-              count += __shfl_xor(count, sh, 64);
-            }
-            const int src = (my_row - r0) << 3;   // back to the lane that owns the server
-            const int my_high = __shfl(high, src & 63, 64), my_count = __shfl(count, src & 63, 64);
-            const uint32_t my_least = __shfl(least, src & 63, 64);
-            if (leaving && my_row >= r0 && my_row < r0 + 8) { slot = my_high; more = my_count > 1; next = my_least; }
+            // over the eight lanes of the row: pairs, quads, then the two quads
+            auto over_row = [](auto f, int v) __attribute__((always_inline)) {
+              v = f(v, __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true));
+              v = f(v, __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true));
+              return f(v, __builtin_amdgcn_mov_dpp(v, 0x141, 0xF, 0xF, true));
+            };
+            high = over_row([](int x, int y) { return x > y ? x : y; }, high);
+            count = over_row([](int x, int y) { return x + y; }, count);
+            // (a request has at most 32768 decodes: the end that follows is nearer than 65535 iterations, or there is none)
+            least = static_cast<uint32_t>(over_row([](int x, int y) { return x < y ? x : y; }, static_cast<int>(least < 0xFFFFu ? least : 0xFFFFu)));
+            const int found = (high & 0xFF) | (count > 1 ? 0x100 : 0) | static_cast<int>(least << 16);
+            // back to the lane that owns the server
+            const uint32_t mine = static_cast<uint32_t>(__shfl(found, ((my_row - r0) << 3) & 63, 64));
+            if (leaving && my_row >= r0 && my_row < r0 + 8) { slot = static_cast<int8_t>(mine); more = mine & 0x100u; next = mine >> 16; }
           }
           if (leaving) {
             leaving = more;
-            nf = next < 0x40000000u ? it + 1u + next : kNever;
+            nf = next < 0xFFFFu ? it + 1u + next : kNever;
             if (slot >= 0) {
               uint32_t *frow = fin + static_cast<size_t>(g) * BS;
               uint64_t *jrow = job + static_cast<size_t>(g) * BS;
@@ -1038,7 +1043,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               const int k = static_cast<int>(jw >> 29) & 7;
               const uint32_t stamp = static_cast<uint32_t>(jw) & 0x1FFFFFFFu;
               const uint32_t Pl = (static_cast<uint32_t>(jw >> 32) & 0xFFFFu) + 1, Dl = static_cast<uint32_t>(jw >> 48) + 1;
-              const int64_t e2e = tn - (static_cast<int64_t>(stamp) + 1) * dt_ns;
+              const int64_t e2e = static_cast<int64_t>(static_cast<uint64_t>(s - stamp) * dt_ns) + rel;   // (T is boundary s + 1)
               lds_add64(&L.tl[k * kNTally + (mixed_now ? SIM_T_S_DM : SIM_T_S_DS)], 1);
               atomicSub(&L.acc[(mixed_now ? AC_YM : AC_YS) + k], 1u);
               lds_add64(&L.tl[k * kNTally + SIM_T_TOKP_DEC], Pl);
@@ -1081,7 +1086,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               const uint32_t stamp = static_cast<uint32_t>(jw) & 0x1FFFFFFFu;
               pe.done = true; pe.k = k; pe.nc = nc;
               pe.P = (static_cast<uint32_t>(jw >> 32) & 0xFFFFu) + 1;
-              pe.ttft = tn - (static_cast<int64_t>(stamp) + 1) * dt_ns;
+              pe.ttft = static_cast<int64_t>(static_cast<uint64_t>(s - stamp) * dt_ns) + rel;
               atomicAdd(reinterpret_cast<unsigned long long *>(&hist[(0 * K + k) * kNBin + hbin(pe.ttft)]), 1ull);
               if constexpr (IM) {
                 // the request keeps its slot: it joins the batch at the restart that follows this completion
@@ -1114,12 +1119,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           // brings is then found to come at an iteration boundary (see `serve`) and starts the iteration anew.
           const int ptok_next = rem > 0 ? chunk_of(rem) : 0;
           if (ptok_next == 0 && nd == 0) {
-            set_event(g, tn, it, false, false);
+            set_event(g, T + rel, it, false, false);
             atomicAnd(bits64(&L.bm_busy[wi]), ~bit);
           } else {
             const uint32_t dur = iteration_ns(ptok_next, static_cast<uint32_t>(nd));
             const uint32_t n = phase_length(static_cast<uint32_t>(nd), rem, dur, nf - it);
-            set_event(g, tn + static_cast<int64_t>(static_cast<uint64_t>(n) * dur), it + n, ptok_next > 0, nd && nf == it + n);
+            set_event(g, T + rel + static_cast<int64_t>(static_cast<uint64_t>(n) * dur), it + n, ptok_next > 0, nd && nf == it + n);
           }
           rec[g].n_cls = nc;
           rec[g].n_join = 0;
@@ -1130,12 +1135,15 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         // a prefill that ended: completion count, recognised prompt tokens, time to first token; the
         // co-resident decodes switch mixed -> solo
         if (pe.done) {
+          int n_classes = K;   // (taken anew, as in tally_iterations)
+          asm volatile("" : "+s"(n_classes));
           lds_add64(&L.tl[pe.k * kNTally + SIM_T_S_P], 1);
           atomicSub(&L.acc[AC_X + pe.k], 1u);
           lds_add64(&L.tl[pe.k * kNTally + SIM_T_TOKP_PRE], pe.P);
           lds_add64(&L.tl[pe.k * kNTally + SIM_T_TTFT_SUM], static_cast<uint64_t>(pe.ttft));
 #pragma unroll
           for (int c = 0; c < kMaxK; ++c) {
+            if (c >= n_classes) break;   // wave-uniform
             const uint32_t v = byte_at(pe.nc, c);
             if (v) {
               lds_add64(&L.tl[c * kNTally + SIM_T_M_MS], v);
@@ -2240,8 +2248,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                   rem = static_cast<int>(a_in);   // an idle prefill slot implies that the running iteration holds no chunk
                   lds_add64(&L.tl[a_k * kNTally + SIM_T_WAIT_STEPS], static_cast<uint64_t>(s - a_stamp));
                   if (n_own) {
+                    int n_classes = K;   // (taken anew, as in tally_iterations)
+                    asm volatile("" : "+s"(n_classes));
 #pragma unroll
                     for (int c = 0; c < kMaxK; ++c) {
+                      if (c >= n_classes) break;   // wave-uniform
                       const uint32_t v = byte_at(nc, c);
                       if (v) {
                         lds_add64(&L.tl[c * kNTally + SIM_T_M_SM], v);
