@@ -110,9 +110,20 @@ __device__ __forceinline__ int select_bit(const uint64_t *bm, const uint16_t *pr
 // the middle of a hot loop) instead of keeping them.
 __device__ __forceinline__ uint32_t pinned(uint32_t v)
 {
-  v = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)));
-  asm volatile("" : "+s"(v));
-  return v;
+  uint32_t own;
+  asm volatile("s_mov_b32 %0, %1" : "=s"(own) : "s"(static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(v)))));
+  return own;
+}
+
+__device__ __forceinline__ int pinned(int v) { return static_cast<int>(pinned(static_cast<uint32_t>(v))); }
+// The same for a pointer to global memory. (Arguments and parameters arrive up to sixteen words at a time; what stays a piece of
+// such a load comes back with the fifteen others, an instruction each, when there was no register for it for a while.)
+template <class T>
+__device__ __forceinline__ T *pinned(T *p)
+{
+  uint64_t own;
+  asm volatile("s_mov_b64 %0, %1" : "=s"(own) : "s"(reinterpret_cast<uint64_t>(p)));
+  return (T *)(__attribute__((address_space(1))) T *)own;
 }
 
 // Sixteen bytes of a slot row, read with the non-temporal hint: a row is read when one of its decodes ends and not
@@ -193,6 +204,7 @@ enum Scalar {
   SC_DLEN = 10,   // entries of the decode buffer ring between head and tail, abandoned ones included
   SC_DSCAN = 11,  // entries of that ring the routing passes of this step have gone past
   SC_COMPACT = 12,// bit k: class queue ring k (bit 8: the decode buffer ring) must be compacted before the appends
+  SC_NSOLO = 13,  // two-buffer routers: completed prefills of this step whose request goes to the solo group
   // randomized router only:
   SC_DLEN_M = 15, // randomized router with abandonment: SC_DLEN / SC_DSCAN of the mixed group's buffer ring
   SC_DSCAN_M = 60,
@@ -241,6 +253,9 @@ struct Lds {
   uint64_t *bm_due;   // [nwords] servers that had their event in this step (and busy ones whose event is next)
   uint64_t *jobs;     // [kJobsLds] the first requests a routing pass places, copied from the decode buffer
   uint64_t *fresh;    // [kJobsLds] abandonment, more than one wave: this step's first completed prefills (two buffers: half each)
+  // two-buffer routers only: completed prefills of this step whose request goes to the solo group, and their ranks
+  uint64_t *bm_solo;  // [nwords]
+  uint16_t *pre_s;    // [nwords]
   uint64_t *bm_lvl;   // [kRouteLevels][nwords] routing pass: servers of the routed group with at most (level) decodes
   uint16_t *pre_lvl;  // [kRouteLevels][nwords] exclusive prefix popcounts of bm_lvl, per level
   uint16_t *pre_c;    // [nwords] exclusive prefix popcounts of bm_comp; in the space of pre_lvl
@@ -261,8 +276,7 @@ struct Lds {
   uint16_t *sel_co;   // [kJobsLds] class | (how many selections before it chose the same class) << 3
   uint16_t *sel_j;    // [kJobsLds] list position of each selection, ordered by class, then by order within the class
   int32_t *sel_n;     // [8] requests the pass takes from the solo group's buffer, per class
-  // two-buffer routers only:
-  uint64_t *solo_w;   // [4] per chunk of 64 completed prefills of a round: which of them go to the solo group
+  uint64_t *spare;    // [4] (held: see the total)
 };
 
 // Carves the dynamic LDS block; 8-byte granules. NWS > 0: the arrays indexed by 64-server word are sized for NWS
@@ -300,6 +314,9 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(bm_due, uint64_t, nw)
   GNR_TAKE(bm_lvl, uint64_t, kRouteLevels * nw)
   GNR_TAKE(bm_comp, uint64_t, nw)
+  const size_t nw_two = p.route_mode == SIM_ROUTE_RANDOM_SPLIT || p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? nw : 0;
+  GNR_TAKE(bm_solo, uint64_t, nw_two)
+  GNR_TAKE(pre_s, uint16_t, nw_two)
   // the ranks of a pass's levels are formed when those of the completions are no longer read (a barrier lies between)
   GNR_TAKE(pre_lvl, uint16_t, kRouteLevels * nw)
   L.pre_c = L.pre_lvl;
@@ -328,7 +345,7 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(sel_co, uint16_t, p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? kJobsLds : 0)
   GNR_TAKE(sel_j, uint16_t, p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? kJobsLds : 0)
   GNR_TAKE(sel_n, int32_t, p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? 8 : 0)
-  GNR_TAKE(solo_w, uint64_t, p.route_mode == SIM_ROUTE_RANDOM_SPLIT || p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? 4 : 0)
+  GNR_TAKE(spare, uint64_t, p.route_mode == SIM_ROUTE_RANDOM_SPLIT || p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? 4 : 0)
 #undef GNR_TAKE
   if (total) *total = off;
   return L;
@@ -576,9 +593,10 @@ struct StepArrays {
 // holds no prefill and fewer than B decodes.
 template <int MAXT, int NWS, bool AB, bool RR, bool IM, bool WS = false, bool DENSE = false>
 __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves_per_simd(MAXT, DENSE)))) gnr_step_kernel(const Params *__restrict__ params, const StepArrays a,
-                                                        const uint32_t key0, const uint32_t key1,
-                                                        const uint32_t step_begin, const uint32_t n_steps)
+                                                        const uint32_t key0_arg, const uint32_t key1_arg,
+                                                        const uint32_t step_begin_arg, const uint32_t n_steps_arg)
 {
+  const uint32_t key0 = pinned(key0_arg), key1 = pinned(key1_arg), step_begin = pinned(step_begin_arg), n_steps = pinned(n_steps_arg);
   const Params &p = *params;   // immutable after creation; read through the scalar cache on demand
   extern __shared__ __align__(16) unsigned char lds_raw[];
   constexpr bool SMALL = MAXT <= 128;
@@ -606,12 +624,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     else if (wave >= 4 || nwaves <= 4) __builtin_amdgcn_s_setprio(1);
   };
   own_priority();
-  const int K = p.K, N = p.N, B = p.B, M = p.M, BS = p.BS;
+  const int K = pinned(p.K), N = pinned(p.N), B = pinned(p.B), M = pinned(p.M), BS = pinned(p.BS);
   const int nper = (N + NT - 1) / NT;
-  const int nwords = p.nwords;
+  const int nwords = pinned(p.nwords);
   // Servers 0..M-1 are the mixed group for the gate and the router. Servers below Mp >= M may hold a prefill:
   // Mp is the largest M the run has had (a prefill in service stays when its server turns solo).
-  const int Mp = p.Mp;
+  const int Mp = pinned(p.Mp);
   const int nwords_m = (Mp + 63) >> 6;   // bitmap words that hold servers with prefill state
   // Iteration-time coefficients, chunk size and step length in ns (each below 2^31: the longest iteration is),
   // window of the on-chip time-between-tokens histogram, class thresholds of the arrival draw: used in every block.
@@ -622,25 +640,27 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   const int gate_mode = static_cast<int>(pinned(static_cast<uint32_t>(p.gate_mode)));
   const uint32_t queue_cap = pinned(p.queue_cap), dbuf_cap = pinned(p.dbuf_cap);
 
-  ServerRec *rec = a.rec + static_cast<size_t>(r) * N;
-  uint32_t *t_rel = a.t_rel + static_cast<size_t>(r) * N;
-  uint32_t *remptok = a.remptok + static_cast<size_t>(r) * N;
-  uint32_t *fin = a.fin + static_cast<size_t>(r) * N * BS;
-  uint64_t *job = a.job + static_cast<size_t>(r) * N * BS;
-  uint32_t *qring = a.qring + static_cast<size_t>(r) * K * queue_cap;
-  uint64_t *dring = a.dring + static_cast<size_t>(r) * dbuf_cap;
-  uint64_t *hist = a.hist + static_cast<size_t>(r) * 3 * K * kNBin;
+  const uint32_t *arr_thr = pinned(a.arr_thr);
+  const uint16_t *len_tab = pinned(a.len_tab), *pat_tab = AB ? pinned(a.pat_tab) : nullptr;
+  ServerRec *rec = pinned(a.rec + static_cast<size_t>(r) * N);
+  uint32_t *t_rel = pinned(a.t_rel + static_cast<size_t>(r) * N);
+  uint32_t *remptok = pinned(a.remptok + static_cast<size_t>(r) * N);
+  uint32_t *fin = pinned(a.fin + static_cast<size_t>(r) * N * BS);
+  uint64_t *job = pinned(a.job + static_cast<size_t>(r) * N * BS);
+  uint32_t *qring = pinned(a.qring + static_cast<size_t>(r) * K * queue_cap);
+  uint64_t *dring = pinned(a.dring + static_cast<size_t>(r) * dbuf_cap);
+  uint64_t *hist = pinned(a.hist + static_cast<size_t>(r) * 3 * K * kNBin);
   uint16_t *ev_g = L.ev_g + wave * kEvPerWave;
   // abandonment only
   const uint32_t cal_n = p.cal_mask + 1u;
-  uint32_t *qdl = AB ? a.qdl + static_cast<size_t>(r) * K * queue_cap : nullptr;
-  uint32_t *ddl = AB ? a.ddl + static_cast<size_t>(r) * dbuf_cap : nullptr;
-  uint32_t *cal = AB ? a.cal + static_cast<size_t>(r) * K * cal_n : nullptr;
-  uint32_t *dcal = AB ? a.dcal + static_cast<size_t>(r) * K * cal_n : nullptr;
+  uint32_t *qdl = AB ? pinned(a.qdl + static_cast<size_t>(r) * K * queue_cap) : nullptr;
+  uint32_t *ddl = AB ? pinned(a.ddl + static_cast<size_t>(r) * dbuf_cap) : nullptr;
+  uint32_t *cal = AB ? pinned(a.cal + static_cast<size_t>(r) * K * cal_n) : nullptr;
+  uint32_t *dcal = AB ? pinned(a.dcal + static_cast<size_t>(r) * K * cal_n) : nullptr;
   const uint32_t *lo_tab = AB ? L.live_off : nullptr;
-  uint64_t *dring_m = RR ? a.dring_m + static_cast<size_t>(r) * dbuf_cap : nullptr;
-  uint32_t *ddl_m = AB && RR ? a.ddl_m + static_cast<size_t>(r) * dbuf_cap : nullptr;
-  uint32_t *dcal_m = AB && RR ? a.dcal_m + static_cast<size_t>(r) * K * cal_n : nullptr;
+  uint64_t *dring_m = RR ? pinned(a.dring_m + static_cast<size_t>(r) * dbuf_cap) : nullptr;
+  uint32_t *ddl_m = AB && RR ? pinned(a.ddl_m + static_cast<size_t>(r) * dbuf_cap) : nullptr;
+  uint32_t *dcal_m = AB && RR ? pinned(a.dcal_m + static_cast<size_t>(r) * K * cal_n) : nullptr;
 
   // ---- load the replication's class state and rebuild the on-chip views of the server state
   for (int i = tid; i < CS_WORDS; i += NT) L.cs[i] = a.cstate[static_cast<size_t>(r) * CS_WORDS + i];
@@ -779,8 +799,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   };
   // (`mixed`: the mixed group's buffer ring of the randomized router)
   auto compact_buffer = [&](uint32_t now, bool mixed) __attribute__((always_inline)) {
-    uint64_t *dring = mixed ? dring_m : a.dring + static_cast<size_t>(r) * dbuf_cap;
-    uint32_t *ddl = mixed ? ddl_m : a.ddl + static_cast<size_t>(r) * dbuf_cap;
+    uint64_t *ring = mixed ? dring_m : dring;
+    uint32_t *dlr = mixed ? ddl_m : ddl;
     const uint32_t hd = static_cast<uint32_t>(L.cs[mixed ? CS_DHEAD_M : CS_DHEAD]);
     uint32_t n = static_cast<uint32_t>(L.sc[mixed ? SC_DLEN_M : SC_DLEN]);
     if (n > dbuf_cap) n = dbuf_cap;
@@ -789,14 +809,14 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       const uint32_t i = off + lane;
       uint32_t pos = hd + i;
       if (pos >= dbuf_cap) pos -= dbuf_cap;
-      const uint64_t jw = i < n ? dring[pos] : 0ull;
-      const uint32_t dl = i < n ? ddl[pos] : 0u;
+      const uint64_t jw = i < n ? ring[pos] : 0ull;
+      const uint32_t dl = i < n ? dlr[pos] : 0u;
       const bool live = i < n && dl > now;
       const uint64_t bal = __ballot(live);
       if (live) {
         uint32_t wp = hd + w + static_cast<uint32_t>(rank_in(bal));
         if (wp >= dbuf_cap) wp -= dbuf_cap;
-        dring[wp] = jw; ddl[wp] = dl;
+        ring[wp] = jw; dlr[wp] = dl;
       }
       w += static_cast<uint32_t>(__popcll(bal));
     }
@@ -806,7 +826,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   // arrival thresholds of the step to come: asked for a step ahead, the first three lanes hold them
   const uint32_t mod_rows = p.mod_period > 0xFFFFFFFFll ? 0xFFFFFFFFu : (p.mod_period > 0 ? static_cast<uint32_t>(p.mod_period) : 1u);
   uint32_t mod_row = step_begin % mod_rows;
-  uint32_t thr_ahead = a.arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
+  uint32_t thr_ahead = arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
   // what `n` steps leave in the class counters at their end enters the sums over steps
   auto add_step_sums = [&](int k, uint32_t n, int qp, int qd, int x, int ym, int ys) __attribute__((always_inline)) {
     lds_add64(&L.tl[k * kNTally + SIM_T_SUM_QP], static_cast<uint64_t>(n) * static_cast<uint32_t>(qp));
@@ -896,7 +916,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   auto next_thresholds = [&]() __attribute__((always_inline)) {   // of the step after the one drawn (in every wave, whether it draws or not)
     if (mod_rows > 1u) {
       mod_row = mod_row + 1u == mod_rows ? 0u : mod_row + 1u;
-      thr_ahead = a.arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
+      thr_ahead = arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
     }
   };
   bool drawn = false;        // the arrivals of the step to come have been drawn
@@ -920,7 +940,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             if (steps_ahead == 0) {
               const uint32_t s_lane = s + (static_cast<uint32_t>(lane) >> lg_n);
               const int g = lane & ((1 << lg_n) - 1);
-              const uint32_t thr = a.arr_thr[mod_rows > 1u ? 3 * static_cast<size_t>(s_lane % mod_rows) : 0];
+              const uint32_t thr = arr_thr[mod_rows > 1u ? 3 * static_cast<size_t>(s_lane % mod_rows) : 0];
               uint32_t w[4];
               philox4x32_10(key0, key1, s_lane, 0u, static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
               ahead = __ballot(g < N && w[0] >= thr);
@@ -937,7 +957,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             if (s == step_end) { T = static_cast<int64_t>(s) * dt_ns; break; }
             if (mod_rows > 1u) {
               mod_row = s % mod_rows;
-              thr_ahead = a.arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
+              thr_ahead = arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
             }
           }
         }
@@ -1060,6 +1080,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         uint32_t m = 0, d = 0;
         bool chunk = false;
         uint64_t comp = 0;
+        uint32_t wait_steps = 0;   // patience of a completed prefill's request in the decode buffer (0: without end)
         PrefillEnd pe; pe.done = false; pe.k = 0; pe.P = 0; pe.ttft = 0; pe.nc = 0;
         if (active) {
           comp = nc_before - nj;   // bytewise: no class joins more decodes than it holds
@@ -1112,6 +1133,12 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               } else {
                 atomicOr(bits64(&L.bm_comp[wi]), bit);
                 atomicOr(bits64(&L.bm_idle[wi]), bit);
+                if constexpr (AB || RR) {   // word 0 of its block: patience in the buffer, word 1: which of two buffers
+                  uint32_t w[4];
+                  philox4x32_10(key0, key1, s, static_cast<uint32_t>(kStreamPatienceD), static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
+                  if constexpr (RR) { if (w[1] < p.solo_thr[k]) atomicOr(bits64(&L.bm_solo[wi]), bit); }
+                  if constexpr (AB) { if ((p.ab_classes >> k) & 1u) wait_steps = pat_tab[static_cast<size_t>(k) * kTableSize + (w[0] >> 16)]; }
+                }
               }
             }
           }
@@ -1130,6 +1157,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           rec[g].n_join = 0;
           rec[g].iter = it;
           rec[g].next_fin = nf;
+          // (in the place of the prompt tokens left, of which there are none, until the request joins its buffer)
+          if constexpr (AB && !IM) { if (pe.done) L.rem[g] = static_cast<uint16_t>(wait_steps); }
         }
         tally_iterations<kTallyRowsHere>(L.ta, L.tbth, tbt_w, tbt_lo, K, m, d, chunk, comp);
         // a prefill that ended: completion count, recognised prompt tokens, time to first token; the
@@ -1187,6 +1216,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           L.bm_due[w_lane] = due;
           if (slots_taken) L.bm_idle[w_lane] &= ~L.bm_comp[w_lane];
           L.bm_comp[w_lane] = 0;
+          if constexpr (RR) L.bm_solo[w_lane] = 0;
         } else {
           due = 0;
         }
@@ -1258,10 +1288,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       }
     }
     ended = 0;
-    uint32_t ncomp_own = 0;   // (the first wave's count of completed prefills)
     if (tid < 64) {
       const uint32_t ncomp = rank_bitmap(L.bm_comp, L.pre_c, nwords_m, Mp);
-      ncomp_own = ncomp;
       if (tid == 0) {
         L.sc[SC_NCOMP] = static_cast<int32_t>(ncomp);
         if constexpr (AB) {
@@ -1280,40 +1308,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       const uint32_t nidle = rank_bitmap(L.bm_idle, L.pre, nwords_m, M);   // idle prefill slots of the mixed group
       if (lane == 0) L.sc[SC_NIDLE] = static_cast<int32_t>(nidle);
     }
-    // Two-buffer routers: word 1 of a completed prefill's block picks its group, and its rank within the group's
-    // ring is the number of earlier completions (in server order) sent to the same group. Up to four waves take a
-    // chunk of 64 completions each: before the barrier they fetch the request, draw its block and publish which of
-    // their 64 go to the solo group; after it every chunk knows the counts before it and appends its requests.
-    // What a wave fetched stays in its registers across the barrier.
-    const int chunk_waves = nwaves < 4 ? nwaves : 4, chunk_first = nwaves >= 6 ? 2 : 0;
-    const int my_chunk = wave - chunk_first;
-    const bool chunk_wave = RR && my_chunk >= 0 && my_chunk < chunk_waves;
-    bool c_active = false, c_solo = false;
-    uint64_t c_jw = 0;
-    uint32_t c_dl = kNever;
-    int c_k = 0;
-    auto draw_chunk = [&](uint32_t first, uint32_t ncomp_all) __attribute__((always_inline)) {
-      const uint32_t j = first + 64u * static_cast<uint32_t>(my_chunk) + lane;
-      c_active = j < ncomp_all;
-      c_solo = false;
-      c_dl = kNever;
-      const int g = c_active ? select_bit(L.bm_comp, L.pre_c, nwords_m, j) : 0;
-      c_jw = rec[g].pf_job;   // (slot 0 for the lanes past the end: read, not used)
-      uint32_t w[4];
-      philox4x32_10(key0, key1, s, static_cast<uint32_t>(kStreamPatienceD), static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
-      c_k = static_cast<int>(c_jw >> 29) & 7;
-      c_solo = c_active && w[1] < p.solo_thr[c_k];
-      if constexpr (AB) {
-        if (c_active && ((p.ab_classes >> c_k) & 1u)) c_dl = s + a.pat_tab[static_cast<size_t>(c_k) * kTableSize + (w[0] >> 16)];
-      }
-      const uint64_t to_solo = __ballot(c_solo);
-      if (lane == 0) L.solo_w[my_chunk] = to_solo;
-    };
-    if constexpr (RR) {
-      if (chunk_wave) {
-        // (each of these waves ranks the completion bitmap itself: the same values as the first wave writes)
-        const uint32_t ncomp_all = wave == 0 ? ncomp_own : rank_bitmap(L.bm_comp, L.pre_c, nwords_m, Mp);
-        draw_chunk(0u, ncomp_all);
+    if constexpr (RR) {   // (another wave where there is one)
+      if (wave == (nwaves > 2 ? 2 : nwaves - 1)) {
+        const uint32_t nsolo = rank_bitmap(L.bm_solo, L.pre_s, nwords_m, Mp);
+        if (lane == 0) L.sc[SC_NSOLO] = static_cast<int32_t>(nsolo);
       }
     }
     __syncthreads();
@@ -1359,7 +1357,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         if ((p.ab_classes >> k) & 1u) {
           uint32_t w[4];
           philox4x32_10(key0, key1, s, static_cast<uint32_t>(kStreamPatienceP + k), j, static_cast<uint32_t>(r), w);
-          dl = s + a.pat_tab[static_cast<size_t>(k) * kTableSize + (w[0] >> 16)];
+          dl = s + pat_tab[static_cast<size_t>(k) * kTableSize + (w[0] >> 16)];
           atomicAdd(&cal[static_cast<size_t>(k) * cal_n + (dl & p.cal_mask)], 1u);
         }
         qdl[static_cast<size_t>(k) * queue_cap + pos] = dl;
@@ -1378,107 +1376,66 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     }
     // completed prefills join the decode buffer in ascending server order
     int ncs = 0, ncm = 0;   // two buffers: how many joined the solo and the mixed group's
-    if constexpr (RR) {
+    {
       const uint32_t ncomp = static_cast<uint32_t>(L.sc[SC_NCOMP]);
-      const uint32_t dc0 = static_cast<uint32_t>(L.cs[CS_DCOUNT]), dc1 = static_cast<uint32_t>(L.cs[CS_DCOUNT_M]);
-      const uint32_t dh0 = static_cast<uint32_t>(L.cs[CS_DHEAD]), dh1 = static_cast<uint32_t>(L.cs[CS_DHEAD_M]);
+      const uint32_t dc0 = static_cast<uint32_t>(L.cs[CS_DCOUNT]), dc1 = RR ? static_cast<uint32_t>(L.cs[CS_DCOUNT_M]) : 0u;
+      const uint32_t dh0 = static_cast<uint32_t>(L.cs[CS_DHEAD]), dh1 = RR ? static_cast<uint32_t>(L.cs[CS_DHEAD_M]) : 0u;
       // ring entries before the tail (with abandonment the dead entries count)
-      const uint32_t fill0 = AB ? static_cast<uint32_t>(L.sc[SC_DLEN]) : dc0, fill1 = AB ? static_cast<uint32_t>(L.sc[SC_DLEN_M]) : dc1;
-      uint32_t seen0 = 0, seen1 = 0;   // completions sent to either group in the rounds before this one
-      const uint32_t per_round = 64u * static_cast<uint32_t>(chunk_waves);
-      for (uint32_t first = 0; first < ncomp; first += per_round) {   // wave-uniform; one round is the rule
-        if (first > 0) {
-          __syncthreads();   // every wave has read the words of the round before
-          if (chunk_wave) draw_chunk(first, ncomp);
-          __syncthreads();
-        }
-        uint32_t solo_before = 0, solo_round = 0;   // in the chunks before this wave's, in the whole round
-        for (int c = 0; c < chunk_waves; ++c) {
-          const uint32_t n = static_cast<uint32_t>(__popcll(L.solo_w[c]));
-          if (c < my_chunk) solo_before += n;
-          solo_round += n;
-        }
-        const uint32_t in_round = ncomp - first < per_round ? ncomp - first : per_round;
-        if (chunk_wave && 64u * static_cast<uint32_t>(my_chunk) < in_round) {   // wave-uniform
-          const bool active = c_active, solo = c_solo;
-          const int k = c_k;
-          const uint64_t bal0 = __ballot(active && solo), bal1 = __ballot(active && !solo);
-          // (the chunks before this one are full)
-          const uint32_t idx = solo ? seen0 + solo_before + static_cast<uint32_t>(rank_in(bal0))
-                                    : seen1 + (64u * static_cast<uint32_t>(my_chunk) - solo_before) + static_cast<uint32_t>(rank_in(bal1));
-          const bool kept = active && (solo ? dc0 : dc1) + idx < dbuf_cap;
-          if (kept) {
-            uint32_t pos = (solo ? dh0 + fill0 : dh1 + fill1) + idx;
-            if (pos >= dbuf_cap) pos -= dbuf_cap;
-            (solo ? dring : dring_m)[pos] = c_jw;
-            if (idx < kJobsLds / 2) {
-              if constexpr (!AB) L.jobs[(solo ? 0u : kJobsLds / 2) + idx] = c_jw;
-              else if (!WS && nwaves > 1) L.fresh[(solo ? 0u : kJobsLds / 2) + idx] = c_jw;
-            }
-            if constexpr (AB) {
-              (solo ? ddl : ddl_m)[pos] = c_dl;
-              if (c_dl != kNever) atomicAdd(&(solo ? dcal : dcal_m)[static_cast<size_t>(k) * cal_n + (c_dl & p.cal_mask)], 1u);
-            }
-          }
-          if (kept) {
-            atomicAdd(&L.cs[CS_QD + k], 1);
-            // the weighted router also counts what waits in the solo group's buffer per class
-            if constexpr (WS) { if (solo) atomicAdd(&L.cs[CS_QDS + k], 1); }
-          } else if (active) {
-            lds_add64(&L.tl[k * kNTally + SIM_T_DROP_D], 1);
-            L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
-          }
-        }
-        seen0 += solo_round;
-        seen1 += in_round - solo_round;
-      }
-      // what each ring accepted (a prefix of what it was sent)
-      const uint32_t room0 = dbuf_cap - dc0, room1 = dbuf_cap - dc1;
-      ncs = uniform(static_cast<int>(seen0 < room0 ? seen0 : room0));
-      ncm = uniform(static_cast<int>(seen1 < room1 ? seen1 : room1));
-    } else {
-      const uint32_t ncomp = static_cast<uint32_t>(L.sc[SC_NCOMP]);
-      const uint32_t dcount = static_cast<uint32_t>(L.cs[CS_DCOUNT]), dhead = static_cast<uint32_t>(L.cs[CS_DHEAD]);
-      const uint32_t dfill = AB ? static_cast<uint32_t>(L.sc[SC_DLEN]) : dcount;   // ring entries before the tail
+      const uint32_t fill0 = AB ? static_cast<uint32_t>(L.sc[SC_DLEN]) : dc0, fill1 = AB && RR ? static_cast<uint32_t>(L.sc[SC_DLEN_M]) : dc1;
       // (64 to a wave, the last wave that ranks the gate's candidates first: it has the least to do next)
       const int comp_turn = wave < n_gate ? n_gate - 1 - wave : wave;
       for (uint32_t j0 = static_cast<uint32_t>(comp_turn) * 64u; j0 < ncomp; j0 += NT) {   // wave-uniform trip count
         const uint32_t j = j0 + lane;
-        const bool active = j < ncomp;
-        int k = 0;
-        bool kept = false;
-        if (active) {
+        if (j < ncomp) {
           const int g = select_bit(L.bm_comp, L.pre_c, nwords_m, j);
           const uint64_t jw = rec[g].pf_job;
-          k = static_cast<int>(jw >> 29) & 7;
-          kept = dcount + j < dbuf_cap;
-          if (kept) {
-            uint32_t pos = dhead + dfill + j;
+          const int k = static_cast<int>(jw >> 29) & 7;
+          uint32_t dl = kNever;
+          if constexpr (AB) {
+            const uint32_t wait_steps = L.rem[g];
+            L.rem[g] = 0;
+            if (wait_steps) dl = s + wait_steps;
+          }
+          bool solo = true;   // the only buffer, or the solo group's
+          uint32_t idx = j;   // its place among those that join that buffer
+          if constexpr (RR) {
+            const uint64_t to_solo = L.bm_solo[g >> 6], bit = 1ull << (g & 63);
+            solo = to_solo & bit;
+            const uint32_t before = L.pre_s[g >> 6] + static_cast<uint32_t>(__popcll(to_solo & (bit - 1ull)));
+            idx = solo ? before : j - before;
+          }
+          if ((solo ? dc0 : dc1) + idx < dbuf_cap) {
+            uint32_t pos = (solo ? dh0 + fill0 : dh1 + fill1) + idx;
             if (pos >= dbuf_cap) pos -= dbuf_cap;
-            dring[pos] = jw;
-            if (j < kJobsLds) {
-              if constexpr (!AB) L.jobs[j] = jw;
-              else if (nwaves > 1) L.fresh[j] = jw;
+            if (solo) dring[pos] = jw; else dring_m[pos] = jw;
+            constexpr uint32_t kHere = RR ? kJobsLds / 2 : kJobsLds;
+            if (idx < kHere) {
+              if constexpr (!AB) L.jobs[(solo ? 0u : kHere) + idx] = jw;
+              else if (!WS && nwaves > 1) L.fresh[(solo ? 0u : kHere) + idx] = jw;
             }
-            if constexpr (AB) {   // patience for the wait in the decode buffer
-              uint32_t dl = kNever;
-              if ((p.ab_classes >> k) & 1u) {
-                uint32_t w[4];
-                philox4x32_10(key0, key1, s, static_cast<uint32_t>(kStreamPatienceD), static_cast<uint32_t>(g),
-                              static_cast<uint32_t>(r), w);
-                dl = s + a.pat_tab[static_cast<size_t>(k) * kTableSize + (w[0] >> 16)];
-                atomicAdd(&dcal[static_cast<size_t>(k) * cal_n + (dl & p.cal_mask)], 1u);
+            if constexpr (AB) {
+              const size_t at = static_cast<size_t>(k) * cal_n + (dl & p.cal_mask);
+              if (solo) {
+                ddl[pos] = dl;
+                if (dl != kNever) atomicAdd(&dcal[at], 1u);
+              } else {
+                ddl_m[pos] = dl;
+                if (dl != kNever) atomicAdd(&dcal_m[at], 1u);
               }
-              ddl[pos] = dl;
             }
+            atomicAdd(&L.cs[CS_QD + k], 1);
+            // the weighted router also counts what waits in the solo group's buffer per class
+            if constexpr (WS) { if (solo) atomicAdd(&L.cs[CS_QDS + k], 1); }
+          } else {
+            lds_add64(&L.tl[k * kNTally + SIM_T_DROP_D], 1);
+            L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
           }
         }
-        if (kept) {
-          atomicAdd(&L.cs[CS_QD + k], 1);
-        } else if (active) {
-          lds_add64(&L.tl[k * kNTally + SIM_T_DROP_D], 1);
-          L.tl[kMaxK * kNTally + SIM_G_OVERFLOW] = 1;
-        }
+      }
+      if constexpr (RR) {   // what each ring accepted (a prefix of what it was sent)
+        const uint32_t room0 = dbuf_cap - dc0, room1 = dbuf_cap - dc1, to_solo = static_cast<uint32_t>(L.sc[SC_NSOLO]);
+        ncs = uniform(static_cast<int>(to_solo < room0 ? to_solo : room0));
+        ncm = uniform(static_cast<int>(ncomp - to_solo < room1 ? ncomp - to_solo : room1));
       }
     }
 
@@ -1893,21 +1850,18 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           }
           // The searches of a candidate in the other classes run side by side on neighbouring lanes, which add up what they
           // find; the candidates of a class follow those of the class before it.
-          int first_of[kMaxK];   // first candidate of each class
-          {
-            int run = 0;
+          const uint32_t cnt_class = lane < (1 << lg) ? static_cast<uint32_t>(cnt2) : 0u;
+          const int first_lane = static_cast<int>(wave_incl_scan(cnt_class) - cnt_class);   // lane k: first candidate of class k
+          int first_of[kMaxK], n_classes = K;
+          asm volatile("" : "+s"(n_classes));   // (taken anew, as in tally_iterations)
 #pragma unroll
-            for (int kk = 0; kk < kMaxK; ++kk) {
-              first_of[kk] = run;
-              if (kk < K) run += __builtin_amdgcn_readlane(cnt2, kk);
-            }
-          }
+          for (int kk = 1; kk < kMaxK; ++kk) first_of[kk] = kk < n_classes ? __builtin_amdgcn_readlane(first_lane, kk) : 0x7FFFFFFF;
           for (int c0 = wave << 6; c0 < (ncand << lg); c0 += n_gate << 6) {   // wave-uniform trip count
             const int c = (c0 + lane) >> lg;
-            int k = 0, m = c, lo = 0;
+            int k = 0, lo = 0;
 #pragma unroll
-            for (int kk = 1; kk < kMaxK; ++kk)
-              if (kk < K && c >= first_of[kk]) { k = kk; m = c - first_of[kk]; }
+            for (int kk = 1; kk < kMaxK; ++kk) k += c >= first_of[kk] ? 1 : 0;
+            const int m = c - __shfl(first_lane, k, 64);
             if (c < ncand) {
               if (k2 == k) {
                 lo = m;
@@ -2212,8 +2166,8 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                   }
                   uint32_t w[4];
                   philox4x32_10(key0, key1, s, 1u, static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
-                  a_in = a.len_tab[(static_cast<size_t>(a_k) * 2 + 0) * kTableSize + (w[0] >> 16)];
-                  a_out = a.len_tab[(static_cast<size_t>(a_k) * 2 + 1) * kTableSize + (w[1] >> 16)];
+                  a_in = len_tab[(static_cast<size_t>(a_k) * 2 + 0) * kTableSize + (w[0] >> 16)];
+                  a_out = len_tab[(static_cast<size_t>(a_k) * 2 + 1) * kTableSize + (w[1] >> 16)];
                 }
                 // ---- where the server stands: `it` iterations are completed; in the middle of one (`mid`: what it is given
                 //      now joins when that one ends), at a boundary, the iterations before it then being tallied, or idle.
