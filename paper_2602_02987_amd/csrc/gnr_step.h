@@ -1002,6 +1002,31 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         // ---- the ends of decodes: one leaves per round, highest slot first (the last slot's request moves into its
         //      place); a second round follows only where several end together
         bool leaving = ev & kEvFin;
+        // The request that leaves (a trip to memory that follows the row's) is asked for where its slot is known and used at the
+        // end, unless another of the server's ends in the same iteration: the next event does not depend on it.
+        int gone_slot = -1;
+        uint64_t gone_job = 0, last_job = 0;
+        uint32_t last_fin = 0;
+        auto leave = [&]() __attribute__((always_inline)) {
+          if (gone_slot >= 0) {
+            uint32_t *frow = fin + static_cast<size_t>(g) * BS;
+            uint64_t *jrow = job + static_cast<size_t>(g) * BS;
+            const int k = static_cast<int>(gone_job >> 29) & 7;
+            const uint32_t stamp = static_cast<uint32_t>(gone_job) & 0x1FFFFFFFu;
+            const uint32_t Pl = (static_cast<uint32_t>(gone_job >> 32) & 0xFFFFu) + 1, Dl = static_cast<uint32_t>(gone_job >> 48) + 1;
+            const int64_t e2e = static_cast<int64_t>(static_cast<uint64_t>(s - stamp) * dt_ns) + rel;   // (T is boundary s + 1)
+            lds_add64(&L.tl[k * kNTally + (mixed_now ? SIM_T_S_DM : SIM_T_S_DS)], 1);
+            atomicSub(&L.acc[(mixed_now ? AC_YM : AC_YS) + k], 1u);
+            lds_add64(&L.tl[k * kNTally + SIM_T_TOKP_DEC], Pl);
+            lds_add64(&L.tl[k * kNTally + SIM_T_TOKD_DEC], Dl);
+            lds_add64(&L.tl[k * kNTally + SIM_T_E2E_SUM], static_cast<uint64_t>(e2e));
+            atomicAdd(reinterpret_cast<unsigned long long *>(&hist[(1 * K + k) * kNBin + hbin(e2e)]), 1ull);
+            nc -= 1ull << (8 * k);
+            if (gone_slot < nd) { frow[gone_slot] = last_fin; jrow[gone_slot] = last_job; }
+            frow[nd] = 0;   // a vacated slot must never match a later iteration index
+          }
+          gone_slot = -1;
+        };
         for (uint64_t lm = __ballot(leaving); lm; lm = __ballot(leaving)) {
           // lane q gets the server, the decodes and the iteration of the q-th row (the other lanes' follow behind them)
           const int nrows = __popcll(lm), my_row = rank_in(lm);
@@ -1056,26 +1081,14 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             leaving = more;
             nf = next < 0xFFFFu ? it + 1u + next : kNever;
             if (slot >= 0) {
-              uint32_t *frow = fin + static_cast<size_t>(g) * BS;
-              uint64_t *jrow = job + static_cast<size_t>(g) * BS;
-              const uint64_t jw = jrow[slot], jl = jrow[nd - 1];
-              const uint32_t fl = frow[nd - 1];
-              const int k = static_cast<int>(jw >> 29) & 7;
-              const uint32_t stamp = static_cast<uint32_t>(jw) & 0x1FFFFFFFu;
-              const uint32_t Pl = (static_cast<uint32_t>(jw >> 32) & 0xFFFFu) + 1, Dl = static_cast<uint32_t>(jw >> 48) + 1;
-              const int64_t e2e = static_cast<int64_t>(static_cast<uint64_t>(s - stamp) * dt_ns) + rel;   // (T is boundary s + 1)
-              lds_add64(&L.tl[k * kNTally + (mixed_now ? SIM_T_S_DM : SIM_T_S_DS)], 1);
-              atomicSub(&L.acc[(mixed_now ? AC_YM : AC_YS) + k], 1u);
-              lds_add64(&L.tl[k * kNTally + SIM_T_TOKP_DEC], Pl);
-              lds_add64(&L.tl[k * kNTally + SIM_T_TOKD_DEC], Dl);
-              lds_add64(&L.tl[k * kNTally + SIM_T_E2E_SUM], static_cast<uint64_t>(e2e));
-              atomicAdd(reinterpret_cast<unsigned long long *>(&hist[(1 * K + k) * kNBin + hbin(e2e)]), 1ull);
-              nc -= 1ull << (8 * k);
               --nd;
-              if (slot < nd) { frow[slot] = fl; jrow[slot] = jl; }
-              frow[nd] = 0;   // a vacated slot must never match a later iteration index
+              gone_slot = slot;
+              const size_t row0 = static_cast<size_t>(g) * BS;
+              gone_job = job[row0 + slot]; last_job = job[row0 + nd];
+              last_fin = fin[row0 + nd];
             }
           }
+          if (IM || __ballot(leaving)) leave();   // wave-uniform
         }
         uint32_t m = 0, d = 0;
         bool chunk = false;
@@ -1153,14 +1166,17 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             const uint32_t n = phase_length(static_cast<uint32_t>(nd), rem, dur, nf - it);
             set_event(g, T + rel + static_cast<int64_t>(static_cast<uint64_t>(n) * dur), it + n, ptok_next > 0, nd && nf == it + n);
           }
-          rec[g].n_cls = nc;
-          rec[g].n_join = 0;
-          rec[g].iter = it;
-          rec[g].next_fin = nf;
           // (in the place of the prompt tokens left, of which there are none, until the request joins its buffer)
           if constexpr (AB && !IM) { if (pe.done) L.rem[g] = static_cast<uint16_t>(wait_steps); }
         }
         tally_iterations<kTallyRowsHere>(L.ta, L.tbth, tbt_w, tbt_lo, K, m, d, chunk, comp);
+        if constexpr (!IM) { leave(); pe.nc = nc; }
+        if (active) {
+          rec[g].n_cls = nc;
+          rec[g].n_join = 0;
+          rec[g].iter = it;
+          rec[g].next_fin = nf;
+        }
         // a prefill that ended: completion count, recognised prompt tokens, time to first token; the
         // co-resident decodes switch mixed -> solo
         if (pe.done) {
@@ -2169,6 +2185,63 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                   a_in = len_tab[(static_cast<size_t>(a_k) * 2 + 0) * kTableSize + (w[0] >> 16)];
                   a_out = len_tab[(static_cast<size_t>(a_k) * 2 + 1) * kTableSize + (w[1] >> 16)];
                 }
+                // ---- its jobs: which one of each level the server takes follows from its rank among the level's members (looked up here,
+                //      while its record is on the way)
+                uint64_t job_of[kRouteLevels];
+                uint32_t takes = 0;
+                const bool has_prefill = g < Mp && (admitted || !(idle & bit));
+                const int gi = g >= M ? 0 : 1;
+                const int lmins = word_of(SC_LMIN);
+                const int first = gi == 0 ? 0 : nl_solo, my_lmin = gi == 0 ? lmins & 0xFFFF : lmins >> 16;
+#pragma unroll
+                for (int t = 0; t < kRouteLevels; ++t) {
+                  if (t < nl_mine) {   // wave-uniform
+                    const uint64_t in = wi >= lvl_first && wi < lvl_end ? L.bm_lvl[t * nwords + wi] : 0ull;
+                    const int q = static_cast<int>(L.pre_lvl[t * nwords + wi]) + __popcll(in & (bit - 1ull));
+                    if ((in & bit) && q < take_r[t]) {
+                      const int j = w_r[t] + q;   // position in this pass
+                      uint64_t &jw = job_of[t];
+                      takes |= 1u << t;
+                      if constexpr (AB) {
+                        jw = L.jobs[j];
+                        if (fresh_kept) {
+                          const int i = RR && gi ? j - placed_solo : j;   // place in the group's buffer, live requests only
+                          const int ci = i - (RR && gi ? dcount0_m : dcount0);
+                          if (ci >= 0) {   // one of this step's completions: it leaves the calendar of its deadline
+                            const uint32_t fill = RR && gi ? dlen_all_m - static_cast<uint32_t>(ncm) : dlen_all - static_cast<uint32_t>(RR ? ncs : jrem - dcount0);
+                            uint32_t pos = (RR ? dheadL[gi] : dhead0) + fill + static_cast<uint32_t>(ci);
+                            if (pos >= dbuf_cap) pos -= dbuf_cap;
+                            if (pos >= dbuf_cap) pos -= dbuf_cap;
+                            constexpr int kHere = RR ? kJobsLds / 2 : kJobsLds;
+                            jw = L.fresh[(RR && gi ? kHere : 0) + (ci < kHere ? ci : 0)];
+                            asm("" : "+v"(jw));   // (see below)
+                            if (ci >= kHere) { if (!RR || gi == 0) jw = dring[pos]; else jw = dring_m[pos]; }
+                            uint32_t dl;
+                            if (!RR || gi == 0) dl = ddl[pos]; else dl = ddl_m[pos];
+                            if (dl != kNever) {
+                              uint32_t *at = &dcal[((jw >> 29) & 7u) * static_cast<size_t>(cal_n) + (dl & p.cal_mask)];
+                              if constexpr (RR) { if (gi) at = &dcal_m[((jw >> 29) & 7u) * static_cast<size_t>(cal_n) + (dl & p.cal_mask)]; }
+                              atomicSub(at, 1u);
+                            }
+                          }
+                        }
+                      } else {   // this step's completions are in LDS too, behind them what has waited in the ring
+                        const int i = RR ? (gi == 0 ? nextL[0] + j : nextL[1] + j - placed_solo) : next + j;
+                        const int ci = i - (RR && gi ? dcount0_m : dcount0);
+                        constexpr int kHere = RR ? kJobsLds / 2 : kJobsLds;
+                        const bool here = ci >= 0 && ci < kHere;
+                        jw = L.jobs[here ? (RR && gi ? kHere : 0) + ci : 0];
+                        asm("" : "+v"(jw));   // (else the two loads become one through a pointer to either memory)
+                        if (!here) {
+                          uint32_t pos = (RR ? dheadL[gi] : dhead0) + static_cast<uint32_t>(i);
+                          if (pos >= dbuf_cap) pos -= dbuf_cap;
+                          if (pos >= dbuf_cap) pos -= dbuf_cap;
+                          if (!RR || gi == 0) jw = dring[pos]; else jw = dring_m[pos];
+                        }
+                      }
+                    }
+                  }
+                }
                 // ---- where the server stands: `it` iterations are completed; in the middle of one (`mid`: what it is given
                 //      now joins when that one ends), at a boundary, the iterations before it then being tallied, or idle.
                 //      A server that has had its event in this step is at the boundary it was started anew from.
@@ -2216,70 +2289,24 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
                     }
                   }
                 }
-                // ---- the jobs: which one of each level the server takes follows from its rank among the level's members
+                // ---- the jobs
                 int nd = n_own;
-                const bool has_prefill = g < Mp && (admitted || !(idle & bit));
-                const int gi = g >= M ? 0 : 1;
-                const int lmins = word_of(SC_LMIN);
-                const int first = gi == 0 ? 0 : nl_solo, my_lmin = gi == 0 ? lmins & 0xFFFF : lmins >> 16;
 #pragma unroll
                 for (int t = 0; t < kRouteLevels; ++t) {
-                  if (t < nl_mine) {   // wave-uniform
-                    const uint64_t in = wi >= lvl_first && wi < lvl_end ? L.bm_lvl[t * nwords + wi] : 0ull;
-                    const int q = static_cast<int>(L.pre_lvl[t * nwords + wi]) + __popcll(in & (bit - 1ull));
-                    if ((in & bit) && q < take_r[t]) {
-                      const int j = w_r[t] + q;   // position in this pass
-                      uint64_t jw;
-                      if constexpr (AB) {
-                        jw = L.jobs[j];
-                        if (fresh_kept) {
-                          const int i = RR && gi ? j - placed_solo : j;   // place in the group's buffer, live requests only
-                          const int ci = i - (RR && gi ? dcount0_m : dcount0);
-                          if (ci >= 0) {   // one of this step's completions: it leaves the calendar of its deadline
-                            const uint32_t fill = RR && gi ? dlen_all_m - static_cast<uint32_t>(ncm) : dlen_all - static_cast<uint32_t>(RR ? ncs : jrem - dcount0);
-                            uint32_t pos = (RR ? dheadL[gi] : dhead0) + fill + static_cast<uint32_t>(ci);
-                            if (pos >= dbuf_cap) pos -= dbuf_cap;
-                            if (pos >= dbuf_cap) pos -= dbuf_cap;
-                            constexpr int kHere = RR ? kJobsLds / 2 : kJobsLds;
-                            jw = L.fresh[(RR && gi ? kHere : 0) + (ci < kHere ? ci : 0)];
-                            asm("" : "+v"(jw));   // (see below)
-                            if (ci >= kHere) { if (!RR || gi == 0) jw = dring[pos]; else jw = dring_m[pos]; }
-                            uint32_t dl;
-                            if (!RR || gi == 0) dl = ddl[pos]; else dl = ddl_m[pos];
-                            if (dl != kNever) {
-                              uint32_t *at = &dcal[((jw >> 29) & 7u) * static_cast<size_t>(cal_n) + (dl & p.cal_mask)];
-                              if constexpr (RR) { if (gi) at = &dcal_m[((jw >> 29) & 7u) * static_cast<size_t>(cal_n) + (dl & p.cal_mask)]; }
-                              atomicSub(at, 1u);
-                            }
-                          }
-                        }
-                      } else {   // this step's completions are in LDS too, behind them what has waited in the ring
-                        const int i = RR ? (gi == 0 ? nextL[0] + j : nextL[1] + j - placed_solo) : next + j;
-                        const int ci = i - (RR && gi ? dcount0_m : dcount0);
-                        constexpr int kHere = RR ? kJobsLds / 2 : kJobsLds;
-                        const bool here = ci >= 0 && ci < kHere;
-                        jw = L.jobs[here ? (RR && gi ? kHere : 0) + ci : 0];
-                        asm("" : "+v"(jw));   // (else the two loads become one through a pointer to either memory)
-                        if (!here) {
-                          uint32_t pos = (RR ? dheadL[gi] : dhead0) + static_cast<uint32_t>(i);
-                          if (pos >= dbuf_cap) pos -= dbuf_cap;
-                          if (pos >= dbuf_cap) pos -= dbuf_cap;
-                          if (!RR || gi == 0) jw = dring[pos]; else jw = dring_m[pos];
-                        }
-                      }
-                      const int k = static_cast<int>(jw >> 29) & 7;
-                      const int slot = my_lmin + (t - first);   // the server holds exactly this many decodes by now
-                      const uint32_t ends = it + static_cast<uint32_t>(jw >> 48) + 1u + (mid ? 1u : 0u);
-                      nf = nd == 0 || ends < nf ? ends : nf;
-                      fin[static_cast<size_t>(g) * BS + slot] = ends;
-                      job[static_cast<size_t>(g) * BS + slot] = jw;
-                      nc += 1ull << (8 * k);
-                      if (mid) nj += 1ull << (8 * k);   // not part of the iterations still to be tallied for this server
-                      nd = slot + 1;
-                      lds_add64(&L.tl[k * kNTally + (has_prefill ? SIM_T_U_DM : SIM_T_U_DS)], 1);
-                      atomicAdd(&L.cs[(has_prefill ? CS_YM : CS_YS) + k], 1);
-                      atomicSub(&L.cs[CS_QD + k], 1);
-                    }
+                  if ((takes >> t) & 1u) {
+                    const uint64_t jw = job_of[t];
+                    const int k = static_cast<int>(jw >> 29) & 7;
+                    const int slot = my_lmin + (t - first);   // the server holds exactly this many decodes by now
+                    const uint32_t ends = it + static_cast<uint32_t>(jw >> 48) + 1u + (mid ? 1u : 0u);
+                    nf = nd == 0 || ends < nf ? ends : nf;
+                    fin[static_cast<size_t>(g) * BS + slot] = ends;
+                    job[static_cast<size_t>(g) * BS + slot] = jw;
+                    nc += 1ull << (8 * k);
+                    if (mid) nj += 1ull << (8 * k);   // not part of the iterations still to be tallied for this server
+                    nd = slot + 1;
+                    lds_add64(&L.tl[k * kNTally + (has_prefill ? SIM_T_U_DM : SIM_T_U_DS)], 1);
+                    atomicAdd(&L.cs[(has_prefill ? CS_YM : CS_YS) + k], 1);
+                    atomicSub(&L.cs[CS_QD + k], 1);
                   }
                 }
                 // ---- the next event
