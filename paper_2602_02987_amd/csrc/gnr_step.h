@@ -1777,7 +1777,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             gate_more = uniform(static_cast<int>(group_sum(left, lg))) > nadm;
           }
           if (tid == 0) L.sc[SC_NADM] = nadm | (gate_more ? 0x10000 : 0);
-          if (gate_mode == SIM_GATE_OCCUPANCY && (ncand << lg) > (n_gate << 6) && ncand > nadm &&
+          if (gate_mode == SIM_GATE_OCCUPANCY && (SMALL ? ncand << lg : ncand) > (n_gate << 6) && ncand > nadm &&
               __ballot(cnt2 > 0 && !(fabs(t2.nx) < 1e9)) == 0) {
             // Long queues offer up to `limit` candidates of every class, `limit` of which are admitted in all, and the others
             // need no rank. The keys of a class rise linearly, so a bound on the key tells how many of its candidates lie
@@ -1867,6 +1867,69 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           uint32_t stamp = kNever;
           if (few && (lane >> lg) < cnt2)
             stamp = gate_stamp(queue_cap, qring, lo_tab, head2, fresh2, s, k2, lane >> lg, kAdmChunk);
+          // Occupancy gate: the key is linear in the sequence number, so the candidates of a class before this one end at an
+          // estimate whose rounding errors are below 1e-8 while the terms are below 1e6: no comparison is needed unless it
+          // lies next to a whole number (equal keys among them). With larger terms the exact comparisons on both sides of
+          // the estimate are made, and if they say otherwise the rest is searched on the side they point to.
+          auto search_near = [](auto before, double est, int most) __attribute__((always_inline)) -> int {
+            int lo = 0, hi = most;
+            const int g0 = est > 0.0 ? (est < static_cast<double>(hi) ? static_cast<int>(est) : hi) : 0;
+            const int l2 = g0 > 1 ? g0 - 1 : 0, h2 = g0 + 2 < hi ? g0 + 2 : hi;
+            const bool b0 = l2 == 0 || before(l2 - 1), b1 = h2 < hi && before(h2);
+            if (b0) lo = b1 ? h2 + 1 : l2; else hi = l2 - 1;
+            if (b0 && !b1) hi = h2;
+            while (lo < hi) {
+              const int mid = (lo + hi) >> 1;
+              if (before(mid)) lo = mid + 1; else hi = mid;
+            }
+            return lo;
+          };
+          // A lane to a candidate, the classes one after another: half the instructions of a lane to each class, since a
+          // candidate's own key is formed once (10000 servers x 256 replications 20.0 -> 19.5 ms per 1000 steps, 2048 x 1024
+          // 19.0 -> 18.8). In workgroups of one or two waves, whose first wave ranks alone, the chain over the classes is
+          // longer than the rounds it saves where there are more than two (1024 servers of four classes x 2048 18.5 -> 18.7).
+          if (!SMALL && gate_mode == SIM_GATE_OCCUPANCY) {   // wave-uniform
+            const double base2 = static_cast<double>(xs2) - t2.nx;
+            const uint64_t some = __ballot(cnt2 > 0), moderate = __ballot(fabs(t2.nx) < 1e6);
+            for (int c0 = wave << 6; c0 < ncand; c0 += n_gate << 6) {   // wave-uniform
+              const int c = c0 + lane;
+              int k = 0;
+#pragma unroll
+              for (int kk = 1; kk < kMaxK; ++kk) k += c >= first_of[kk] ? 1 : 0;
+              const int m = c - __shfl(first_lane, k, 64);
+              const double own_nx = L.gtab[GT_NX * kMaxK + k], own_invx = L.gtab[GT_INVX * kMaxK + k];
+              const double a = (static_cast<double>(L.cs[CS_X + k] + m) - own_nx) * own_invx;   // as gate_key has it
+              int rank = m;
+              for (int j = 0; j < K; ++j) {   // wave-uniform
+                if (!((some >> j) & 1ull)) continue;
+                const int cnt = __builtin_amdgcn_readlane(cnt2, j);
+                const double reach = a * readlane_f64(t2.xstar, j), est = reach - readlane_f64(base2, j), up = ceil(est);
+                int n = static_cast<int>(up);   // (of one too large for it no use is made)
+                n = n < 0 ? 0 : (n < cnt ? n : cnt);
+                const bool small_terms = fabs(reach) < 1e6 && ((moderate >> j) & 1ull);
+                if (c < ncand && j != k && !(fabs((up - est) - 0.5) < 0.5 - 1e-6 && small_terms)) {
+                  const ClassTargets tj = load_targets(L.gtab, j);
+                  const int xj = __builtin_amdgcn_readlane(xs2, j), qj = __builtin_amdgcn_readlane(qp2, j);
+                  const GateKey key = {a, static_cast<double>(L.cs[CS_QP + k] - m) - L.gtab[GT_NQ * kMaxK + k]};
+                  auto before = [&](int i) __attribute__((always_inline)) -> bool {   // is the i-th of class j admitted before it
+                    return gate_before(gate_key(SIM_GATE_OCCUPANCY, queue_cap, tj, qring, lo_tab, xj, qj, 0u, 0u, s, j, i, kAdmChunk), j, key, k);
+                  };
+                  if (small_terms) {   // next to a whole number: that one is compared
+                    const int at = static_cast<int>(rint(est));
+                    n = at < 0 ? 0 : (at < cnt ? at + (before(at) ? 1 : 0) : cnt);
+                  } else {
+                    n = search_near(before, est, cnt);
+                  }
+                }
+                rank += j == k ? 0 : n;
+              }
+              if (c < ncand && rank < nadm) {
+                L.adm[rank] = static_cast<uint16_t>(k | (m << 3));
+                atomicAdd(&L.sc[SC_ADMK + k], 1);
+              }
+            }
+          } else {
+          const int mode_here = SMALL ? gate_mode : gate_mode == SIM_GATE_PRIORITY ? SIM_GATE_PRIORITY : SIM_GATE_FCFS;
           for (int c0 = wave << 6; c0 < (ncand << lg); c0 += n_gate << 6) {   // wave-uniform trip count
             const int c = (c0 + lane) >> lg;
             int k = 0, lo = 0;
@@ -1888,35 +1951,25 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               } else if (cnt2 > 0) {   // those before it form a prefix of the class
                 // this candidate's own key: one trip to LDS
                 const ClassTargets own = load_targets(L.gtab, k);
-                const GateKey key = gate_key(gate_mode, queue_cap, own, qring, lo_tab, L.cs[CS_X + k], L.cs[CS_QP + k],
+                const GateKey key = gate_key(mode_here, queue_cap, own, qring, lo_tab, L.cs[CS_X + k], L.cs[CS_QP + k],
                                              static_cast<uint32_t>(L.cs[CS_QHEAD + k]), fresh_of(k), s, k, m, kAdmChunk);
                 auto before = [&](int j) __attribute__((always_inline)) -> bool {   // is the j-th of class k2 admitted before it
-                  return gate_before(gate_key(gate_mode, queue_cap, t2, qring, lo_tab, xs2, qp2, head2, fresh2, s, k2, j, kAdmChunk), k2, key, k);
+                  return gate_before(gate_key(mode_here, queue_cap, t2, qring, lo_tab, xs2, qp2, head2, fresh2, s, k2, j, kAdmChunk), k2, key, k);
                 };
-                int hi = cnt2;
-                if (gate_mode == SIM_GATE_OCCUPANCY) {
-                  // The key is linear in the sequence number, so the prefix ends at an estimate whose rounding errors are
-                  // below 1e-8 while the terms are below 1e6: no comparison is needed unless it lies next to a whole
-                  // number (equal keys among them). There, or with larger terms, the exact comparisons on both sides of
-                  // it are made, and if they say otherwise the search below runs over the side they point to.
-                  const double reach = key.a * t2.xstar, est = reach - (static_cast<double>(xs2) - t2.nx);
-                  const int g0 = est > 0.0 ? (est < static_cast<double>(hi) ? static_cast<int>(est) : hi) : 0;
-                  if (fabs(est - rint(est)) > 1e-6 && fabs(reach) < 1e6 && fabs(t2.nx) < 1e6) {
-                    lo = est > 0.0 ? (g0 + 1 < hi ? g0 + 1 : hi) : 0;
-                    hi = lo;
-                  } else {
-                    const int l2 = g0 > 1 ? g0 - 1 : 0, h2 = g0 + 2 < hi ? g0 + 2 : hi;
-                    const bool b0 = l2 == 0 || before(l2 - 1), b1 = h2 < hi && before(h2);
-                    if (b0) lo = b1 ? h2 + 1 : l2; else hi = l2 - 1;
-                    if (b0 && !b1) hi = h2;
-                  }
+                if (SMALL && gate_mode == SIM_GATE_OCCUPANCY) {
+                  const double reach = key.a * t2.xstar, est = reach - (static_cast<double>(xs2) - t2.nx), up = ceil(est);
+                  if (fabs((up - est) - 0.5) < 0.5 - 1e-6 && fabs(reach) < 1e6 && fabs(t2.nx) < 1e6)
+                    lo = up > 0.0 ? (up < static_cast<double>(cnt2) ? static_cast<int>(up) : cnt2) : 0;
+                  else
+                    lo = search_near(before, est, cnt2);
                 } else if (gate_mode == SIM_GATE_PRIORITY) {   // one key for the whole class
-                  lo = before(0) ? hi : 0;
-                  hi = lo;
-                }
-                while (lo < hi) {
-                  const int mid = (lo + hi) >> 1;
-                  if (before(mid)) lo = mid + 1; else hi = mid;
+                  lo = before(0) ? cnt2 : 0;
+                } else {
+                  int hi = cnt2;
+                  while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (before(mid)) lo = mid + 1; else hi = mid;
+                  }
                 }
               }
             }
@@ -1925,6 +1978,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
               L.adm[rank] = static_cast<uint16_t>(k | (m << 3));
               atomicAdd(&L.sc[SC_ADMK + k], 1);
             }
+          }
           }
           }
         }
