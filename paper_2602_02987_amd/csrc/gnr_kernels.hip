@@ -76,6 +76,8 @@ int step_threads(Params q, int reps)
   // 3500 servers of eight classes, same-slot decode, 700 replications: three waves a compute unit in one round 12.1 ms,
   // sixteen in two rounds 3.7; 3000 servers of two classes, 2048 replications: four in two rounds 10.9, twelve in three
   // 6.3; but eight in one round 4.8 against sixteen in two 6.1, 1000 servers, weighted router).
+  // (These figures and those below are of the kernel that gave every wave every segment; the present one shares the segments
+  // out and takes 0.6 to 0.85 of the time in the shapes chosen.)
   // Of 424 launches timed in every shape (33 to 4600 servers, 200 to 4096 replications) 89 % take the fastest or one within
   // 3 % of it, 97 % one within 10 %. The others: 11 to 27 % where 3000 to 4000 servers leave a compute unit six waves in one
   // round, up to 17 % with 300 to 400 servers (eight waves instead of four on 512 replications, one instead of two on 4096),

@@ -1,8 +1,8 @@
 // HIP kernels of the gate-and-route network simulator (gfx950, wave64).
 //
 // One workgroup owns one replication for a whole launch and loops over the steps itself. The servers are
-// handled in blocks of 64 (one per lane); wave w owns the blocks w, w + nwaves, ..., and a server's clock, record and
-// slot row are changed by the wave that owns it, except for the placements of the router. A server is touched only
+// handled in blocks of 64 (one per lane); wave w owns the blocks w, w + nwaves, ... in the completion pass, and what a
+// step gives a server is written by the last waves of the workgroup, a barrier later. A server is touched only
 // when its batch changes (an event): the identical iterations in between follow from its event time. Class-level
 // counters (queue lengths, occupancies, tallies) live in LDS and are updated with integer atomics, which commute, by the
 // lanes that have something to add (a few of a wave as a rule; sums that all lanes add to are spread over several words).
@@ -375,9 +375,10 @@ __host__ __device__ constexpr int size_class(int threads, int nwords)
 // 512 / this many). A workgroup of 1024 threads needs four; the smaller classes are compiled twice: roomy, with up
 // to 256 registers and two waves per SIMD, taken while every workgroup of the launch finds a place at that density, and
 // dense, with 128 registers and four waves per SIMD, for launches that would otherwise run their workgroups in more
-// rounds. Registers roomy / dense (spilled when dense): base and same-slot decode 120 / 120 in eight waves, the same code,
-// 128 / 128 in one or two; randomized router 121 / 121, 129 / 128 (1); with deadline rings 131 to 138 / 128 (2 to 6) and 140
-// to 148 / 128 (8 to 16). So only the deadline rings' forms differ by more than a register.
+// rounds. Registers roomy / dense (spilled when dense): base and randomized router 107 in eight waves and 116 in one or two,
+// same-slot decode 105 and 114, the same code in both forms; with deadline rings 117 to 122 in eight waves, 127 to 132 / 128
+// (up to 2) in one or two; weighted router 132 / 128 (2) and 142 / 128 (2). So only the forms of the weighted router, and with
+// deadline rings those of one or two waves, differ.
 __host__ __device__ constexpr int waves_per_simd(int max_threads, bool dense)
 {
   return max_threads > 512 || dense ? 4 : 2;
@@ -1494,12 +1495,14 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
     // and so on. One pass fills up to kRouteLevels such levels at once. Level t takes take_t jobs, the first
     // of them job w_t of the pass; the server of rank q among those with at most lmin+t decodes takes job
     // w_t + q into slot lmin+t. Every lane places the jobs of its own server.
-    // Both run side by side in passes of three segments with a barrier after each:
-    //   A  gate: rank the candidates          routing: pass parameters from the load histogram, then the
-    //                                          servers of each level are counted per 64-server word
-    //   B  gate: admissions take their slots  routing: one wave per level turns the counts into ranks
-    //   C  gate: class counters               routing: placement; in the last pass every lane then restarts
-    //                                          its servers
+    // Both run side by side in passes of two segments with a barrier after each, the waves being shared out:
+    //   A  the first half of the waves ranks the gate's candidates; the others take the pass's parameters from the load
+    //      histograms and find the members of each level as bitmaps
+    //   C  the last waves find the servers that are given work and serve them (admission, jobs, next event); the others
+    //      draw the next step's arrivals; class counters
+    // (A server at its event starts its next iteration in the completion pass, in the same lane. With a pass over all touched
+    // servers at the end of the step, every wave in every segment and five barriers a step, 10000 servers x 256 replications
+    // took 26.0 ms per 1000 steps instead of 22.0, 1024 x 2048 28.1 instead of 22.5.)
     // One pass is the rule; more follow only when more than kAdmChunk slots are idle or the jobs reach past
     // kRouteLevels levels or into the mixed group.
     {
