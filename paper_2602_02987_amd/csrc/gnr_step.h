@@ -995,7 +995,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
       const uint32_t t2 = ((s >> 8) + (static_cast<uint32_t>(r) >> 8)) & 1u;
       if (t2 != turn) { turn = t2; own_priority(); }
     }
-    // (No barrier here: a wave goes from its last settling straight into the next step's completion pass. Until the
+    // (No barrier here: a wave goes from a step's last pass straight into the next step's completion pass. Until the
     // barrier that ends it a wave touches its own servers and bitmap words only, and adds to sums that nobody reads before.)
     // abandonment only: how many waiting requests of class `tid` leave at the start of this step (asked for
     // here, used after the completion pass)
@@ -1562,8 +1562,6 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
         // buffers (each buffer has a wave of its own, on different SIMDs).
         const int ring_wave = nwaves >= 8 ? route_first : nwaves - 1;
         const int ring_wave_m = nwaves >= 8 ? route_first + 1 : nwaves - 1;
-        // the weighted router's selection is long: it runs in segment A beside the gate's ranking, on waves that are
-        // given nothing else to do there; the plain walk of a ring runs in segment B
         // one wave walks a ring from where the last pass stopped and stages the next `need` waiting jobs
         // (in the first pass this step's completions may not have reached the ring: they are taken from `fresh`)
         const bool fresh_kept = AB && !WS && nwaves > 1 && pass == 0;
