@@ -27,13 +27,19 @@ _TARGETS = {
 
 
 @pytest.mark.parametrize("targets", list(_TARGETS))
-@pytest.mark.parametrize("N,laid_out,K,theta", [(2000, 2500, 8, 0.0), (2000, 2500, 3, 0.0), (600, 8, 6, 0.2), (700, 8, 2, 0.0)])
-def test_long_queues(B, oracle_mod, targets, N, laid_out, K, theta):
+# servers, replications the handle is laid out for, waves a workgroup then has (from four on a lane takes a candidate and goes
+# through the classes, below that the classes have a lane each), classes, patience rate
+@pytest.mark.parametrize("N,laid_out,waves,K,theta", [
+    (2000, 2500, 2, 8, 0.0), (2000, 2500, 2, 3, 0.0), (600, 8, 8, 6, 0.2), (700, 8, 8, 2, 0.0),
+    (1000, 2100, 1, 5, 0.0), (1500, 600, 4, 8, 0.0), (1500, 600, 4, 3, 0.2), (700, 8, 8, 8, 0.0), (2000, 4, 16, 8, 0.2), (2000, 4, 16, 7, 0.0),
+])
+def test_long_queues(B, oracle_mod, targets, N, laid_out, waves, K, theta):
     # more arrivals than the mixed group can take; constant prompts, so that many slots fall free together
     cls = [_limits_class(lam=3.0 * (k + 1) / (K * (K + 1) / 2), in_p0=250.0 + 250.0 * (k % 2), out_p0=3.0, theta=theta) for k in range(K)]
     cfg = _limits_cfg("cut", cls, N=N, M=N // 60, B=6, steps=0, x_star=[_TARGETS[targets](k) for k in range(K)],
                       queue_cap=4096, dbuf_cap=2048)
     cfg = replace(cfg, qp_star=[0.01 * (k % 3) for k in range(K)])
+    assert B.sim_launch_plan(cfg, laid_out)[0] == 64 * waves
     sim, orc = B.Sim(cfg, max_replications=laid_out), oracle_mod.Oracle(cfg)
     for M, n in ((N // 60, 120), (N // 5, 1), (N // 5, 40), (N // 20, 60)):
         for e in (sim, orc):

@@ -1,6 +1,7 @@
 """GPU parity where the gate's ranking and the routing pass change form: one to eight classes (two, four or eight lanes to
 a candidate), every gate, all routers, workgroups of two waves that own many words and queue more servers in a pass than
-the queue holds, and of several waves with a ragged last word."""
+the queue holds, and of several waves with a ragged last word; and where the groups of servers end inside or on the border of
+the sixteen servers that a lane of the level pass looks at."""
 from dataclasses import replace
 
 import pytest
@@ -52,3 +53,21 @@ def test_pass_shapes(B, oracle_mod, N, laid_out, K, gate, route, theta):
             assert_replication_equal(sim, orc, r, what=f"N={N} K={K} {gate} {route} after {orc.steps_done()} steps")
     assert_stats_equal(sim.stats(), orc.stats())
     assert orc.stats()["tally"][:, 6:8].sum() > N // 8   # decodes have ended
+
+
+# Both groups take jobs on several levels until no slot is left. Split and end of the servers on, before and behind a border of
+# sixteen servers and of a word; one wave and (N > 64) several.
+@pytest.mark.parametrize("laid_out", [4, 4500])
+@pytest.mark.parametrize("N,M", [(15, 7), (16, 15), (17, 16), (31, 1), (33, 17), (48, 32), (63, 31), (64, 48), (65, 33), (80, 63), (81, 64),
+                                 (127, 65), (129, 79), (161, 80), (337, 161)])
+def test_level_borders(B, oracle_mod, N, M, laid_out):
+    cls = [_limits_class(lam=2.2, in_p0=60.0, out_p0=260.0), _limits_class(lam=1.6, in_p0=120.0, out_p0=400.0)]
+    cfg = _limits_cfg("levels", cls, N=N, M=M, B=5, steps=0, x_star=[0.3, 0.3], queue_cap=4096, dbuf_cap=2048)
+    sim, orc = B.Sim(cfg, max_replications=laid_out), oracle_mod.Oracle(cfg)
+    for n in (60, 1, 140, 300):
+        sim.run(n, cfg.replications)
+        orc.run(n)
+        for r in range(cfg.replications):
+            assert_replication_equal(sim, orc, r, what=f"N={N} M={M} after {orc.steps_done()} steps")
+    loads = orc.slots(0)["n_dec"]
+    assert loads[M:].max() == 5 and loads[:M].max() == 4 and loads[M:].min() >= 3   # both groups were filled
