@@ -1,6 +1,6 @@
-"""One- and two-wave workgroups whose tables share space (the lanes that scan slot rows with the admissions, the ranks of
-completions and idle slots with those of the routing levels, and in one wave the completed prefills with the last routing
-level): against the oracle with a few and with many words, several gate passes and several levels a step."""
+"""One- and two-wave workgroups, whose tables are small (64 admissions and 64 staged requests a pass, 96 queued servers a
+wave) and whose ranks of completions share space with those of the routing levels: against the oracle with a few and with
+many words, several gate passes and several levels a step."""
 from dataclasses import replace
 
 import pytest
