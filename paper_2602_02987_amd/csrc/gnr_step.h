@@ -290,7 +290,6 @@ struct Lds {
   uint16_t *sel_co;   // [kJobsLds] class | (how many selections before it chose the same class) << 3
   uint16_t *sel_j;    // [kJobsLds] list position of each selection, ordered by class, then by order within the class
   int32_t *sel_n;     // [8] requests the pass takes from the solo group's buffer, per class
-  uint64_t *spare;    // [4] (held: see the total)
 };
 
 // Carves the dynamic LDS block; 8-byte granules. NWS > 0: the arrays indexed by 64-server word are sized for NWS
@@ -359,9 +358,8 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(sel_co, uint16_t, p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? kJobsLds : 0)
   GNR_TAKE(sel_j, uint16_t, p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? kJobsLds : 0)
   GNR_TAKE(sel_n, int32_t, p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? 8 : 0)
-  GNR_TAKE(spare, uint64_t, p.route_mode == SIM_ROUTE_RANDOM_SPLIT || p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? 4 : 0)
 #undef GNR_TAKE
-  if (total) *total = off;
+  if (total) *total = off + (nw_two ? 32 : 0);   // (held like the rest, with two buffers)
   return L;
 }
 // Size classes of the step kernel: 0 workgroups of one or two waves (small tables, arrays sized by the
@@ -411,28 +409,6 @@ __device__ __forceinline__ uint32_t rank_bitmap(const uint64_t *bm, uint16_t *pr
   return running;
 }
 
-// Wave totals with data-parallel-primitive adds: four steps inside each row of 16 lanes, then the row
-// totals are passed on (row 0 -> 1, 2 -> 3, then 1 -> 2 and 3); lane 63 ends with the total, which is
-// returned as a wave-uniform value. All 64 lanes must be active.
-__device__ __forceinline__ uint32_t wave_sum32(uint32_t v)
-{
-  v = dpp_add<0xB1, 0xF>(v);    // quad_perm [1,0,3,2]
-  v = dpp_add<0x4E, 0xF>(v);    // quad_perm [2,3,0,1]
-  v = dpp_add<0x141, 0xF>(v);   // row_half_mirror
-  v = dpp_add<0x140, 0xF>(v);   // row_mirror
-  v = dpp_add<0x142, 0xA>(v);   // row_bcast 15 into rows 1 and 3
-  v = dpp_add<0x143, 0xC>(v);   // row_bcast 31 into rows 2 and 3
-  return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(v), 63));
-}
-// 64-bit total of values below 2^58: three 32-bit totals of 16-, 16- and 26-bit pieces.
-__device__ __forceinline__ uint64_t wave_sum64(uint64_t v)
-{
-  const uint64_t s0 = wave_sum32(static_cast<uint32_t>(v) & 0xFFFFu);
-  const uint64_t s1 = wave_sum32(static_cast<uint32_t>(v >> 16) & 0xFFFFu);
-  const uint64_t s2 = wave_sum32(static_cast<uint32_t>(v >> 32));
-  return s0 + (s1 << 16) + (s2 << 32);
-}
-
 // The same value of the lane that a data-parallel-primitive control pairs this one with.
 template <int CTRL>
 __device__ __forceinline__ double dpp_of(double v)
@@ -463,17 +439,6 @@ __device__ __forceinline__ double readlane_f64(double v, int l)
   const uint32_t lo = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(b), l));
   const uint32_t hi = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(b >> 32), l));
   return __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo));
-}
-
-// Sum over the wave of per-class byte vectors (8 x uint8, each <= 128): 16-bit fields, even and odd classes.
-__device__ __forceinline__ void wave_sum_bytes(uint64_t v, uint64_t &even, uint64_t &odd)
-{
-  even = wave_sum64(v & 0x00FF00FF00FF00FFull);
-  odd = wave_sum64((v >> 8) & 0x00FF00FF00FF00FFull);
-}
-__device__ __forceinline__ uint32_t class_field(uint64_t even, uint64_t odd, int c)
-{
-  return static_cast<uint32_t>(((c & 1) ? odd : even) >> (16 * (c >> 1))) & 0xFFFFu;
 }
 
 // Adds the tallies of executed iterations to the workgroup's totals: per lane
