@@ -73,27 +73,28 @@ int step_threads(Params q, int reps)
   // blocks of servers to work on and all workgroups of the launch find a place at once (at most four waves per SIMD): the
   // largest workgroup that keeps the rounds lowest. Rounds count as they are while a full compute unit holds two waves a
   // SIMD or more; with fewer nothing hides a wave's latency, and a round counts by as much as waves are missing (100 steps,
-  // 3500 servers of eight classes, same-slot decode, 700 replications: three waves a compute unit in one round 12.1 ms,
-  // sixteen in two rounds 3.7; 3000 servers of two classes, 2048 replications: four in two rounds 10.9, twelve in three
-  // 6.3; but eight in one round 4.8 against sixteen in two 6.1, 1000 servers, weighted router).
-  // (These figures and those below are of the kernel that gave every wave every segment; the present one shares the segments
-  // out and takes 0.6 to 0.85 of the time in the shapes chosen.)
-  // Of 424 launches timed in every shape (33 to 4600 servers, 200 to 4096 replications) 89 % take the fastest or one within
-  // 3 % of it, 97 % one within 10 %. The others: 11 to 27 % where 3000 to 4000 servers leave a compute unit six waves in one
-  // round, up to 17 % with 300 to 400 servers (eight waves instead of four on 512 replications, one instead of two on 4096),
-  // 9 % with two waves instead of one at 127 to 190 servers in dense rounds, and with sixteen instead of eight on 800 to
-  // 1000 servers with patience and 200 replications.
-  // With fewer than two blocks to a wave the larger workgroup gains nothing where the launch needs more than two waves a SIMD
-  // for it (256 servers, 1024 replications: 128 threads 11.3 ms per 1000 steps, 256 threads 11.4). With deadline rings
-  // eight waves pay in the dense form too, from a block a wave on: the walks of the rings and the class selection take waves
-  // of their own, which in four waves rank and count beside it (500 steps of 512 replications, 256 threads roomy -> 512
-  // dense: abandonment, 700 servers 8.9 -> 8.3 ms; weighted router 12.7 -> 10.8; convergence instance of 500 servers
-  // 8.4 -> 7.8. Without such rings -4 to +3 %: 600 servers of two classes 6.4 -> 6.6; four waves instead of two -4 to +1 %
-  // with them).
+  // 3500 servers of eight classes, same-slot decode, 700 replications: three waves a compute unit in one round 8.7 ms,
+  // sixteen in two rounds 3.2; 3000 servers of two classes, 2048 replications: four in two rounds 6.6, twelve in three
+  // 4.4; but eight in one round 3.3 against sixteen in two 4.1, 1000 servers of four classes, weighted router, 2048).
+  // With fewer than two blocks to a wave the larger workgroup is left out where the launch needs more than two waves a SIMD
+  // for it. That holds from four waves to eight (500 steps of 512 replications, 256 threads roomy, 512 dense: 600 servers
+  // of two classes 4.4 and 4.7 ms, 700 of four 5.1 and 5.6). With deadline rings eight dense waves are taken from a block a wave
+  // on: the walks of the rings and the class selection take waves of their own. It pays with the weighted router (700
+  // servers of four classes 8.4 and 8.1 ms), no longer without (with patience 5.8 and 6.2, convergence instance of 500
+  // servers 5.7 and 5.8).
+  // The rule was set with a kernel that gave every wave every segment of a step; its lines were timed again with the present
+  // one (the figures here) and stand where they were. Of 400 launches timed in every shape (33 to 4600 servers, 200 to 4096
+  // replications, all routers and gates) it takes the fastest in 76 %, one within 3 % of it in 85 %, one within 10 % in 92 %.
+  // The others: one wave instead of two, dense, with 65 to 190 servers and 1024 to 2048 replications (up to 32 %), two instead of
+  // four with 140 to 380 servers and 500 to 1000 (up to 16 %; 256 servers, 1024 replications, 1000 steps 9.1 and 8.8 ms) and with
+  // 1200 to 1900 servers and 2000 to 4000 (up to 19 %), six waves a compute unit instead of sixteen with 3500 servers (29 to
+  // 41 %), sixteen a workgroup instead of eight with 2000 to 4600 servers and 200 to 260 (4 to 8 %).
   constexpr int kRound = 840;   // (divisible by one to eight waves)
   const int blocks = (q.N + 63) / 64;
   int best = 64, best_cost = 0;
-  for (int t = 64; t <= 1024 && t / 64 < 2 * blocks; t *= 2) {   // (a wave more than there are blocks only waits)
+  // (no more waves than fewer than twice the blocks. Gate, router and serving have waves of their own, so one more can still pay:
+  // two waves with 33 to 64 servers take 3 to 23 % less than the one they get here, four with 65 to 128 up to 13 %)
+  for (int t = 64; t <= 1024 && t / 64 < 2 * blocks; t *= 2) {
     q.threads = t;
     const size_t lds = step_lds_bytes(q);
     if (lds > kLdsPerComputeUnit) break;
