@@ -19,18 +19,18 @@ FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-ffp-contract=o
          # no packed fp32 instructions in device code (the host pass does not know the feature and says so)
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wall", "-Wno-unused-function",
          # atomics stay one per lane: a few lanes of a wave have something to add as a rule, and where all have the sum is
-         # spread over several words. The compiler's rewrite into wave-wide scans costs 5 % with 1024 servers x 2048
-         # replications (28.1 -> 29.4 ms per 1000 steps), 9 % with the weighted router (11.3 -> 12.2 per 300), 7 % with
-         # immediate decode (22.8 -> 24.4 per 2000), nothing with 10000 servers x 256, and gives 1 % with 256 x 1024
+         # spread over several words. The compiler's rewrite into wave-wide scans costs 60 % with the randomized router (10000
+         # servers x 256 replications 6.9 -> 11.0 ms per 300 steps), 46 % with the weighted one (9.0 -> 13.0), 14 % with
+         # immediate decode (19.8 -> 22.6 per 2000), 7 % with the convergence instance, 0 to 1 % with the base router
          "-mllvm", "-amdgpu-atomic-optimizer-strategy=None",
-         # loops are unrolled where the source asks for it (#pragma unroll); measured faster than unrolling the others by
-         # heuristic too with the kernel that executed every iteration, with this one 0 to 1.5 % slower on the timed cases
-         # (10000 servers x 256 replications 25.6 -> 26.0 ms per 1000 steps) and 2 % smaller
+         # loops are unrolled where the source asks for it (#pragma unroll). Unrolling the others by heuristic too, which the kernel
+         # that executed every iteration lost by, changes the timed cases by -0.7 to +0.4 % with this one, which is noise
          "-fno-unroll-loops",
          # the step kernel lives at its register limit: loop strength reduction and the hoisting of loop invariants
-         # in machine code both trade registers for instructions, which here ends in spills (sixteen waves: base form 22
-         # registers with them and none without, weighted router 41 and 4; 10000 servers x 256 replications 27.9 -> 26.0 ms
-         # per 1000 steps, 1024 x 2048 29.9 -> 28.1, weighted router 11.9 -> 11.3 per 300)
+         # in machine code both trade registers for instructions, which here ends in spills (sixteen waves: base form 7
+         # registers with them and none without, weighted router 28 and 2; two waves dense 6 and none). They cost 3 % with 1024
+         # servers x 2048 replications (17.9 -> 18.5 ms per 1000 steps) and with the convergence instance, 4 % with the weighted
+         # router (9.0 -> 9.3 per 300), 1 % with 2048 x 1024, nothing with 10000 x 256, and give 1 % with 256 x 1024
          "-mllvm", "-disable-lsr", "-mllvm", "-disable-machine-licm"]
 
 
