@@ -214,21 +214,22 @@ __device__ __forceinline__ void lds_add64(uint64_t *p, uint64_t v)
 enum Scalar {
   SC_NIDLE = 0, SC_NCOMP,
   SC_HEAD = 2,    // [8] head of each class queue as the pass's admissions find it
-  // abandonment only:
+  // two-buffer routers only:
+  SC_NSOLO = 13,  // completed prefills of this step whose request goes to the solo group
+  // deadline rings (abandonment, weighted router) only:
   SC_DLEN = 10,   // entries of the decode buffer ring between head and tail, abandoned ones included
   SC_DSCAN = 11,  // entries of that ring the routing passes of this step have gone past
-  SC_COMPACT = 12,// bit k: class queue ring k (bit 8: the decode buffer ring) must be compacted before the appends
-  SC_NSOLO = 13,  // two-buffer routers: completed prefills of this step whose request goes to the solo group
-  // randomized router only:
-  SC_DLEN_M = 15, // randomized router with abandonment: SC_DLEN / SC_DSCAN of the mixed group's buffer ring
+  SC_COMPACT = 12,// bit k: class queue ring k (bits 8, 9: the decode buffer rings) must be compacted before the appends
+  SC_DLEN_M = 15, // two buffers: SC_DLEN / SC_DSCAN of the mixed group's buffer ring
   SC_DSCAN_M = 60,
-  SC_NADM = 61,   // admissions of the pass (bit 16: another gate pass follows)
-  SC_LEVELS = 62, // the pass's routing levels: how many, of them the solo group's (8 bits each), bit 16: another pass follows
-  SC_LMIN = 63,   // lowest level of the solo and (16 bits up) of the mixed group
   SC_QLEN = 32,   // [8] entries of each class queue ring between head and tail, abandoned ones included
+  // every variant:
   SC_TAKE = 16,   // [8] accepted arrivals this step
   SC_TAIL = 24,   // [8] ring position of the first accepted arrival
   SC_ADMK = 40,   // [8] admissions per class in this gate pass
+  SC_NADM = 61,   // admissions of the pass (bit 16: another gate pass follows)
+  SC_LEVELS = 62, // the pass's routing levels: how many, of them the solo group's (8 bits each), bit 16: another pass follows
+  SC_LMIN = 63,   // lowest level of the solo and (16 bits up) of the mixed group
   SC_TAKE_T = 48, // [kRouteLevels] jobs each level of the routing pass takes
   SC_CNT_T = 52,  // [kRouteLevels] servers with exactly the level's decodes
   SC_W_T = 56,    // [kRouteLevels] jobs of the pass that come before each level
@@ -337,11 +338,13 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(fresh, uint64_t, p.dl_rings && waves > 1 ? kJobsLds : 0)
   GNR_TAKE(ta, uint64_t, (TA_TBT + (NWS ? kMaxK : p.K)) * (SMALL ? kTallyRowsSmall : kTallyRows))
   // What is refused for want of room, and how many workgroups share a compute unit, follows from the total. Both were set
-  // and measured with the tables of a kernel that executed every iteration (two words and a row list per queued server,
-  // four-byte ranks, ...), and the total is theirs in every configuration: the tables above never need more (one and two
-  // waves go up to 5120 servers), and where they need less (12 KB of 145 with 10000 servers) the rest is held free. A few
-  // bytes more cost a round or half the waves (200 steps: 33 servers of eight classes with patience, 4096 replications,
-  // 10248 bytes in two rounds 4.9 ms, 10032 in one 3.2; 100 steps: 900 servers, 2048 replications 4.8, 4.2).
+  // with the tables of a kernel that executed every iteration (two words and a row list per queued server, four-byte
+  // ranks, ...), and the total is theirs in every configuration: the tables above never need more (one and two waves go up
+  // to 5120 servers), and where they need less the rest is held free: 18,000 bytes of 148,368 with 10000 servers of six
+  // classes, 3,920 of 38,800 with 2048 of eight, 1,520 of 20,112 with 1024 of four. A few bytes more cost a round or half
+  // the waves (200 steps: 33 servers of eight classes with patience, 4096 replications, 10248 bytes in two rounds 4.7 ms,
+  // 10032 in one 3.1; 100 steps: 900 servers of eight classes with patience, 2048 replications, 20488 bytes in two rounds
+  // 5.5 ms, 20424 in one 3.1).
   constexpr size_t held_fixed = sizeof(uint64_t) * (kTallyWords + kJobsLds) + sizeof(int32_t) * (CS_WORDS + SC_WORDS + kMaxK) +
                                 sizeof(double) * 5 * kMaxK + 6 * kAdmChunk + sizeof(uint32_t) * 2 * kLoadBins;
   const size_t held = held_fixed + waves * (8 * kEvPerWave + 256) + 80 * nw + 2 * ((4 * (nw + 1) + 7) & ~size_t(7));
@@ -604,7 +607,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   // finish every sweep early and the last four late, and the barrier waits for those. Raising the priority of the
   // younger waves evens this out. Workgroups of up to four waves share their SIMDs with others of their kind: the draw of the
   // next step's arrivals has a lower priority than the rest (nobody waits for it as long as another wave serves), and
-  // workgroups that follow one another by as many as there are compute units, and so come to share one, take turns at
+  // workgroups that follow one another by as many as there are compute units (256), and so come to share one, take turns at
   // a higher one. Left to the order of their age the youngest end last, alone with the SIMD: 1024 servers x 2048
   // replications 18.4 -> 17.9 ms per 1000 steps, 256 x 1024 9.42 -> 9.19, 2048 x 1024 18.6 -> 18.1 (turns of 128 steps the same,
   // of 16 steps half of it).
@@ -1852,8 +1855,11 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           };
           // A lane to a candidate, the classes one after another: half the instructions of a lane to each class, since a
           // candidate's own key is formed once (10000 servers x 256 replications 20.0 -> 19.5 ms per 1000 steps, 2048 x 1024
-          // 19.0 -> 18.8). In workgroups of one or two waves, whose first wave ranks alone, the chain over the classes is
-          // longer than the rounds it saves where there are more than two (1024 servers of four classes x 2048 18.5 -> 18.7).
+          // 19.0 -> 18.8). In workgroups of one or two waves, whose first wave ranks alone and decides 64 admissions a pass, it
+          // gains nothing but with the fewest servers, and the chain over the classes costs as much as it saves; a lane to each
+          // class stays there. Measured with a lane to a candidate against a lane to each class: 8 servers of two classes 0.98,
+          // 256 x 1024 and 700 x 2048 of two 1.003 and 1.005, 1024 x 2048 of two 0.999, of four 1.012, of eight 1.003, 128 x
+          // 4096 of two 1.012 (the runs of one side differ by 0.5 %).
           if (!SMALL && gate_mode == SIM_GATE_OCCUPANCY) {   // wave-uniform
             const double base2 = static_cast<double>(xs2) - t2.nx;
             const uint64_t some = __ballot(cnt2 > 0), moderate = __ballot(fabs(t2.nx) < 1e6);
@@ -2449,7 +2455,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
           if constexpr (WS) {   // what the pass took from the solo group's buffer, per class
             if (tid >= NT - 64 && lane < K) L.cs[CS_QDS + lane] -= L.sel_n[lane];
           }
-          if (wave == route_first && lane == 0) {   // (by differences: another wave may already be at the next step's events)
+          if (wave == route_first && lane == 0) {   // (nobody else is at the histograms before the barrier; an add waits for no old count)
 #pragma unroll
             for (int gi = 0; gi < 2; ++gi) {
               if (nG[gi] > 0) {
