@@ -14,14 +14,12 @@ size_t step_lds_bytes(const Params &p)
   // same code as on the device forms the pointers, and those stay inside a real object this way (the largest
   // configuration the library accepts needs less than a fifth of it).
   alignas(16) static unsigned char block[1 << 20];
-  size_t total = 0;
   switch (size_class(p.threads, p.nwords)) {
-    case 0: lds_carve<static_words(0), true>(p, block, &total); break;
-    case 1: lds_carve<static_words(1)>(p, block, &total); break;
-    case 2: lds_carve<static_words(2)>(p, block, &total); break;
-    default: lds_carve<static_words(3)>(p, block, &total); break;
+    case 0: return lds_carve<static_words(0), true>(p, block).bytes;
+    case 1: return lds_carve<static_words(1)>(p, block).bytes;
+    case 2: return lds_carve<static_words(2)>(p, block).bytes;
+    default: return lds_carve<static_words(3)>(p, block).bytes;
   }
-  return total;
 }
 
 constexpr size_t kLdsPerComputeUnit = 160 * 1024;

@@ -291,6 +291,7 @@ struct Lds {
   uint16_t *sel_co;   // [kJobsLds] class | (how many selections before it chose the same class) << 3
   uint16_t *sel_j;    // [kJobsLds] list position of each selection, ordered by class, then by order within the class
   int32_t *sel_n;     // [8] requests the pass takes from the solo group's buffer, per class
+  size_t bytes;       // of the whole block
 };
 
 // Carves the dynamic LDS block; 8-byte granules. NWS > 0: the arrays indexed by 64-server word are sized for NWS
@@ -301,7 +302,7 @@ struct Lds {
 constexpr int kStaticWordsLarge = kMaxN / 64;   // any N the library accepts
 constexpr int kStaticWordsMedium = 160;          // N up to 10240: three kilobytes less
 template <int NWS, bool SMALL = false>
-__host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char *base, size_t *total)
+__host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char *base)
 {
   constexpr int kEvPerWave = SMALL ? kEvPerWaveSmall : gnr::kEvPerWave;       // (these shadow the large tables' sizes)
   constexpr int kJobsLds = SMALL ? kJobsLdsSmall : gnr::kJobsLds;
@@ -362,7 +363,7 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(sel_j, uint16_t, p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? kJobsLds : 0)
   GNR_TAKE(sel_n, int32_t, p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? 8 : 0)
 #undef GNR_TAKE
-  if (total) *total = off + (nw_two ? 32 : 0);   // (held like the rest, with two buffers)
+  L.bytes = off + (nw_two ? 32 : 0);   // (held like the rest, with two buffers)
   return L;
 }
 // Size classes of the step kernel: 0 workgroups of one or two waves (small tables, arrays sized by the
@@ -593,7 +594,7 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   constexpr int kJobsLds = SMALL ? kJobsLdsSmall : gnr::kJobsLds;
   constexpr int kAdmChunk = SMALL ? kAdmChunkSmall : gnr::kAdmChunk;
   constexpr int kTallyRowsHere = SMALL ? kTallyRowsSmall : kTallyRows;
-  const Lds L = lds_carve<NWS, SMALL>(p, lds_raw, nullptr);
+  const Lds L = lds_carve<NWS, SMALL>(p, lds_raw);
 
   const int r = blockIdx.x;
   const int tid = threadIdx.x;
