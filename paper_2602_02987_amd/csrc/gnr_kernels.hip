@@ -86,7 +86,8 @@ int step_threads(Params q, int reps)
   // The others: one wave instead of two, dense, with 65 to 190 servers and 1024 to 2048 replications (up to 32 %), two instead of
   // four with 140 to 380 servers and 500 to 1000 (up to 16 %; 256 servers, 1024 replications, 1000 steps 9.1 and 8.8 ms) and with
   // 1200 to 1900 servers and 2000 to 4000 (up to 19 %), six waves a compute unit instead of sixteen with 3500 servers (29 to
-  // 41 %), sixteen a workgroup instead of eight with 2000 to 4600 servers and 200 to 260 (4 to 8 %).
+  // 41 %), sixteen a workgroup instead of eight with 2000 to 4600 servers and 200 to 260 (4 to 8 %), eight dense waves instead of
+  // four with 500 to 1600 servers and 250 to 510 (2 to 9 %).
   constexpr int kRound = 840;   // (divisible by one to eight waves)
   const int blocks = (q.N + 63) / 64;
   int best = 64, best_cost = 0;

@@ -1855,10 +1855,13 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
             return lo;
           };
           // A lane to a candidate, the classes one after another: half the instructions of a lane to each class, since a
-          // candidate's own key is formed once (10000 servers x 256 replications 20.0 -> 19.5 ms per 1000 steps, 2048 x 1024
-          // 19.0 -> 18.8). In workgroups of one or two waves, whose first wave ranks alone and decides 64 admissions a pass, it
-          // gains nothing but with the fewest servers, and the chain over the classes costs as much as it saves; a lane to each
-          // class stays there. Measured with a lane to a candidate against a lane to each class: 8 servers of two classes 0.98,
+          // candidate's own key is formed once. It pays where candidates are many (10000 servers x 256 replications past a load
+          // peak 22.9 -> 22.5 ms per 1000 steps, 2048 x 1024 18.9 -> 18.7) and with two classes (1024 x 256 8.7 -> 8.6). Where a lane
+          // to each class takes one round of the waves anyway, the chain over the classes is longer: 1024 x 256 of four classes
+          // 10.5 -> 10.7, 1000 x 200 of six 10.2 -> 10.5, 2048 x 256 of eight 12.4 -> 13.2. (Both forms in one kernel, the few
+          // candidates by class, take these back and cost two-class launches 1 to 2 %.) In workgroups of one or two waves, whose
+          // first wave ranks alone and decides 64 admissions a pass, it gains nothing but with the fewest servers; a lane to each
+          // class stays there. Its time with a lane to a candidate over that with a lane to each class: 8 servers of two classes 0.98,
           // 256 x 1024 and 700 x 2048 of two 1.003 and 1.005, 1024 x 2048 of two 0.999, of four 1.012, of eight 1.003, 128 x
           // 4096 of two 1.012 (the runs of one side differ by 0.5 %).
           if (!SMALL && gate_mode == SIM_GATE_OCCUPANCY) {   // wave-uniform
