@@ -280,13 +280,13 @@ int static_workspace(void **dev_ptr, size_t *bytes)
 
 // ------------------------------------------------------------------ launchers ----
 // The step kernel's policy variants, each compiled in a translation unit of its own (gnr_step_<variant>.hip).
-StepKernel step_kernel_plain(int size_class, bool dense);
-StepKernel step_kernel_rr(int size_class, bool dense);
-StepKernel step_kernel_im(int size_class, bool dense);
-StepKernel step_kernel_ab(int size_class, bool dense);
-StepKernel step_kernel_ab_rr(int size_class, bool dense);
-StepKernel step_kernel_ab_im(int size_class, bool dense);
-StepKernel step_kernel_ws(int size_class, bool dense);
+StepKernel step_kernel_plain(int form, bool dense);
+StepKernel step_kernel_rr(int form, bool dense);
+StepKernel step_kernel_im(int form, bool dense);
+StepKernel step_kernel_ab(int form, bool dense);
+StepKernel step_kernel_ab_rr(int form, bool dense);
+StepKernel step_kernel_ab_im(int form, bool dense);
+StepKernel step_kernel_ws(int form, bool dense);
 
 static int hip_ok(hipError_t e) { return e == hipSuccess ? SIM_OK : SIM_EHIP; }
 
@@ -299,7 +299,15 @@ int launch_reset(const Params &p, int reps, void *stream)
 int launch_steps(const Params &p, int reps, int threads, size_t lds_bytes, uint32_t step_begin, uint32_t n_steps,
                  void *stream)
 {
-  const int size = size_class(threads, p.nwords);
+  int form = 0;
+  switch (threads) {
+    case 64: form = 0; break;
+    case 128: form = 1; break;
+    case 256: form = 2; break;
+    case 512: form = 3; break;
+    case 1024: form = 2 + size_class(threads, p.nwords); break;
+    default: return SIM_EINVAL;
+  }
   const bool ab = p.dl_rings != 0;
   // The roomy form of a small size class holds two waves per SIMD, the dense form four: the dense one is taken when
   // the launch then needs fewer rounds of workgroups (every workgroup runs for the whole launch, so a workgroup
@@ -307,11 +315,11 @@ int launch_steps(const Params &p, int reps, int threads, size_t lds_bytes, uint3
   const bool dense = step_dense(reps, threads, lds_bytes);
   StepKernel kernel = nullptr;
   switch (p.route_mode) {
-    case SIM_ROUTE_SOLO_FIRST: kernel = ab ? step_kernel_ab(size, dense) : step_kernel_plain(size, dense); break;
-    case SIM_ROUTE_RANDOM_SPLIT: kernel = ab ? step_kernel_ab_rr(size, dense) : step_kernel_rr(size, dense); break;
-    case SIM_ROUTE_IMMEDIATE: kernel = ab ? step_kernel_ab_im(size, dense) : step_kernel_im(size, dense); break;
+    case SIM_ROUTE_SOLO_FIRST: kernel = ab ? step_kernel_ab(form, dense) : step_kernel_plain(form, dense); break;
+    case SIM_ROUTE_RANDOM_SPLIT: kernel = ab ? step_kernel_ab_rr(form, dense) : step_kernel_rr(form, dense); break;
+    case SIM_ROUTE_IMMEDIATE: kernel = ab ? step_kernel_ab_im(form, dense) : step_kernel_im(form, dense); break;
     // (the weighted router is the randomized router's variant with deadline rings plus the class draws)
-    case SIM_ROUTE_WEIGHTED_SPLIT: kernel = ab ? step_kernel_ws(size, dense) : nullptr; break;
+    case SIM_ROUTE_WEIGHTED_SPLIT: kernel = ab ? step_kernel_ws(form, dense) : nullptr; break;
     default: break;
   }
   if (!kernel) return SIM_EINVAL;

@@ -377,8 +377,8 @@ __host__ __device__ constexpr int size_class(int threads, int nwords)
 // 512 / this many). A workgroup of 1024 threads needs four; the smaller classes are compiled twice: roomy, with up
 // to 256 registers and two waves per SIMD, taken while every workgroup of the launch finds a place at that density, and
 // dense, with 128 registers and four waves per SIMD, for launches that would otherwise run their workgroups in more
-// rounds. Registers roomy / dense (spilled when dense): base and randomized router 107 in eight waves and 116 in one or two,
-// same-slot decode 105 and 114, the same code in both forms; with deadline rings 117 to 122 in eight waves, 127 to 132 / 128
+// rounds. Registers roomy / dense (spilled when dense): base and randomized router 108 in eight waves and 114 in one,
+// same-slot decode 105 and 113, the same code in both forms; with deadline rings 117 to 122 in eight waves, 127 to 132 / 128
 // (up to 2) in one or two; weighted router 132 / 128 (2) and 142 / 128 (2). So only the forms of the weighted router, and with
 // deadline rings those of one or two waves, differ.
 __host__ __device__ constexpr int waves_per_simd(int max_threads, bool dense)
@@ -581,15 +581,15 @@ struct StepArrays {
 // IM: the variant with immediate same-slot decode (no router): a request whose prefill ends goes on decoding on
 // its own server, placed there by the lane that finishes the server; a server is offered to the gate while it
 // holds no prefill and fewer than B decodes.
-template <int MAXT, int NWS, bool AB, bool RR, bool IM, bool WS = false, bool DENSE = false>
-__global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves_per_simd(MAXT, DENSE)))) gnr_step_kernel(const Params *__restrict__ params, const StepArrays a,
+template <int NT, int NWS, bool AB, bool RR, bool IM, bool WS = false, bool DENSE = false>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NT, DENSE)))) gnr_step_kernel(const Params *__restrict__ params, const StepArrays a,
                                                         const uint32_t key0_arg, const uint32_t key1_arg,
                                                         const uint32_t step_begin_arg, const uint32_t n_steps_arg)
 {
   const uint32_t key0 = pinned(key0_arg), key1 = pinned(key1_arg), step_begin = pinned(step_begin_arg), n_steps = pinned(n_steps_arg);
   const Params &p = *params;   // immutable after creation; read through the scalar cache on demand
   extern __shared__ __align__(16) unsigned char lds_raw[];
-  constexpr bool SMALL = MAXT <= 128;
+  constexpr bool SMALL = NT <= 128;
   constexpr int kEvPerWave = SMALL ? kEvPerWaveSmall : gnr::kEvPerWave;       // (these shadow the large tables' sizes)
   constexpr int kJobsLds = SMALL ? kJobsLdsSmall : gnr::kJobsLds;
   constexpr int kAdmChunk = SMALL ? kAdmChunkSmall : gnr::kAdmChunk;
@@ -598,11 +598,10 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
 
   const int r = blockIdx.x;
   const int tid = threadIdx.x;
-  const int NT = blockDim.x;
   const int lane = tid & 63;
   // wave-uniform values are made scalar explicitly, so that loops and branches on them are scalar too
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int nwaves = NT >> 6;
+  constexpr int nwaves = NT >> 6;
   const int wave_base = wave << 6;
   // The instruction arbiter of a SIMD prefers its oldest wave: left alone, the first four waves of the workgroup
   // finish every sweep early and the last four late, and the barrier waits for those. Raising the priority of the
@@ -2614,19 +2613,27 @@ __global__ void __launch_bounds__(MAXT) __attribute__((amdgpu_waves_per_eu(waves
   if (tid < K) gt[tid * kNTally + SIM_T_TOK_PREF] = gt[tid * kNTally + SIM_T_TOKP_PRE] + L.acc[tid];
 }
 
-// The step kernel of one policy variant for a size class (see size_class), in its roomy or, for the two smaller
-// classes, its dense form (see waves_per_simd). Each variant is compiled in a translation unit of its own.
+// The step kernel of one policy variant: `form` is 0 to 3 for workgroups of 64, 128, 256 and 512 threads, in their roomy or
+// dense form (see waves_per_simd), 4 and 5 for those of 1024 (see size_class). Every workgroup size is compiled by itself, so
+// that the count of waves and what follows from it are constants and not values kept in lanes of vector registers. Compiled
+// for two sizes each, with the count read at run time, the timed cases took 1 to 7 % longer (8 servers x 16 replications 16.7 ->
+// 15.7 ms per 10^4 steps, 256 x 1024 9.15 -> 8.61 per 1000, 1024 x 2048 17.85 -> 17.20, 10000 x 256 18.7 -> 18.4, 3001 x 77
+// 5.80 -> 5.58 per 500). Each variant is compiled in a translation unit of its own.
 using StepKernel = void (*)(const Params *, StepArrays, uint32_t, uint32_t, uint32_t, uint32_t);
 #define GNR_STEP_VARIANT(name, AB, RR, IM, WS)                                                             \
-  StepKernel name(int size_class, bool dense)                                                              \
+  StepKernel name(int form, bool dense)                                                                    \
   {                                                                                                        \
-    static const StepKernel table[6] = {gnr_step_kernel<128, static_words(0), AB, RR, IM, WS>,             \
-                                        gnr_step_kernel<512, static_words(1), AB, RR, IM, WS>,             \
+    static const StepKernel roomy[6] = {gnr_step_kernel<64, 0, AB, RR, IM, WS>,                            \
+                                        gnr_step_kernel<128, 0, AB, RR, IM, WS>,                           \
+                                        gnr_step_kernel<256, 0, AB, RR, IM, WS>,                           \
+                                        gnr_step_kernel<512, 0, AB, RR, IM, WS>,                           \
                                         gnr_step_kernel<1024, static_words(2), AB, RR, IM, WS>,            \
-                                        gnr_step_kernel<1024, static_words(3), AB, RR, IM, WS>,            \
-                                        gnr_step_kernel<128, static_words(0), AB, RR, IM, WS, true>,       \
-                                        gnr_step_kernel<512, static_words(1), AB, RR, IM, WS, true>};      \
-    return table[dense && size_class <= 1 ? 4 + size_class : size_class];                                  \
+                                        gnr_step_kernel<1024, static_words(3), AB, RR, IM, WS>};           \
+    static const StepKernel full[4] = {gnr_step_kernel<64, 0, AB, RR, IM, WS, true>,                       \
+                                       gnr_step_kernel<128, 0, AB, RR, IM, WS, true>,                      \
+                                       gnr_step_kernel<256, 0, AB, RR, IM, WS, true>,                      \
+                                       gnr_step_kernel<512, 0, AB, RR, IM, WS, true>};                     \
+    return dense && form < 4 ? full[form] : roomy[form];                                                   \
   }
 
 }  // namespace gnr
