@@ -48,7 +48,7 @@ __device__ __forceinline__ void philox_rounds(uint32_t k0, uint32_t k1, uint32_t
 __device__ __forceinline__ void philox4x32_10(uint32_t k0, uint32_t k1, uint32_t c0, uint32_t c1, uint32_t c2,
                                               uint32_t c3, uint32_t (&w)[4])
 {
-  asm volatile("" : "+s"(k0), "+s"(k1));   // (the round keys are formed anew: see draw_arrivals)
+  asm volatile("" : "+s"(k0), "+s"(k1));   // (the round keys are formed anew: see draw_words)
   philox_rounds<1>(k0, k1, c0, c1, c2, c3, w);
 }
 
@@ -250,7 +250,7 @@ constexpr int kTallyRows = 16, kTallyRowsSmall = 8;
 // 64 requests at a time (more passes when a step brings more), and a wave finishes its queued servers when more than
 // 32 wait.
 constexpr int kEvPerWave = 128;   // servers a wave can queue for finishing; when full the queue is drained early
-constexpr int kEvPerWaveSmall = 96, kJobsLdsSmall = 64, kAdmChunkSmall = 64;
+constexpr int kHeldEvSmall = 96, kJobsLdsSmall = 64, kAdmChunkSmall = 64;
 constexpr int kRouteLevels = 4;
 constexpr int kJobsLds = 256;      // requests of a routing pass staged in LDS; later ones are read from the buffer
 
@@ -304,8 +304,7 @@ constexpr int kStaticWordsMedium = 160;          // N up to 10240: three kilobyt
 template <int NWS, bool SMALL = false>
 __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char *base)
 {
-  constexpr int kEvPerWave = SMALL ? kEvPerWaveSmall : gnr::kEvPerWave;       // (these shadow the large tables' sizes)
-  constexpr int kJobsLds = SMALL ? kJobsLdsSmall : gnr::kJobsLds;
+  constexpr int kJobsLds = SMALL ? kJobsLdsSmall : gnr::kJobsLds;             // (these shadow the large tables' sizes)
   constexpr int kAdmChunk = SMALL ? kAdmChunkSmall : gnr::kAdmChunk;
   Lds L;
   size_t off = 0;
@@ -348,7 +347,7 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   // 5.5 ms, 20424 in one 3.1).
   constexpr size_t held_fixed = sizeof(uint64_t) * (kTallyWords + kJobsLds) + sizeof(int32_t) * (CS_WORDS + SC_WORDS + kMaxK) +
                                 sizeof(double) * 5 * kMaxK + 6 * kAdmChunk + sizeof(uint32_t) * 2 * kLoadBins;
-  const size_t held = held_fixed + waves * (8 * kEvPerWave + 256) + 80 * nw + 2 * ((4 * (nw + 1) + 7) & ~size_t(7));
+  const size_t held = held_fixed + waves * (8 * (SMALL ? kHeldEvSmall : kEvPerWave) + 256) + 80 * nw + 2 * ((4 * (nw + 1) + 7) & ~size_t(7));
   off = off < held ? held : off;
   // from here on the offsets depend on the configuration
   GNR_TAKE(ev_t, uint32_t, p.N)
@@ -377,8 +376,8 @@ __host__ __device__ constexpr int size_class(int threads, int nwords)
 // 512 / this many). A workgroup of 1024 threads needs four; the smaller classes are compiled twice: roomy, with up
 // to 256 registers and two waves per SIMD, taken while every workgroup of the launch finds a place at that density, and
 // dense, with 128 registers and four waves per SIMD, for launches that would otherwise run their workgroups in more
-// rounds. Registers roomy / dense (spilled when dense): base and randomized router 108 in eight waves and 114 in one,
-// same-slot decode 105 and 113, the same code in both forms; with deadline rings 117 to 122 in eight waves, 127 to 132 / 128
+// rounds. Registers roomy / dense (spilled when dense): base and randomized router 107 in eight waves and 116 in one or two,
+// same-slot decode 105 and 114, the same code in both forms; with deadline rings 117 to 122 in eight waves, 127 to 132 / 128
 // (up to 2) in one or two; weighted router 132 / 128 (2) and 142 / 128 (2). So only the forms of the weighted router, and with
 // deadline rings those of one or two waves, differ.
 __host__ __device__ constexpr int waves_per_simd(int max_threads, bool dense)
@@ -590,8 +589,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   const Params &p = *params;   // immutable after creation; read through the scalar cache on demand
   extern __shared__ __align__(16) unsigned char lds_raw[];
   constexpr bool SMALL = NT <= 128;
-  constexpr int kEvPerWave = SMALL ? kEvPerWaveSmall : gnr::kEvPerWave;       // (these shadow the large tables' sizes)
-  constexpr int kJobsLds = SMALL ? kJobsLdsSmall : gnr::kJobsLds;
+  constexpr int kJobsLds = SMALL ? kJobsLdsSmall : gnr::kJobsLds;             // (these shadow the large tables' sizes)
   constexpr int kAdmChunk = SMALL ? kAdmChunkSmall : gnr::kAdmChunk;
   constexpr int kTallyRowsHere = SMALL ? kTallyRowsSmall : kTallyRows;
   const Lds L = lds_carve<NWS, SMALL>(p, lds_raw);
@@ -619,20 +617,20 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     else if (wave >= 4 || nwaves <= 4) __builtin_amdgcn_s_setprio(1);
   };
   own_priority();
-  const int K = pinned(p.K), N = pinned(p.N), B = pinned(p.B), M = pinned(p.M), BS = pinned(p.BS);
+  int K = pinned(p.K), N = pinned(p.N), B = pinned(p.B), M = pinned(p.M), BS = pinned(p.BS);
   const int nper = (N + NT - 1) / NT;
-  const int nwords = pinned(p.nwords);
+  int nwords = pinned(p.nwords);
   // Servers 0..M-1 are the mixed group for the gate and the router. Servers below Mp >= M may hold a prefill:
   // Mp is the largest M the run has had (a prefill in service stays when its server turns solo).
-  const int Mp = pinned(p.Mp);
-  const int nwords_m = (Mp + 63) >> 6;   // bitmap words that hold servers with prefill state
+  int Mp = pinned(p.Mp);
+  int nwords_m = (Mp + 63) >> 6;   // bitmap words that hold servers with prefill state
   // Iteration-time coefficients, chunk size and step length in ns (each below 2^31: the longest iteration is),
   // window of the on-chip time-between-tokens histogram, class thresholds of the arrival draw: used in every block.
   const uint32_t c0_ns = pinned(static_cast<uint32_t>(p.c0)), cpre_ns = pinned(static_cast<uint32_t>(p.cpre));
   const uint32_t cdec_ns = pinned(static_cast<uint32_t>(p.cdec)), dt_ns = pinned(static_cast<uint32_t>(p.dt));
   const int chunk_max = static_cast<int>(pinned(static_cast<uint32_t>(p.C)));
   const int tbt_w = static_cast<int>(pinned(static_cast<uint32_t>(p.tbt_w))), tbt_lo = static_cast<int>(pinned(static_cast<uint32_t>(p.tbt_lo)));
-  const int gate_mode = static_cast<int>(pinned(static_cast<uint32_t>(p.gate_mode)));
+  int gate_mode = static_cast<int>(pinned(static_cast<uint32_t>(p.gate_mode)));
   const uint32_t queue_cap = pinned(p.queue_cap), dbuf_cap = pinned(p.dbuf_cap);
 
   const uint32_t *arr_thr = pinned(a.arr_thr);
@@ -818,10 +816,11 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     if (lane == 0) L.sc[mixed ? SC_DLEN_M : SC_DLEN] = static_cast<int32_t>(w);
   };
 
-  // arrival thresholds of the step to come: asked for a step ahead, the first three lanes hold them
+  // arrival thresholds of the step that is drawn next: the first three lanes hold them. Those of the one after it are asked for
   const uint32_t mod_rows = p.mod_period > 0xFFFFFFFFll ? 0xFFFFFFFFu : (p.mod_period > 0 ? static_cast<uint32_t>(p.mod_period) : 1u);
-  uint32_t mod_row = step_begin % mod_rows;
-  uint32_t thr_ahead = arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
+  uint32_t thr_ahead = arr_thr[3 * static_cast<size_t>(step_begin % mod_rows) + (lane < 2 ? lane : 2)];
+  uint32_t mod_row = (step_begin + 1u) % mod_rows;
+  uint32_t thr_asked = arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];   // of mod_row
   // what `n` steps leave in the class counters at their end enters the sums over steps
   auto add_step_sums = [&](int k, uint32_t n, int qp, int qd, int x, int ym, int ys) __attribute__((always_inline)) {
     lds_add64(&L.tl[k * kNTally + SIM_T_SUM_QP], static_cast<uint64_t>(n) * static_cast<uint32_t>(qp));
@@ -841,52 +840,91 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // and `ahead` would be shifted by its whole width), and the search is left out: of the steps of two classes 33 % are quiet
   // with 33 servers and 13 % with 64 (58 % with 16, 36 % with 32), of four classes at 0.95 of the capacity 11 and 1.5 %.
   constexpr int kQuietServers = 32;
-  const bool quiet_search = SMALL && NT == 64 && N <= kQuietServers;
+  const bool quiet_search = NT == 64 && N <= kQuietServers;
   const int lg_n = N <= 1 ? 0 : 32 - __clz(N - 1);   // a step's servers take 2^lg_n lanes
-  uint64_t ahead = 0;    // servers with arrivals in the steps drawn ahead, the step to come in the lowest 2^lg_n bits
-  int steps_ahead = 0;   // how many
+  uint64_t ahead = 0;       // servers with arrivals in the steps drawn ahead, the step to come in the lowest 2^lg_n bits
+  int steps_ahead = 0;      // how many
+  uint32_t requests = 0;    // this lane's requests in the step it has drawn: how many, and three bits of class number each
+  auto class_of = [&](uint32_t word) __attribute__((always_inline)) -> int {
+    int k = 0;
+#pragma unroll
+    for (int c = 0; c + 1 < kMaxK; ++c) k += word >= L.cthr[c];
+    return k < K ? k : K - 1;
+  };
+  auto draw_block = [&](uint32_t sd) __attribute__((always_inline)) {   // steps sd, sd + 1, ...
+    const uint32_t s_lane = sd + (static_cast<uint32_t>(lane) >> lg_n);
+    const int g = lane & ((1 << lg_n) - 1);
+    const uint32_t *thr = arr_thr + (mod_rows > 1u ? 3 * static_cast<size_t>(s_lane % mod_rows) : 0);
+    const uint32_t thr0 = thr[0], thr1 = thr[1], thr2 = thr[2];
+    uint32_t w[4];
+    philox4x32_10(key0, key1, s_lane, 0u, static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
+    requests = g < N && w[0] >= thr0 ? 1u + (w[0] >= thr1) + (w[0] >= thr2) : 0u;
+    ahead = __ballot(requests != 0);
+    requests |= static_cast<uint32_t>(class_of(w[1]) << 2 | class_of(w[2]) << 5 | class_of(w[3]) << 8);
+    steps_ahead = 64 >> lg_n;
+  };
   // ---- arrivals: one random block per server and step, word 0 -> count, words 1.. -> classes. Word 0 alone is worked out
-  //      for every server (its last rounds take half the products); the few servers that get requests are queued and
-  //      their blocks drawn in full, one a lane. Draws those of step `sd` for the words first, first + stride, ... (wave-uniform).
-  auto draw_arrivals = [&](uint32_t sd, int first, int stride) __attribute__((always_inline)) {
+  //      for every server (its last rounds take half the products), for 64 of them (a bitmap word) at a time, two words with the same
+  //      round keys, and a step ahead; the few servers that get requests are queued and their blocks drawn in full, one a lane.
+  //      In workgroups of eight waves and more with one decode buffer some waves draw while the others work off the events (a wave with
+  //      all the events of two has its lanes full: 10000 servers of six classes have 450 a step, 28 a wave); their requests are
+  //      counted behind the barriers that follow. 10000 servers x 256 replications 18.3 -> 17.15 ms per 1000 steps, 3001 x 77 5.60 ->
+  //      5.39 per 500, 500 x 3 with same-slot decode 19.4 -> 18.8 per 2000. In smaller workgroups, where the events are the longest
+  //      part, and with two buffers, where serving is, all waves work off the events and those that do not serve draw beside the ones
+  //      that do (draws beside the events: 1024 x 2048 in two waves 16.8 -> 17.8 ms, 2048 x 1024 in four 17.2 -> 17.6, 10000 x 256 with
+  //      the randomized router 6.76 -> 6.86 per 300).
+  constexpr int kHits = NT <= 64 ? 2 : 1;
+  uint64_t hits[kHits] = {};
+  constexpr bool kBeside = NT >= 512 && !RR;
+  // (with more than eight words a wave the events need more than half of the waves)
+  const int n_drain = !kBeside ? nwaves : nwords > 8 * nwaves ? nwaves * 5 / 8 : nwaves / 2;
+  const int n_draw = nwaves - n_drain, drain_first = n_draw;
+  bool drawn = false;   // the step to come has been drawn (kBeside: by this wave, and its requests are not yet counted)
+  // The words first, first + stride, ...: lane j of `hits` gets the servers of the j-th one that have requests. (One wave alone
+  // may have more than 64: then also of the j + 64-th.)
+  auto draw_words = [&](uint32_t sd, int first, int stride) __attribute__((always_inline)) {
     const uint32_t thr0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 0));
-    const uint32_t thr1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 1));
-    const uint32_t thr2 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 2));
     // the random block's first round has the server in one product only; the other one is the same for all
     const uint64_t ps = static_cast<uint64_t>(0xD2511F53u) * sd;
-    const uint32_t c2_1 = pinned(static_cast<uint32_t>(ps >> 32) ^ static_cast<uint32_t>(r) ^ key1), c3_1 = static_cast<uint32_t>(ps);
-    for (int b0 = first; b0 < nwords; b0 += 64 * stride) {   // wave-uniform; 64 words a round, one a lane
-      uint64_t hits = 0;
-      auto first_word = [&](int blk, uint32_t k0, uint32_t k1) __attribute__((always_inline)) -> uint64_t {   // servers with requests
-        const uint64_t pg = static_cast<uint64_t>(0xCD9E8D57u) * static_cast<uint32_t>((blk << 6) + lane);
+    const uint32_t c2_1 = static_cast<uint32_t>(ps >> 32) ^ static_cast<uint32_t>(r) ^ key1, c3_1 = static_cast<uint32_t>(ps);
+    for (int j = 0; first + j * stride < nwords; j += 2) {   // wave-uniform
+      // the round keys are formed anew with scalar additions: as loop invariants there are twenty of them, and they are
+      // kept in lanes of vector registers, from which each costs two vector instructions a round
+      uint32_t k0 = key0, k1 = key1;
+      asm volatile("" : "+s"(k0), "+s"(k1));
+      uint64_t hit[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int word = first + (j + u) * stride;
+        const uint64_t pg = static_cast<uint64_t>(0xCD9E8D57u) * static_cast<uint32_t>((word << 6) + lane);
         uint32_t w[4];
         philox_rounds<2>(k0 + 0x9E3779B9u, k1 + 0xBB67AE85u, static_cast<uint32_t>(pg >> 32) ^ k0, static_cast<uint32_t>(pg), c2_1, c3_1, w);
-        return __ballot(w[0] >= thr0);
-      };
-      int j = 0, blk = b0;
-      for (; j < 64 && blk + stride < nwords; j += 2, blk += 2 * stride) {   // wave-uniform; two words with the same round keys
-        // the round keys are formed anew with scalar additions: as loop invariants there are twenty of them, and they are
-        // kept in lanes of vector registers, from which each costs two vector instructions a round
-        uint32_t k0 = key0, k1 = key1;
-        asm volatile("" : "+s"(k0), "+s"(k1));
-        const uint64_t hit0 = first_word(blk, k0, k1), hit1 = first_word(blk + stride, k0, k1);
-        hits = writelane64(writelane64(hits, hit0, j), hit1, j + 1);
+        hit[u] = __ballot(w[0] >= thr0);
       }
-      if (j < 64 && blk < nwords) {
-        uint32_t k0 = key0, k1 = key1;
-        asm volatile("" : "+s"(k0), "+s"(k1));
-        hits = writelane64(hits, first_word(blk, k0, k1), j);
-      }
-      const int word = b0 + lane * stride;
-      hits &= bits_below(word, N);   // (of a lane without a word it is empty)
+      if (kHits == 1 || j < 64)
+        hits[0] = writelane64(writelane64(hits[0], hit[0], j), hit[1], j + 1);
+      else
+        hits[kHits - 1] = writelane64(writelane64(hits[kHits - 1], hit[0], j - 64), hit[1], j - 63);
+    }
+  };
+  // Those servers' blocks in full: their requests are added to the step's arrivals.
+  auto count_requests = [&](uint32_t sd, int first, int stride) __attribute__((always_inline)) {
+    const uint32_t thr1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 1));
+    const uint32_t thr2 = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(thr_ahead), 2));
+#pragma unroll
+    for (int h = 0; h < kHits; ++h) {
+      if (first + 64 * h * stride >= nwords) break;   // wave-uniform
+      const int word = first + (lane + 64 * h) * stride;
+      uint64_t left = kHits == 1 || h == 0 ? hits[0] : hits[kHits - 1];
+      left &= bits_below(word, N);   // (of a lane without a word it is empty)
       int n = 0;
-      for (uint64_t todo = __ballot(hits != 0); todo;) {   // a lane queues one server of its word at a time
-        if (hits) {
-          ev_g[n + rank_in(todo)] = static_cast<uint16_t>((word << 6) + __ffsll(static_cast<long long>(hits)) - 1);
-          hits &= hits - 1ull;
+      for (uint64_t todo = __ballot(left != 0); todo;) {   // a lane queues one server of its word at a time
+        if (left) {
+          ev_g[n + rank_in(todo)] = static_cast<uint16_t>((word << 6) + __ffsll(static_cast<long long>(left)) - 1);
+          left &= left - 1ull;
         }
         n += __popcll(todo);
-        todo = __ballot(hits != 0);
+        todo = __ballot(left != 0);
         if (n > kEvPerWave - 64 || !todo) {
           for (int e0 = 0; e0 < n; e0 += 64) {   // wave-uniform
             if (e0 + lane < n) {
@@ -896,10 +934,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
 #pragma unroll
               for (int i = 0; i < 3; ++i) {
                 if (i >= count) break;
-                int k = 0;
-#pragma unroll
-                for (int c = 0; c + 1 < kMaxK; ++c) k += w[i + 1] >= L.cthr[c];
-                atomicAdd(&L.acc[k < K ? k : K - 1], 1u);
+                atomicAdd(&L.acc[class_of(w[i + 1])], 1u);
               }
             }
           }
@@ -908,13 +943,18 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
       }
     }
   };
-  auto next_thresholds = [&]() __attribute__((always_inline)) {   // of the step after the one drawn (in every wave, whether it draws or not)
+  auto next_thresholds = [&]() __attribute__((always_inline)) {   // of the step that is drawn next
     if (mod_rows > 1u) {
+      thr_ahead = thr_asked;
       mod_row = mod_row + 1u == mod_rows ? 0u : mod_row + 1u;
-      thr_ahead = arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
+      thr_asked = arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
     }
   };
-  bool drawn = false;        // the arrivals of the step to come have been drawn
+  // What follows from these (conditions, products, masks) is formed anew in every segment of a step. Left to itself the compiler
+  // forms all of it once, before the first step: 150 scalar values, kept in lanes of vector registers.
+  auto anew = [&]() __attribute__((always_inline)) {
+    asm volatile("" : "+s"(K), "+s"(N), "+s"(B), "+s"(M), "+s"(BS), "+s"(nwords), "+s"(Mp), "+s"(nwords_m), "+s"(gate_mode));
+  };
   bool slots_taken = false;  // bm_comp holds the prefill slots the last gate pass has given away, and they are still in bm_idle
 
   const uint32_t step_end = step_begin + n_steps;
@@ -922,8 +962,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   int64_t T = 0;
   for (uint32_t s = step_begin; s < step_end; ++s, ++ended) {
     T = (static_cast<int64_t>(s) + 1) * dt_ns;
+    anew();
     if constexpr (SMALL) {
-      if (quiet_search) {
+      if (quiet_search) {   // (here all arrivals are drawn by the block)
         bool search = s != step_begin;
         if constexpr (AB)   // (while nobody waits nobody leaves)
           search = search && __ballot(lane < K && (L.cs[CS_QP + (lane & (kMaxK - 1))] | L.cs[CS_QD + (lane & (kMaxK - 1))]) != 0) == 0;
@@ -932,15 +973,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
           const int64_t never = static_cast<int64_t>(1) << 62;
           int64_t rel = (L.bm_busy[0] >> lane) & 1ull ? event_time(lane < N ? lane : 0, T) : never;   // (events lie after the step before)
           for (; s < step_end; ++s) {
-            if (steps_ahead == 0) {
-              const uint32_t s_lane = s + (static_cast<uint32_t>(lane) >> lg_n);
-              const int g = lane & ((1 << lg_n) - 1);
-              const uint32_t thr = arr_thr[mod_rows > 1u ? 3 * static_cast<size_t>(s_lane % mod_rows) : 0];
-              uint32_t w[4];
-              philox4x32_10(key0, key1, s_lane, 0u, static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
-              ahead = __ballot(g < N && w[0] >= thr);
-              steps_ahead = 64 >> lg_n;
-            }
+            if (steps_ahead == 0) draw_block(s);
             if ((ahead & ((1ull << (1 << lg_n)) - 1ull)) || __ballot(rel <= 0)) break;
             rel -= dt_ns;
             ahead >>= 1 << lg_n;
@@ -950,13 +983,19 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
             ended += s - s_first;
             T = (static_cast<int64_t>(s) + 1) * dt_ns;
             if (s == step_end) { T = static_cast<int64_t>(s) * dt_ns; break; }
-            if (mod_rows > 1u) {
-              mod_row = s % mod_rows;
-              thr_ahead = arr_thr[3 * static_cast<size_t>(mod_row) + (lane < 2 ? lane : 2)];
-            }
           }
         }
-        if (steps_ahead > 0) { ahead >>= 1 << lg_n; --steps_ahead; }   // this step is gone through now
+        // this step is gone through now: the lanes that have drawn it add its requests to the arrivals
+        if (steps_ahead == 0) draw_block(s);
+        if ((lane >> lg_n) == (64 >> lg_n) - steps_ahead) {
+#pragma unroll
+          for (int i = 0; i < 3; ++i) {
+            if (i >= static_cast<int>(requests & 3u)) break;
+            atomicAdd(&L.acc[(requests >> (2 + 3 * i)) & 7u], 1u);
+          }
+        }
+        ahead >>= 1 << lg_n;
+        --steps_ahead;
       }
     }
     if (nwaves > 1 && nwaves <= 4) {
@@ -980,27 +1019,32 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     //      lanes need of their servers' records is asked for first, together with the slot rows of the servers whose
     //      event is the end of a decode: eight lanes read a row, 16 bytes per lane and load, eight rows at a time.
     auto drain_events = [&](int nev) __attribute__((always_inline)) {
+      int lane_here = lane;   // (likewise: thirteen vector registers)
+      asm volatile("" : "+v"(lane_here));
+      __builtin_assume(lane_here >= 0 && lane_here < 64);
       for (int e0 = 0; e0 < nev; e0 += 64) {
         const bool queued = e0 + lane < nev;
         const int g = queued ? static_cast<int>(ev_g[e0 + lane]) : 0;
         const int wi = g >> 6;
+        // (every lane reads: those without a server that of server 0)
+        uint64_t nc = rec[g].n_cls, nj = rec[g].n_join, pf = rec[g].pf_job;
+        const uint32_t it_tal = rec[g].iter;
+        uint32_t nf = rec[g].next_fin;
+        const uint32_t ev = L.ev_it[g], it = ev & kEvIter;
+        int nd = static_cast<int>(L.loads[g]);
+        int rem = static_cast<int>(L.rem[g < Mp ? g : 0]);   // (without a mixed group: of the array behind)
+        rem = g < Mp ? rem : 0;
         // exact completion time, relative to T: within a step of it
         const int32_t rel = static_cast<int32_t>(((L.ev_t[g] - static_cast<uint32_t>(T >> 8)) << 8) + L.ev_lo[g] - (static_cast<uint32_t>(T) & 255u));
         const bool active = queued && rel <= 0;
         const uint64_t bit = active ? 1ull << (g & 63) : 0ull;
-        uint64_t nc = 0, nj = 0, pf = 0;
-        uint32_t it_tal = 0, nf = 0;
-        if (active) { nc = rec[g].n_cls; nj = rec[g].n_join; pf = rec[g].pf_job; it_tal = rec[g].iter; nf = rec[g].next_fin; }
-        const uint32_t ev = active ? L.ev_it[g] : 0u, it = ev & kEvIter;
-        int nd = active ? static_cast<int>(L.loads[g]) : 0;
         const int nd_before = nd;
         const bool has_chunk = ev & kEvChunk;
-        int rem = active && g < Mp ? static_cast<int>(L.rem[g]) : 0;
         const bool mixed_now = rem > 0;
         const uint64_t nc_before = nc;
         // ---- the ends of decodes: one leaves per round, highest slot first (the last slot's request moves into its
         //      place); a second round follows only where several end together
-        bool leaving = ev & kEvFin;
+        bool leaving = active && (ev & kEvFin);
         // The request that leaves (a trip to memory that follows the row's) is asked for where its slot is known and used at the
         // end, unless another of the server's ends in the same iteration: the next event does not depend on it.
         int gone_slot = -1;
@@ -1036,7 +1080,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
           bool more = false;
           uint32_t next = 0xFFFFFFFFu;
           for (int r0 = 0; r0 < nrows; r0 += 8) {   // wave-uniform
-            const int row = r0 + (lane >> 3), l8 = lane & 7;
+            const int row = r0 + (lane_here >> 3), l8 = lane_here & 7;
             const int o_gn = __shfl(row_gn, row & 63, 64);
             const int o_g = o_gn & 0xFFFF, o_nd = row < nrows ? o_gn >> 16 : 0;
             const uint32_t o_it = static_cast<uint32_t>(__shfl(row_it, row & 63, 64));
@@ -1199,33 +1243,41 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
       }
     };
 
-    // ---- completion pass: the arrivals, where they have not been drawn yet, and which servers have their event in this
-    //      step (one clock per server and step is all that is read). What a word has but one of is kept one word a lane.
-    if (!drawn) {
-      draw_arrivals(s, wave, nwaves);
-      next_thresholds();
+    // ---- completion pass: the arrivals (see draw_words), and which servers have their event in this step (one clock per server and
+    //      step is all that is read). What a word has but one of is kept one word a lane.
+    if (!quiet_search) {
+      if constexpr (kBeside) {
+        if (wave < n_draw) {
+          if (s == step_begin) draw_words(s, wave, n_draw);
+          if (s == step_begin || drawn) count_requests(s, wave, n_draw);
+          next_thresholds();
+          if (s + 1u < step_end) draw_words(s + 1u, wave, n_draw);
+          drawn = true;
+        }
+      } else {
+        if (!drawn) {
+          draw_words(s, wave, nwaves);
+          count_requests(s, wave, nwaves);
+          next_thresholds();
+        }
+        drawn = false;
+      }
     }
-    drawn = false;
-    {
+    if (wave >= drain_first) {
       const uint32_t T_hi = static_cast<uint32_t>(T >> 8);
-      for (int b0 = wave; b0 < nwords; b0 += 64 * nwaves) {   // wave-uniform; the wave's words, 64 a round, one a lane
-        const int w_lane = b0 + lane * nwaves;
+      for (int b0 = wave - drain_first; b0 < nwords; b0 += 64 * n_drain) {   // wave-uniform; the wave's words, 64 a round, one a lane
+        const int w_lane = b0 + lane * n_drain;
         uint64_t due = 0;
         // (lanes past the last server are not busy; a clock a few ns ahead may pass here for its upper bits: the servers
         // queued are looked at exactly)
-        auto clock_of = [&](int j) __attribute__((always_inline)) {
-          const int g = ((b0 + j * nwaves) << 6) + lane;
-          return L.ev_t[g < N ? g : N - 1];
-        };
-        int j = 0;
-        for (; j < 64 && b0 + (j + 3) * nwaves < nwords; j += 4) {   // wave-uniform
+        int at = (b0 << 6) + lane;   // the word's server of this lane
+        for (int j = 0; j < 64 && b0 + j * n_drain < nwords; j += 4) {   // wave-uniform; up to three words past the last one: no lane's
           uint32_t ev[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) ev[u] = clock_of(j + u);
+          for (int u = 0; u < 4; ++u) { ev[u] = L.ev_t[at < N ? at : N - 1]; at += n_drain << 6; }
 #pragma unroll
           for (int u = 0; u < 4; ++u) due = writelane64(due, __ballot(static_cast<int32_t>(ev[u] - T_hi) <= 0), j + u);
         }
-        for (; j < 64 && b0 + j * nwaves < nwords; ++j) due = writelane64(due, __ballot(static_cast<int32_t>(clock_of(j) - T_hi) <= 0), j);
         if (w_lane < nwords) {
           due &= L.bm_busy[w_lane];
           L.bm_due[w_lane] = due;
@@ -1240,15 +1292,16 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
           const int src = __ffsll(static_cast<long long>(todo)) - 1;
           const uint64_t dm = readlane64(due, src);
           todo &= todo - 1ull;
-          if (lane_in(dm)) ev_g[nev + rank_in(dm)] = static_cast<uint16_t>(((b0 + src * nwaves) << 6) + lane);
+          if (lane_in(dm)) ev_g[nev + rank_in(dm)] = static_cast<uint16_t>(((b0 + src * n_drain) << 6) + lane);
           nev += __popcll(dm);
           if (nev > kEvPerWave - 64 || !todo) { drain_events(nev); nev = 0; }
         }
       }
-      slots_taken = false;
     }
+    slots_taken = false;
     __syncthreads();
 
+    anew();
     // ================= arrivals into the class queues; ranks of completions and idle slots =================
     if (tid < K) {
       const int k = tid;
@@ -1330,6 +1383,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
       }
     }
     __syncthreads();
+    anew();
     // what follows is shared out: the first waves rank the gate's candidates, the others look for the router's servers
     const int n_gate = nwaves > 1 ? nwaves >> 1 : 1, route_first = nwaves > 1 ? n_gate : 0, n_route = nwaves - route_first;
     if constexpr (AB) {
@@ -1721,6 +1775,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         };
 
         // ---------------- segment A ----------------
+        anew();
         const int nidle = gate_on ? uniform(L.sc[SC_NIDLE]) : 0;
         if (gate_on && wave < n_gate) {
           const int limit = nidle < kAdmChunk ? nidle : kAdmChunk;
@@ -2117,6 +2172,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         __syncthreads();
 
         // ---------------- segment C ----------------
+        anew();
         const int sc_pass = L.sc[lane];   // one word a lane: one trip to LDS
         auto word_of = [&](int i) __attribute__((always_inline)) { return __builtin_amdgcn_readlane(sc_pass, i); };
         const int nadm = gate_on ? word_of(SC_NADM) & 0xFFFF : 0;
@@ -2165,17 +2221,23 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         // The servers that are given work: the admissions take the first nadm idle prefill slots, in every routing level the
         // first take_r of its members get a job. The last waves find these servers (a lane looks at a word), queue 64 of them
         // and serve those, one a lane; as long as no level is of the mixed group no server gets both, and admissions
-        // and jobs are served by waves of their own. The other waves draw the next step's arrivals meanwhile.
+        // and jobs are served by waves of their own. The other waves see to the next step's arrivals meanwhile.
         const int work = nadm + placed;   // (servers, or more: one may get an admission and jobs)
         const int n_adm = (nadm + 63) >> 6, n_job = (placed + 63) >> 6, n_both = (work + 63) >> 6;
         const bool apart = nadm > 0 && placed > 0 && nl_here == nl_solo && nwaves >= 4 && n_adm + n_job <= (nwaves >> 1);
         const int n_serve = apart ? n_adm + n_job : n_both < nwaves ? n_both : nwaves;
-        const bool draws_here = work > 0 && !drawn && s + 1u < step_end && n_serve < nwaves && 16 * (nwaves - n_serve) >= nwords;
+        // (left to the next completion pass, where all waves take part, if these would get more than sixteen words each)
+        const bool draws_here = !kBeside && work > 0 && !drawn && s + 1u < step_end && n_serve < nwaves && 16 * (nwaves - n_serve) >= nwords;
         if (work > 0 && wave < nwaves - n_serve) {
-          // (left to the next completion pass, where all waves take part, if these would get more than sixteen words each)
-          if (draws_here) {
+          if constexpr (kBeside) {
+            if (wave < n_draw && drawn) {
+              count_requests(s + 1u, wave, n_draw);
+              drawn = false;
+            }
+          } else if (draws_here) {
             __builtin_amdgcn_s_setprio(0);
-            draw_arrivals(s + 1u, wave, nwaves - n_serve);
+            draw_words(s + 1u, wave, nwaves - n_serve);
+            count_requests(s + 1u, wave, nwaves - n_serve);
             own_priority();
           }
         } else if (work > 0) {
@@ -2614,11 +2676,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
 }
 
 // The step kernel of one policy variant: `form` is 0 to 3 for workgroups of 64, 128, 256 and 512 threads, in their roomy or
-// dense form (see waves_per_simd), 4 and 5 for those of 1024 (see size_class). Every workgroup size is compiled by itself, so
-// that the count of waves and what follows from it are constants and not values kept in lanes of vector registers. Compiled
-// for two sizes each, with the count read at run time, the timed cases took 1 to 7 % longer (8 servers x 16 replications 16.7 ->
-// 15.7 ms per 10^4 steps, 256 x 1024 9.15 -> 8.61 per 1000, 1024 x 2048 17.85 -> 17.20, 10000 x 256 18.7 -> 18.4, 3001 x 77
-// 5.80 -> 5.58 per 500). Each variant is compiled in a translation unit of its own.
+// dense form (see waves_per_simd), 4 and 5 for those of 1024 (see size_class). Every workgroup size is compiled by itself: the
+// counts of waves, and what follows from them, are constants. Each variant is compiled in a translation unit of its own.
 using StepKernel = void (*)(const Params *, StepArrays, uint32_t, uint32_t, uint32_t, uint32_t);
 #define GNR_STEP_VARIANT(name, AB, RR, IM, WS)                                                             \
   StepKernel name(int form, bool dense)                                                                    \
