@@ -35,8 +35,6 @@ struct sim_t {
 
 namespace {
 
-constexpr uint32_t kStepsPerLaunch = 2048;
-
 struct Layout {
   size_t arr_thr, len_tab, rec, t_rel, remptok, fin, job, qring, dring, cstate, tally, hist,
       digest, reduced, params, pat_tab, qdl, ddl, cal, dcal, dring_m, ddl_m, dcal_m, total;

@@ -22,6 +22,9 @@ constexpr int kTallyWords = kMaxK * kNTally + kNGlobal;  // per replication, uin
 constexpr int64_t kIdle = INT64_MAX;
 constexpr uint32_t kIdleRel = 0xFFFFFFFFu;   // the same in a server's stored clock (see Params::t_rel)
 constexpr int kAdmChunk = 256;    // admissions decided per gate pass
+constexpr uint32_t kStepsPerLaunch = 2048;
+// (a launch counts the tokens of a class in 32 bits: no decode emits more than one a step, and one more that the launch before began)
+static_assert(static_cast<uint64_t>(kMaxN) * kMaxB * (kStepsPerLaunch + 1) < (uint64_t(1) << 32), "token counts of a launch");
 constexpr int kMaxTbtBins = 256;  // width of the on-chip time-between-tokens histogram window
 
 // Per-replication class-level state, int32 words (persisted between launches).
