@@ -2462,7 +2462,11 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
           do {   // (a second time round only where even all waves are too few)
             uint32_t before[2] = {0, 0};   // members of the levels in the words before
             n_all = 0;
-            for (int w0 = 0; w0 < nwords; w0 += 64) {   // wave-uniform
+            // (words of a group none of whose servers this wave serves are left out: 10000 x 256, 38 of 157 words mixed, 16.25 ->
+            // 15.62 ms per 1000 steps)
+            const int w_first = nadm_here > 0 || (nl_mine > 0 && nl_here > nl_solo) ? 0 : M >> 6;
+            const int w_last = nl_mine > 0 && nl_solo > 0 ? nwords : nwords_m;
+            for (int w0 = w_first; w0 < w_last; w0 += 64) {   // wave-uniform
               const int w = w0 + lane;
               uint64_t adm = 0, got = 0;
               if (nadm_here > 0 && w0 < nwords_m) {   // wave-uniform
