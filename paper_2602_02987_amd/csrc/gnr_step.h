@@ -731,22 +731,34 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   const uint64_t admissible = __ballot(lane < K && (gate_mode != SIM_GATE_OCCUPANCY || L.gtab[GT_INVX * kMaxK + (lane & (kMaxK - 1))] > 0.0));
   auto bits64 = [](uint64_t *p) __attribute__((always_inline)) { return reinterpret_cast<unsigned long long *>(p); };
 
+  // (what the next round reads is asked for a round ahead)
+  struct Stored { uint64_t nc, nj; uint32_t it, nf, tr, pk; };
+  auto stored = [&](int g) __attribute__((always_inline)) -> Stored {
+    Stored v = {0, 0, 0, 0, kIdleRel, 0};
+    if (g < N) {
+      v.nc = rec[g].n_cls; v.nj = rec[g].n_join; v.it = rec[g].iter; v.nf = rec[g].next_fin;
+      v.tr = t_rel[g];
+      if (g < Mp) v.pk = remptok[g];
+    }
+    return v;
+  };
+  Stored asked = stored(tid);
   for (int i = 0; i < nper; ++i) {
     const int g = i * NT + tid;
     const bool valid = g < N;
     bool busy = false, idle_slot = false;
+    const Stored have = asked;
+    asked = stored(g + NT);
     if (valid) {
-      const ServerRec &sr = rec[g];
-      const uint64_t nc = sr.n_cls, nj = sr.n_join;
-      const uint32_t it = sr.iter, nf = sr.next_fin, tr = t_rel[g];
+      const uint64_t nc = have.nc, nj = have.nj;
+      const uint32_t it = have.it, nf = have.nf, tr = have.tr;
       const uint32_t nd = byte_sum(nc);
       L.loads[g] = static_cast<uint8_t>(nd);
       atomicAdd(&L.lh[(g < M ? kLoadBins : 0) + nd], 1u);
       int rem = 0, ptok = 0;
       if (g < Mp) {   // the prompt tokens left stay in LDS during the launch
-        const uint32_t pk = remptok[g];
-        rem = pk_rem(pk);
-        ptok = pk_ptok(pk);
+        rem = pk_rem(have.pk);
+        ptok = pk_ptok(have.pk);
         L.rem[g] = static_cast<uint16_t>(rem);
         idle_slot = rem == 0 && (!IM || static_cast<int>(nd) < B);
       }
@@ -2607,6 +2619,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // the sums over steps get the last step's counters (those of the others are in them)
   if (tid < K) add_step_sums(tid, ended, L.cs[CS_QP + tid], L.cs[CS_QD + tid], L.cs[CS_X + tid], L.cs[CS_YM + tid], L.cs[CS_YS + tid]);
   if (tid == 0) L.tl[kMaxK * kNTally + SIM_G_STEPS] += n_steps;
+  if (tid < 8) L.acc[tid] = 0;   // prompt tokens already processed of the prefills in service
   if constexpr (AB) {   // the rings leave the launch without dead entries
     const uint32_t s_last = step_begin + n_steps - 1u;
     for (int k = wave; k < K; k += nwaves) compact_queue(k, s_last, 0u);
@@ -2614,85 +2627,89 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     if constexpr (RR) {
       if (wave == (nwaves > 1 ? nwaves - 2 : 0)) compact_buffer(s_last, true);
     }
-    __syncthreads();
   }
+  uint64_t *gt = a.tally + static_cast<size_t>(r) * kTallyWords;
+  const uint64_t prompt_before = tid < K ? gt[tid * kNTally + SIM_T_TOKP_PRE] : 0ull;
+  __syncthreads();
 
-  // ---- tally what each server has completed since its last event; its clock and prefill as of now
+  // ---- tally what each server has completed since its last event; its clock and prefill as of now (a block's records are
+  //      asked for a round ahead)
+  struct Kept { uint64_t nc, nj, pf; uint32_t it; };
+  auto kept = [&](int g) __attribute__((always_inline)) -> Kept {
+    Kept v = {0, 0, 0, 0};
+    if (g < N) { v.nc = rec[g].n_cls; v.nj = rec[g].n_join; v.pf = rec[g].pf_job; v.it = rec[g].iter; }
+    return v;
+  };
+  Kept ahead_rec = kept((wave << 6) + lane);
   for (int blk = wave; blk < nwords; blk += nwaves) {
     const int g = (blk << 6) + lane;
     const uint64_t bit = 1ull << lane;
     const bool busy = L.bm_busy[blk] & bit;
+    const Kept sr = ahead_rec;
+    ahead_rec = kept(g + NT);
     uint32_t m = 0, d = 0, tr = kIdleRel;
     bool chunk = false;
     uint64_t comp = 0;
+    int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0, ptok = 0;
     if (busy) {
-      comp = rec[g].n_cls - rec[g].n_join;
+      comp = sr.nc - sr.nj;
       chunk = L.ev_it[g] & kEvChunk;
-      const int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0, ptok = chunk ? chunk_of(rem) : 0;
+      ptok = chunk ? chunk_of(rem) : 0;
       const uint32_t dur = iteration_ns(ptok, byte_sum(comp));
       const int64_t rel = event_time(g, T);
-      const uint32_t left = joins_next(rec[g].n_join, rem, chunk) ? 1u : iterations_left(static_cast<uint64_t>(rel), dur);
+      const uint32_t left = joins_next(sr.nj, rem, chunk) ? 1u : iterations_left(static_cast<uint64_t>(rel), dur);
       const uint32_t it = (L.ev_it[g] & kEvIter) - left;
-      m = it - rec[g].iter;
+      m = it - sr.it;
       d = dur;
       tr = static_cast<uint32_t>(rel - static_cast<int64_t>(static_cast<uint64_t>(left - 1u) * dur));
       if (m) rec[g].iter = it;
-      if (ptok > 0) L.rem[g] = static_cast<uint16_t>(rem - static_cast<int>(m) * ptok);
+      if (ptok > 0) rem -= static_cast<int>(m) * ptok;
     }
     if (g < N) t_rel[g] = tr;
+    if (g < Mp) {   // prompt tokens left, those of the running chunk
+      uint32_t pk = 0;
+      if (rem) {
+        const uint32_t Pl = (static_cast<uint32_t>(sr.pf >> 32) & 0xFFFFu) + 1, k = static_cast<uint32_t>(sr.pf >> 29) & 7u;
+        atomicAdd(&L.acc[k], Pl - static_cast<uint32_t>(rem));
+        pk = static_cast<uint32_t>(rem) | (static_cast<uint32_t>(chunk ? chunk_of(rem) : 0) << 16) | (k << 29);
+      }
+      remptok[g] = pk;
+    }
     tally_iterations<kTallyRowsHere>(L.ta, L.tbth, tbt_w, tbt_lo, K, m, d, chunk, comp);
   }
   __syncthreads();
 
-  // ---- the sums of the executed iterations, folded
+  // ---- the sums of the executed iterations, folded; the time-between-tokens counts of this launch, whose total is the
+  //      emitted-token tally. What is added to the totals in memory is added by atomics: nothing waits for an old value.
   if (tid < TA_TBT + K) {
     uint64_t tot = 0;
+#pragma unroll
     for (int i = 0; i < kTallyRowsHere; ++i) tot += L.ta[tid * kTallyRowsHere + i];
     constexpr int kGlob = kMaxK * kNTally;
     L.tl[tid >= TA_TBT ? (tid - TA_TBT) * kNTally + SIM_T_TBT_SUM
                        : kGlob + (tid == TA_ITERS ? SIM_G_ITERS_SOLO : tid == TA_ITERS + 1 ? SIM_G_ITERS_MIX :
                                   tid == TA_BUSY ? SIM_G_BUSY_SOLO : SIM_G_BUSY_MIX)] = tot;
   }
-  // ---- the emitted-token tally is the total of the time-between-tokens counts of this launch
-  if (tid < K) {
-    uint64_t tot = 0;
-    for (int b = 0; b < p.tbt_w; ++b) tot += static_cast<uint32_t>(L.tbth[(tid >> 1) * p.tbt_w + b] >> (32 * (tid & 1)));
-    L.tl[tid * kNTally + SIM_T_TOK_EMIT] += tot;
-  }
-  if (tid < 8) L.acc[tid] = 0;
-  __syncthreads();
-
-  // ---- write the prefill words and the class state back; add this launch's tallies to the totals
-  for (int i = 0; i < nper; ++i) {
-    const int g = i * NT + tid;
-    if (g >= N) break;
-    if (g < Mp) {   // prompt tokens already processed of the prefill in service
-      const uint32_t rem = L.rem[g];
-      uint32_t pk = 0;
-      if (rem) {
-        const uint64_t jw = rec[g].pf_job;
-        const uint32_t Pl = (static_cast<uint32_t>(jw >> 32) & 0xFFFFu) + 1, k = static_cast<uint32_t>(jw >> 29) & 7u;
-        atomicAdd(&L.acc[k], Pl - rem);
-        const bool chunk = L.ev_it[g] & kEvChunk;
-        const uint32_t cmax = static_cast<uint32_t>(p.C);
-        pk = rem | ((chunk ? (rem < cmax ? rem : cmax) : 0u) << 16) | (k << 29);
-      }
-      remptok[g] = pk;
+  for (int i = tid; i < K * tbt_w; i += NT) {
+    const int k = i / tbt_w, b = i - k * tbt_w;
+    const uint32_t n = static_cast<uint32_t>(L.tbth[(k >> 1) * tbt_w + b] >> (32 * (k & 1)));
+    if (n) {
+      atomicAdd(reinterpret_cast<unsigned long long *>(&hist[(2 * K + k) * kNBin + tbt_lo + b]), static_cast<unsigned long long>(n));
+      lds_add64(&L.tl[k * kNTally + SIM_T_TOK_EMIT], n);
     }
   }
   for (int i = tid; i < CS_WORDS; i += NT) a.cstate[static_cast<size_t>(r) * CS_WORDS + i] = L.cs[i];
-  uint64_t *gt = a.tally + static_cast<size_t>(r) * kTallyWords;
-  for (int i = tid; i < kTallyWords; i += NT) {
-    if (i == kMaxK * kNTally + SIM_G_OVERFLOW) gt[i] |= L.tl[i]; else gt[i] += L.tl[i];
-  }
-  for (int i = tid; i < K * p.tbt_w; i += NT) {
-    const int k = i / p.tbt_w, b = i % p.tbt_w;
-    const uint32_t n = static_cast<uint32_t>(L.tbth[(k >> 1) * p.tbt_w + b] >> (32 * (k & 1)));
-    if (n) hist[(2 * K + k) * kNBin + p.tbt_lo + b] += n;
-  }
   __syncthreads();
+
+  for (int i = tid; i < kTallyWords; i += NT) {
+    const uint64_t v = L.tl[i];
+    if (v) {
+      if (i == kMaxK * kNTally + SIM_G_OVERFLOW) atomicOr(reinterpret_cast<unsigned long long *>(&gt[i]), static_cast<unsigned long long>(v));
+      else atomicAdd(reinterpret_cast<unsigned long long *>(&gt[i]), static_cast<unsigned long long>(v));
+    }
+  }
   // prompt tokens processed so far = prompt tokens of completed prefills + progress of those in service
-  if (tid < K) gt[tid * kNTally + SIM_T_TOK_PREF] = gt[tid * kNTally + SIM_T_TOKP_PRE] + L.acc[tid];
+  if (tid < K) gt[tid * kNTally + SIM_T_TOK_PREF] = prompt_before + L.tl[tid * kNTally + SIM_T_TOKP_PRE] + L.acc[tid];
 }
 
 // The step kernel of one policy variant: `form` is 0 to 3 for workgroups of 64, 128, 256 and 512 threads, in their roomy or
