@@ -27,8 +27,18 @@ struct sim_t {
   unsigned char *ws;
   size_t ws_bytes;
   int device;
-  // kernel timing: one pair of events per launch, read out and destroyed by drain_events
-  std::vector<std::pair<hipEvent_t, hipEvent_t>> pending;
+  // kernel timing: one pair of events per launch, read out by drain_events, which keeps them for later launches
+  std::vector<std::pair<hipEvent_t, hipEvent_t>> pending, spare;
+  // Totals over replications as sim_stats reads them: pinned host memory that the reduce kernel writes itself (of handles made
+  // by sim_create; without it they are copied out of the workspace). A copy of these 36 KB to pageable memory took 20 us and a
+  // second wait, of the 59 us of a call that advances 8 servers x 16 replications by one step and reads the statistics.
+  uint64_t *totals = nullptr;
+  ~sim_t()
+  {
+    for (auto *list : {&pending, &spare})
+      for (auto &pr : *list) { (void)hipEventDestroy(pr.first); (void)hipEventDestroy(pr.second); }
+    if (totals) (void)hipHostFree(totals);
+  }
   int64_t launches;
   double kernel_ms;
 };
@@ -220,32 +230,34 @@ void drain_events(sim_t *h)
   for (auto &pr : h->pending) {
     float ms = 0.f;
     if (hipEventElapsedTime(&ms, pr.first, pr.second) == hipSuccess) h->kernel_ms += ms;
-    (void)hipEventDestroy(pr.first);
-    (void)hipEventDestroy(pr.second);
+    h->spare.push_back(pr);
   }
   h->pending.clear();
 }
 
 double ratio(double a, double b) { return b > 0.0 ? a / b : 0.0; }
 
-double percentile(const uint64_t *hist, int pct)
+// Median, 95th and 99th percentile: the lower edge of the bin that holds rank ceil(q n), all in one pass.
+void percentiles(const uint64_t *hist, double &p50, double &p95, double &p99)
 {
+  p50 = p95 = p99 = 0.0;
   uint64_t n = 0;
   for (int b = 0; b < kNBin; ++b) n += hist[b];
-  if (n == 0) return 0.0;
-  const uint64_t rank = (n * static_cast<uint64_t>(pct) + 99) / 100;
+  if (n == 0) return;
+  constexpr uint64_t pct[3] = {50, 95, 99};
+  double *const out[3] = {&p50, &p95, &p99};
   uint64_t cum = 0;
-  for (int b = 0; b < kNBin; ++b) {
+  int i = 0;
+  for (int b = 0; b < kNBin && i < 3; ++b) {
     cum += hist[b];
-    if (cum >= rank) return static_cast<double>(host_hedge(b)) * 1e-9;
+    while (i < 3 && cum >= (n * pct[i] + 99) / 100) *out[i++] = static_cast<double>(host_hedge(b)) * 1e-9;
   }
-  return static_cast<double>(host_hedge(kNBin - 1)) * 1e-9;
 }
 
 }  // namespace
 
 namespace {
-int create_in(const sim_config *cfg, int max_replications, void *dev_workspace, size_t bytes, sim_t **out);
+int create_in(const sim_config *cfg, int max_replications, void *dev_workspace, size_t bytes, bool may_allocate, sim_t **out);
 }
 
 extern "C" {
@@ -270,7 +282,7 @@ int sim_workspace_bytes(const sim_config *cfg, int max_replications, size_t *out
 
 int sim_create(const sim_config *cfg, int max_replications, void *dev_workspace, size_t bytes, sim_t **out)
 {
-  return create_in(cfg, max_replications, dev_workspace, bytes, out);
+  return create_in(cfg, max_replications, dev_workspace, bytes, true, out);
 }
 
 int sim_create_static(const sim_config *cfg, int max_replications, sim_t **out)
@@ -279,13 +291,13 @@ int sim_create_static(const sim_config *cfg, int max_replications, sim_t **out)
   size_t bytes = 0;
   const int rc = static_workspace(&ws, &bytes);   // no allocation: the address of the library's own device array
   if (rc != SIM_OK) return rc;
-  return create_in(cfg, max_replications, ws, bytes, out);
+  return create_in(cfg, max_replications, ws, bytes, false, out);
 }
 
 }  // extern "C"
 
 namespace {
-int create_in(const sim_config *cfg, int max_replications, void *dev_workspace, size_t bytes, sim_t **out)
+int create_in(const sim_config *cfg, int max_replications, void *dev_workspace, size_t bytes, bool may_allocate, sim_t **out)
 {
   try {
     Ticks t;
@@ -410,6 +422,13 @@ int create_in(const sim_config *cfg, int max_replications, void *dev_workspace, 
          hipMemcpy(w + L.pat_tab, pat.data(), pat.size() * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess)) {
       return SIM_EHIP;
     }
+    if (may_allocate) {
+      void *mem = nullptr;
+      if (hipHostMalloc(&mem, (kTallyWords + static_cast<size_t>(3) * cfg->K * kNBin) * sizeof(uint64_t), hipHostMallocDefault) == hipSuccess)
+        h->totals = static_cast<uint64_t *>(mem);
+      else
+        (void)hipGetLastError();
+    }
     *out = hold.release();
     return SIM_OK;
   } catch (...) {   // host allocation failed (std::bad_alloc, std::length_error): nothing crosses the C boundary
@@ -438,8 +457,14 @@ int sim_run(sim_t *h, int64_t steps, int replications, uint64_t seed, void *hip_
     while (left > 0) {
       const uint32_t n = static_cast<uint32_t>(left < kStepsPerLaunch ? left : kStepsPerLaunch);
       hipEvent_t e0 = nullptr, e1 = nullptr;
-      bool timed = hipEventCreate(&e0) == hipSuccess;
-      if (timed && hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); timed = false; }
+      bool timed = true;
+      if (!h->spare.empty()) {
+        e0 = h->spare.back().first; e1 = h->spare.back().second;
+        h->spare.pop_back();
+      } else {
+        timed = hipEventCreate(&e0) == hipSuccess;
+        if (timed && hipEventCreate(&e1) != hipSuccess) { (void)hipEventDestroy(e0); timed = false; }
+      }
       if (timed) (void)hipEventRecord(e0, st);
       const int rc = launch_steps(h->p, replications, h->threads, h->lds_bytes, static_cast<uint32_t>(h->steps_done), n, hip_stream);
       if (timed) { (void)hipEventRecord(e1, st); h->pending.emplace_back(e0, e1); }
@@ -522,15 +547,19 @@ int sim_stats(sim_t *h, sim_stats_t *st, void *hip_stream)
 {
   try {
     if (!h || !st || !h->started || !on_device(h)) return SIM_EINVAL;
-    int rc = launch_reduce(h->p, h->reps, hip_stream);
+    int rc = launch_reduce(h->p, h->reps, h->totals ? h->totals : h->p.reduced, hip_stream);
     if (rc != SIM_OK) return rc;
     rc = sync(h, hip_stream);
     if (rc != SIM_OK) return rc;
     const int K = h->cfg.K;
-    const size_t nh = static_cast<size_t>(3) * K * kNBin;
-    std::vector<uint64_t> red(kTallyWords + nh);
-    rc = copy_out(red.data(), h->p.reduced, red.size() * sizeof(uint64_t));
-    if (rc != SIM_OK) return rc;
+    std::vector<uint64_t> copied;
+    const uint64_t *red = h->totals;
+    if (!red) {
+      copied.resize(kTallyWords + static_cast<size_t>(3) * K * kNBin);
+      rc = copy_out(copied.data(), h->p.reduced, copied.size() * sizeof(uint64_t));
+      if (rc != SIM_OK) return rc;
+      red = copied.data();
+    }
   
     std::memset(st, 0, sizeof *st);
     st->K = K; st->replications = h->reps; st->steps = h->steps_done;
@@ -539,7 +568,7 @@ int sim_stats(sim_t *h, sim_stats_t *st, void *hip_stream)
     for (int k = 0; k < K; ++k)
       for (int t = 0; t < kNTally; ++t) st->tally[k][t] = red[static_cast<size_t>(k) * kNTally + t];
     for (int t = 0; t < kNGlobal; ++t) st->glob[t] = red[static_cast<size_t>(kMaxK) * kNTally + t];
-    const uint64_t *hs = red.data() + kTallyWords;
+    const uint64_t *hs = red + kTallyWords;
     const double server_time = static_cast<double>(h->cfg.N) * st->sim_time * static_cast<double>(h->reps);
     const double server_steps = static_cast<double>(h->cfg.N) * static_cast<double>(h->steps_done) * static_cast<double>(h->reps);
     double xlo = 0, xhi = 0, ylo = 0, yhi = 0, slo = 0;
@@ -576,9 +605,9 @@ int sim_stats(sim_t *h, sim_stats_t *st, void *hip_stream)
       const uint64_t *h0 = hs + (static_cast<size_t>(0) * K + k) * kNBin;
       const uint64_t *h1 = hs + (static_cast<size_t>(1) * K + k) * kNBin;
       const uint64_t *h2 = hs + (static_cast<size_t>(2) * K + k) * kNBin;
-      st->ttft_p50[k] = percentile(h0, 50); st->ttft_p95[k] = percentile(h0, 95); st->ttft_p99[k] = percentile(h0, 99);
-      st->e2e_p50[k] = percentile(h1, 50); st->e2e_p95[k] = percentile(h1, 95); st->e2e_p99[k] = percentile(h1, 99);
-      st->tbt_p50[k] = percentile(h2, 50); st->tbt_p95[k] = percentile(h2, 95); st->tbt_p99[k] = percentile(h2, 99);
+      percentiles(h0, st->ttft_p50[k], st->ttft_p95[k], st->ttft_p99[k]);
+      percentiles(h1, st->e2e_p50[k], st->e2e_p95[k], st->e2e_p99[k]);
+      percentiles(h2, st->tbt_p50[k], st->tbt_p95[k], st->tbt_p99[k]);
       if (k == 0 || st->mean_x[k] < xlo) xlo = st->mean_x[k];
       if (k == 0 || st->mean_x[k] > xhi) xhi = st->mean_x[k];
       if (k == 0 || st->mean_ys[k] < ylo) ylo = st->mean_ys[k];
@@ -738,7 +767,6 @@ int sim_snapshot(sim_t *h, int r, sim_state_t *out, void *hip_stream)
 int sim_destroy(sim_t *h)
 {
   if (!h) return SIM_EINVAL;
-  for (auto &pr : h->pending) { (void)hipEventDestroy(pr.first); (void)hipEventDestroy(pr.second); }
   delete h;
   return SIM_OK;
 }

@@ -117,7 +117,7 @@ uint32_t selection_weight_units(double w);  // round(w * 2^20) clamped to [1, 2^
 int launch_reset(const Params &p, int reps, void *stream);
 int launch_steps(const Params &p, int reps, int threads, size_t lds_bytes, uint32_t step_begin, uint32_t n_steps,
                  void *stream);
-int launch_reduce(const Params &p, int reps, void *stream);
+int launch_reduce(const Params &p, int reps, uint64_t *out, void *stream);   // out: kTallyWords + 3*K*kNBin words the device can write
 int launch_digest(const Params &p, int reps, int64_t t_end, void *stream);   // t_end: the boundary the last launch ended at, ns
 // the library's static device workspace on the current device (address resolved once per device)
 int static_workspace(void **dev_ptr, size_t *bytes);

@@ -134,7 +134,7 @@ __global__ void gnr_reset_kernel(const Params p, const int reps)
 // one after the other, each row cost a round trip (2048 replications of four classes: 1480 us; 1024 of two: 515 us; 256
 // of six: 158 us), while the rows are 8 bytes a lane, whole lines a wave.
 constexpr int kReduceWaves = 16, kReduceAhead = 8;
-__global__ void __launch_bounds__(64 * kReduceWaves) gnr_reduce_kernel(const Params p, const int reps)
+__global__ void __launch_bounds__(64 * kReduceWaves) gnr_reduce_kernel(const Params p, const int reps, uint64_t *__restrict__ out)
 {
   __shared__ uint64_t part[kReduceWaves][64];
   const int nh = 3 * p.K * kNBin;
@@ -158,7 +158,7 @@ __global__ void __launch_bounds__(64 * kReduceWaves) gnr_reduce_kernel(const Par
   __syncthreads();
   if (wave == 0 && i < kTallyWords + nh) {
     for (int w = 1; w < nwaves; ++w) acc += part[w][lane];
-    p.reduced[i] = acc;
+    out[i] = acc;
   }
 }
 
@@ -336,12 +336,12 @@ int launch_steps(const Params &p, int reps, int threads, size_t lds_bytes, uint3
   return hip_ok(hipGetLastError());
 }
 
-int launch_reduce(const Params &p, int reps, void *stream)
+int launch_reduce(const Params &p, int reps, uint64_t *out, void *stream)
 {
   const int n = kTallyWords + 3 * p.K * kNBin;
   // a wave for every row group it can keep in flight, up to sixteen
   const int waves = reps >= kReduceAhead * kReduceWaves ? kReduceWaves : (reps + kReduceAhead - 1) / kReduceAhead;
-  hipLaunchKernelGGL(gnr_reduce_kernel, dim3((n + 63) / 64), dim3(64 * waves), 0, static_cast<hipStream_t>(stream), p, reps);
+  hipLaunchKernelGGL(gnr_reduce_kernel, dim3((n + 63) / 64), dim3(64 * waves), 0, static_cast<hipStream_t>(stream), p, reps, out);
   return hip_ok(hipGetLastError());
 }
 
