@@ -296,18 +296,27 @@ int launch_reset(const Params &p, int reps, void *stream)
   return hip_ok(hipGetLastError());
 }
 
+// Which compilation of the step kernel a launch takes. Sixteen waves: with up to 80 words (5120 servers) steps overlap whatever the
+// policy (3000 servers x 64, randomized router 4.5 % faster, weighted 4.5 %; x 256 with patience 11 %); with more they do not with two
+// buffers or deadline rings (10000 x 256, randomized router 6.38 -> 6.50 ms per 300 steps, weighted 8.61 -> 8.77, with patience
+// 6.24 -> 6.47: no wave waits for the ones that serve there, or every wave is slowed down by as much as the wait was long).
+static int step_form(int threads, int nwords)
+{
+  switch (threads) {
+    case 64: return 0;
+    case 128: return 1;
+    case 256: return 2;
+    case 512: return 3;
+    case 1024: return nwords <= 80 ? 6 : 2 + size_class(threads, nwords);
+    default: return -1;
+  }
+}
+
 int launch_steps(const Params &p, int reps, int threads, size_t lds_bytes, uint32_t step_begin, uint32_t n_steps,
                  void *stream)
 {
-  int form = 0;
-  switch (threads) {
-    case 64: form = 0; break;
-    case 128: form = 1; break;
-    case 256: form = 2; break;
-    case 512: form = 3; break;
-    case 1024: form = 2 + size_class(threads, p.nwords); break;
-    default: return SIM_EINVAL;
-  }
+  const int form = step_form(threads, p.nwords);
+  if (form < 0) return SIM_EINVAL;
   const bool ab = p.dl_rings != 0;
   // The roomy form of a small size class holds two waves per SIMD, the dense form four: the dense one is taken when
   // the launch then needs fewer rounds of workgroups (every workgroup runs for the whole launch, so a workgroup

@@ -268,14 +268,14 @@ struct Lds {
   int32_t *sc;        // [SC_WORDS]
   uint64_t *tl;       // [kTallyWords]
   uint64_t *tbth;     // [(K + 1) / 2][tbt_w] time between tokens: counts of two classes a word, 32 bits each
-  uint64_t *bm_idle;  // [nwords] servers below Mp with no prefill in service (the gate looks at those below M)
-  uint64_t *bm_comp;  // [nwords] servers whose prefill completed this step (read until the pass's first segment ends)
+  uint64_t *bm_idle;  // [nwords] servers below Mp with no prefill in service (the gate looks at those below M), as of the ranks in pre
+  uint64_t *bm_comp;  // [2][nwords_m] servers whose prefill completed this step (immediate decode: that may be admitted to again), steps in turn
   uint64_t *bm_busy;  // [nwords] servers running an iteration
-  uint64_t *bm_due;   // [nwords] servers that had their event in this step (and busy ones whose event is next)
+  uint64_t *bm_just;  // [2][nwords] servers that went idle in this step (steps in turn)
   uint64_t *jobs;     // [kJobsLds] the first requests a routing pass places, copied from the decode buffer
   uint64_t *fresh;    // [kJobsLds] abandonment, more than one wave: this step's first completed prefills (two buffers: half each)
   // two-buffer routers only: completed prefills of this step whose request goes to the solo group, and their ranks
-  uint64_t *bm_solo;  // [nwords]
+  uint64_t *bm_solo;  // [2][nwords_m] (steps in turn)
   uint16_t *pre_s;    // [nwords]
   uint64_t *bm_lvl;   // [kRouteLevels][nwords] routing pass: servers of the routed group with at most (level) decodes
   uint16_t *pre_lvl;  // [kRouteLevels][nwords] exclusive prefix popcounts of bm_lvl, per level
@@ -305,6 +305,8 @@ struct Lds {
 // ones and those behind them then sits at an offset the compiler knows (an immediate in the LDS instruction)
 // instead of one it has to keep in a register, or to spill and fetch back, at every access. Used for the
 // workgroups of sixteen waves (N up to 64 NWS servers). NWS = 0: everything sized by the configuration.
+// Whether workgroups of this size have the bitmaps that overlapping steps take in turn (see kOverlap in the step kernel).
+__host__ __device__ constexpr bool steps_overlap(int threads) { return threads >= 512; }
 constexpr int kStaticWordsLarge = kMaxN / 64;   // any N the library accepts
 constexpr int kStaticWordsMedium = 160;          // N up to 10240: three kilobytes less
 template <int NWS, bool SMALL = false>
@@ -316,6 +318,8 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   size_t off = 0;
   const size_t nw = NWS ? static_cast<size_t>(NWS) : static_cast<size_t>(p.nwords);
   const size_t waves = NWS ? 16u : static_cast<size_t>(p.threads / 64);
+  const size_t turns = steps_overlap(static_cast<int>(64 * waves)) ? 2 : 1;   // bitmaps that steps take in turn
+  const size_t nw_m = NWS ? nw : static_cast<size_t>((p.Mp + 63) / 64);   // words with servers that may hold a prefill
 #define GNR_TAKE(field, type, count)                       \
   L.field = reinterpret_cast<type *>(base + off);          \
   off += (sizeof(type) * static_cast<size_t>(count) + 7) & ~size_t(7);
@@ -331,11 +335,11 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(ev_g, uint16_t, waves * kEvPerWave)
   GNR_TAKE(bm_idle, uint64_t, nw)
   GNR_TAKE(bm_busy, uint64_t, nw)
-  GNR_TAKE(bm_due, uint64_t, nw)
+  GNR_TAKE(bm_just, uint64_t, turns * nw)
   GNR_TAKE(bm_lvl, uint64_t, kRouteLevels * nw)
-  GNR_TAKE(bm_comp, uint64_t, nw)
+  GNR_TAKE(bm_comp, uint64_t, turns * nw_m)
   const size_t nw_two = p.route_mode == SIM_ROUTE_RANDOM_SPLIT || p.route_mode == SIM_ROUTE_WEIGHTED_SPLIT ? nw : 0;
-  GNR_TAKE(bm_solo, uint64_t, nw_two)
+  GNR_TAKE(bm_solo, uint64_t, nw_two ? turns * nw_m : 0)
   GNR_TAKE(pre_s, uint16_t, nw_two)
   // the ranks of a pass's levels are formed when those of the completions are no longer read (a barrier lies between)
   GNR_TAKE(pre_lvl, uint16_t, kRouteLevels * nw)
@@ -590,7 +594,7 @@ struct StepArrays {
 // IM: the variant with immediate same-slot decode (no router): a request whose prefill ends goes on decoding on
 // its own server, placed there by the lane that finishes the server; a server is offered to the gate while it
 // holds no prefill and fewer than B decodes.
-template <int NT, int NWS, bool AB, bool RR, bool IM, bool WS = false, bool DENSE = false>
+template <int NT, int NWS, bool AB, bool RR, bool IM, bool WS = false, bool DENSE = false, bool OV = steps_overlap(NT)>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NT, DENSE)))) gnr_step_kernel(const Params *__restrict__ params, const StepArrays a,
                                                         const uint32_t key0_arg, const uint32_t key1_arg,
                                                         const uint32_t step_begin_arg, const uint32_t n_steps_arg)
@@ -727,6 +731,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     }
     return n;
   };
+  constexpr bool kOverlap = OV;
+  // bitmaps that steps take in turn where they overlap: how far apart they are
+  const int turn_words = !kOverlap ? 0 : NWS ? NWS : nwords, turn_words_m = !kOverlap ? 0 : NWS ? NWS : nwords_m;
   // classes that the gate may admit: under the occupancy gate those with a positive target
   const uint64_t admissible = __ballot(lane < K && (gate_mode != SIM_GATE_OCCUPANCY || L.gtab[GT_INVX * kMaxK + (lane & (kMaxK - 1))] > 0.0));
   auto bits64 = [](uint64_t *p) __attribute__((always_inline)) { return reinterpret_cast<unsigned long long *>(p); };
@@ -776,7 +783,13 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     const int wi = (i * NT + wave_base) >> 6;
     if (lane == 0 && wi < nwords) {
       L.bm_idle[wi] = bi; L.bm_busy[wi] = bb;
-      L.bm_due[wi] = 0;
+      L.bm_just[wi] = 0;
+      L.bm_just[turn_words + wi] = 0;
+      if (wi < nwords_m) {
+        L.bm_comp[wi] = 0;
+        L.bm_comp[turn_words_m + wi] = 0;
+        if constexpr (RR) { L.bm_solo[wi] = 0; L.bm_solo[turn_words_m + wi] = 0; }
+      }
     }
   }
   __syncthreads();
@@ -898,8 +911,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   constexpr int kHits = NT <= 64 ? 2 : 1;
   uint64_t hits[kHits] = {};
   constexpr bool kBeside = NT >= 512 && !RR;
-  // (with more than eight words a wave the events need more than half of the waves)
-  const int n_drain = !kBeside ? nwaves : nwords > 8 * nwaves ? nwaves * 5 / 8 : nwaves / 2;
+  // (with more than eight words a wave the events need more than half of the waves: of 10000 servers 9, 10, 11 of sixteen take
+  // 15.8, 15.6, 15.9 ms per 1000 steps, and 10 and 11 take 15.0 and 14.8 where steps overlap and the words are drawn four at a time)
+  const int n_drain = !kBeside ? nwaves : nwords > 8 * nwaves ? nwaves * 11 / 16 : nwaves / 2;
   const int n_draw = nwaves - n_drain, drain_first = n_draw;
   bool drawn = false;   // the step to come has been drawn (kBeside: by this wave, and its requests are not yet counted)
   // The words first, first + stride, ...: lane j of `hits` gets the servers of the j-th one that have requests. (One wave alone
@@ -909,7 +923,55 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     // the random block's first round has the server in one product only; the other one is the same for all
     const uint64_t ps = static_cast<uint64_t>(0xD2511F53u) * sd;
     const uint32_t c2_1 = static_cast<uint32_t>(ps >> 32) ^ static_cast<uint32_t>(r) ^ key1, c3_1 = static_cast<uint32_t>(ps);
-    for (int j = 0; first + j * stride < nwords; j += 2) {   // wave-uniform
+    int j = 0;
+    // Many words a wave: four at a time, with the round keys formed anew in vector registers. (An instruction that reads a scalar
+    // register takes the vector unit four cycles, an exclusive-or of three vector registers two and a half, measured; 10000
+    // servers x 256 replications, 32 words a wave, 14.9 -> 14.7 ms per 1000 steps; with a few words a wave it gains nothing.)
+    if constexpr (NT == 1024 && kBeside) {
+      if (nwords > 8 * nwaves) {   // wave-uniform
+        constexpr int kAtOnce = 4;
+        // ... and the second round's products with what is the same for all
+        const uint64_t b_2 = static_cast<uint64_t>(0xCD9E8D57u) * c2_1;
+        const uint32_t n0_2 = static_cast<uint32_t>(b_2 >> 32) ^ (key0 + 0x9E3779B9u), n2_2 = c3_1 ^ (key1 + 0xBB67AE85u);
+        for (; first + (j + 2) * stride < nwords; j += kAtOnce) {   // wave-uniform
+          uint32_t c0[kAtOnce], c1[kAtOnce], c2[kAtOnce], c3[kAtOnce];
+#pragma unroll
+          for (int u = 0; u < kAtOnce; ++u) {
+            const int word = first + (j + u) * stride;
+            const uint64_t pg = static_cast<uint64_t>(0xCD9E8D57u) * static_cast<uint32_t>((word << 6) + lane);
+            const uint64_t a_2 = static_cast<uint64_t>(0xD2511F53u) * (static_cast<uint32_t>(pg >> 32) ^ key0);
+            c0[u] = static_cast<uint32_t>(pg) ^ n0_2;
+            c1[u] = static_cast<uint32_t>(b_2);
+            c2[u] = static_cast<uint32_t>(a_2 >> 32) ^ n2_2;
+            c3[u] = static_cast<uint32_t>(a_2);
+          }
+          uint32_t k0 = key0 + 2u * 0x9E3779B9u, k1 = key1 + 2u * 0xBB67AE85u;
+          asm volatile("" : "+v"(k0), "+v"(k1));
+#pragma unroll
+          for (int round = 3; round <= 10; ++round) {
+#pragma unroll
+            for (int u = 0; u < kAtOnce; ++u) {
+              const uint64_t pa = static_cast<uint64_t>(0xD2511F53u) * c0[u];
+              const uint64_t pb = static_cast<uint64_t>(0xCD9E8D57u) * c2[u];
+              c0[u] = xor3(static_cast<uint32_t>(pb >> 32), c1[u], k0);
+              c2[u] = xor3(static_cast<uint32_t>(pa >> 32), c3[u], k1);
+              c1[u] = static_cast<uint32_t>(pb);
+              c3[u] = static_cast<uint32_t>(pa);
+            }
+            k0 += 0x9E3779B9u;
+            k1 += 0xBB67AE85u;
+            asm volatile("" : "+v"(k0), "+v"(k1));
+          }
+#pragma unroll
+          for (int u = 0; u < kAtOnce; ++u) {
+            const uint64_t hit = __ballot(c0[u] >= thr0);
+            if (kHits == 1 || j < 64) hits[0] = writelane64(hits[0], hit, j + u);
+            else hits[kHits - 1] = writelane64(hits[kHits - 1], hit, j + u - 64);
+          }
+        }
+      }
+    }
+    for (; first + j * stride < nwords; j += 2) {   // wave-uniform; two words with the same round keys
       // the round keys are formed anew with scalar additions: as loop invariants there are twenty of them, and they are
       // kept in lanes of vector registers, from which each costs two vector instructions a round
       uint32_t k0 = key0, k1 = key1;
@@ -977,8 +1039,60 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   auto anew = [&]() __attribute__((always_inline)) {
     asm volatile("" : "+s"(K), "+s"(N), "+s"(B), "+s"(M), "+s"(BS), "+s"(nwords), "+s"(Mp), "+s"(nwords_m), "+s"(gate_mode));
   };
-  bool slots_taken = false;  // bm_comp holds the prefill slots the last gate pass has given away, and they are still in bm_idle
+  // Where steps overlap (kOverlap) no barrier separates a step's last segment from the next step's completion pass: the waves that
+  // serve nobody go on at once. (A step of a workgroup of eight waves and more spent a quarter to a third of its time in waits, most of
+  // it there: a few waves serve, 8 to 12 thousand cycles, while the others wait. 500 servers x 3, same-slot decode 18.4 -> 14.4 ms per
+  // 2000 steps, convergence instance 19.6 -> 17.8, 3001 x 77 4.98 -> 4.50 per 500, 10000 x 256 15.6 -> 14.8 per 1000. In workgroups of
+  // up to four waves, where everything that does not serve draws, it costs 2 to 5 %: 1024 x 2048 16.4 -> 17.0, 256 x 1024 8.1 -> 8.5;
+  // and with two buffers or deadline rings and more than 5120 servers 1 to 3 %: weighted router 8.62 -> 8.77, see step_form.)
+  // What makes it sound: the servers that are given work belong to the waves that serve them until the next barrier. Every other wave
+  // leaves them out of the words it looks at (`others`, lane j: of its j-th word; it follows from the pass's words, as for the waves
+  // that serve); those whose event comes in the next step already (`late`: lanes, late_g: the server) are queued by the wave that has
+  // served them. What serving reads is not changed by a completion pass: bitmaps of completions and of servers that went idle are kept
+  // for two steps in turn, slots given away and become idle change the bitmap of idle ones behind the next barrier (take_slots).
+  // Counters are added to by atomics on both sides. The calendars are asked behind that barrier.
+  // A wave looks at the words first, first + stride, ..., or (pairs) first, first + 1, first + stride, first + stride + 1, ...
+  int scan_first = wave - drain_first, scan_stride = n_drain, scan_pairs = 0;
+  uint64_t others = 0, late = 0;   // late: lanes whose server (late_g) this wave has served and whose event comes next
+  int late_g = 0;
 
+  // The first `left` members of a lane's word: all of them, or (one word a level) some.
+  auto first_members = [&](uint64_t in, int left) __attribute__((always_inline)) -> uint64_t {
+    const int c = __popcll(in);
+    uint64_t out = left >= c ? in : 0ull;
+    const uint64_t part = __ballot(left > 0 && left < c);
+    if (part) {   // wave-uniform
+      const int src = __ffsll(static_cast<long long>(part)) - 1;
+      const uint64_t w = readlane64(in, src);
+      out = writelane64(out, __ballot(lane_in(w) && rank_in(w) < __builtin_amdgcn_readlane(left, src)), src);
+    }
+    return out;
+  };
+  int slots_given = 0;       // idle prefill slots that the last gate pass has given away: the first ones of bm_idle, still in it
+  bool slots_taken = false;  // (where steps do not overlap) bm_comp holds those slots
+  // The slots given away leave the bitmap of idle ones, those of the step's completions (`news`) enter it; by one whole wave. (Not when
+  // they are given away and become idle: waves that serve look at the bitmap while others are in the next completion pass.)
+  auto take_slots = [&](const uint64_t *news) __attribute__((always_inline)) {
+    for (int w0 = 0; w0 < nwords_m; w0 += 64) {   // wave-uniform
+      const int w = w0 + lane;
+      uint64_t idle = 0, fresh_bits = 0;
+      int left = 0;
+      if (w < nwords_m) {
+        idle = L.bm_idle[w];
+        left = slots_given - static_cast<int>(L.pre[w]);
+        if (news) fresh_bits = news[w];
+      }
+      const uint64_t given = first_members(idle & bits_below(w, M), left);
+      if (w < nwords_m) L.bm_idle[w] = (idle & ~given) | fresh_bits;
+    }
+  };
+  auto clear_bitmaps = [&](int at, int at_m) __attribute__((always_inline)) {   // by one whole wave
+    for (int w = lane; w < nwords; w += 64) L.bm_just[at + w] = 0;
+    for (int w = lane; w < nwords_m; w += 64) {
+      L.bm_comp[at_m + w] = 0;
+      if constexpr (RR) L.bm_solo[at_m + w] = 0;
+    }
+  };
   const uint32_t step_end = step_begin + n_steps;
 
   int64_t T = 0;
@@ -1024,18 +1138,21 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
       const uint32_t t2 = ((s >> 8) + (static_cast<uint32_t>(r) >> 8)) & 1u;
       if (t2 != turn) { turn = t2; own_priority(); }
     }
-    // (No barrier here: a wave goes from a step's last pass straight into the next step's completion pass. Until the
-    // barrier that ends it a wave touches its own servers and bitmap words only, and adds to sums that nobody reads before.)
-    // abandonment only: how many waiting requests of class `tid` leave at the start of this step (asked for
-    // here, used after the completion pass)
+    // abandonment only: how many waiting requests of class `tid` leave at the start of this step. Asked for here and used after the
+    // completion pass, or, where steps overlap, behind it: those that the step before has taken out of the calendars must be out.
     uint32_t n_leave_p = 0, n_leave_d = 0, n_leave_dm = 0;
-    if constexpr (AB) {
-      if (tid < K) {
-        n_leave_p = atomicExch(&cal[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
-        n_leave_d = atomicExch(&dcal[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
-        if constexpr (RR) n_leave_dm = atomicExch(&dcal_m[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
+    auto ask_leaving = [&]() __attribute__((always_inline)) {
+      if constexpr (AB) {
+        if (tid < K) {
+          n_leave_p = atomicExch(&cal[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
+          n_leave_d = atomicExch(&dcal[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
+          if constexpr (RR) n_leave_dm = atomicExch(&dcal_m[static_cast<size_t>(tid) * cal_n + (s & p.cal_mask)], 0u);
+        }
       }
-    }
+    };
+    if constexpr (!kOverlap) ask_leaving();
+    // the bitmaps that steps take in turn: this step's
+    const int side = s & 1u ? turn_words : 0, side_m = s & 1u ? turn_words_m : 0;
     // ---- 2. events: one server per lane (uniform control flow; lanes beyond the queue idle). Tallies the iterations
     //      since the last event, removes the decodes that emitted their last token, advances the prefill. What the
     //      lanes need of their servers' records is asked for first, together with the slot rows of the servers whose
@@ -1172,7 +1289,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
             atomicSub(&L.lh[hb + nd_before], 1u);
             atomicAdd(&L.lh[hb + nd], 1u);
             if constexpr (IM) {   // a full server (it holds no prefill then) has a slot again
-              if (nd_before == B && g < Mp) atomicOr(bits64(&L.bm_idle[wi]), bit);
+              if (nd_before == B && g < Mp) atomicOr(bits64(kOverlap ? &L.bm_comp[side_m + wi] : &L.bm_idle[wi]), bit);
             }
           }
           // the prefill advances by the chunks of those iterations
@@ -1206,15 +1323,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
                   L.loads[g] = static_cast<uint8_t>(nd);
                   lds_add64(&L.tl[k * kNTally + SIM_T_U_DS], 1);
                   atomicAdd(&L.acc[AC_YS + k], 1u);
-                  if (nd < B) atomicOr(bits64(&L.bm_idle[wi]), bit);
+                  if (nd < B) atomicOr(bits64(kOverlap ? &L.bm_comp[side_m + wi] : &L.bm_idle[wi]), bit);
                 }
               } else {
-                atomicOr(bits64(&L.bm_comp[wi]), bit);
-                atomicOr(bits64(&L.bm_idle[wi]), bit);
+                atomicOr(bits64(&L.bm_comp[side_m + wi]), bit);
+                if constexpr (!kOverlap) atomicOr(bits64(&L.bm_idle[wi]), bit);
                 if constexpr (AB || RR) {   // word 0 of its block: patience in the buffer, word 1: which of two buffers
                   uint32_t w[4];
                   philox4x32_10(key0, key1, s, static_cast<uint32_t>(kStreamPatienceD), static_cast<uint32_t>(g), static_cast<uint32_t>(r), w);
-                  if constexpr (RR) { if (w[1] < p.solo_thr[k]) atomicOr(bits64(&L.bm_solo[wi]), bit); }
+                  if constexpr (RR) { if (w[1] < p.solo_thr[k]) atomicOr(bits64(&L.bm_solo[side_m + wi]), bit); }
                   if constexpr (AB) { if ((p.ab_classes >> k) & 1u) wait_steps = pat_tab[static_cast<size_t>(k) * kTableSize + (w[0] >> 16)]; }
                 }
               }
@@ -1226,6 +1343,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
           if (ptok_next == 0 && nd == 0) {
             set_event(g, T + rel, it, false, false);
             atomicAnd(bits64(&L.bm_busy[wi]), ~bit);
+            atomicOr(bits64(&L.bm_just[side + wi]), bit);
           } else {
             const uint32_t dur = iteration_ns(ptok_next, static_cast<uint32_t>(nd));
             const uint32_t n = phase_length(static_cast<uint32_t>(nd), rem, dur, nf - it);
@@ -1285,46 +1403,63 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         drawn = false;
       }
     }
-    if (wave >= drain_first) {
+    if (wave >= drain_first || late) {   // wave-uniform
       const uint32_t T_hi = static_cast<uint32_t>(T >> 8);
-      for (int b0 = wave - drain_first; b0 < nwords; b0 += 64 * n_drain) {   // wave-uniform; the wave's words, 64 a round, one a lane
-        const int w_lane = b0 + lane * n_drain;
+      int nev = 0;   // servers queued by this wave (wave-uniform)
+      if (late) {
+        if (lane_in(late)) ev_g[rank_in(late)] = static_cast<uint16_t>(late_g);
+        nev = __popcll(late);
+      }
+      for (int j0 = 0;; j0 += 64) {   // wave-uniform; the wave's words, 64 a round, one a lane
+        const int first = scan_first + (j0 >> scan_pairs) * scan_stride;
+        if (first >= nwords && nev == 0) break;
+        const int w_lane = first + (lane >> scan_pairs) * scan_stride + (lane & scan_pairs);
+        const int step_1 = scan_pairs ? 1 : scan_stride, step_2 = scan_pairs ? scan_stride - 1 : scan_stride;
         uint64_t due = 0;
         // (lanes past the last server are not busy; a clock a few ns ahead may pass here for its upper bits: the servers
         // queued are looked at exactly)
-        int at = (b0 << 6) + lane;   // the word's server of this lane
-        for (int j = 0; j < 64 && b0 + j * n_drain < nwords; j += 4) {   // wave-uniform; up to three words past the last one: no lane's
+        int at = (first << 6) + lane;   // the word's server of this lane
+        for (int j = 0; j < 64 && first + (j >> scan_pairs) * scan_stride < nwords; j += 4) {   // wave-uniform; up to three words past the last one: no lane's
           uint32_t ev[4];
 #pragma unroll
-          for (int u = 0; u < 4; ++u) { ev[u] = L.ev_t[at < N ? at : N - 1]; at += n_drain << 6; }
+          for (int u = 0; u < 4; ++u) { ev[u] = L.ev_t[at < N ? at : N - 1]; at += (u & 1 ? step_2 : step_1) << 6; }
 #pragma unroll
           for (int u = 0; u < 4; ++u) due = writelane64(due, __ballot(static_cast<int32_t>(ev[u] - T_hi) <= 0), j + u);
         }
-        if (w_lane < nwords) {
-          due &= L.bm_busy[w_lane];
-          L.bm_due[w_lane] = due;
-          if (slots_taken) L.bm_idle[w_lane] &= ~L.bm_comp[w_lane];
-          L.bm_comp[w_lane] = 0;
-          if constexpr (RR) L.bm_solo[w_lane] = 0;
-        } else {
-          due = 0;
+        due &= w_lane < nwords ? L.bm_busy[w_lane] & ~others : 0ull;
+        if constexpr (!kOverlap) {   // (its own words: nobody else is at them)
+          if (w_lane < nwords) {
+            L.bm_just[w_lane] = 0;
+            if (w_lane < nwords_m) {
+              if (slots_taken) L.bm_idle[w_lane] &= ~L.bm_comp[w_lane];
+              L.bm_comp[w_lane] = 0;
+              if constexpr (RR) L.bm_solo[w_lane] = 0;
+            }
+          }
         }
-        int nev = 0;   // servers queued by this wave (wave-uniform)
-        for (uint64_t todo = __ballot(due != 0); todo;) {
-          const int src = __ffsll(static_cast<long long>(todo)) - 1;
-          const uint64_t dm = readlane64(due, src);
-          todo &= todo - 1ull;
-          if (lane_in(dm)) ev_g[nev + rank_in(dm)] = static_cast<uint16_t>(((b0 + src * n_drain) << 6) + lane);
-          nev += __popcll(dm);
+        others = 0;   // (only a wave alone has more than 64 words, and none of its servers is another's)
+        for (uint64_t todo = __ballot(due != 0); todo || nev > 0;) {
+          if (todo) {
+            const int src = __ffsll(static_cast<long long>(todo)) - 1;
+            const uint64_t dm = readlane64(due, src);
+            todo &= todo - 1ull;
+            const int w = first + (src >> scan_pairs) * scan_stride + (src & scan_pairs);
+            if (lane_in(dm)) ev_g[nev + rank_in(dm)] = static_cast<uint16_t>((w << 6) + lane);
+            nev += __popcll(dm);
+          }
           if (nev > kEvPerWave - 64 || !todo) { drain_events(nev); nev = 0; }
         }
       }
     }
+    late = 0;
     slots_taken = false;
     __syncthreads();
 
     anew();
     // ================= arrivals into the class queues; ranks of completions and idle slots =================
+    if constexpr (kOverlap) ask_leaving();
+    uint32_t ncomp_all = 0;
+    if constexpr (!IM) { if (tid < 64) ncomp_all = rank_bitmap(L.bm_comp + side_m, L.pre_c, nwords_m, Mp); }
     if (tid < K) {
       const int k = tid;
       // (everything that is needed is read first: one trip to LDS)
@@ -1379,7 +1514,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     }
     ended = 0;
     if (tid < 64) {
-      const uint32_t ncomp = rank_bitmap(L.bm_comp, L.pre_c, nwords_m, Mp);
+      const uint32_t ncomp = ncomp_all;
       if (tid == 0) {
         L.sc[SC_NCOMP] = static_cast<int32_t>(ncomp);
         if constexpr (AB) {
@@ -1395,12 +1530,17 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
       }
     }
     if (NT == 64 ? tid < 64 : (tid >= 64 && tid < 128)) {
+      if constexpr (kOverlap) take_slots(L.bm_comp + side_m);
       const uint32_t nidle = rank_bitmap(L.bm_idle, L.pre, nwords_m, M);   // idle prefill slots of the mixed group
       if (lane == 0) L.sc[SC_NIDLE] = static_cast<int32_t>(nidle);
     }
+    if constexpr (kOverlap) {   // (what the step before had in these has been read)
+      if (wave == nwaves - 1) clear_bitmaps(turn_words - side, turn_words_m - side_m);
+    }
+    slots_given = 0;
     if constexpr (RR) {   // (another wave where there is one)
       if (wave == (nwaves > 2 ? 2 : nwaves - 1)) {
-        const uint32_t nsolo = rank_bitmap(L.bm_solo, L.pre_s, nwords_m, Mp);
+        const uint32_t nsolo = rank_bitmap(L.bm_solo + side_m, L.pre_s, nwords_m, Mp);
         if (lane == 0) L.sc[SC_NSOLO] = static_cast<int32_t>(nsolo);
       }
     }
@@ -1483,7 +1623,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
       for (uint32_t j0 = static_cast<uint32_t>(comp_turn) * 64u; j0 < ncomp; j0 += NT) {   // wave-uniform trip count
         const uint32_t j = j0 + lane;
         if (j < ncomp) {
-          const int g = select_bit(L.bm_comp, L.pre_c, nwords_m, j);
+          const int g = select_bit(L.bm_comp + side_m, L.pre_c, nwords_m, j);
           const uint64_t jw = rec[g].pf_job;
           const int k = static_cast<int>(jw >> 29) & 7;
           uint32_t dl = kNever;
@@ -1495,7 +1635,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
           bool solo = true;   // the only buffer, or the solo group's
           uint32_t idx = j;   // its place among those that join that buffer
           if constexpr (RR) {
-            const uint64_t to_solo = L.bm_solo[g >> 6], bit = 1ull << (g & 63);
+            const uint64_t to_solo = L.bm_solo[side_m + (g >> 6)], bit = 1ull << (g & 63);
             solo = to_solo & bit;
             const uint32_t before = L.pre_s[g >> 6] + static_cast<uint32_t>(__popcll(to_solo & (bit - 1ull)));
             idx = solo ? before : j - before;
@@ -1587,8 +1727,14 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         return w[0];
       };
       for (int pass = 0; gate_on || route_on; ++pass) {
-        if (slots_taken) {   // (in a pass after the first)
-          for (int w = tid; w < nwords; w += NT) L.bm_idle[w] &= ~L.bm_comp[w];
+        if constexpr (kOverlap) {
+          if (pass > 0 && slots_given > 0) {
+            if (tid < 64) take_slots(nullptr);
+            slots_given = 0;
+            __syncthreads();
+          }
+        } else if (slots_taken) {   // (in a pass after the first)
+          for (int w = tid; w < nwords_m; w += NT) L.bm_idle[w] &= ~L.bm_comp[w];
           slots_taken = false;
           __syncthreads();
         }
@@ -2279,7 +2425,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
           auto serve = [&](int nsrv) __attribute__((always_inline)) {   // (up to 64)
               const bool active = lane < nsrv;
               uint32_t m = 0, d = 0;   // iterations to tally
-              bool chunk = false;
+              bool chunk = false, comes_next = false;
               uint64_t comp = 0;
               if (active) {
                 const int entry = ev_g[lane], g = entry & 0x7FFF, wi = g >> 6;
@@ -2288,7 +2434,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
                 uint64_t nc = rec[g].n_cls, nj = rec[g].n_join;
                 uint32_t it_tal = rec[g].iter, nf = rec[g].next_fin;
                 const uint64_t idle = L.bm_idle[wi];
-                const bool busy = L.bm_busy[wi] & bit, due = L.bm_due[wi] & bit;
+                const bool busy = L.bm_busy[wi] & bit, due = L.bm_just[side + wi] & bit;
                 const int n_own = static_cast<int>(L.loads[g]);   // decodes of the server
                 int rem = g < Mp ? static_cast<int>(L.rem[g]) : 0;
                 const uint32_t ev = L.ev_it[g];
@@ -2454,22 +2600,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
                 rec[g].n_join = nj;
                 rec[g].iter = it_tal;
                 rec[g].next_fin = nf;
+                if constexpr (kOverlap) {
+                  comes_next = event_time(g, T + dt_ns) <= 0;
+                  late_g = g;
+                }
               }
+              if constexpr (kOverlap) late = __ballot(comes_next);
               tally_iterations<kTallyRowsHere>(L.ta, L.tbth, tbt_w, tbt_lo, K, m, d, chunk, comp);
           };
-          // Which servers: the members of every level before a lane's word are counted, two levels in one sum. The first
-          // `left` members of a word: all of them, or (one word a level) some.
-          auto first_members = [&](uint64_t in, int left) __attribute__((always_inline)) -> uint64_t {
-            const int c = __popcll(in);
-            uint64_t out = left >= c ? in : 0ull;
-            const uint64_t part = __ballot(left > 0 && left < c);
-            if (part) {   // wave-uniform
-              const int src = __ffsll(static_cast<long long>(part)) - 1;
-              const uint64_t w = readlane64(in, src);
-              out = writelane64(out, __ballot(lane_in(w) && rank_in(w) < __builtin_amdgcn_readlane(left, src)), src);
-            }
-            return out;
-          };
+          // Which servers: the members of every level before a lane's word are counted, two levels in one sum.
           int lo = my_serve << 6, n_all = 0;   // this wave's are lo, lo + 1, ... of n_all
           do {   // (a second time round only where even all waves are too few)
             uint32_t before[2] = {0, 0};   // members of the levels in the words before
@@ -2491,7 +2630,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
                 adm = first_members(slots, left);
                 got = adm;
                 // (other waves may still look at bm_idle: the slots given away are taken out of it later)
-                if (my_serve == 0 && w < nwords_m) L.bm_comp[w] = adm;
+                if constexpr (!kOverlap) { if (my_serve == 0 && w < nwords_m) L.bm_comp[w] = adm; }
               }
 #pragma unroll
               for (int t0 = 0; t0 < kRouteLevels; t0 += 2) {
@@ -2546,7 +2685,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
           next_thresholds();
           drawn = true;
         }
-        if (nadm > 0) slots_taken = true;
         if (placed > 0) {
           if constexpr (WS) {   // what the pass took from the solo group's buffer, per class
             if (tid >= NT - 64 && lane < K) L.cs[CS_QDS + lane] -= L.sel_n[lane];
@@ -2572,7 +2710,76 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         }
         route_on = levels & 0x10000;
         gate_on = gate_more;
-        if (work > 0 || gate_on || route_on) __syncthreads();   // (the same for every thread)
+        if (nadm > 0) { slots_given = nadm; slots_taken = true; }
+        // Where the step ends here, every wave goes on by itself, as long as the servers that are given work are known to the others.
+        const bool apart_next = kOverlap && work > 0 && n_serve < nwaves && !gate_on && !route_on;
+        if (gate_on || route_on || (work > 0 && !apart_next)) __syncthreads();   // (the same for every thread)
+        if (!apart_next) late = 0;
+        scan_first = wave - drain_first; scan_stride = n_drain; scan_pairs = 0;
+        others = 0;
+        if (apart_next) {
+          // The waves that serve come last. Where the others are three times as many these look at all words, else, where the events
+          // are not shared by all waves, at two for one of the waves that serve (10000 x 256, four or five of eleven serve).
+          {
+            const int n_busy = n_serve < n_drain ? n_serve : n_drain, n_free = n_drain - n_busy;
+            if (n_free >= 3 * n_busy) {
+              scan_stride = n_free;
+              if (wave >= nwaves - n_busy) scan_first = nwords;
+            } else if (kBeside) {
+              scan_stride = 2 * n_free + n_busy;
+              scan_pairs = wave < nwaves - n_busy ? 1 : 0;
+              scan_first = scan_pairs ? 2 * (wave - drain_first) : 2 * n_free + wave - (nwaves - n_busy);
+            }
+          }
+          if (wave < drain_first) scan_first = nwords;
+          const int w = scan_first + (lane >> scan_pairs) * scan_stride + (lane & scan_pairs);
+          if (scan_first < nwords) {
+            if (nadm > 0) {   // the first nadm idle slots
+              uint64_t slots = 0;
+              int left = 0;
+              if (w < nwords_m) {
+                slots = L.bm_idle[w] & bits_below(w, M);
+                left = nadm - static_cast<int>(L.pre[w]);
+              }
+              others = first_members(slots, left);
+            }
+            // of each group all members of the levels below its last one, and the first take_r of the last one
+#pragma unroll
+            for (int gi = 0; gi < 2; ++gi) {
+              const int t_first = gi == 0 ? 0 : nl_solo, t_last = (gi == 0 ? nl_solo : nl_here) - 1;
+              const int w_begin = gi == 0 ? M >> 6 : 0, w_end = gi == 0 ? nwords : (M + 63) >> 6;
+              if (t_last >= t_first) {   // wave-uniform
+                const uint64_t *lvl = L.bm_lvl + t_last * nwords;
+                const int take = word_of(SC_TAKE_T + t_last);
+                int members = 0;
+                for (int t = t_first; t <= t_last; ++t) members += word_of(SC_CNT_T + t);
+                int cut_word = nwords;    // the word that has the last of the first `take`
+                uint64_t cut_set = 0;     // those of them in that word
+                if (take < members) {
+                  int before = 0;
+                  for (int w0 = w_begin; w0 < w_end; w0 += 64) {   // wave-uniform
+                    const uint64_t in = w0 + lane < w_end ? lvl[w0 + lane] : 0ull;
+                    const int c = __popcll(in), upto = before + static_cast<int>(wave_incl_scan(static_cast<uint32_t>(c)));
+                    const uint64_t here = __ballot(upto >= take);
+                    if (here) {
+                      const int src = __ffsll(static_cast<long long>(here)) - 1;
+                      const uint64_t set = readlane64(in, src);
+                      const int n = take - (__builtin_amdgcn_readlane(upto, src) - __popcll(set));
+                      cut_word = w0 + src;
+                      cut_set = __ballot(lane_in(set) && rank_in(set) < n);
+                      break;
+                    }
+                    before = __builtin_amdgcn_readlane(upto, 63);
+                  }
+                }
+                if (w >= w_begin && w < w_end) {
+                  others |= w < cut_word ? lvl[w] : w == cut_word ? cut_set : 0ull;
+                  if (t_last > t_first) others |= lvl[w - nwords];
+                }
+              }
+            }
+          }
+        }
       }
       if constexpr (AB) {
         if (tid == 0) {   // the head moves past everything the routing passes walked over
@@ -2713,18 +2920,22 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
 }
 
 // The step kernel of one policy variant: `form` is 0 to 3 for workgroups of 64, 128, 256 and 512 threads, in their roomy or
-// dense form (see waves_per_simd), 4 and 5 for those of 1024 (see size_class). Every workgroup size is compiled by itself: the
-// counts of waves, and what follows from them, are constants. Each variant is compiled in a translation unit of its own.
+// dense form (see waves_per_simd), 4 to 6 for those of 1024 (see step_form). Every workgroup size is compiled by itself, so
+// that the count of waves and what follows from it are constants and not values kept in lanes of vector registers: compiled for
+// two sizes each, with the count read at run time, the timed cases took 1 to 7 % longer (8 servers x 16 replications 16.7
+// instead of 15.7 ms per 10^4 steps, 256 x 1024 9.15 instead of 8.61 per 1000, 1024 x 2048 17.85 instead of 17.20, 3001 x 77 5.80
+// instead of 5.58 per 500). Each variant is compiled in a translation unit of its own.
 using StepKernel = void (*)(const Params *, StepArrays, uint32_t, uint32_t, uint32_t, uint32_t);
 #define GNR_STEP_VARIANT(name, AB, RR, IM, WS)                                                             \
   StepKernel name(int form, bool dense)                                                                    \
   {                                                                                                        \
-    static const StepKernel roomy[6] = {gnr_step_kernel<64, 0, AB, RR, IM, WS>,                            \
+    static const StepKernel roomy[7] = {gnr_step_kernel<64, 0, AB, RR, IM, WS>,                            \
                                         gnr_step_kernel<128, 0, AB, RR, IM, WS>,                           \
                                         gnr_step_kernel<256, 0, AB, RR, IM, WS>,                           \
                                         gnr_step_kernel<512, 0, AB, RR, IM, WS>,                           \
-                                        gnr_step_kernel<1024, static_words(2), AB, RR, IM, WS>,            \
-                                        gnr_step_kernel<1024, static_words(3), AB, RR, IM, WS>};           \
+                                        gnr_step_kernel<1024, static_words(2), AB, RR, IM, WS, false, !(AB || RR)>, \
+                                        gnr_step_kernel<1024, static_words(3), AB, RR, IM, WS, false, !(AB || RR)>, \
+                                        gnr_step_kernel<1024, static_words(2), AB, RR, IM, WS>};           \
     static const StepKernel full[4] = {gnr_step_kernel<64, 0, AB, RR, IM, WS, true>,                       \
                                        gnr_step_kernel<128, 0, AB, RR, IM, WS, true>,                      \
                                        gnr_step_kernel<256, 0, AB, RR, IM, WS, true>,                      \
