@@ -21,6 +21,9 @@ constexpr int kNGlobal = SIM_NGLOBAL;
 constexpr int kTallyWords = kMaxK * kNTally + kNGlobal;  // per replication, uint64
 constexpr int64_t kIdle = INT64_MAX;
 constexpr uint32_t kIdleRel = 0xFFFFFFFFu;   // the same in a server's stored clock (see Params::t_rel)
+// Finish word of a slot without a decode: above every iteration a decode can end in (a run has fewer than 2^29 steps, and an iteration
+// is no shorter than a step), so that an occupied slot's word is never below the completed iterations and a free one's never next to them.
+constexpr uint32_t kFreeSlot = 0x7FFFFFFFu;
 constexpr int kAdmChunk = 256;    // admissions decided per gate pass
 constexpr uint32_t kStepsPerLaunch = 2048;
 // (a launch counts the tokens of a class in 32 bits: no decode emits more than one a step, and one more that the launch before began)

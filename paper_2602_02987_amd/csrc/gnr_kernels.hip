@@ -117,7 +117,7 @@ __global__ void gnr_reset_kernel(const Params p, const int reps)
     p.rec[i] = ServerRec{0, 0, 0, 0, kNever};
     p.t_rel[i] = kIdleRel; p.remptok[i] = 0;
   }
-  for (size_t i = t0; i < n_srv * p.BS; i += stride) p.fin[i] = 0;   // free slots never match an iteration index
+  for (size_t i = t0; i < n_srv * p.BS; i += stride) p.fin[i] = kFreeSlot;
   for (size_t i = t0; i < static_cast<size_t>(reps) * CS_WORDS; i += stride) p.cstate[i] = 0;
   for (size_t i = t0; i < static_cast<size_t>(reps) * kTallyWords; i += stride) p.tally[i] = 0;
   for (size_t i = t0; i < static_cast<size_t>(reps) * 3 * p.K * kNBin; i += stride) p.hist[i] = 0;

@@ -270,7 +270,8 @@ struct Lds {
   uint64_t *tbth;     // [(K + 1) / 2][tbt_w] time between tokens: counts of two classes a word, 32 bits each
   uint64_t *bm_idle;  // [nwords] servers below Mp with no prefill in service (the gate looks at those below M), as of the ranks in pre
   uint64_t *bm_comp;  // [2][nwords_m] servers whose prefill completed this step (immediate decode: that may be admitted to again), steps in turn
-  uint64_t *bm_busy;  // [nwords] servers running an iteration
+  uint64_t *bm_busy;  // [nwords, or one more: even] servers running an iteration
+  uint64_t *bm_others;// [the same] steps that overlap: of a wave's words the servers that others have been given, for the next completion pass
   uint64_t *bm_just;  // [2][nwords] servers that went idle in this step (steps in turn)
   uint64_t *jobs;     // [kJobsLds] the first requests a routing pass places, copied from the decode buffer
   uint64_t *fresh;    // [kJobsLds] abandonment, more than one wave: this step's first completed prefills (two buffers: half each)
@@ -334,7 +335,8 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   GNR_TAKE(lh, uint32_t, 2 * kLoadBins)
   GNR_TAKE(ev_g, uint16_t, waves * kEvPerWave)
   GNR_TAKE(bm_idle, uint64_t, nw)
-  GNR_TAKE(bm_busy, uint64_t, nw)
+  GNR_TAKE(bm_busy, uint64_t, (nw + 1) & ~size_t(1))
+  GNR_TAKE(bm_others, uint64_t, turns > 1 ? (nw + 1) & ~size_t(1) : 0)
   GNR_TAKE(bm_just, uint64_t, turns * nw)
   GNR_TAKE(bm_lvl, uint64_t, kRouteLevels * nw)
   GNR_TAKE(bm_comp, uint64_t, turns * nw_m)
@@ -785,6 +787,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
       L.bm_idle[wi] = bi; L.bm_busy[wi] = bb;
       L.bm_just[wi] = 0;
       L.bm_just[turn_words + wi] = 0;
+      if constexpr (kOverlap) L.bm_others[wi] = 0;
       if (wi < nwords_m) {
         L.bm_comp[wi] = 0;
         L.bm_comp[turn_words_m + wi] = 0;
@@ -792,6 +795,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
       }
     }
   }
+  if (tid == 0 && (nwords & 1)) L.bm_busy[nwords] = 0;   // (clocks are looked at for two words at a time)
   __syncthreads();
 
   // ---- abandonment only: ring compaction, one wave per ring. Entries whose deadline is not after `now` are
@@ -1046,14 +1050,15 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // up to four waves, where everything that does not serve draws, it costs 2 to 5 %: 1024 x 2048 16.4 -> 17.0, 256 x 1024 8.1 -> 8.5;
   // and with two buffers or deadline rings and more than 5120 servers 1 to 3 %: weighted router 8.62 -> 8.77, see step_form.)
   // What makes it sound: the servers that are given work belong to the waves that serve them until the next barrier. Every other wave
-  // leaves them out of the words it looks at (`others`, lane j: of its j-th word; it follows from the pass's words, as for the waves
+  // leaves them out of the words it looks at (bm_others, of its own words; it follows from the pass's words, as for the waves
   // that serve); those whose event comes in the next step already (`late`: lanes, late_g: the server) are queued by the wave that has
   // served them. What serving reads is not changed by a completion pass: bitmaps of completions and of servers that went idle are kept
   // for two steps in turn, slots given away and become idle change the bitmap of idle ones behind the next barrier (take_slots).
   // Counters are added to by atomics on both sides. The calendars are asked behind that barrier.
-  // A wave looks at the words first, first + stride, ..., or (pairs) first, first + 1, first + stride, first + stride + 1, ...
-  int scan_first = wave - drain_first, scan_stride = n_drain, scan_pairs = 0;
-  uint64_t others = 0, late = 0;   // late: lanes whose server (late_g) this wave has served and whose event comes next
+  // A wave looks at the pairs of words first, first + stride, ... below the end (and below the last one)
+  int scan_first = wave - drain_first, scan_stride = n_drain, scan_end = nwords;
+  constexpr int kPairsAtOnce = 4;
+  uint64_t late = 0;   // lanes whose server (late_g) this wave has served and whose event comes next
   int late_g = 0;
 
   // The first `left` members of a lane's word: all of them, or (one word a level) some.
@@ -1205,7 +1210,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
             atomicAdd(reinterpret_cast<unsigned long long *>(&hist[(1 * K + k) * kNBin + hbin(e2e)]), 1ull);
             nc -= 1ull << (8 * k);
             if (gone_slot < nd) { frow[gone_slot] = last_fin; jrow[gone_slot] = last_job; }
-            frow[nd] = 0;   // a vacated slot must never match a later iteration index
+            frow[nd] = kFreeSlot;
           }
           gone_slot = -1;
         };
@@ -1227,7 +1232,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
             uint4 v[4];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              v[q] = make_uint4(0u, 0u, 0u, 0u);   // (0: an empty slot, never an iteration a decode ends in)
+              v[q] = make_uint4(kFreeSlot, kFreeSlot, kFreeSlot, kFreeSlot);
               if (32 * q < BS && 4 * (l8 + 8 * q) < o_nd) v[q] = stream_load(frow + 32 * q);
             }
             int high = -1, count = 0;
@@ -1410,42 +1415,61 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         if (lane_in(late)) ev_g[rank_in(late)] = static_cast<uint16_t>(late_g);
         nev = __popcll(late);
       }
-      for (int j0 = 0;; j0 += 64) {   // wave-uniform; the wave's words, 64 a round, one a lane
-        const int first = scan_first + (j0 >> scan_pairs) * scan_stride;
-        if (first >= nwords && nev == 0) break;
-        const int w_lane = first + (lane >> scan_pairs) * scan_stride + (lane & scan_pairs);
-        const int step_1 = scan_pairs ? 1 : scan_stride, step_2 = scan_pairs ? scan_stride - 1 : scan_stride;
-        uint64_t due = 0;
-        // (lanes past the last server are not busy; a clock a few ns ahead may pass here for its upper bits: the servers
-        // queued are looked at exactly)
-        int at = (first << 6) + lane;   // the word's server of this lane
-        for (int j = 0; j < 64 && first + (j >> scan_pairs) * scan_stride < nwords; j += 4) {   // wave-uniform; up to three words past the last one: no lane's
-          uint32_t ev[4];
-#pragma unroll
-          for (int u = 0; u < 4; ++u) { ev[u] = L.ev_t[at < N ? at : N - 1]; at += (u & 1 ? step_2 : step_1) << 6; }
-#pragma unroll
-          for (int u = 0; u < 4; ++u) due = writelane64(due, __ballot(static_cast<int32_t>(ev[u] - T_hi) <= 0), j + u);
-        }
-        due &= w_lane < nwords ? L.bm_busy[w_lane] & ~others : 0ull;
+      // A lane looks at two neighbouring servers of a pair of words; what it finds enters the lower end of its masks, so that after
+      // `seen` pairs the i-th pair's servers are bits 2 (seen - 1 - i) and the one above. (A server a lane, the ballots collected a word
+      // a lane and the words queued one after another, took twice the vector instructions for a clock and fifteen more a word: 1024 x
+      // 2048 16.76 -> 16.25 ms per 1000 steps, 2048 x 1024 17.05 -> 16.42, 3001 x 77 4.74 -> 4.53 per 500, randomized router 5.48 -> 5.36
+      // per 300, 10000 x 256 14.14 -> 14.05.)
+      const int last_pair = (nwords - 1) >> 1, npairs = scan_end <= last_pair ? scan_end : last_pair + 1;
+      const uint32_t T_past = T_hi + 1u;
+      const int last_clock = (N - 1) & ~1;
+      for (int first = scan_first;; first += 16 * scan_stride) {   // wave-uniform; the wave's pairs of words, sixteen a round
+        if (first >= npairs && nev == 0) break;
         if constexpr (!kOverlap) {   // (its own words: nobody else is at them)
-          if (w_lane < nwords) {
-            L.bm_just[w_lane] = 0;
-            if (w_lane < nwords_m) {
-              if (slots_taken) L.bm_idle[w_lane] &= ~L.bm_comp[w_lane];
-              L.bm_comp[w_lane] = 0;
-              if constexpr (RR) L.bm_solo[w_lane] = 0;
+          const int w = 2 * (first + (lane >> 1) * scan_stride) + (lane & 1);
+          if (lane < 32 && w < nwords) {
+            L.bm_just[w] = 0;
+            if (w < nwords_m) {
+              if (slots_taken) L.bm_idle[w] &= ~L.bm_comp[w];
+              L.bm_comp[w] = 0;
+              if constexpr (RR) L.bm_solo[w] = 0;
             }
           }
         }
-        others = 0;   // (only a wave alone has more than 64 words, and none of its servers is another's)
-        for (uint64_t todo = __ballot(due != 0); todo || nev > 0;) {
+        uint32_t due = 0, own = 0;
+        int seen = 0;
+        // (servers past the last one are not busy; a clock a few ns ahead may pass here for its upper bits: the servers
+        // queued are looked at exactly)
+        for (; seen < 16 && first + seen * scan_stride < npairs; seen += kPairsAtOnce) {   // wave-uniform; up to three pairs past the last one
+          uint2 ev[kPairsAtOnce];
+          uint32_t here[kPairsAtOnce];
+          int n_bits[kPairsAtOnce];
+#pragma unroll
+          for (int u = 0; u < kPairsAtOnce; ++u) {
+            const int pair = first + (seen + u) * scan_stride, at = pair < npairs ? pair : last_pair, g = (at << 7) + 2 * lane;
+            n_bits[u] = pair < npairs ? 2 : 0;
+            ev[u] = *reinterpret_cast<const uint2 *>(L.ev_t + (g < last_clock ? g : last_clock));
+            const int byte = (at << 4) + (lane >> 2);
+            here[u] = reinterpret_cast<const uint8_t *>(L.bm_busy)[byte];
+            if constexpr (kOverlap) here[u] &= ~static_cast<uint32_t>(reinterpret_cast<const uint8_t *>(L.bm_others)[byte]);
+          }
+#pragma unroll
+          for (int u = 0; u < kPairsAtOnce; ++u) {
+            due = __builtin_amdgcn_alignbit(due, ev[u].y - T_past, 31);
+            due = __builtin_amdgcn_alignbit(due, ev[u].x - T_past, 31);
+            own = (own << 2) | __builtin_amdgcn_ubfe(here[u], static_cast<uint32_t>(lane & 3) << 1, static_cast<uint32_t>(n_bits[u]));
+          }
+        }
+        due &= own;
+        for (uint64_t todo = __ballot(due != 0); todo || nev > 0;) {   // a lane queues one of its servers at a time
           if (todo) {
-            const int src = __ffsll(static_cast<long long>(todo)) - 1;
-            const uint64_t dm = readlane64(due, src);
-            todo &= todo - 1ull;
-            const int w = first + (src >> scan_pairs) * scan_stride + (src & scan_pairs);
-            if (lane_in(dm)) ev_g[nev + rank_in(dm)] = static_cast<uint16_t>((w << 6) + lane);
-            nev += __popcll(dm);
+            if (due) {
+              const int b = __ffs(static_cast<int>(due)) - 1;
+              ev_g[nev + rank_in(todo)] = static_cast<uint16_t>(((first + (seen - 1 - (b >> 1)) * scan_stride) << 7) + 2 * lane + (b & 1));
+              due &= due - 1u;
+            }
+            nev += __popcll(todo);
+            todo = __ballot(due != 0);
           }
           if (nev > kEvPerWave - 64 || !todo) { drain_events(nev); nev = 0; }
         }
@@ -2715,24 +2739,32 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         const bool apart_next = kOverlap && work > 0 && n_serve < nwaves && !gate_on && !route_on;
         if (gate_on || route_on || (work > 0 && !apart_next)) __syncthreads();   // (the same for every thread)
         if (!apart_next) late = 0;
-        scan_first = wave - drain_first; scan_stride = n_drain; scan_pairs = 0;
-        others = 0;
+        scan_first = wave - drain_first; scan_stride = n_drain; scan_end = nwords;
+        if constexpr (kOverlap) {
         if (apart_next) {
           // The waves that serve come last. Where the others are three times as many these look at all words, else, where the events
-          // are not shared by all waves, at two for one of the waves that serve (10000 x 256, four or five of eleven serve).
-          {
-            const int n_busy = n_serve < n_drain ? n_serve : n_drain, n_free = n_drain - n_busy;
-            if (n_free >= 3 * n_busy) {
+          // are not shared by all waves, at two pairs for one of the waves that serve (10000 x 256, four or five of eleven serve), which
+          // have the last pairs. What does not divide falls to the waves that serve: a wave with more than 64 events takes twice as long.
+          const int n_busy = n_serve < n_drain ? n_serve : n_drain, n_free = n_drain - n_busy;
+          const bool serves = wave >= nwaves - n_busy, some = n_free < 3 * n_busy;
+          if (!some || kBeside) {
+            const int npairs = (nwords + 1) >> 1, share = 2 * n_free + n_busy;
+            const int each = static_cast<int>((static_cast<float>(npairs + share) - 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(share)));   // rounded up
+            const int ends_at = !some ? npairs : npairs - n_busy * uniform(each);
+            if (!serves) {
               scan_stride = n_free;
-              if (wave >= nwaves - n_busy) scan_first = nwords;
-            } else if (kBeside) {
-              scan_stride = 2 * n_free + n_busy;
-              scan_pairs = wave < nwaves - n_busy ? 1 : 0;
-              scan_first = scan_pairs ? 2 * (wave - drain_first) : 2 * n_free + wave - (nwaves - n_busy);
+              scan_end = ends_at > 0 ? ends_at : 0;
+            } else {
+              scan_stride = n_busy;
+              scan_first = (ends_at > 0 ? ends_at : 0) + wave - (nwaves - n_busy);
             }
           }
-          if (wave < drain_first) scan_first = nwords;
-          const int w = scan_first + (lane >> scan_pairs) * scan_stride + (lane & scan_pairs);
+        }
+        if (wave < drain_first) scan_first = nwords;
+        // (no wave has more than sixteen pairs, of 96 and of 40 in workgroups of sixteen and of eight waves)
+        const int pair_here = scan_first + (lane >> 1) * scan_stride, w = pair_here < scan_end ? 2 * pair_here + (lane & 1) : nwords;
+        uint64_t others = 0;
+        if (apart_next) {
           if (scan_first < nwords) {
             if (nadm > 0) {   // the first nadm idle slots
               uint64_t slots = 0;
@@ -2779,6 +2811,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
               }
             }
           }
+        }
+        if (lane < 32 && w < nwords) L.bm_others[w] = others;
         }
       }
       if constexpr (AB) {

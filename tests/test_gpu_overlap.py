@@ -27,6 +27,7 @@ _POLICY = {"solo": (W.ROUTE_SOLO_FIRST, W.GATE_OCCUPANCY), "random": (W.ROUTE_RA
     (2050, 64, 0.5, 8, 100, 16),     # a word of mixed servers, few servers a step
     (2050, 1300, 4.6, 3, 100, 16),   # about a hundred admissions and jobs a step
     (5121, 3000, 4.6, 3, 100, 16),   # more than 64 words, more than 64 of each group a step
+    (10239, 2100, 0.8, 3, 100, 16),  # eleven of sixteen waves look at 80 pairs of words
 ])
 def test_served_servers_belong_to_those_that_serve(B, oracle_mod, N, M, lam, cap, prompt, waves, theta, policy):
     K = 2
