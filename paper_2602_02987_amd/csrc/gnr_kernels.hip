@@ -80,28 +80,33 @@ int step_threads(Params q, int reps)
   // on: the walks of the rings and the class selection take waves of their own. It pays with the weighted router (700
   // servers of four classes 8.4 and 8.1 ms), no longer without (with patience 5.8 and 6.2, convergence instance of 500
   // servers 5.7 and 5.8).
-  // The rule was set with a kernel that gave every wave every segment of a step; its lines were timed again with the present
-  // one (the figures here) and stand where they were. Of 400 launches timed in every shape (33 to 4600 servers, 200 to 4096
-  // replications, all routers and gates) it takes the fastest in 76 %, one within 3 % of it in 85 %, one within 10 % in 92 %.
-  // The others: one wave instead of two, dense, with 65 to 190 servers and 1024 to 2048 replications (up to 32 %), two instead of
-  // four with 140 to 380 servers and 500 to 1000 (up to 16 %; 256 servers, 1024 replications, 1000 steps 9.1 and 8.8 ms) and with
-  // 1200 to 1900 servers and 2000 to 4000 (up to 19 %), six waves a compute unit instead of sixteen with 3500 servers (29 to
-  // 41 %), sixteen a workgroup instead of eight with 2000 to 4600 servers and 200 to 260 (4 to 8 %), eight dense waves instead of
-  // four with 500 to 1600 servers and 250 to 510 (2 to 9 %).
+  // Timed again with steps that overlap in workgroups of eight waves (300 steps, 385 launches of 40 to 4500 servers, 4 to 2000
+  // replications, every router): with two to four blocks more waves pay, for the gate, the router and the waves that serve have waves of
+  // their own then. Time with the rule that stood here over that with this one, two to four blocks: same-slot decode 1.12 to 1.25 with
+  // 512 threads where a compute unit has one workgroup, 1.03 to 1.19 where it has two; both buffers with patience 1.12 to 1.29 and 1.07
+  // to 1.21; weighted router 1.05 to 1.16 and 1.05 to 1.14; patience 1.04 to 1.23 and 1.00 to 1.15. The base router's 512 threads are
+  // no faster than 256 there (0.93 to 1.02), which are 5 to 8 % faster than 128. With three or four workgroups a compute unit 256 dense
+  // threads give 4 to 18 % with deadline rings and nothing or less without; with five to eight 128 give 8 to 20 % over 64. Eight dense
+  // waves give same-slot decode 14 to 21 % with five to 22 blocks too.
+  // What is left (nothing keeps a shape from being better): two and more waves for one block 8 to 39 %, four dense waves instead of
+  // two with five to seven blocks and deadline rings 3 to 23 %, sixteen waves instead of eight with the base router, five to 30 blocks and
+  // up to 256 replications 7 to 14 %, eight instead of sixteen with two buffers or same-slot decode and 32 blocks and more 2 to 9 %,
+  // four instead of eight dense ones with the base router and 22 to 32 blocks 3 to 6 %.
   constexpr int kRound = 840;   // (divisible by one to eight waves)
   const int blocks = (q.N + 63) / 64;
   int best = 64, best_cost = 0;
-  // (no more waves than fewer than twice the blocks. Gate, router and serving have waves of their own, so one more can still pay:
-  // two waves with 33 to 64 servers take 3 to 23 % less than the one they get here, four with 65 to 128 up to 13 %)
-  for (int t = 64; t <= 1024 && t / 64 < 2 * blocks; t *= 2) {
+  const bool few = blocks >= 2 && blocks <= 4, more_roles = q.dl_rings || q.route_mode != SIM_ROUTE_SOLO_FIRST;
+  const int most = few ? (more_roles ? 8 : 4) : 2 * blocks - 1;
+  for (int t = 64; t <= 1024 && t / 64 <= most; t *= 2) {
     q.threads = t;
     const size_t lds = step_lds_bytes(q);
     if (lds > kLdsPerComputeUnit) break;
     const int waves = t / 64, rounds = launch_rounds(reps, t, lds, 4), held = waves * workgroups_at_once(t, lds, 4);
     const int cost = rounds * (kRound / (held < 8 ? held : 8));
     // few blocks a wave, and dense (sixteen waves have no roomy form)
-    const bool rings_pay = q.dl_rings && t == 512 && blocks >= 8;
-    const bool thin = blocks < 2 * waves && !rings_pay && (t > 512 || launch_rounds(reps, t, lds, 2) > rounds);
+    const bool pays = t == 512 ? (q.dl_rings && blocks >= 8) || (few && more_roles) || q.route_mode == SIM_ROUTE_IMMEDIATE
+                               : few && (t == 128 || (t == 256 && q.dl_rings));
+    const bool thin = blocks < 2 * waves && !pays && (t > 512 || launch_rounds(reps, t, lds, 2) > rounds);
     if (best_cost == 0 || cost < best_cost || (cost == best_cost && !thin)) { best = t; best_cost = cost; }
   }
   return best;

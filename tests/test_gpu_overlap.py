@@ -27,7 +27,10 @@ _POLICY = {"solo": (W.ROUTE_SOLO_FIRST, W.GATE_OCCUPANCY), "random": (W.ROUTE_RA
     (2050, 64, 0.5, 8, 100, 16),     # a word of mixed servers, few servers a step
     (2050, 1300, 4.6, 3, 100, 16),   # about a hundred admissions and jobs a step
     (5121, 3000, 4.6, 3, 100, 16),   # more than 64 words, more than 64 of each group a step
-    (10239, 2100, 0.8, 3, 100, 16),  # eleven of sixteen waves look at 80 pairs of words
+    (65, 30, 4.6, 3, 100, 8),        # two to four words, more waves than words
+    (192, 100, 4.6, 3, 100, 8),
+    (201, 64, 0.8, 4, 300, 8),
+    (8705, 2100, 0.8, 3, 100, 16),   # eleven of sixteen waves look at the clocks, the last pair of words has one server
 ])
 def test_served_servers_belong_to_those_that_serve(B, oracle_mod, N, M, lam, cap, prompt, waves, theta, policy):
     K = 2
@@ -39,6 +42,8 @@ def test_served_servers_belong_to_those_that_serve(B, oracle_mod, N, M, lam, cap
                   w_mixed=[0.2, 0.8])
     if policy == "immediate":
         cfg = replace(cfg, M=N)
+    if N <= 256 and policy == "solo" and not theta:   # (no overlap: four waves)
+        waves = 4
     assert B.sim_launch_plan(cfg, cfg.replications)[0] == 64 * waves
     sim, orc = B.Sim(cfg), oracle_mod.Oracle(cfg)
     for n in (1, 2, 60, 61):   # (launches that end where others would have gone on)

@@ -66,3 +66,18 @@ def test_recorded_shapes(K, N, M, theta, route, chunk_cost, replications, shape)
         assert e.value.code == -1
     else:
         assert tuple(B.sim_launch_plan(cfg, replications)) == shape
+
+
+# Two to four blocks of servers: more waves where router, patience or same-slot decode have roles of their own for them. One block, five
+# and more keep fewer waves than twice the blocks.
+@pytest.mark.parametrize("N,theta,route,replications,shape", [
+    (64, 0.0, IMMEDIATE, 4, (64, 2)), (65, 0.0, IMMEDIATE, 4, (512, 2)), (128, 0.0, RANDOM, 256, (512, 2)), (256, 0.1, SOLO, 16, (512, 2)),
+    (100, 0.0, WEIGHTED, 300, (512, 4)), (190, 0.0, IMMEDIATE, 512, (512, 4)), (190, 0.0, RANDOM, 513, (128, 2)), (100, 0.1, SOLO, 1000, (256, 4)),
+    (100, 0.0, IMMEDIATE, 1000, (128, 2)), (65, 0.0, SOLO, 4, (256, 2)), (256, 0.0, SOLO, 256, (256, 2)), (190, 0.0, SOLO, 512, (256, 2)),
+    (128, 0.0, SOLO, 2000, (128, 4)), (128, 0.1, RANDOM, 4000, (64, 4)), (257, 0.0, SOLO, 4, (512, 2)), (320, 0.0, IMMEDIATE, 512, (512, 4)),
+    (320, 0.0, RANDOM, 512, (256, 2)), (900, 0.0, IMMEDIATE, 1000, (256, 4)),
+])
+def test_few_blocks_and_many_roles(N, theta, route, replications, shape):
+    from paper_2602_02987_amd import binding as B
+    M = N if route == IMMEDIATE else N // 4
+    assert tuple(B.sim_launch_plan(_cfg(4, N, M, theta, route), replications))[0::2] == shape
