@@ -625,9 +625,26 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // a higher one. Left to the order of their age the youngest end last, alone with the SIMD: 1024 servers x 2048
   // replications 18.4 -> 17.9 ms per 1000 steps, 256 x 1024 9.42 -> 9.19, 2048 x 1024 18.6 -> 18.1 (turns of 128 steps the same,
   // of 16 steps half of it).
+  // With sixteen waves and one decode buffer the waves that draw (the first ones, which have time left) come last and those that
+  // serve first, at the highest priority while they do: 10000 servers x 256 13.81 -> 13.54 ms per 1000 steps. With two buffers, where all
+  // waves work off the events, those that serve have it and the others none before one another: weighted router 7.49 -> 7.30 per 300,
+  // convergence instance (eight waves) 17.76 -> 17.57 per 2000; the randomized router's sixteen waves (5.25 -> 5.27) and same-slot decode's
+  // eight (14.31 -> 14.49) gain nothing by either and keep the order of their age.
+  constexpr bool kDrawLast = NT == 1024 && !RR, kEqual = RR && (WS || NT == 512), kServeFirst = kDrawLast || kEqual;
+  const int nwords_all = p.nwords;
+  constexpr bool kBeside = NT >= 512 && !RR;
+  // (with more than eight words a wave the events need more than half of the waves: of 10000 servers 9, 10, 11 of sixteen take
+  // 15.8, 15.6, 15.9 ms per 1000 steps, and 10 and 11 take 15.0 and 14.8 where steps overlap and the words are drawn four at a time)
+  const int n_drain = !kBeside ? nwaves : nwords_all > 8 * nwaves ? nwaves * 11 / 16 : nwaves / 2;
+  const int n_draw = nwaves - n_drain, drain_first = n_draw;
   uint32_t turn = 0;   // in workgroups of two to four waves
   auto own_priority = [&]() __attribute__((always_inline)) {
-    if (wave >= 12) __builtin_amdgcn_s_setprio(3);
+    if (kEqual) __builtin_amdgcn_s_setprio(1);
+    else if (kDrawLast) {
+      if (wave >= 12) __builtin_amdgcn_s_setprio(2);
+      else if (wave >= n_draw) __builtin_amdgcn_s_setprio(1);
+      else __builtin_amdgcn_s_setprio(0);
+    } else if (wave >= 12) __builtin_amdgcn_s_setprio(3);
     else if (wave >= 8) __builtin_amdgcn_s_setprio(2);
     else if (turn) __builtin_amdgcn_s_setprio(2);
     else if (wave >= 4 || nwaves <= 4) __builtin_amdgcn_s_setprio(1);
@@ -914,11 +931,6 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   //      the randomized router 6.76 -> 6.86 per 300).
   constexpr int kHits = NT <= 64 ? 2 : 1;
   uint64_t hits[kHits] = {};
-  constexpr bool kBeside = NT >= 512 && !RR;
-  // (with more than eight words a wave the events need more than half of the waves: of 10000 servers 9, 10, 11 of sixteen take
-  // 15.8, 15.6, 15.9 ms per 1000 steps, and 10 and 11 take 15.0 and 14.8 where steps overlap and the words are drawn four at a time)
-  const int n_drain = !kBeside ? nwaves : nwords > 8 * nwaves ? nwaves * 11 / 16 : nwaves / 2;
-  const int n_draw = nwaves - n_drain, drain_first = n_draw;
   bool drawn = false;   // the step to come has been drawn (kBeside: by this wave, and its requests are not yet counted)
   // The words first, first + stride, ...: lane j of `hits` gets the servers of the j-th one that have requests. (One wave alone
   // may have more than 64: then also of the j + 64-th.)
@@ -2458,6 +2470,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
             own_priority();
           }
         } else if (work > 0) {
+          if constexpr (kServeFirst) __builtin_amdgcn_s_setprio(3);
           // this wave is the my_serve-th of n_serve_kind that serve its kind
           const bool for_jobs = !apart || wave >= nwaves - n_job, for_adm = !apart || !for_jobs;
           const int n_serve_kind = !apart ? n_serve : for_jobs ? n_job : n_adm;
@@ -2724,6 +2737,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
             if (n_all > lo) serve(n_all - lo < 64 ? n_all - lo : 64);
             lo += n_serve_kind << 6;
           } while (lo < n_all);
+          if constexpr (kServeFirst) own_priority();
         }
         if (draws_here) {
           next_thresholds();
