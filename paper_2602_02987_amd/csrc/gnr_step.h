@@ -639,9 +639,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   constexpr bool kDrawLast = NT == 1024 && !RR, kEqual = RR && (WS || NT == 512), kServeFirst = kDrawLast || kEqual;
   const int nwords_all = p.nwords;
   constexpr bool kBeside = NT >= 512 && !RR;
-  // (with more than eight words a wave the events need more than half of the waves: of 10000 servers 9, 10, 11 of sixteen take
-  // 15.8, 15.6, 15.9 ms per 1000 steps, and 10 and 11 take 15.0 and 14.8 where steps overlap and the words are drawn four at a time)
-  const int n_drain = !kBeside ? nwaves : nwords_all > 8 * nwaves ? nwaves * 11 / 16 : nwaves / 2;
+  // (10000 servers, 10, 11 and 12 of sixteen waves 13.57, 13.61 and 13.42 ms per 1000 steps; 3001 servers, 8, 10 and 12 of them 4.464,
+  // 4.481 and 4.459 per 500. Of eight waves half, with more than eight words a wave five)
+  const int n_drain = !kBeside ? nwaves : nwaves == 16 ? 12 : nwords_all > 8 * nwaves ? nwaves * 11 / 16 : nwaves / 2;
   const int n_draw = nwaves - n_drain, drain_first = n_draw;
   uint32_t turn = 0;   // in workgroups of two to four waves
   auto own_priority = [&]() __attribute__((always_inline)) {
@@ -2788,7 +2788,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         if constexpr (kOverlap) {
         if (apart_next) {
           // The waves that serve come last. Where the others are three times as many these look at all words, else, where the events
-          // are not shared by all waves, at two pairs for one of the waves that serve (10000 x 256, four or five of eleven serve), which
+          // are not shared by all waves, at two pairs for one of the waves that serve (10000 x 256, four or five of twelve serve), which
           // have the last pairs. What does not divide falls to the waves that serve: a wave with more than 64 events takes twice as long.
           const int n_busy = n_serve < n_drain ? n_serve : n_drain, n_free = n_drain - n_busy;
           const bool serves = wave >= nwaves - n_busy, some = n_free < 3 * n_busy;

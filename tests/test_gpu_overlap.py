@@ -30,7 +30,7 @@ _POLICY = {"solo": (W.ROUTE_SOLO_FIRST, W.GATE_OCCUPANCY), "random": (W.ROUTE_RA
     (65, 30, 4.6, 3, 100, 8),        # two to four words, more waves than words
     (192, 100, 4.6, 3, 100, 8),
     (201, 64, 0.8, 4, 300, 8),
-    (8705, 2100, 0.8, 3, 100, 16),   # eleven of sixteen waves look at the clocks, the last pair of words has one server
+    (8705, 2100, 0.8, 3, 100, 16),   # twelve of sixteen waves look at the clocks, the last pair of words has one server
 ])
 def test_served_servers_belong_to_those_that_serve(B, oracle_mod, N, M, lam, cap, prompt, waves, theta, policy):
     K = 2
