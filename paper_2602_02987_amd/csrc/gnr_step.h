@@ -637,6 +637,11 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // convergence instance (eight waves) 17.76 -> 17.57 per 2000; the randomized router's sixteen waves (5.25 -> 5.27) and same-slot decode's
   // eight (14.31 -> 14.49) gain nothing by either and keep the order of their age.
   constexpr bool kDrawLast = NT == 1024 && !RR, kEqual = RR && (WS || NT == 512), kServeFirst = kDrawLast || kEqual;
+  // Four waves a SIMD, of workgroups of two and four: what follows the events, short segments that others wait for, goes before the
+  // events and draws of the other workgroups (500 servers x 2000 3.32 -> 3.19 ms per 300 steps, 900 x 1000 same-slot decode 3.40 -> 3.30,
+  // 1500 x 1800 randomized router 9.32 -> 9.15, 1024 x 2048 16.14 -> 16.05 per 1000, 2048 x 1024 16.18 -> 16.11; with two waves a
+  // SIMD 256 x 1024 8.17 -> 8.37).
+  constexpr bool kChainFirst = DENSE && NT >= 128 && NT <= 256;
   const int nwords_all = p.nwords;
   constexpr bool kBeside = NT >= 512 && !RR;
   // (10000 servers, 10, 11 and 12 of sixteen waves 13.57, 13.61 and 13.42 ms per 1000 steps; 3001 servers, 8, 10 and 12 of them 4.464,
@@ -1168,7 +1173,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     }
     if (nwaves > 1 && nwaves <= 4) {
       const uint32_t t2 = ((s >> 8) + (static_cast<uint32_t>(r) >> 8)) & 1u;
-      if (t2 != turn) { turn = t2; own_priority(); }
+      if (kChainFirst || t2 != turn) { turn = t2; own_priority(); }
     }
     // abandonment only: how many waiting requests of class `tid` leave at the start of this step. Asked for here and used after the
     // completion pass, or, where steps overlap, behind it: those that the step before has taken out of the calendars must be out.
@@ -1512,6 +1517,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     late = 0;
     slots_taken = false;
     __syncthreads();
+    if constexpr (kChainFirst) __builtin_amdgcn_s_setprio(3);
 
     anew();
     // ================= arrivals into the class queues; ranks of completions and idle slots =================
@@ -2476,7 +2482,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
             __builtin_amdgcn_s_setprio(0);
             draw_words(s + 1u, wave, nwaves - n_serve);
             count_requests(s + 1u, wave, nwaves - n_serve);
-            own_priority();
+            if constexpr (kChainFirst) __builtin_amdgcn_s_setprio(3); else own_priority();
           }
         } else if (work > 0) {
           if constexpr (kServeFirst) __builtin_amdgcn_s_setprio(3);
