@@ -301,10 +301,7 @@ int launch_reset(const Params &p, int reps, void *stream)
   return hip_ok(hipGetLastError());
 }
 
-// Which compilation of the step kernel a launch takes. Sixteen waves: with up to 80 words (5120 servers) steps overlap whatever the
-// policy (3000 servers x 64, randomized router 4.5 % faster, weighted 4.5 %; x 256 with patience 11 %); with more they do not with two
-// buffers or deadline rings (10000 x 256, randomized router 6.38 -> 6.50 ms per 300 steps, weighted 8.61 -> 8.77, with patience
-// 6.24 -> 6.47: no wave waits for the ones that serve there, or every wave is slowed down by as much as the wait was long).
+// Which compilation of the step kernel a launch takes.
 static int step_form(int threads, int nwords)
 {
   switch (threads) {
@@ -312,7 +309,7 @@ static int step_form(int threads, int nwords)
     case 128: return 1;
     case 256: return 2;
     case 512: return 3;
-    case 1024: return nwords <= 80 ? 6 : 2 + size_class(threads, nwords);
+    case 1024: return 2 + size_class(threads, nwords);
     default: return -1;
   }
 }

@@ -602,7 +602,7 @@ struct StepArrays {
 // IM: the variant with immediate same-slot decode (no router): a request whose prefill ends goes on decoding on
 // its own server, placed there by the lane that finishes the server; a server is offered to the gate while it
 // holds no prefill and fewer than B decodes.
-template <int NT, int NWS, bool AB, bool RR, bool IM, bool WS = false, bool DENSE = false, bool OV = steps_overlap(NT)>
+template <int NT, int NWS, bool AB, bool RR, bool IM, bool WS = false, bool DENSE = false>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NT, DENSE)))) gnr_step_kernel(const Params *__restrict__ params, const StepArrays a,
                                                         const uint32_t key0_arg, const uint32_t key1_arg,
                                                         const uint32_t step_begin_arg, const uint32_t n_steps_arg)
@@ -636,14 +636,14 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // waves work off the events, those that serve have it and the others none before one another: weighted router 7.49 -> 7.30 per 300,
   // convergence instance (eight waves) 17.76 -> 17.57 per 2000; the randomized router's sixteen waves (5.25 -> 5.27) and same-slot decode's
   // eight (14.31 -> 14.49) gain nothing by either and keep the order of their age.
-  constexpr bool kDrawLast = NT == 1024 && !RR, kEqual = RR && (WS || NT == 512), kServeFirst = kDrawLast || kEqual;
+  constexpr bool kDrawLast = NT == 1024, kEqual = RR && NT == 512, kServeFirst = kDrawLast || kEqual;
   // Four waves a SIMD, of workgroups of two and four: what follows the events, short segments that others wait for, goes before the
   // events and draws of the other workgroups (500 servers x 2000 3.32 -> 3.19 ms per 300 steps, 900 x 1000 same-slot decode 3.40 -> 3.30,
   // 1500 x 1800 randomized router 9.32 -> 9.15, 1024 x 2048 16.14 -> 16.05 per 1000, 2048 x 1024 16.18 -> 16.11; with two waves a
   // SIMD 256 x 1024 8.17 -> 8.37).
   constexpr bool kChainFirst = DENSE && NT >= 128 && NT <= 256;
   const int nwords_all = p.nwords;
-  constexpr bool kBeside = NT >= 512 && !RR;
+  constexpr bool kBeside = NT >= 512 && (!RR || NT == 1024);
   // (10000 servers, 10, 11 and 12 of sixteen waves 13.57, 13.61 and 13.42 ms per 1000 steps; 3001 servers, 8, 10 and 12 of them 4.464,
   // 4.481 and 4.459 per 500. Of eight waves half, with more than eight words a wave five)
   const int n_drain = !kBeside ? nwaves : nwaves == 16 ? 12 : nwords_all > 8 * nwaves ? nwaves * 11 / 16 : nwaves / 2;
@@ -761,7 +761,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     }
     return n;
   };
-  constexpr bool kOverlap = OV;
+  constexpr bool kOverlap = steps_overlap(NT);
   // bitmaps that steps take in turn where they overlap: how far apart they are
   const int turn_words = !kOverlap ? 0 : NWS ? NWS : nwords, turn_words_m = !kOverlap ? 0 : NWS ? NWS : nwords_m;
   // classes that the gate may admit: under the occupancy gate those with a positive target
@@ -3011,7 +3011,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
 }
 
 // The step kernel of one policy variant: `form` is 0 to 3 for workgroups of 64, 128, 256 and 512 threads, in their roomy or
-// dense form (see waves_per_simd), 4 to 6 for those of 1024 (see step_form). Every workgroup size is compiled by itself, so
+// dense form (see waves_per_simd), 4 and 5 for those of 1024 (see step_form). Every workgroup size is compiled by itself, so
 // that the count of waves and what follows from it are constants and not values kept in lanes of vector registers: compiled for
 // two sizes each, with the count read at run time, the timed cases took 1 to 7 % longer (8 servers x 16 replications 16.7
 // instead of 15.7 ms per 10^4 steps, 256 x 1024 9.15 instead of 8.61 per 1000, 1024 x 2048 17.85 instead of 17.20, 3001 x 77 5.80
@@ -3020,13 +3020,12 @@ using StepKernel = void (*)(const Params *, StepArrays, uint32_t, uint32_t, uint
 #define GNR_STEP_VARIANT(name, AB, RR, IM, WS)                                                             \
   StepKernel name(int form, bool dense)                                                                    \
   {                                                                                                        \
-    static const StepKernel roomy[7] = {gnr_step_kernel<64, 0, AB, RR, IM, WS>,                            \
+    static const StepKernel roomy[6] = {gnr_step_kernel<64, 0, AB, RR, IM, WS>,                            \
                                         gnr_step_kernel<128, 0, AB, RR, IM, WS>,                           \
                                         gnr_step_kernel<256, 0, AB, RR, IM, WS>,                           \
                                         gnr_step_kernel<512, 0, AB, RR, IM, WS>,                           \
-                                        gnr_step_kernel<1024, static_words(2), AB, RR, IM, WS, false, !(AB || RR)>, \
-                                        gnr_step_kernel<1024, static_words(3), AB, RR, IM, WS, false, !(AB || RR)>, \
-                                        gnr_step_kernel<1024, static_words(2), AB, RR, IM, WS>};           \
+                                        gnr_step_kernel<1024, static_words(2), AB, RR, IM, WS>,            \
+                                        gnr_step_kernel<1024, static_words(3), AB, RR, IM, WS>};           \
     static const StepKernel full[4] = {gnr_step_kernel<64, 0, AB, RR, IM, WS, true>,                       \
                                        gnr_step_kernel<128, 0, AB, RR, IM, WS, true>,                      \
                                        gnr_step_kernel<256, 0, AB, RR, IM, WS, true>,                      \
