@@ -631,11 +631,10 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // a higher one. Left to the order of their age the youngest end last, alone with the SIMD: 1024 servers x 2048
   // replications 18.4 -> 17.9 ms per 1000 steps, 256 x 1024 9.42 -> 9.19, 2048 x 1024 18.6 -> 18.1 (turns of 128 steps the same,
   // of 16 steps half of it).
-  // With sixteen waves and one decode buffer the waves that draw (the first ones, which have time left) come last and those that
-  // serve first, at the highest priority while they do: 10000 servers x 256 13.81 -> 13.54 ms per 1000 steps. With two buffers, where all
-  // waves work off the events, those that serve have it and the others none before one another: weighted router 7.49 -> 7.30 per 300,
-  // convergence instance (eight waves) 17.76 -> 17.57 per 2000; the randomized router's sixteen waves (5.25 -> 5.27) and same-slot decode's
-  // eight (14.31 -> 14.49) gain nothing by either and keep the order of their age.
+  // With sixteen waves the waves that draw (the first ones, which have time left) come last and those that serve first, at the highest
+  // priority while they do: 10000 servers x 256 13.83 -> 13.63 ms per 1000 steps. In eight with two buffers, where all waves work off
+  // the events, those that serve have it and the others none before one another: convergence instance 17.76 -> 17.57 per 2000; with one
+  // buffer eight gain nothing by either (same-slot decode 14.31 -> 14.49) and keep the order of their age.
   constexpr bool kDrawLast = NT == 1024, kEqual = RR && NT == 512, kServeFirst = kDrawLast || kEqual;
   // Four waves a SIMD, of workgroups of two and four: what follows the events, short segments that others wait for, goes before the
   // events and draws of the other workgroups (500 servers x 2000 3.32 -> 3.19 ms per 300 steps, 900 x 1000 same-slot decode 3.40 -> 3.30,
@@ -655,9 +654,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
       if (wave >= 12) __builtin_amdgcn_s_setprio(2);
       else if (wave >= n_draw) __builtin_amdgcn_s_setprio(1);
       else __builtin_amdgcn_s_setprio(0);
-    } else if (wave >= 12) __builtin_amdgcn_s_setprio(3);
-    else if (wave >= 8) __builtin_amdgcn_s_setprio(2);
-    else if (turn) __builtin_amdgcn_s_setprio(2);
+    } else if (turn) __builtin_amdgcn_s_setprio(2);
     else if (wave >= 4 || nwaves <= 4) __builtin_amdgcn_s_setprio(1);
   };
   own_priority();
@@ -933,13 +930,13 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // ---- arrivals: one random block per server and step, word 0 -> count, words 1.. -> classes. Word 0 alone is worked out
   //      for every server (its last rounds take half the products), for 64 of them (a bitmap word) at a time, two words with the same
   //      round keys, and a step ahead; the few servers that get requests are queued and their blocks drawn in full, one a lane.
-  //      In workgroups of eight waves and more with one decode buffer some waves draw while the others work off the events (a wave with
-  //      all the events of two has its lanes full: 10000 servers of six classes have 450 a step, 28 a wave); their requests are
-  //      counted behind the barriers that follow. 10000 servers x 256 replications 18.3 -> 17.15 ms per 1000 steps, 3001 x 77 5.60 ->
-  //      5.39 per 500, 500 x 3 with same-slot decode 19.4 -> 18.8 per 2000. In smaller workgroups, where the events are the longest
-  //      part, and with two buffers, where serving is, all waves work off the events and those that do not serve draw beside the ones
-  //      that do (draws beside the events: 1024 x 2048 in two waves 16.8 -> 17.8 ms, 2048 x 1024 in four 17.2 -> 17.6, 10000 x 256 with
-  //      the randomized router 6.76 -> 6.86 per 300).
+  //      In workgroups of sixteen waves, and of eight with one decode buffer, some waves draw while the others work off the events (a
+  //      wave with all the events of two has its lanes full: 10000 servers of six classes have 450 a step, 28 a wave); their requests
+  //      are counted behind the barriers that follow. 10000 servers x 256 replications 18.3 -> 17.15 ms per 1000 steps, 3001 x 77 5.60
+  //      -> 5.39 per 500, 500 x 3 with same-slot decode 19.4 -> 18.8 per 2000. In smaller workgroups, where the events are the longest
+  //      part, and in eight waves with two buffers, where serving is, all waves work off the events and those that do not serve draw
+  //      beside the ones that do (draws beside the events: 1024 x 2048 in two waves 16.8 -> 17.8 ms, 2048 x 1024 in four 17.2 -> 17.6,
+  //      convergence instance in eight 17.45 -> 18.71 per 2000).
   constexpr int kHits = NT <= 64 ? 2 : 1;
   uint64_t hits[kHits] = {};
   bool drawn = false;   // the step to come has been drawn (kBeside: by this wave, and its requests are not yet counted)
@@ -1070,8 +1067,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // serve nobody go on at once. (A step of a workgroup of eight waves and more spent a quarter to a third of its time in waits, most of
   // it there: a few waves serve, 8 to 12 thousand cycles, while the others wait. 500 servers x 3, same-slot decode 18.4 -> 14.4 ms per
   // 2000 steps, convergence instance 19.6 -> 17.8, 3001 x 77 4.98 -> 4.50 per 500, 10000 x 256 15.6 -> 14.8 per 1000. In workgroups of
-  // up to four waves, where everything that does not serve draws, it costs 2 to 5 %: 1024 x 2048 16.4 -> 17.0, 256 x 1024 8.1 -> 8.5;
-  // and with two buffers or deadline rings and more than 5120 servers 1 to 3 %: weighted router 8.62 -> 8.77, see step_form.)
+  // up to four waves, where everything that does not serve draws, it costs 2 to 5 %: 1024 x 2048 16.4 -> 17.0, 256 x 1024 8.1 -> 8.5.
+  // Two buffers and more than 5120 servers need draws beside the events for it: 10000 x 256, randomized router 5.24 -> 4.76 per 300 with
+  // both, 5.36 with the overlap alone, weighted router 7.35 -> 6.84 and 7.54; with patience 8000 x 200 3.24 -> 2.98 per 200.)
   // What makes it sound: the servers that are given work belong to the waves that serve them until the next barrier. Every other wave
   // leaves them out of the words it looks at (bm_others, of its own words; it follows from the pass's words, as for the waves
   // that serve); those whose event comes in the next step already (`late`: lanes, late_g: the server) are queued by the wave that has
