@@ -88,10 +88,10 @@ int step_threads(Params q, int reps)
   // no faster than 256 there (0.93 to 1.02), which are 5 to 8 % faster than 128. With three or four workgroups a compute unit 256 dense
   // threads give 4 to 18 % with deadline rings and nothing or less without; with five to eight 128 give 8 to 20 % over 64. Eight dense
   // waves give same-slot decode 14 to 21 % with five to 22 blocks too.
-  // What is left (nothing keeps a shape from being better): two and more waves for one block 8 to 39 %, four dense waves instead of
-  // two with five to seven blocks and deadline rings 3 to 23 %, sixteen waves instead of eight with the base router, five to 30 blocks and
-  // up to 256 replications 7 to 14 %, eight instead of sixteen with two buffers or same-slot decode and 32 blocks and more 2 to 9 %,
-  // four instead of eight dense ones with the base router and 22 to 32 blocks 3 to 6 %.
+  // What is left: two and more waves for one block 8 to 39 %, four dense waves instead of two with five to seven blocks and
+  // deadline rings 3 to 23 %, sixteen waves instead of eight with the base router, five to 30 blocks and up to 256 replications up to 8 %,
+  // eight instead of sixteen with same-slot decode and 32 to 47 blocks 3 to 7 %, four instead of eight dense ones with the base router
+  // and 16 to 32 blocks up to 13 %.
   constexpr int kRound = 840;   // (divisible by one to eight waves)
   const int blocks = (q.N + 63) / 64;
   int best = 64, best_cost = 0;
@@ -301,14 +301,18 @@ int launch_reset(const Params &p, int reps, void *stream)
   return hip_ok(hipGetLastError());
 }
 
-// Which compilation of the step kernel a launch takes.
+// Which compilation of the step kernel a launch takes. Of eight waves all work off the events, and who does not serve draws beside the
+// ones that do, up to 40 words (2560 servers): 300 servers x 4 2.03 -> 1.88 ms per 300 steps, 1024 x 256 2.76 -> 2.58, 1500 x 40 2.82 ->
+// 2.64, with patience 900 x 400 4.74 -> 4.57 per 400; with more words four draw beside the events: 3000 x 500 4.19 and 4.25, 4500 x 500
+// 2.53 and 2.80 per 200. With same-slot decode, which has no jobs to serve, four draw whatever the size (900 x 400 3.14 and 3.82 per
+// 400), with two buffers none.
 static int step_form(int threads, int nwords)
 {
   switch (threads) {
     case 64: return 0;
     case 128: return 1;
     case 256: return 2;
-    case 512: return 3;
+    case 512: return nwords <= 40 ? 3 : 6;
     case 1024: return 2 + size_class(threads, nwords);
     default: return -1;
   }

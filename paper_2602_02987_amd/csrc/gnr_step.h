@@ -602,7 +602,7 @@ struct StepArrays {
 // IM: the variant with immediate same-slot decode (no router): a request whose prefill ends goes on decoding on
 // its own server, placed there by the lane that finishes the server; a server is offered to the gate while it
 // holds no prefill and fewer than B decodes.
-template <int NT, int NWS, bool AB, bool RR, bool IM, bool WS = false, bool DENSE = false>
+template <int NT, int NWS, bool AB, bool RR, bool IM, bool WS = false, bool DENSE = false, bool BESIDE = NT == 1024 || (NT == 512 && IM)>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NT, DENSE)))) gnr_step_kernel(const Params *__restrict__ params, const StepArrays a,
                                                         const uint32_t key0_arg, const uint32_t key1_arg,
                                                         const uint32_t step_begin_arg, const uint32_t n_steps_arg)
@@ -632,17 +632,17 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // replications 18.4 -> 17.9 ms per 1000 steps, 256 x 1024 9.42 -> 9.19, 2048 x 1024 18.6 -> 18.1 (turns of 128 steps the same,
   // of 16 steps half of it).
   // With sixteen waves the waves that draw (the first ones, which have time left) come last and those that serve first, at the highest
-  // priority while they do: 10000 servers x 256 13.83 -> 13.63 ms per 1000 steps. In eight with two buffers, where all waves work off
-  // the events, those that serve have it and the others none before one another: convergence instance 17.76 -> 17.57 per 2000; with one
-  // buffer eight gain nothing by either (same-slot decode 14.31 -> 14.49) and keep the order of their age.
-  constexpr bool kDrawLast = NT == 1024, kEqual = RR && NT == 512, kServeFirst = kDrawLast || kEqual;
+  // priority while they do: 10000 servers x 256 13.83 -> 13.63 ms per 1000 steps. In eight that all work off the events those that
+  // serve have it and the others none before one another: convergence instance 17.76 -> 17.57 per 2000; where some of eight draw they
+  // gain nothing by either (same-slot decode 14.31 -> 14.49) and keep the order of their age.
+  constexpr bool kDrawLast = NT == 1024, kEqual = NT == 512 && !BESIDE, kServeFirst = kDrawLast || kEqual;
   // Four waves a SIMD, of workgroups of two and four: what follows the events, short segments that others wait for, goes before the
   // events and draws of the other workgroups (500 servers x 2000 3.32 -> 3.19 ms per 300 steps, 900 x 1000 same-slot decode 3.40 -> 3.30,
   // 1500 x 1800 randomized router 9.32 -> 9.15, 1024 x 2048 16.14 -> 16.05 per 1000, 2048 x 1024 16.18 -> 16.11; with two waves a
   // SIMD 256 x 1024 8.17 -> 8.37).
   constexpr bool kChainFirst = DENSE && NT >= 128 && NT <= 256;
   const int nwords_all = p.nwords;
-  constexpr bool kBeside = NT >= 512 && (!RR || NT == 1024);
+  constexpr bool kBeside = BESIDE;   // some waves draw while the others work off the events
   // (10000 servers, 10, 11 and 12 of sixteen waves 13.57, 13.61 and 13.42 ms per 1000 steps; 3001 servers, 8, 10 and 12 of them 4.464,
   // 4.481 and 4.459 per 500. Of eight waves half, with more than eight words a wave five)
   const int n_drain = !kBeside ? nwaves : nwaves == 16 ? 12 : nwords_all > 8 * nwaves ? nwaves * 11 / 16 : nwaves / 2;
@@ -930,11 +930,11 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   // ---- arrivals: one random block per server and step, word 0 -> count, words 1.. -> classes. Word 0 alone is worked out
   //      for every server (its last rounds take half the products), for 64 of them (a bitmap word) at a time, two words with the same
   //      round keys, and a step ahead; the few servers that get requests are queued and their blocks drawn in full, one a lane.
-  //      In workgroups of sixteen waves, and of eight with one decode buffer, some waves draw while the others work off the events (a
+  //      In workgroups of sixteen waves, and of eight where step_form says so, some waves draw while the others work off the events (a
   //      wave with all the events of two has its lanes full: 10000 servers of six classes have 450 a step, 28 a wave); their requests
   //      are counted behind the barriers that follow. 10000 servers x 256 replications 18.3 -> 17.15 ms per 1000 steps, 3001 x 77 5.60
   //      -> 5.39 per 500, 500 x 3 with same-slot decode 19.4 -> 18.8 per 2000. In smaller workgroups, where the events are the longest
-  //      part, and in eight waves with two buffers, where serving is, all waves work off the events and those that do not serve draw
+  //      part, and in eight waves, where serving is, all waves work off the events and those that do not serve draw
   //      beside the ones that do (draws beside the events: 1024 x 2048 in two waves 16.8 -> 17.8 ms, 2048 x 1024 in four 17.2 -> 17.6,
   //      convergence instance in eight 17.45 -> 18.71 per 2000).
   constexpr int kHits = NT <= 64 ? 2 : 1;
@@ -3009,8 +3009,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
 }
 
 // The step kernel of one policy variant: `form` is 0 to 3 for workgroups of 64, 128, 256 and 512 threads, in their roomy or
-// dense form (see waves_per_simd), 4 and 5 for those of 1024 (see step_form). Every workgroup size is compiled by itself, so
-// that the count of waves and what follows from it are constants and not values kept in lanes of vector registers: compiled for
+// dense form (see waves_per_simd), 4 and 5 for those of 1024, 6 for those of 512 some of whose waves draw (see step_form; with
+// two buffers the same as 3, with same-slot decode 3 is the same as 6). Every workgroup size is compiled by itself, so that the count of waves and what follows from it are constants and not values kept in lanes of vector registers: compiled for
 // two sizes each, with the count read at run time, the timed cases took 1 to 7 % longer (8 servers x 16 replications 16.7
 // instead of 15.7 ms per 10^4 steps, 256 x 1024 9.15 instead of 8.61 per 1000, 1024 x 2048 17.85 instead of 17.20, 3001 x 77 5.80
 // instead of 5.58 per 500). Each variant is compiled in a translation unit of its own.
@@ -3018,17 +3018,20 @@ using StepKernel = void (*)(const Params *, StepArrays, uint32_t, uint32_t, uint
 #define GNR_STEP_VARIANT(name, AB, RR, IM, WS)                                                             \
   StepKernel name(int form, bool dense)                                                                    \
   {                                                                                                        \
-    static const StepKernel roomy[6] = {gnr_step_kernel<64, 0, AB, RR, IM, WS>,                            \
+    static const StepKernel roomy[7] = {gnr_step_kernel<64, 0, AB, RR, IM, WS>,                            \
                                         gnr_step_kernel<128, 0, AB, RR, IM, WS>,                           \
                                         gnr_step_kernel<256, 0, AB, RR, IM, WS>,                           \
                                         gnr_step_kernel<512, 0, AB, RR, IM, WS>,                           \
                                         gnr_step_kernel<1024, static_words(2), AB, RR, IM, WS>,            \
-                                        gnr_step_kernel<1024, static_words(3), AB, RR, IM, WS>};           \
-    static const StepKernel full[4] = {gnr_step_kernel<64, 0, AB, RR, IM, WS, true>,                       \
+                                        gnr_step_kernel<1024, static_words(3), AB, RR, IM, WS>,            \
+                                        gnr_step_kernel<512, 0, AB, RR, IM, WS, false, !(RR)>};            \
+    static const StepKernel full[7] = {gnr_step_kernel<64, 0, AB, RR, IM, WS, true>,                       \
                                        gnr_step_kernel<128, 0, AB, RR, IM, WS, true>,                      \
                                        gnr_step_kernel<256, 0, AB, RR, IM, WS, true>,                      \
-                                       gnr_step_kernel<512, 0, AB, RR, IM, WS, true>};                     \
-    return dense && form < 4 ? full[form] : roomy[form];                                                   \
+                                       gnr_step_kernel<512, 0, AB, RR, IM, WS, true>,                      \
+                                       nullptr, nullptr,   /* (sixteen waves are dense as they are) */     \
+                                       gnr_step_kernel<512, 0, AB, RR, IM, WS, true, !(RR)>};              \
+    return dense && full[form] ? full[form] : roomy[form];                                                 \
   }
 
 }  // namespace gnr
