@@ -25,8 +25,8 @@ HBM_PEAK_GBS = 8000.0
 # occupancy rocprofv3 derives for it. These are STORED figures, not taken in this run: they hold for the kernel
 # sources whose hash is given (compared with the current sources; on a mismatch the figures read null) and for the
 # state named in `state`. The line says so in `roofline.traffic_source` / `roofline.occupancy.source`.
-TRAFFIC = {"sources_sha256": "5604d412f8131fc677fc8a3c6bb637fc842ff8602b8d9c6cdbff2cc40e490d60",
-           "bytes_per_launch": 51706995330, "occupancy_percent": 49.358415,
+TRAFFIC = {"sources_sha256": "adfc2f0b7cdf652fc282b95493b0079f3eb15f7a0604288f5ee0af1623a26a95",
+           "bytes_per_launch": 54001199171, "occupancy_percent": 49.097352,
            "state": "config 5 after 30000 untimed steps, mean of 2 launches of 1000 steps",
            "profile": "profiles/gnr_step_kernel_cfg5_hbm_traffic.md"}
 

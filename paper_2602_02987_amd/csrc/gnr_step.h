@@ -1,8 +1,8 @@
 // HIP kernels of the gate-and-route network simulator (gfx950, wave64).
 //
 // One workgroup owns one replication for a whole launch and loops over the steps itself. The servers are
-// handled in blocks of 64 (one per lane); wave w owns the blocks w, w + nwaves, ... in the completion pass, and what a
-// step gives a server is written by the last waves of the workgroup, a barrier later. A server is touched only
+// handled in blocks of 64 (one per lane), of which a wave looks at some pairs in the completion pass, and what a step gives
+// a server is written by the last waves of the workgroup, a barrier later, or while the others go on. A server is touched only
 // when its batch changes (an event): the identical iterations in between follow from its event time. Class-level
 // counters (queue lengths, occupancies, tallies) live in LDS and are updated with integer atomics, which commute, by the
 // lanes that have something to add (a few of a wave as a rule; sums that all lanes add to are spread over several words).
@@ -358,8 +358,8 @@ __host__ __device__ __forceinline__ Lds lds_carve(const Params &p, unsigned char
   // What is refused for want of room, and how many workgroups share a compute unit, follows from the total. Both were set
   // with the tables of a kernel that executed every iteration (two words and a row list per queued server, four-byte
   // ranks, ...), and the total is theirs in every configuration: the tables above never need more (one and two waves go up
-  // to 5120 servers), and where they need less the rest is held free: 18,000 bytes of 148,368 with 10000 servers of six
-  // classes, 3,920 of 38,800 with 2048 of eight, 1,520 of 20,112 with 1024 of four. A few bytes more cost a round or half
+  // to 5120 servers), and where they need less the rest is held free: 14,128 bytes of 148,368 with 10000 servers of six
+  // classes, 4,064 of 38,800 with 2048 of eight, 1,432 of 20,112 with 1024 of four. A few bytes more cost a round or half
   // the waves (200 steps: 33 servers of eight classes with patience, 4096 replications, 10248 bytes in two rounds 4.7 ms,
   // 10032 in one 3.1; 100 steps: 900 servers of eight classes with patience, 2048 replications, 20488 bytes in two rounds
   // 5.5 ms, 20424 in one 3.1).
@@ -394,10 +394,10 @@ __host__ __device__ constexpr int size_class(int threads, int nwords)
 // 512 / this many). A workgroup of 1024 threads needs four; the smaller classes are compiled twice: roomy, with up
 // to 256 registers and two waves per SIMD, taken while every workgroup of the launch finds a place at that density, and
 // dense, with 128 registers and four waves per SIMD, for launches that would otherwise run their workgroups in more
-// rounds. Registers roomy / dense (spilled when dense): base and randomized router 107 in eight waves and 116 in one or two,
-// same-slot decode 105 and 114, the same code in both forms; with deadline rings 117 to 122 in eight waves, 127 to 132 / 128
-// (up to 2) in one or two; weighted router 132 / 128 (2) and 142 / 128 (2). So only the forms of the weighted router, and with
-// deadline rings those of one or two waves, differ.
+// rounds. Registers roomy / dense (spilled when dense): base and randomized router, same-slot decode 107 to 113 in two waves and
+// more and 117 to 121 in one, the same code in both forms; with deadline rings 116 to 127, in one wave 128 to 136 / 128 (up to 2);
+// weighted router 136 to 139 / 128 (4) and in one wave 150 / 128 (8). So only the forms of the weighted router, and with deadline
+// rings those of one wave, differ.
 __host__ __device__ constexpr int waves_per_simd(int max_threads, bool dense)
 {
   return max_threads > 512 || dense ? 4 : 2;
