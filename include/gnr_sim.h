@@ -188,7 +188,9 @@ int sim_workspace_bytes(const sim_config *cfg, int max_replications, size_t *out
  * handle). SIM_EINVAL: bad sizes (more than SIM_MAXR replications among them), negative target, M outside [0,N], dt > c0, negative theta, p_solo outside
  * [0,1] or missing under RANDOM_SPLIT, total
  * arrival mean per server-step above 0.05 (the per-step count is truncated at 3).
- * SIM_ENOMEM: workspace too small. The library never allocates device memory itself.
+ * SIM_ENOMEM: workspace too small. The library never allocates device memory itself;
+ * a handle keeps pinned host memory for the totals that sim_stats reads (36 KB with two classes, 140 KB with eight),
+ * unless there is none to be had.
  * The handle belongs to the device that is current at this call: every later call on it must be made
  * with the same device current (SIM_EINVAL otherwise). The launch shape of the handle (see sim_launch_plan) is
  * fixed here for `max_replications` replications; runs with fewer use the same shape, results do not depend on it. */
