@@ -189,8 +189,9 @@ int sim_workspace_bytes(const sim_config *cfg, int max_replications, size_t *out
  * [0,1] or missing under RANDOM_SPLIT, total
  * arrival mean per server-step above 0.05 (the per-step count is truncated at 3).
  * SIM_ENOMEM: workspace too small. The library never allocates device memory itself;
- * a handle keeps pinned host memory for the totals that sim_stats reads (36 KB with two classes, 140 KB with eight),
- * unless there is none to be had.
+ * a handle has a block of pinned host memory for the totals that sim_stats reads (140 KB), unless there is none to be had.
+ * The library keeps the blocks for later handles until the process ends, at most 32 on each device; handles beyond
+ * those copy the totals instead (20 us more in each sim_stats).
  * The handle belongs to the device that is current at this call: every later call on it must be made
  * with the same device current (SIM_EINVAL otherwise). The launch shape of the handle (see sim_launch_plan) is
  * fixed here for `max_replications` replications; runs with fewer use the same shape, results do not depend on it. */
@@ -259,6 +260,8 @@ int sim_launch_shape(sim_t *h, int *threads, size_t *lds_bytes);
  * out pointer may be NULL. SIM_EINVAL as for sim_create. */
 int sim_launch_plan(const sim_config *cfg, int replications, int *threads, size_t *lds_bytes, int *waves_per_simd);
 
+/* Frees the handle. Waits for nothing: neither for its own work (whose workspace must stay until that has ended) nor for that
+ * of others. */
 int sim_destroy(sim_t *h);
 const char *sim_strerror(int err);
 

@@ -4,12 +4,60 @@
 #include <cmath>
 #include <cstring>
 #include <memory>
+#include <mutex>
 #include <new>
 #include <vector>
 
 #include "gnr_internal.h"
 
 using namespace gnr;
+
+namespace {
+
+// Pinned host memory for the totals that sim_stats reads. hipHostFree waits for everything the device has been given, which the
+// end of a handle must not (behind another handle's run of 40000 steps on a stream of its own 328 ms, without it 0.01), so a block is kept
+// for the handles that follow: at most kMostBlocks a device (4.5 MB), until the process ends. A handle that finds none free
+// copies its totals out of the workspace.
+struct TotalsBlock {
+  int device;
+  bool taken;
+  uint64_t *mem;
+  TotalsBlock *next;
+};
+constexpr int kMostBlocks = 32;
+std::mutex blocks_lock;
+TotalsBlock *blocks = nullptr;
+
+TotalsBlock *take_block(int device)   // the current device
+{
+  const std::lock_guard<std::mutex> hold(blocks_lock);
+  int n = 0;
+  for (TotalsBlock *b = blocks; b; b = b->next) {
+    if (b->device != device) continue;
+    if (!b->taken) { b->taken = true; return b; }
+    ++n;
+  }
+  if (n >= kMostBlocks) return nullptr;
+  TotalsBlock *made = new (std::nothrow) TotalsBlock{device, true, nullptr, blocks};
+  if (!made) return nullptr;
+  void *mem = nullptr;
+  if (hipHostMalloc(&mem, (kTallyWords + static_cast<size_t>(3) * kMaxK * kNBin) * sizeof(uint64_t), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    delete made;
+    return nullptr;
+  }
+  made->mem = static_cast<uint64_t *>(mem);
+  blocks = made;
+  return made;
+}
+
+void give_back(TotalsBlock *b)
+{
+  const std::lock_guard<std::mutex> hold(blocks_lock);
+  b->taken = false;
+}
+
+}  // namespace
 
 struct sim_t {
   sim_config cfg;
@@ -32,12 +80,12 @@ struct sim_t {
   // Totals over replications as sim_stats reads them: pinned host memory that the reduce kernel writes itself (of handles made
   // by sim_create; without it they are copied out of the workspace). A copy of these 36 KB to pageable memory took 20 us and a
   // second wait, of the 59 us of a call that advances 8 servers x 16 replications by one step and reads the statistics.
-  uint64_t *totals = nullptr;
+  TotalsBlock *totals = nullptr;
   ~sim_t()
   {
     for (auto *list : {&pending, &spare})
       for (auto &pr : *list) { (void)hipEventDestroy(pr.first); (void)hipEventDestroy(pr.second); }
-    if (totals) (void)hipHostFree(totals);
+    if (totals) give_back(totals);
   }
   int64_t launches;
   double kernel_ms;
@@ -422,13 +470,7 @@ int create_in(const sim_config *cfg, int max_replications, void *dev_workspace, 
          hipMemcpy(w + L.pat_tab, pat.data(), pat.size() * sizeof(uint16_t), hipMemcpyHostToDevice) != hipSuccess)) {
       return SIM_EHIP;
     }
-    if (may_allocate) {
-      void *mem = nullptr;
-      if (hipHostMalloc(&mem, (kTallyWords + static_cast<size_t>(3) * cfg->K * kNBin) * sizeof(uint64_t), hipHostMallocDefault) == hipSuccess)
-        h->totals = static_cast<uint64_t *>(mem);
-      else
-        (void)hipGetLastError();
-    }
+    if (may_allocate) h->totals = take_block(h->device);
     *out = hold.release();
     return SIM_OK;
   } catch (...) {   // host allocation failed (std::bad_alloc, std::length_error): nothing crosses the C boundary
@@ -547,13 +589,16 @@ int sim_stats(sim_t *h, sim_stats_t *st, void *hip_stream)
 {
   try {
     if (!h || !st || !h->started || !on_device(h)) return SIM_EINVAL;
-    int rc = launch_reduce(h->p, h->reps, h->totals ? h->totals : h->p.reduced, hip_stream);
+    int rc = launch_reduce(h->p, h->reps, h->totals ? h->totals->mem : h->p.reduced, hip_stream);
     if (rc != SIM_OK) return rc;
     rc = sync(h, hip_stream);
-    if (rc != SIM_OK) return rc;
+    if (rc != SIM_OK) {
+      h->totals = nullptr;   // (the kernel may write there yet: the block goes to nobody else)
+      return rc;
+    }
     const int K = h->cfg.K;
     std::vector<uint64_t> copied;
-    const uint64_t *red = h->totals;
+    const uint64_t *red = h->totals ? h->totals->mem : nullptr;
     if (!red) {
       copied.resize(kTallyWords + static_cast<size_t>(3) * K * kNBin);
       rc = copy_out(copied.data(), h->p.reduced, copied.size() * sizeof(uint64_t));
