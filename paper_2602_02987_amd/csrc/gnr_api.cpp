@@ -273,7 +273,8 @@ int copy_out(void *dst, const void *src, size_t bytes)
   return hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost) == hipSuccess ? SIM_OK : SIM_EHIP;
 }
 
-void drain_events(sim_t *h)
+// (the lists have room for every pair: see room_for_pair)
+void drain_events(sim_t *h) noexcept
 {
   for (auto &pr : h->pending) {
     float ms = 0.f;
@@ -281,6 +282,15 @@ void drain_events(sim_t *h)
     h->spare.push_back(pr);
   }
   h->pending.clear();
+}
+
+constexpr size_t kPendingPairs = 64;   // a run waits for its launches when as many have been timed and not been read out
+// Room for one more pair of events in either list, so that nothing between a launch and the books on it can fail.
+void room_for_pair(sim_t *h)
+{
+  const size_t n = h->pending.size() + h->spare.size() + 1;
+  h->pending.reserve(n);
+  h->spare.reserve(n);
 }
 
 double ratio(double a, double b) { return b > 0.0 ? a / b : 0.0; }
@@ -471,6 +481,8 @@ int create_in(const sim_config *cfg, int max_replications, void *dev_workspace, 
       return SIM_EHIP;
     }
     if (may_allocate) h->totals = take_block(h->device);
+    h->pending.reserve(kPendingPairs + 1);
+    h->spare.reserve(kPendingPairs + 1);
     *out = hold.release();
     return SIM_OK;
   } catch (...) {   // host allocation failed (std::bad_alloc, std::length_error): nothing crosses the C boundary
@@ -498,6 +510,7 @@ int sim_run(sim_t *h, int64_t steps, int replications, uint64_t seed, void *hip_
     int64_t left = steps;
     while (left > 0) {
       const uint32_t n = static_cast<uint32_t>(left < kStepsPerLaunch ? left : kStepsPerLaunch);
+      room_for_pair(h);
       hipEvent_t e0 = nullptr, e1 = nullptr;
       bool timed = true;
       if (!h->spare.empty()) {
@@ -514,7 +527,7 @@ int sim_run(sim_t *h, int64_t steps, int replications, uint64_t seed, void *hip_
       h->launches += 1;
       h->steps_done += n;
       left -= n;
-      if (h->pending.size() >= 64) {   // bound the number of live events
+      if (h->pending.size() >= kPendingPairs) {   // bound the number of live events
         if (hipStreamSynchronize(st) != hipSuccess) return SIM_EHIP;
         drain_events(h);
       }

@@ -81,10 +81,10 @@ hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b)
 
 // ---- the launches: the totals of a handle are its seed, so that one can tell whose they are
 namespace gnr {
-static int launches_fail = 0;
+static int launches_fail = 0, steps_launched = 0;
 static uint64_t *last_totals = nullptr;
 int launch_reset(const Params &, int, void *) { return SIM_OK; }
-int launch_steps(const Params &, int, int, size_t, uint32_t, uint32_t, void *) { return SIM_OK; }
+int launch_steps(const Params &, int, int, size_t, uint32_t, uint32_t n, void *) { steps_launched += static_cast<int>(n); return SIM_OK; }
 int launch_reduce(const Params &p, int, uint64_t *out, void *)
 {
   if (launches_fail) return SIM_EHIP;
@@ -216,9 +216,60 @@ static void threads()
   device = 0;
 }
 
+// A launch's pair of events is read once and kept or destroyed once, whichever host allocation fails on the way, and what the
+// handle knows of its steps is what has been launched.
+static void timing_events()
+{
+  for (int launches : {1, 3, 63, 64, 65, 130})
+    for (int fail_at = 1; fail_at <= 4; ++fail_at)
+      for (bool in_run : {false, true}) {
+        Made m = make(2);
+        gnr::steps_launched = 0;
+        elapsed_asked = 0;
+        int refused = 0, asked = 0;
+        for (int i = 0; i < launches; ++i) {
+          allocations_left = in_run ? fail_at : -1;
+          const int rc = sim_run(m.h, 10, 2, 5, nullptr);
+          allocations_left = -1;
+          EXPECT(rc == SIM_OK || rc == SIM_ENOMEM);
+          refused += rc != SIM_OK;
+        }
+        double ms = 0.0;
+        int64_t n = 0;
+        allocations_left = in_run ? -1 : fail_at;
+        const int rc = sim_kernel_time(m.h, &n, &ms, 0, nullptr);
+        allocations_left = -1;
+        EXPECT(rc == SIM_OK || rc == SIM_ENOMEM);
+        asked = elapsed_asked;
+        EXPECT(sim_kernel_time(m.h, &n, &ms, 0, nullptr) == SIM_OK);
+        EXPECT(n == launches - refused && ms == static_cast<double>(n));
+        EXPECT(asked == n && elapsed_asked == n);
+        EXPECT(gnr::steps_launched == 10 * n);
+        EXPECT(sim_run(m.h, 10, 2, 5, nullptr) == SIM_OK);
+        sim_stats_t st;
+        EXPECT(sim_stats(m.h, &st, nullptr) == SIM_OK && st.steps == 10 * (n + 1));
+        EXPECT(sim_kernel_time(m.h, &n, &ms, 0, nullptr) == SIM_OK && ms == static_cast<double>(n));
+        EXPECT(sim_destroy(m.h) == SIM_OK);
+        EXPECT(events->empty());
+      }
+  // a wait that fails leaves the pairs where they are
+  Made m = make(2);
+  sync_fails = true;
+  for (int i = 0; i < 200; ++i) {
+    const int rc = sim_run(m.h, 10, 2, 5, nullptr);
+    EXPECT(rc == (i < 63 ? SIM_OK : SIM_EHIP));
+  }
+  sync_fails = false;
+  double ms = 0.0;
+  int64_t n = 0;
+  EXPECT(sim_kernel_time(m.h, &n, &ms, 0, nullptr) == SIM_OK && n == 200 && ms == 200.0);
+  EXPECT(sim_destroy(m.h) == SIM_OK);
+}
+
 int main()
 {
   blocks();
+  timing_events();
   threads();
   EXPECT(bad_events == 0);
   EXPECT(events->empty());
