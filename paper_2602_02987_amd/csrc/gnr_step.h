@@ -1023,7 +1023,8 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     for (int h = 0; h < kHits; ++h) {
       if (first + 64 * h * stride >= nwords) break;   // wave-uniform
       const int word = first + (lane + 64 * h) * stride;
-      uint64_t left = kHits == 1 || h == 0 ? hits[0] : hits[kHits - 1];
+      // (what has been counted is taken out, so that behind the last step, for which nothing is drawn, there is nothing to count)
+      uint64_t &left = hits[kHits == 1 ? 0 : h];
       left &= bits_below(word, N);   // (of a lane without a word it is empty)
       int n = 0;
       for (uint64_t todo = __ballot(left != 0); todo;) {   // a lane queues one server of its word at a time
