@@ -66,7 +66,7 @@ int step_threads(Params q, int reps)
 {
   // A replication with many servers fills the LDS of a compute unit, runs alone there and wants all sixteen
   // waves to hide latency.
-  if (q.N > 5120) return 1024;
+  if (q.N > 64 * kMostWordsEight) return 1024;
   // Smaller replications share a compute unit. A workgroup steps faster the more waves it has, as long as its waves have
   // blocks of servers to work on and all workgroups of the launch find a place at once (at most four waves per SIMD): the
   // largest workgroup that keeps the rounds lowest. Rounds count as they are while a full compute unit holds two waves a
@@ -312,7 +312,7 @@ static int step_form(int threads, int nwords)
     case 64: return 0;
     case 128: return 1;
     case 256: return 2;
-    case 512: return nwords <= 40 ? 3 : 6;
+    case 512: return nwords <= 40 ? 3 : nwords <= kMostWordsEight ? 6 : -1;
     case 1024: return 2 + size_class(threads, nwords);
     default: return -1;
   }

@@ -314,6 +314,7 @@ struct Lds {
 // workgroups of sixteen waves (N up to 64 NWS servers). NWS = 0: everything sized by the configuration.
 // Whether workgroups of this size have the bitmaps that overlapping steps take in turn (see kOverlap in the step kernel).
 __host__ __device__ constexpr bool steps_overlap(int threads) { return threads >= 512; }
+constexpr int kMostWordsEight = 80;   // words of a workgroup of up to eight waves
 constexpr int kStaticWordsLarge = kMaxN / 64;   // any N the library accepts
 constexpr int kStaticWordsMedium = 160;          // N up to 10240: three kilobytes less
 template <int NWS, bool SMALL = false>
@@ -405,6 +406,57 @@ __host__ __device__ constexpr int waves_per_simd(int max_threads, bool dense)
 __host__ __device__ constexpr int static_words(int size_class)
 {
   return size_class <= 1 ? 0 : (size_class == 2 ? kStaticWordsMedium : kStaticWordsLarge);
+}
+
+// How many of a workgroup's waves, the last ones, work off the events. With draws beside them (10000 servers, 10, 11 and 12 of sixteen
+// waves 13.57, 13.61 and 13.42 ms per 1000 steps; 3001 servers, 8, 10 and 12 of them 4.464, 4.481 and 4.459 per 500) twelve of
+// sixteen; of eight half, with more than eight words a wave five.
+__host__ __device__ __forceinline__ constexpr int event_waves(int nwaves, bool beside, int nwords)
+{
+  return !beside ? nwaves : nwaves == 16 ? 12 : nwords > 8 * nwaves ? nwaves * 11 / 16 : nwaves / 2;
+}
+
+// The pairs of bitmap words that a wave looks at in a completion pass: first, first + stride, ... below the end.
+struct Scan { int first, stride, end; };
+// Where steps overlap: those of the i-th of n_drain waves, of which the last n_busy serve the step before. Where the others are three
+// times as many these look at all words, else, where the events are not shared by all waves, at two pairs for one of the waves that
+// serve (10000 x 256, four or five of twelve serve), which have the last pairs. What does not divide falls to the waves that
+// serve: a wave with more than 64 events takes twice as long. `each`: npairs over scan_share(..), rounded up;
+// `end`: of all, npairs or more.
+__host__ __device__ __forceinline__ constexpr int scan_share(int n_drain, int n_busy) { return 2 * (n_drain - n_busy) + n_busy; }
+__host__ __device__ __forceinline__ constexpr Scan overlapping_scan(int i, int npairs, int end, int n_drain, int n_busy, int each, bool beside)
+{
+  const int n_free = n_drain - n_busy;
+  const bool some = n_free < 3 * n_busy;
+  Scan mine = {i, n_drain, end};
+  if (!some || beside) {
+    const int ends_at = !some ? npairs : npairs - n_busy * each;
+    if (i < n_free) {
+      mine.stride = n_free;
+      mine.end = ends_at > 0 ? ends_at : 0;
+    } else {
+      mine.stride = n_busy;
+      mine.first = (ends_at > 0 ? ends_at : 0) + i - n_free;
+    }
+  }
+  return mine;
+}
+
+// What others have been given is noted for one round of the completion pass (bm_others): no wave may have more pairs than that.
+constexpr int kPairsARound = 16;
+constexpr bool a_round_is_enough(int nwaves, bool beside, int most_words)
+{
+  for (int words = 1; words <= most_words; ++words) {
+    const int npairs = (words + 1) / 2, n_drain = event_waves(nwaves, beside, words);
+    for (int n_busy = 0; n_busy <= n_drain; ++n_busy) {
+      const int each = (npairs + scan_share(n_drain, n_busy) - 1) / scan_share(n_drain, n_busy);
+      for (int i = 0; i < n_drain; ++i) {
+        const Scan mine = n_busy ? overlapping_scan(i, npairs, npairs, n_drain, n_busy, each, beside) : Scan{i, n_drain, npairs};
+        if (mine.end - mine.first > kPairsARound * mine.stride) return false;
+      }
+    }
+  }
+  return true;
 }
 
 // Bits of bitmap word w that belong to servers below `nbits`.
@@ -643,9 +695,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
   constexpr bool kChainFirst = DENSE && NT >= 128 && NT <= 256;
   const int nwords_all = p.nwords;
   constexpr bool kBeside = BESIDE;   // some waves draw while the others work off the events
-  // (10000 servers, 10, 11 and 12 of sixteen waves 13.57, 13.61 and 13.42 ms per 1000 steps; 3001 servers, 8, 10 and 12 of them 4.464,
-  // 4.481 and 4.459 per 500. Of eight waves half, with more than eight words a wave five)
-  const int n_drain = !kBeside ? nwaves : nwaves == 16 ? 12 : nwords_all > 8 * nwaves ? nwaves * 11 / 16 : nwaves / 2;
+  const int n_drain = !kBeside || nwaves == 16 ? event_waves(nwaves, kBeside, 0) : event_waves(nwaves, kBeside, nwords_all);   // (mostly a constant)
   const int n_draw = nwaves - n_drain, drain_first = n_draw;
   uint32_t turn = 0;   // in workgroups of two to four waves
   auto own_priority = [&]() __attribute__((always_inline)) {
@@ -759,6 +809,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
     return n;
   };
   constexpr bool kOverlap = steps_overlap(NT);
+  static_assert(!kOverlap || a_round_is_enough(nwaves, kBeside, NT == 1024 ? NWS : kMostWordsEight), "pairs of words a wave looks at");
   // bitmaps that steps take in turn where they overlap: how far apart they are
   const int turn_words = !kOverlap ? 0 : NWS ? NWS : nwords, turn_words_m = !kOverlap ? 0 : NWS ? NWS : nwords_m;
   // classes that the gate may admit: under the occupancy gate those with a positive target
@@ -1461,7 +1512,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
       const int last_pair = (nwords - 1) >> 1, npairs = scan_end <= last_pair ? scan_end : last_pair + 1;
       const uint32_t T_past = T_hi + 1u;
       const int last_clock = (N - 1) & ~1;
-      for (int first = scan_first;; first += 16 * scan_stride) {   // wave-uniform; the wave's pairs of words, sixteen a round
+      for (int first = scan_first;; first += kPairsARound * scan_stride) {   // wave-uniform; the wave's pairs of words, sixteen a round
         if (first >= npairs && nev == 0) break;
         if constexpr (!kOverlap) {   // (its own words: nobody else is at them)
           const int w = 2 * (first + (lane >> 1) * scan_stride) + (lane & 1);
@@ -1478,7 +1529,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         int seen = 0;
         // (servers past the last one are not busy; a clock a few ns ahead may pass here for its upper bits: the servers
         // queued are looked at exactly)
-        for (; seen < 16 && first + seen * scan_stride < npairs; seen += kPairsAtOnce) {   // wave-uniform; up to three pairs past the last one
+        for (; seen < kPairsARound && first + seen * scan_stride < npairs; seen += kPairsAtOnce) {   // wave-uniform; up to three pairs past the last one
           uint2 ev[kPairsAtOnce];
           uint32_t here[kPairsAtOnce];
           int n_bits[kPairsAtOnce];
@@ -2792,26 +2843,14 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         scan_first = wave - drain_first; scan_stride = n_drain; scan_end = nwords;
         if constexpr (kOverlap) {
           if (apart_next) {
-            // The waves that serve come last. Where the others are three times as many these look at all words, else, where the events
-            // are not shared by all waves, at two pairs for one of the waves that serve (10000 x 256, four or five of twelve serve), which
-            // have the last pairs. What does not divide falls to the waves that serve: a wave with more than 64 events takes twice as long.
-            const int n_busy = n_serve < n_drain ? n_serve : n_drain, n_free = n_drain - n_busy;
-            const bool serves = wave >= nwaves - n_busy, some = n_free < 3 * n_busy;
-            if (!some || kBeside) {
-              const int npairs = (nwords + 1) >> 1, share = 2 * n_free + n_busy;
-              const int each = static_cast<int>((static_cast<float>(npairs + share) - 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(share)));   // rounded up
-              const int ends_at = !some ? npairs : npairs - n_busy * uniform(each);
-              if (!serves) {
-                scan_stride = n_free;
-                scan_end = ends_at > 0 ? ends_at : 0;
-              } else {
-                scan_stride = n_busy;
-                scan_first = (ends_at > 0 ? ends_at : 0) + wave - (nwaves - n_busy);
-              }
-            }
+            // The waves that serve come last.
+            const int npairs = (nwords + 1) >> 1, n_busy = n_serve < n_drain ? n_serve : n_drain, share = scan_share(n_drain, n_busy);
+            const int each = static_cast<int>((static_cast<float>(npairs + share) - 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(share)));   // rounded up
+            const Scan mine = overlapping_scan(wave - drain_first, npairs, nwords, n_drain, n_busy, uniform(each), kBeside);
+            scan_first = mine.first; scan_stride = mine.stride; scan_end = mine.end;
           }
           if (wave < drain_first) scan_first = nwords;
-          // (no wave has more than sixteen pairs, of 96 and of 40 in workgroups of sixteen and of eight waves)
+          // (no wave has more than kPairsARound pairs: a_round_is_enough)
           const int pair_here = scan_first + (lane >> 1) * scan_stride, w = pair_here < scan_end ? 2 * pair_here + (lane & 1) : nwords;
           uint64_t others = 0;
           if (apart_next) {
@@ -2862,7 +2901,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
               }
             }
           }
-          if (lane < 32 && w < nwords) L.bm_others[w] = others;
+          if (lane < 2 * kPairsARound && w < nwords) L.bm_others[w] = others;
         }
       }
       if constexpr (AB) {
