@@ -82,3 +82,18 @@ def test_eight_waves_with_many_words(B, oracle_mod, N, M, lam, cap, prompt, repl
             assert_replication_equal(sim, orc, r, what=f"{policy} theta={theta} N={N} after {orc.steps_done()} steps")
     if replications == 2:
         assert_stats_equal(sim.stats(), orc.stats())
+
+
+# The layout for more than 160 words (same-slot decode keeps a solo group here: with a prefill slot on every server it does not fit).
+@pytest.mark.parametrize("policy", list(_POLICY))
+@pytest.mark.parametrize("theta", [0.0, 40.0])
+def test_sixteen_waves_with_the_most_words(B, oracle_mod, theta, policy):
+    cfg = replace(_overlap_cfg(10305, 2100, 0.8, 3, 100, theta, policy), M=2100)
+    assert B.sim_launch_plan(cfg, cfg.replications)[0] == 1024
+    sim, orc = B.Sim(cfg), oracle_mod.Oracle(cfg)
+    for n in (1, 2, 60, 61):
+        sim.run(n)
+        orc.run(n)
+        for r in range(cfg.replications):
+            assert_replication_equal(sim, orc, r, what=f"{policy} theta={theta} after {orc.steps_done()} steps")
+    assert_stats_equal(sim.stats(), orc.stats())
