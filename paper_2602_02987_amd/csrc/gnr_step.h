@@ -396,9 +396,9 @@ __host__ __device__ constexpr int size_class(int threads, int nwords)
 // to 256 registers and two waves per SIMD, taken while every workgroup of the launch finds a place at that density, and
 // dense, with 128 registers and four waves per SIMD, for launches that would otherwise run their workgroups in more
 // rounds. Registers roomy / dense (spilled when dense): base and randomized router, same-slot decode 107 to 113 in two waves and
-// more and 117 to 121 in one, the same code in both forms; with deadline rings 116 to 127, in one wave 128 to 136 / 128 (up to 2);
-// weighted router 136 to 139 / 128 (4) and in one wave 150 / 128 (8). So only the forms of the weighted router, and with deadline
-// rings those of one wave, differ.
+// more and 117 to 121 in one, as many in either form; with deadline rings 118 to 127, in one wave 128 to 136 / 128 (up to 1);
+// weighted router 136 to 139 / 128 (4) and in one wave 150 / 128 (8). Without deadline rings the two forms of one and of eight waves
+// do the same, with a few spilled scalars more or less; those of two and four waves differ in their priorities (kChainFirst).
 __host__ __device__ constexpr int waves_per_simd(int max_threads, bool dense)
 {
   return max_threads > 512 || dense ? 4 : 2;
@@ -2814,7 +2814,9 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
           if constexpr (WS) {   // what the pass took from the solo group's buffer, per class
             if (tid >= NT - 64 && lane < K) L.cs[CS_QDS + lane] -= L.sel_n[lane];
           }
-          if (wave == route_first && lane == 0) {   // (nobody else is at the histograms before the barrier; an add waits for no old count)
+          // (by atomics: where steps overlap other waves may be at the next step's events already, which change the same histograms.
+          // Nobody reads them before the barriers that follow.)
+          if (wave == route_first && lane == 0) {
 #pragma unroll
             for (int gi = 0; gi < 2; ++gi) {
               if (nG[gi] > 0) {
