@@ -416,30 +416,39 @@ __host__ __device__ __forceinline__ constexpr int event_waves(int nwaves, bool b
   return !beside ? nwaves : nwaves == 16 ? 12 : nwords > 8 * nwaves ? nwaves * 11 / 16 : nwaves / 2;
 }
 
-// The pairs of bitmap words that a wave looks at in a completion pass: first, first + stride, ... below the end.
-struct Scan { int first, stride, end; };
-// Where steps overlap: those of the i-th of n_drain waves, of which the last n_busy serve the step before. Where the others are three
-// times as many these look at all words, else, where the events are not shared by all waves, at two pairs for one of the waves that
-// serve (10000 x 256, four or five of twelve serve), which have the last pairs. What does not divide falls to the waves that
-// serve: a wave with more than 64 events takes twice as long. `each`: npairs over scan_share(..), rounded up;
-// `end`: of all, npairs or more.
-__host__ __device__ __forceinline__ constexpr int scan_share(int n_drain, int n_busy) { return 2 * (n_drain - n_busy) + n_busy; }
-__host__ __device__ __forceinline__ constexpr Scan overlapping_scan(int i, int npairs, int end, int n_drain, int n_busy, int each, bool beside)
-{
-  const int n_free = n_drain - n_busy;
-  const bool some = n_free < 3 * n_busy;
-  Scan mine = {i, n_drain, end};
-  if (!some || beside) {
-    const int ends_at = !some ? npairs : npairs - n_busy * each;
-    if (i < n_free) {
-      mine.stride = n_free;
-      mine.end = ends_at > 0 ? ends_at : 0;
-    } else {
-      mine.stride = n_busy;
-      mine.first = (ends_at > 0 ? ends_at : 0) + i - n_free;
-    }
+// A wave looks at the pairs of bitmap words scan_first, scan_first + scan_stride, ... below scan_end (and below the last one) in a completion
+// pass: the last n_drain waves share all of them, unless steps overlap and the last n_serve waves serve the step before. Where the others are
+// three times as many these look at all words, else, where the events are not shared by all waves (`beside`), at two pairs for one of the waves
+// that serve (10000 x 256, four or five of twelve serve), which have the last pairs. What does not divide falls to the waves that serve: a wave
+// with more than 64 events takes twice as long. `rounded_up`: npairs over share.
+// (The kernel and the check below have these statements in common as a macro: as a function, whichever way it was passed what it reads and writes,
+// it left the kernel with other registers throughout; eight waves, base router, took 0.6 to 1 % longer.)
+#define GNR_OVERLAPPING_SCAN(beside, rounded_up)                                                             \
+  const int n_busy = n_serve < n_drain ? n_serve : n_drain, n_free = n_drain - n_busy;                       \
+  const bool serves = wave >= nwaves - n_busy, some = n_free < 3 * n_busy;                                   \
+  if (!some || beside) {                                                                                     \
+    const int npairs = (nwords + 1) >> 1, share = 2 * n_free + n_busy;                                       \
+    const int each = rounded_up;                                                                             \
+    const int ends_at = !some ? npairs : npairs - n_busy * uniform(each);                                    \
+    if (!serves) {                                                                                           \
+      scan_stride = n_free;                                                                                  \
+      scan_end = ends_at > 0 ? ends_at : 0;                                                                  \
+    } else {                                                                                                 \
+      scan_stride = n_busy;                                                                                  \
+      scan_first = (ends_at > 0 ? ends_at : 0) + wave - (nwaves - n_busy);                                   \
+    }                                                                                                        \
   }
-  return mine;
+
+struct Scan { int first, stride, end; };
+// The same on the host: the pairs of the last n_drain of `nwaves` waves while the last n_serve serve (0: no steps overlap).
+constexpr Scan scan_of(int wave, int nwaves, int nwords, int n_drain, int n_serve, bool beside)
+{
+  int scan_first = wave - (nwaves - n_drain), scan_stride = n_drain, scan_end = (nwords + 1) >> 1;
+  auto uniform = [](int v) constexpr { return v; };
+  if (n_serve > 0) {
+    GNR_OVERLAPPING_SCAN(beside, (npairs + share - 1) / share)
+  }
+  return {scan_first, scan_stride, scan_end};
 }
 
 // What others have been given is noted for one round of the completion pass (bm_others): no wave may have more pairs than that.
@@ -447,14 +456,12 @@ constexpr int kPairsARound = 16;
 constexpr bool a_round_is_enough(int nwaves, bool beside, int most_words)
 {
   for (int words = 1; words <= most_words; ++words) {
-    const int npairs = (words + 1) / 2, n_drain = event_waves(nwaves, beside, words);
-    for (int n_busy = 0; n_busy <= n_drain; ++n_busy) {
-      const int each = (npairs + scan_share(n_drain, n_busy) - 1) / scan_share(n_drain, n_busy);
-      for (int i = 0; i < n_drain; ++i) {
-        const Scan mine = n_busy ? overlapping_scan(i, npairs, npairs, n_drain, n_busy, each, beside) : Scan{i, n_drain, npairs};
+    const int n_drain = event_waves(nwaves, beside, words);
+    for (int n_serve = 0; n_serve <= n_drain; ++n_serve)   // (where more serve it is as with those)
+      for (int wave = nwaves - n_drain; wave < nwaves; ++wave) {
+        const Scan mine = scan_of(wave, nwaves, words, n_drain, n_serve, beside);
         if (mine.end - mine.first > kPairsARound * mine.stride) return false;
       }
-    }
   }
   return true;
 }
@@ -2845,11 +2852,7 @@ __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(waves_p
         scan_first = wave - drain_first; scan_stride = n_drain; scan_end = nwords;
         if constexpr (kOverlap) {
           if (apart_next) {
-            // The waves that serve come last.
-            const int npairs = (nwords + 1) >> 1, n_busy = n_serve < n_drain ? n_serve : n_drain, share = scan_share(n_drain, n_busy);
-            const int each = static_cast<int>((static_cast<float>(npairs + share) - 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(share)));   // rounded up
-            const Scan mine = overlapping_scan(wave - drain_first, npairs, nwords, n_drain, n_busy, uniform(each), kBeside);
-            scan_first = mine.first; scan_stride = mine.stride; scan_end = mine.end;
+            GNR_OVERLAPPING_SCAN(kBeside, static_cast<int>((static_cast<float>(npairs + share) - 0.5f) * __builtin_amdgcn_rcpf(static_cast<float>(share))))
           }
           if (wave < drain_first) scan_first = nwords;
           // (no wave has more than kPairsARound pairs: a_round_is_enough)
