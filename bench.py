@@ -25,8 +25,8 @@ HBM_PEAK_GBS = 8000.0
 # occupancy rocprofv3 derives for it. These are STORED figures, not taken in this run: they hold for the kernel
 # sources whose hash is given (compared with the current sources; on a mismatch the figures read null) and for the
 # state named in `state`. The line says so in `roofline.traffic_source` / `roofline.occupancy.source`.
-TRAFFIC = {"sources_sha256": "794f05bd0b051757d80e90d4ced488c02a4408250248c098bf1ca8813c7110c5",
-           "bytes_per_launch": 53931024497, "occupancy_percent": 49.088253,
+TRAFFIC = {"sources_sha256": "2edf9f04a49014a91d2c60c72ae49c9581ef422baf9e4e55a45c7eee6cf4b092",
+           "bytes_per_launch": 53998013959, "occupancy_percent": 49.096144,
            "state": "config 5 after 30000 untimed steps, mean of 2 launches of 1000 steps",
            "profile": "profiles/gnr_step_kernel_cfg5_hbm_traffic.md"}
 
